@@ -136,7 +136,7 @@ def model_bytes(spec, prec, pr):
 # The sources the operator apply's grid passes are compiled from (the FFT passes with the fused
 # multiplier, and the declarations and helpers they include); the traffic counters in profiles/
 # stand only while these are unchanged.
-DIGEST_SOURCES = ("fft.hip", "kernels.h", "common.h", "tables.h")
+DIGEST_SOURCES = ("fft.hip", "fft_core.h", "kernels.h", "common.h", "tables.h")
 
 
 def sources_digest():

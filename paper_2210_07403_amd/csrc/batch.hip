@@ -42,6 +42,7 @@ using Tuned = LaunchShape;
 
 template <typename T> struct GroupWork {
   GridTables<T> tab;
+  Tw2<T> tw2;                // 2-D: the tables of the passes
   T* real = nullptr;          // [problem][grid]
   cplx<T>* spec = nullptr;    // [problem][half spectrum]
   cplx<T>* wtab = nullptr;    // weight table in this precision
@@ -56,7 +57,11 @@ struct Group {
   double kappa = 0;
   std::vector<int> probs;     // batch indices, in group order
   MarkerGeom geom{};
-  int64_t ntot = 0, nxh = 0, nxp = 0, nspec = 0;   // nxp: half-spectrum row pitch (128-byte rows)
+  // half spectra of one problem: 3-D [z][y][nxp] (rows padded to 128 bytes), 2-D transposed (spec2_size)
+  int64_t ntot = 0, nxh = 0, nxp = 0;
+  template <typename T> int64_t nspec(int dim) const {
+    return dim == 2 ? spec2_size<T>(n[0], n[1]) : nxp * n[1] * n[2];
+  }
   int64_t nib = 0;            // markers of the group
   int64_t aoff = 0;           // offset of the group's first unknown in batch vectors
   double *X = nullptr, *nrm = nullptr, *ds = nullptr, *f = nullptr, *wt = nullptr;
@@ -162,6 +167,7 @@ template <typename T> MultDesc group_desc(const Group& G, const GroupWork<T>& W,
   md.dim = dim;
   md.nxh = (int)G.nxh;
   md.nxp = (int)G.nxp;
+  md.nyp = (int)spec2_pitch<T>(G.n[1]);
   md.stokes = 0;
   md.nc = 1;
   md.fk[0] = FK_MASS;
@@ -184,19 +190,28 @@ template <typename T> void group_pipeline(ibdl_batch_s* B, Group& G, GroupWork<T
   const MultDesc md = group_desc<T>(G, W, B->dim);
   // the spread wrote the busy tiles only: the x pass reads their row segments and takes the rest
   // of each row as zero (no clearing of the fields)
+  if (B->dim == 2) {
+    Rows2 rw;
+    rw.hi = G.n[1] - 1;
+    const Rows2 out = rw;
+    rw.seg = G.seg_all;
+    rw.seg_log2 = __builtin_ctz((unsigned)G.geom.tile[0] / 2);
+    rw.seg_per_field = 1;
+    fft2_x_r2c<T>(W.real, W.spec, G.n[0], G.n[1], np, W.tw2, B->st, tn.rpb, rw);
+    fft2_lines<T>(W.spec, G.n[1], 1, md, W.tw2, B->st, np, G.nspec<T>(2), tn.wz, RowMask());
+    fft2_x_c2r<T>(W.spec, W.real, G.n[0], G.n[1], np, W.tw2, B->st, tn.rpb, out);
+    return;
+  }
   RowList rl;
   rl.rpf = rows;
   rl.seg = G.seg_all;
   rl.seg_log2 = __builtin_ctz((unsigned)G.geom.tile[0] / 2);
   fft_x_r2c<T>(W.real, W.spec, G.n[0], rows, W.tab.tw[0], B->st, tn.rpb, rl, G.nxp);
-  if (B->dim == 3)
-    fft_strided<T>(W.spec, G.n[1], (int64_t)np * G.n[2] * G.nxp, G.nxp, G.nxp * G.n[1], G.nxp, false, W.tab.tw[1],
-                   B->st, 0, RowMask(), G.nxh);
-  const int last = B->dim - 1;
-  fft_fused_last<T>(W.spec, G.n[last], G.nspec / G.n[last], 1, md, W.tab.tw[last], B->st, np, G.nspec, tn.wz);
-  if (B->dim == 3)
-    fft_strided<T>(W.spec, G.n[1], (int64_t)np * G.n[2] * G.nxp, G.nxp, G.nxp * G.n[1], G.nxp, true, W.tab.tw[1],
-                   B->st, 0, RowMask(), G.nxh);
+  fft_strided<T>(W.spec, G.n[1], (int64_t)np * G.n[2] * G.nxp, G.nxp, G.nxp * G.n[1], G.nxp, false, W.tab.tw[1], B->st,
+                 0, RowMask(), G.nxh);
+  fft_fused_last<T>(W.spec, G.n[2], G.nxp * G.n[1], 1, md, W.tab.tw[2], B->st, np, G.nspec<T>(3), tn.wz);
+  fft_strided<T>(W.spec, G.n[1], (int64_t)np * G.n[2] * G.nxp, G.nxp, G.nxp * G.n[1], G.nxp, true, W.tab.tw[1], B->st,
+                 0, RowMask(), G.nxh);
   fft_x_c2r<T>(W.spec, W.real, G.n[0], rows, W.tab.tw[0], B->st, tn.rpb, RowList(), G.nxp);
 }
 
@@ -323,7 +338,6 @@ template <typename T> void tune_tiles(ibdl_batch_s* B, Group& G, GroupWork<T>& W
   IBDL_HIP(hipEventCreate(&e1));
   int best = 16;
   float best_ms = 1e30f;
-  const int64_t rows = (int64_t)np * G.n[1];
   for (int tx : {16, 32, 64}) {
     if (G.n[0] / tx > 64 || G.n[0] < tx || G.n[1] < 256 / tx) continue;
     use(tx);
@@ -333,13 +347,14 @@ template <typename T> void tune_tiles(ibdl_batch_s* B, Group& G, GroupWork<T>& W
     for (int2& v : it) v.x = 0;
     int2* ditems = (int2*)B->dalloc(sizeof(int2) * std::max<size_t>(it.size(), 1));
     IBDL_HIP(hipMemcpyAsync(ditems, it.data(), sizeof(int2) * it.size(), hipMemcpyHostToDevice, B->st));
-    RowList rl;
-    rl.rpf = rows;
-    rl.seg = G.seg_all;
-    rl.seg_log2 = __builtin_ctz((unsigned)tx / 2);
+    Rows2 rw;
+    rw.hi = G.n[1] - 1;
+    rw.seg = G.seg_all;
+    rw.seg_log2 = __builtin_ctz((unsigned)tx / 2);
+    rw.seg_per_field = 1;
     auto run = [&]() {
       spread2_queue<T>(dsg, ditems, (int)it.size(), q - G.aoff, B->spread_blocks, B->st);
-      fft_x_r2c<T>(W.real, W.spec, G.n[0], rows, W.tab.tw[0], B->st, 0, rl, G.nxp);
+      fft2_x_r2c<T>(W.real, W.spec, G.n[0], G.n[1], np, W.tw2, B->st, 0, rw);
     };
     for (int k = 0; k < 2; ++k) run();
     IBDL_HIP(hipEventRecord(e0, B->st));
@@ -368,8 +383,12 @@ template <typename T> GroupWork<T>& group_work(ibdl_batch_s* B, Group& G) {
   if (W.ready) return W;
   const int np = (int)G.probs.size();
   W.tab = make_grid_tables<T>(B->dim, G.n, G.L, G.geom.h, true, [&](size_t bytes) { return B->dalloc(bytes); });
+  if (B->dim == 2) {
+    cplx<T>* st = (cplx<T>*)B->dalloc(sizeof(cplx<T>) * fft2_table_len<T>(G.n[0], G.n[1]));
+    W.tw2 = fft2_tables<T>(G.n[0], G.n[1], W.tab.tw[0], W.tab.tw[1], st, B->st);
+  }
   W.real = (T*)B->dalloc(sizeof(T) * G.ntot * np);
-  W.spec = (cplx<T>*)B->dalloc(sizeof(cplx<T>) * G.nspec * np);
+  W.spec = (cplx<T>*)B->dalloc(sizeof(cplx<T>) * G.nspec<T>(B->dim) * np);
   W.wtab = (cplx<T>*)B->dalloc(sizeof(cplx<T>) * G.nib * 24);
   weight_table<T>(G.wt, G.nib, W.wtab, B->st);
   grid_fill_zero<T>(W.real, G.ntot * np, B->st);
@@ -384,10 +403,10 @@ template <typename T> GroupWork<T>& group_work(ibdl_batch_s* B, Group& G) {
 // narrower pair is taken only when it is at least 3% faster.
 template <typename T> void tune_group(ibdl_batch_s* B, Group& G, GroupWork<T>& W) {
   const int np = (int)G.probs.size();
-  const TuneKey key{1, B->dim, G.n[0], G.n[1], G.n[2], (int)sizeof(T), 1, pow2_bucket(np)};
+  const TuneKey key{B->dim == 2 ? 11 : 1, B->dim, G.n[0], G.n[1], G.n[2], (int)sizeof(T), 1, pow2_bucket(np)};
   if (tune_get(key, &W.tune)) return;
-  const int rmax = fft_x_rpb_max<T>(G.n[0]);
-  const int wmax = fft_line_w_max<T>(G.n[B->dim - 1]);
+  const int rmax = B->dim == 2 ? fft2_rows_max<T>(G.n[0]) : fft_x_rpb_max<T>(G.n[0]);
+  const int wmax = B->dim == 2 ? fft2_lines_max<T>(G.n[1], 1) : fft_line_w_max<T>(G.n[2]);
   hipEvent_t e0, e1;
   IBDL_HIP(hipEventCreate(&e0));
   IBDL_HIP(hipEventCreate(&e1));
@@ -846,7 +865,6 @@ ibdl_status_t ibdl_batch_create(int32_t nprob, const ibdl_config_t* cfgs, const 
       G.ntot = (int64_t)G.n[0] * G.n[1] * G.n[2];
       G.nxh = G.n[0] / 2 + 1;
       G.nxp = (G.nxh + 15) / 16 * 16;
-      G.nspec = G.nxp * G.n[1] * G.n[2];
       const int64_t ntile = (int64_t)g.ntile[0] * g.ntile[1] * g.ntile[2] * np;
       const int64_t maxlist = G.nib * (dim == 2 ? 6 : 12);   // tiles a 6-node window meets (2-D: 4-row tiles)
       G.X = (double*)B->dalloc(sizeof(double) * G.nib * dim);

@@ -1,19 +1,15 @@
-// Periodic-grid FFT passes for gfx950 (wave64), hand-written Stockham autosort.
-//
-// A line of N points is owned by T = N / RMAX threads; thread i holds elements i + s*T
-// (s < RMAX) in registers.  Each radix-R stage does R-point DFTs in registers; stages
-// exchange through LDS; the first stage reads global memory and the last stage leaves the
-// natural-order result in the same register pattern, so a forward and an inverse transform
-// chain without an LDS round trip (used by the fused last-axis pass).
+// FFT passes of three-dimensional grids for gfx950 (wave64), hand-written Stockham autosort
+// (fft_core.h).
 //
 // Passes:  x axis  real <-> half spectrum, by an N/2-point complex FFT of (x_2n + i x_2n+1)
 //                  and the standard even/odd split; rows are staged in LDS with coalesced
 //                  cooperative loads and stores.
-//          strided in-place C2C along y (3-D middle axis), tiles of W adjacent lines so each
+//          strided in-place C2C along y (the middle axis), tiles of W adjacent lines so each
 //                  row of the tile is one contiguous segment.
-//          fused   last axis: forward FFT of every input field, Fourier multiplier
-//                  (screened Poisson / Poisson / Brinkman-Stokes, see mult_coef), inverse FFT of
-//                  the output fields, in one kernel: the spectra never go back to HBM.
+//          fused   last axis: forward FFT of every input field, Fourier multiplier of the scalar
+//                  operators, inverse FFT of the output fields, in one kernel: the spectra never
+//                  go back to HBM.
+#include "fft_core.h"
 #include "kernels.h"
 
 namespace ibdl {
@@ -28,144 +24,11 @@ constexpr int kLdsBytes = 65536;
 constexpr int kLineBlock = 512;
 constexpr int kLineLds = 98304;
 
-// Stockham plan of a length-N line: RMAX elements per thread (the radix of every stage but the last),
-// T = N / RMAX threads per line
-constexpr int plan_rmax(int N) { return (N <= 16) ? N : ((N == 32 || N == 64 || N == 512) ? 8 : 16); }
-template <int N, int RMX = plan_rmax(N)> struct Plan {
-  static constexpr int RMAX = RMX;
-  static constexpr int T = N / RMAX;
-  static constexpr int LR = ilog2c(RMAX);
-  static constexpr int NFULL = ilog2c(N) / LR;
-  static constexpr int REM = N >> (NFULL * LR);
-  static constexpr int NST = NFULL + (REM > 1 ? 1 : 0);
-  static constexpr int radix(int s) { return s < NFULL ? RMAX : REM; }
-  static constexpr int pw(int s) { return 1 << (s * LR); }
-};
-
-__host__ __device__ constexpr double c16(int m) {
-  return m == 0 ? 1.0 : m == 1 ? 0.92387953251128675613 : m == 2 ? 0.70710678118654752440
-       : m == 3 ? 0.38268343236508977173 : m == 4 ? 0.0 : m == 5 ? -0.38268343236508977173
-       : m == 6 ? -0.70710678118654752440 : -0.92387953251128675613;
-}
-__host__ __device__ constexpr double s16(int m) {
-  return m == 0 ? 0.0 : m == 1 ? 0.38268343236508977173 : m == 2 ? 0.70710678118654752440
-       : m == 3 ? 0.92387953251128675613 : m == 4 ? 1.0 : m == 5 ? 0.92387953251128675613
-       : m == 6 ? 0.70710678118654752440 : 0.38268343236508977173;
-}
-
-// In-register DFT of size R (2, 4, 8, 16), natural order in and out.
-template <int R, bool INV, typename C>
-__device__ __forceinline__ void dft(C* x) {
-  using T = decltype(C::x);
-  if constexpr (R == 2) {
-    C a = x[0], b = x[1];
-    x[0] = cadd(a, b);
-    x[1] = csub(a, b);
-  } else if constexpr (R == 4) {
-    C s02 = cadd(x[0], x[2]), d02 = csub(x[0], x[2]);
-    C s13 = cadd(x[1], x[3]), d13 = mul_mi<INV>(csub(x[1], x[3]));
-    x[0] = cadd(s02, s13);
-    x[2] = csub(s02, s13);
-    x[1] = cadd(d02, d13);
-    x[3] = csub(d02, d13);
-  } else {
-    constexpr int H = R / 2;
-    C e[H], o[H];
-#pragma unroll
-    for (int j = 0; j < H; ++j) {
-      e[j] = x[2 * j];
-      o[j] = x[2 * j + 1];
-    }
-    dft<H, INV>(e);
-    dft<H, INV>(o);
-#pragma unroll
-    for (int k = 0; k < H; ++k) {
-      const int m = k * (16 / R);
-      C t;
-      if (k == 0) {
-        t = o[k];
-      } else if (4 * k == R) {
-        t = mul_mi<INV>(o[k]);
-      } else {
-        C w = mk<C>((T)c16(m), (T)(INV ? s16(m) : -s16(m)));
-        t = cmul(o[k], w);
-      }
-      x[k] = cadd(e[k], t);
-      x[k + H] = csub(e[k], t);
-    }
-  }
-}
-
-// BATCH (a table in global memory): all twiddles of the stage are loaded before the first is used,
-// so that their loads are in flight together rather than one latency each; a table staged in LDS
-// is read as it is used.
-template <int N, int S, bool INV, bool BATCH, int RMX, typename C>
-__device__ __forceinline__ void stage_compute(C* v, int i, const C* __restrict__ tw, int tws) {
-  using P = Plan<N, RMX>;
-  constexpr int R = P::radix(S), PP = P::pw(S), NB = P::RMAX / R, TT = P::T;
-  if constexpr (PP > 1) {
-    C w[NB][R];
-#pragma unroll
-    for (int m = 0; m < NB; ++m) {
-      const int k = (i + m * TT) & (PP - 1);
-#pragma unroll
-      for (int j = 1; j < R; ++j) w[m][j] = tw[(j * k * (N / (PP * R))) * tws];
-    }
-    if constexpr (BATCH) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int m = 0; m < NB; ++m)
-#pragma unroll
-      for (int j = 1; j < R; ++j) {
-        if (INV) w[m][j].y = -w[m][j].y;
-        v[m + j * NB] = cmul(v[m + j * NB], w[m][j]);
-      }
-  }
-#pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    C x[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) x[j] = v[m + j * NB];
-    dft<R, INV>(x);
-#pragma unroll
-    for (int j = 0; j < R; ++j) v[m + j * NB] = x[j];
-  }
-}
-
-// LDS slot of line element e: e * es, or, for a contiguous line (es = 1) with PAD > 0, e plus one
-// pad slot every 2^PAD elements, so that a stage's strided stores do not fall into the same banks
-template <int PAD> __device__ __forceinline__ int lslot(int e, int es) { return PAD ? e + (e >> PAD) : e * es; }
-
-template <int N, int S, int RMX, int PAD = 0, typename C>
-__device__ __forceinline__ void stage_store(const C* v, int i, C* lds, int es) {
-  using P = Plan<N, RMX>;
-  constexpr int R = P::radix(S), PP = P::pw(S), NB = P::RMAX / R, TT = P::T;
-#pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    const int b = i + m * TT;
-    const int k = b & (PP - 1);
-#pragma unroll
-    for (int j = 0; j < R; ++j) lds[lslot<PAD>((b - k) * R + k + j * PP, es)] = v[m + j * NB];
-  }
-}
-
-template <int N, int RMX, int PAD = 0, typename C>
-__device__ __forceinline__ void line_load(C* v, int i, const C* lds, int es) {
-#pragma unroll
-  for (int s = 0; s < RMX; ++s) v[s] = lds[lslot<PAD>(i + s * Plan<N, RMX>::T, es)];
-}
-
 // Global loads / stores of a line's register elements i + s*T: element o0 + (i + s*T) * es of the
 // launch-uniform array base.  Addresses are base plus a 32-bit byte offset (the launchers check
 // that no launch spans 4 GiB), i.e. a scalar base and one 32-bit register per access.  One
 // validity branch per line; the row mask is uniform across the launch, so its test is a scalar
 // branch around the masked form.
-template <typename C> __device__ __forceinline__ const C& at(const C* base, unsigned byte) {
-  return *reinterpret_cast<const C*>(reinterpret_cast<const char*>(base) + (size_t)byte);
-}
-template <typename C> __device__ __forceinline__ C& at(C* base, unsigned byte) {
-  return *reinterpret_cast<C*>(reinterpret_cast<char*>(base) + (size_t)byte);
-}
-
 template <int N, int RMX, typename C>
 __device__ __forceinline__ void line_gload(C* v, const C* __restrict__ base, unsigned o0, unsigned es, int i,
                                            bool valid, const RowMask& m) {
@@ -206,11 +69,6 @@ __device__ __forceinline__ void line_gstore(const C* v, C* __restrict__ base, un
   }
 }
 
-// 1/x: the hardware reciprocal in single precision (about one ulp, well inside what the float
-// path resolves), an exact division in double
-__device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double recip(double x) { return 1.0 / x; }
-
 // Full line transform on registers v (pattern i + s*T).  All threads of the block must call it
 // (it contains block barriers when N needs more than one stage).  lds: this line's exchange
 // buffer with element stride es; the caller must not rely on its contents afterwards.
@@ -236,14 +94,8 @@ __device__ __forceinline__ const C* stage_table(C* dst, const C* __restrict__ tw
   return dst;
 }
 
-constexpr int pow2floor(int v) { return v >= 2 ? 2 * pow2floor(v / 2) : 1; }
-
-// Rows per block of the x-axis passes (rows of M = nx / 2 complex points).  Up to M = 1024: as many
-// rows as fit 256 threads and 64 KiB of LDS beside the twiddle table.  Longer rows (M = 2048, 4096:
-// 4096 and 8192 points along x) take one row per block and M / 8 threads, and read the twiddle table
-// from global memory (it stays in L2), which leaves the row alone in LDS (up to 72 KiB) and two or
-// more blocks per CU.
-constexpr int kMaxRow = 4096;
+// Rows per block of the x-axis passes (rows of M = nx / 2 complex points): as many rows as fit 256
+// threads and 64 KiB of LDS beside the twiddle table.
 constexpr int xrmax(int M) { return plan_rmax(M) < 8 ? plan_rmax(M) : 8; }   // elements per thread, x passes
 template <typename TR, int M> struct RowCfg {
   static constexpr int RMX = xrmax(M);
@@ -423,14 +275,10 @@ __global__ __launch_bounds__((RowCfg<T, M>::BLK)) void k_x_c2r(const cplx<T>* __
 template <typename T> constexpr int rmax_t(int N) {
   return sizeof(T) == 8 && N <= 256 && plan_rmax(N) > 8 ? 8 : plan_rmax(N);
 }
-// Elements per thread of the general fused last-axis passes: those that keep two accumulators or
-// two input spectra per element (Stokes, the transposed Stokes pass) and the 1024-point double
-// ones hold 8 instead of 16, and 4 for double two-accumulator lines of 512 points or more, which
-// keeps them clear of register spills and raises occupancy (the single-field pass k_fused1 keeps
-// the default).
-template <typename T> constexpr int fused_rmax(int N, int nacc) {
-  return (sizeof(T) == 8 && nacc >= 2 && N >= 512) ? 4   // double, two accumulators, long lines
-         : (plan_rmax(N) > 8 && (nacc >= 2 || (sizeof(T) == 8 && N >= 1024)) ? 8 : rmax_t<T>(N));
+// Elements per thread of the general fused last-axis passes: the 1024-point double ones hold 8 instead
+// of 16, which keeps them clear of register spills (the single-field pass k_fused1 keeps the default).
+template <typename T> constexpr int fused_rmax(int N) {
+  return plan_rmax(N) > 8 && sizeof(T) == 8 && N >= 1024 ? 8 : rmax_t<T>(N);
 }
 template <typename T, int N, int RX = rmax_t<T>(N), int BLK = kBlock, int LDS = kLdsBytes> struct TileCfg {
   static constexpr int RMX = RX;
@@ -531,317 +379,63 @@ __global__ __launch_bounds__(kLineBlock) void k_strided(cplx<T>* __restrict__ da
 }
 
 // ------------------------------------------------------------------ Fourier multiplier
-// Coefficient of input field kind fk for output component o at one mode.
-//   scalar:  u^ = alpha*sc * (sum_f c_f F^_f) / (c2*sigma - c0),  c_f = i k~_d (FK_D*) or 1 (FK_MASS);
-//            zero where c2*sigma - c0 = 0 (mean-zero inverse).
-//   Stokes:  u^ = alpha*sc * [ i k~ s^/ell + (1/lam) P^ (G^ + mu v^) ],  ell = -sigma,
-//            lam = c2*ell + c0, P^ = I - k~ k~^T / ell (I at ell = 0), s = (A11 + A22)/2,
-//            v_i = sum_j i k~_j A_ij; 1/ell and 1/lam read as 0 where they vanish.
-//   pressure (mode 3, Stokes fields, one output; the G fields hold eta S Q - g~):
-//            p^ = alpha*sc * [ -i k~_j G^_j + mu k~_i k~_j A^_ij + (c2 sigma - c0) s^ ] / ell.
-template <typename T>
-__device__ __forceinline__ cplx<T> mult_coef(const MultDesc& md, int fk, int o, T sig, const T* kt) {
-  using C = cplx<T>;
-  if (!md.stokes) {
-    const T den = (T)md.c2 * sig - (T)md.c0;
-    const T g = den == (T)0 ? (T)0 : (T)(md.alpha * md.sc) * recip(den);
-    if (fk == FK_MASS) return mk<C>(g, 0);
-    return mk<C>(0, g * kt[fk]);
-  }
-  const T ell = -sig;
-  const T il = ell == (T)0 ? (T)0 : recip(ell);
-  const T lam = (T)md.c2 * ell + (T)md.c0;
-  const T is = lam == (T)0 ? (T)0 : recip(lam);
-  const T ko = kt[o];
-  const T P0 = (o == 0 ? (T)1 : (T)0) - ko * kt[0] * il;
-  const T P1 = (o == 1 ? (T)1 : (T)0) - ko * kt[1] * il;
-  const T mu = (T)md.mu, a = (T)(md.alpha * md.sc);
-  if (md.mode == 3) {   // pressure (2-D): [i k~.(g^ - f^) + (c2 sigma - c0) s^] / ell
-    const T lamh = (T)0.5 * ((T)md.c2 * sig - (T)md.c0);
-    switch (fk) {
-      case FK_A11: return mk<C>(a * il * (mu * kt[0] * kt[0] + lamh), 0);
-      case FK_A12: return mk<C>(a * il * ((T)2 * mu * kt[0] * kt[1]), 0);
-      case FK_A22: return mk<C>(a * il * (mu * kt[1] * kt[1] + lamh), 0);
-      case FK_G1: return mk<C>(0, -a * il * kt[0]);
-      default: return mk<C>(0, -a * il * kt[1]);
-    }
-  }
-  switch (fk) {
-    case FK_A11: return mk<C>(0, a * ((T)0.5 * ko * il + mu * is * P0 * kt[0]));
-    case FK_A12: return mk<C>(0, a * (mu * is * (P0 * kt[1] + P1 * kt[0])));
-    case FK_A22: return mk<C>(0, a * ((T)0.5 * ko * il + mu * is * P1 * kt[1]));
-    case FK_G1: return mk<C>(a * is * P0, 0);
-    default: return mk<C>(a * is * P1, 0);
-  }
-}
-
-// The Stokes coefficient of mult_coef with 1/ell and 1/lam of the mode given (2-D: k~ = (k0, k1)).
-template <typename T>
-__device__ __forceinline__ cplx<T> stokes_coef(const MultDesc& md, int fk, int o, T sig, T k0, T k1, T il, T is) {
-  using C = cplx<T>;
-  const T ko = o == 0 ? k0 : k1;
-  const T P0 = (o == 0 ? (T)1 : (T)0) - ko * k0 * il;
-  const T P1 = (o == 1 ? (T)1 : (T)0) - ko * k1 * il;
-  const T mu = (T)md.mu, a = (T)(md.alpha * md.sc);
-  if (md.mode == 3) {
-    const T lamh = (T)0.5 * ((T)md.c2 * sig - (T)md.c0);
-    switch (fk) {
-      case FK_A11: return mk<C>(a * il * (mu * k0 * k0 + lamh), 0);
-      case FK_A12: return mk<C>(a * il * ((T)2 * mu * k0 * k1), 0);
-      case FK_A22: return mk<C>(a * il * (mu * k1 * k1 + lamh), 0);
-      case FK_G1: return mk<C>(0, -a * il * k0);
-      default: return mk<C>(0, -a * il * k1);
-    }
-  }
-  switch (fk) {
-    case FK_A11: return mk<C>(0, a * ((T)0.5 * ko * il + mu * is * P0 * k0));
-    case FK_A12: return mk<C>(0, a * (mu * is * (P0 * k1 + P1 * k0)));
-    case FK_A22: return mk<C>(0, a * ((T)0.5 * ko * il + mu * is * P1 * k1));
-    case FK_G1: return mk<C>(a * is * P0, 0);
-    default: return mk<C>(a * is * P1, 0);
-  }
-}
-
-// Where a line of the last-axis passes lives and which modes it holds.  3-D: line l of the (jy, jx)
-// plane, elements strided by P, element e is mode e; 2-D: line jx, elements strided by P = nxp.
-// SPLIT (2-D lines of a four-step y transform, md.split = N1, see fft_fused_last): line
-// (jx, k1 = l / nxp) holds the y modes k1 + N1 e, stored from row k1 N with stride nxp, and takes the
-// twiddles w_n^(e k1) between the two factors' transforms.
-template <int N, bool SPLIT> struct LineGeo {
-  unsigned base, es;   // first element, element stride
-  int k1, ms;
-  __device__ __forceinline__ LineGeo(const MultDesc& md, int l, int64_t P, int jx, int jy2) {
-    if constexpr (SPLIT) {
-      base = (unsigned)(jy2 * N * md.nxp + jx);
-      es = (unsigned)md.nxp;
-      k1 = jy2;
-      ms = md.split;
-    } else {
-      base = (unsigned)l;
-      es = (unsigned)P;
-      k1 = 0;
-      ms = 1;
-    }
-  }
-  __device__ __forceinline__ int mode(int e) const {   // mode index along the line of element e
-    if constexpr (SPLIT) return k1 + ms * e;
-    else return e;
-  }
-  __device__ __forceinline__ int tws() const { return SPLIT ? ms : 1; }   // twiddle stride of the N-point transforms
-};
-
-// the four-step twiddles w_n^(e k1) (conjugated for the inverse) on a line's register elements
-template <int RM, int TT, typename C>
-__device__ __forceinline__ void split_twiddle(C* v, int i, int k1, const C* __restrict__ twn, bool inv) {
-  C w[RM];
-#pragma unroll
-  for (int s = 0; s < RM; ++s) w[s] = twn[(i + s * TT) * k1];
-#pragma unroll
-  for (int s = 0; s < RM; ++s) v[s] = cmul(v[s], inv ? cconj(w[s]) : w[s]);
-}
-
-template <typename T, int N, int NO, bool STOKES, bool SPLIT>
+// u^ = alpha*sc * (sum_f c_f F^_f) / (c2*sigma - c0), c_f = i k~_d (FK_D*) or 1 (FK_MASS); zero where
+// c2*sigma - c0 = 0 (mean-zero inverse).
+// Line l = jy nxp + jx of the (jy, jx) plane, elements strided by the plane size P; element e is mode e.
+template <typename T, int N>
 __global__ __launch_bounds__(kBlock) void k_fused(cplx<T>* __restrict__ data, int64_t P, MultDesc md,
                                                   const cplx<T>* __restrict__ twg, int W, int64_t bstride, RowMask rm) {
   using C = cplx<T>;
-  using TC = TileCfg<T, N, fused_rmax<T>(N, NO)>;
+  using TC = TileCfg<T, N, fused_rmax<T>(N)>;
   constexpr int RM = TC::RMX, TT = TC::T_;
   extern __shared__ __align__(16) unsigned char smem[];
   C* lds = reinterpret_cast<C*>(smem);
   data += (int64_t)blockIdx.y * bstride;   // problem of a batch
   const int tid = threadIdx.x;
-  const int tws = SPLIT ? md.split : 1;
-  const C* tw = TC::TWL ? stage_table(lds + N * W, twg, N, tid, W * TC::T_, tws) : twg;
-  const int ltws = TC::TWL ? 1 : tws;
+  const C* tw = TC::TWL ? stage_table(lds + N * W, twg, N, tid, W * TC::T_) : twg;
   const int c = tid & (W - 1), i = tid / W;
   unsigned lq_, li_;   // row and x mode of this thread's line; padding lines are skipped
   const bool valid = tile_lines(md.map, tile_of_block<C>(W), c, W, (unsigned)md.nxp, (unsigned)md.nxh, P, lq_, li_);
-  const int l = (int)(lq_ * (unsigned)md.nxp + li_);
-  const int64_t FS = P * N;
-  // mode indices of this line: 2-D l = jx (+ nxp k1 with a split), e = jy; 3-D l = jy*nxh + jx, e = jz
-  const int jx = (int)(valid ? li_ : 0u);
-  const int jy2 = (int)(valid ? lq_ : 0u);
-  const bool d3 = md.dim == 3;
-  const LineGeo<N, SPLIT> lg(md, l, P, jx, jy2);
-  const T* sgl = static_cast<const T*>(md.sig[d3 ? 2 : 1]);   // symbols along the line
-  const T* ktl_ = static_cast<const T*>(md.kt[d3 ? 2 : 1]);
-  T sig_l = static_cast<const T*>(md.sig[0])[jx];
-  T ktl[3];
-  ktl[0] = static_cast<const T*>(md.kt[0])[jx];
-  ktl[1] = 0;
-  ktl[2] = 0;
-  if (d3) {
-    sig_l += static_cast<const T*>(md.sig[1])[jy2];
-    ktl[1] = static_cast<const T*>(md.kt[1])[jy2];
-  }
-  const int la = d3 ? 2 : 1;   // index of the line axis among the derivative components
-  C acc[NO][RM];
-#pragma unroll
-  for (int o = 0; o < NO; ++o)
-#pragma unroll
-    for (int s = 0; s < RM; ++s) acc[o][s] = mk<C>(0, 0);
-  T gfac[RM];   // scalar: multiplier alpha*sc / (c2 sigma - c0); Stokes (2-D): 1/ell
-  T glam[STOKES ? RM : 1];   // Stokes: 1/lam
-  if constexpr (!STOKES) {
-#pragma unroll
-    for (int s = 0; s < RM; ++s) {
-      const T den = (T)md.c2 * (sig_l + sgl[lg.mode(i + s * TT)]) - (T)md.c0;
-      gfac[s] = den == (T)0 ? (T)0 : (T)(md.alpha * md.sc) * recip(den);
-    }
-  } else {
-#pragma unroll
-    for (int s = 0; s < RM; ++s) {
-      const T ell = -(sig_l + sgl[lg.mode(i + s * TT)]);
-      gfac[s] = ell == (T)0 ? (T)0 : recip(ell);
-      const T lam = (T)md.c2 * ell + (T)md.c0;
-      glam[s] = lam == (T)0 ? (T)0 : recip(lam);
-    }
-  }
-
-  for (int f = 0; f < md.nc; ++f) {
-    C v[RM];
-    line_gload<N, RM>(v, data, (unsigned)(f * FS + lg.base), lg.es, i, valid, rm);
-    if constexpr (SPLIT) split_twiddle<RM, TT>(v, i, lg.k1, twg, false);
-    fft_line<N, false, !TC::TWL, RM>(v, i, lds + c, W, tw, ltws);
-    const int fk = md.fk[f];
-    if constexpr (!STOKES) {
-      if (fk == FK_MASS) {
-#pragma unroll
-        for (int s = 0; s < RM; ++s) acc[0][s] = cadd(acc[0][s], cscale(v[s], gfac[s]));
-      } else if (fk == la) {   // derivative along the line axis: k~ varies per element
-#pragma unroll
-        for (int s = 0; s < RM; ++s) acc[0][s] = cadd(acc[0][s], mul_ir(v[s], gfac[s] * ktl_[lg.mode(i + s * TT)]));
-      } else {                 // derivative across lines: k~ is constant on the line
-        const T kc = ktl[fk];
-#pragma unroll
-        for (int s = 0; s < RM; ++s) acc[0][s] = cadd(acc[0][s], mul_ir(v[s], gfac[s] * kc));
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < RM; ++s) {   // Stokes is two-dimensional: k~ = (k~ across lines, k~ along)
-        const int e = lg.mode(i + s * TT);
-        const T sig = sig_l + sgl[e];
-#pragma unroll
-        for (int o = 0; o < NO; ++o)
-          acc[o][s] = cadd(acc[o][s], cmul(stokes_coef<T>(md, fk, o, sig, ktl[0], ktl_[e], gfac[s], glam[s]), v[s]));
-      }
-    }
-  }
-#pragma unroll
-  for (int o = 0; o < NO; ++o) {
-    fft_line<N, true, !TC::TWL, RM>(acc[o], i, lds + c, W, tw, ltws);
-    if constexpr (SPLIT) split_twiddle<RM, TT>(acc[o], i, lg.k1, twg, true);
-    line_gstore<N, RM>(acc[o], data, (unsigned)(o * FS + lg.base), lg.es, i, valid, rm);
-  }
-}
-
-// The Stokes pass of 2-D problems with up to five input fields, the transforms of all fields taken
-// together: each radix stage works on every field's registers before one pair of barriers and one
-// LDS exchange (a buffer per field), and the two outputs' inverse transforms likewise.  A line
-// then waits for the latency of two transforms instead of nc + 2 in sequence (k_fused<.., STOKES>).
-// The double-precision 1024-point lines (one line of 256 threads per workgroup, half a thousand
-// lines per problem) stay bound by the L2 requests of their 16-byte row accesses.  Twiddles are
-// read from global memory (L2).
-constexpr int kStokesFields = 5;
-constexpr int kStokesLds = 81920;   // two workgroups per CU
-template <typename T, int N> struct StokesCfg {
-  static constexpr int RMX = fused_rmax<T>(N, 2);
-  static constexpr int T_ = Plan<N, RMX>::T;
-  static constexpr int W0 = kBlock / T_;
-  static constexpr int WL = kStokesLds / (kStokesFields * N * (int)sizeof(cplx<T>));
-  static constexpr int W = pow2floor((W0 < WL ? W0 : WL) > 0 ? (W0 < WL ? W0 : WL) : 1);
-  static constexpr int NT = W * T_;
-};
-
-template <int N, bool INV, int NF, int RMX, int S = 0, typename C>
-__device__ __forceinline__ void fft_lines_multi(C (&v)[NF][RMX], int nf, int i, C* lds, int es, int fstride,
-                                                const C* __restrict__ tw, int tws) {
-  if constexpr (S < Plan<N, RMX>::NST) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-      if (f < nf) stage_compute<N, S, INV, true, RMX>(v[f], i, tw, tws);
-    if constexpr (S + 1 < Plan<N, RMX>::NST) {
-      __syncthreads();
-#pragma unroll
-      for (int f = 0; f < NF; ++f)
-        if (f < nf) stage_store<N, S, RMX>(v[f], i, lds + f * fstride, es);
-      __syncthreads();
-#pragma unroll
-      for (int f = 0; f < NF; ++f)
-        if (f < nf) line_load<N, RMX>(v[f], i, lds + f * fstride, es);
-    }
-    fft_lines_multi<N, INV, NF, RMX, S + 1>(v, nf, i, lds, es, fstride, tw, tws);
-  }
-}
-
-template <typename T, int N, bool SPLIT>
-__global__ __launch_bounds__(kBlock) void k_fused_stokes2(cplx<T>* __restrict__ data, int64_t P, MultDesc md,
-                                                          const cplx<T>* __restrict__ twg, int W, int64_t bstride,
-                                                          RowMask rm) {
-  using C = cplx<T>;
-  using SC = StokesCfg<T, N>;
-  constexpr int RM = SC::RMX, TT = SC::T_, NF = kStokesFields;
-  extern __shared__ __align__(16) unsigned char smem[];
-  C* lds = reinterpret_cast<C*>(smem);
-  data += (int64_t)blockIdx.y * bstride;   // problem of a batch
-  const int tid = threadIdx.x;
-  const int tws = SPLIT ? md.split : 1;
-  const int c = tid & (W - 1), i = tid / W;
-  unsigned lq_, li_;   // row and x mode of this thread's line; padding lines are skipped
-  const bool valid = tile_lines(md.map, tile_of_block<C>(W), c, W, (unsigned)md.nxp, (unsigned)md.nxh, P, lq_, li_);
-  const int l = (int)(lq_ * (unsigned)md.nxp + li_);
+  const unsigned l = lq_ * (unsigned)md.nxp + li_;
   const int64_t FS = P * N;
   const int jx = (int)(valid ? li_ : 0u);
-  const int jy2 = (int)(valid ? lq_ : 0u);
-  const LineGeo<N, SPLIT> lg(md, l, P, jx, jy2);
-  const T* sgl = static_cast<const T*>(md.sig[1]);
-  const T* ktl_ = static_cast<const T*>(md.kt[1]);
-  const T sig_l = static_cast<const T*>(md.sig[0])[jx];
-  const T kx = static_cast<const T*>(md.kt[0])[jx];
-  const int nc = md.nc;
-  C v[NF][RM];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    if (f < nc) {
-      line_gload<N, RM>(v[f], data, (unsigned)(f * FS + lg.base), lg.es, i, valid, rm);
-      if constexpr (SPLIT) split_twiddle<RM, TT>(v[f], i, lg.k1, twg, false);
-    } else {
-#pragma unroll
-      for (int s = 0; s < RM; ++s) v[f][s] = mk<C>(0, 0);
-    }
-  }
-  fft_lines_multi<N, false, NF, RM>(v, nc, i, lds + c, W, N * W, twg, tws);
-  C acc[2][RM];
+  const int jy = (int)(valid ? lq_ : 0u);
+  const T* sgl = static_cast<const T*>(md.sig[2]);   // symbols along the line
+  const T* ktl_ = static_cast<const T*>(md.kt[2]);
+  const T sig_l = static_cast<const T*>(md.sig[0])[jx] + static_cast<const T*>(md.sig[1])[jy];
+  const T ktl[2] = {static_cast<const T*>(md.kt[0])[jx], static_cast<const T*>(md.kt[1])[jy]};
+  C acc[RM];
+  T gfac[RM];   // multiplier alpha*sc / (c2 sigma - c0)
 #pragma unroll
   for (int s = 0; s < RM; ++s) {
-    const int e = lg.mode(i + s * TT);
-    const T sig = sig_l + sgl[e];
-    const T ke = ktl_[e];
-    const T ell = -sig;
-    const T il = ell == (T)0 ? (T)0 : recip(ell);
-    const T lam = (T)md.c2 * ell + (T)md.c0;
-    const T is = lam == (T)0 ? (T)0 : recip(lam);
-    acc[0][s] = mk<C>(0, 0);
-    acc[1][s] = mk<C>(0, 0);
+    acc[s] = mk<C>(0, 0);
+    const T den = (T)md.c2 * (sig_l + sgl[i + s * TT]) - (T)md.c0;
+    gfac[s] = den == (T)0 ? (T)0 : (T)(md.alpha * md.sc) * recip(den);
+  }
+  for (int f = 0; f < md.nc; ++f) {
+    C v[RM];
+    line_gload<N, RM>(v, data, (unsigned)(f * FS + l), (unsigned)P, i, valid, rm);
+    fft_line<N, false, !TC::TWL, RM>(v, i, lds + c, W, tw, 1);
+    const int fk = md.fk[f];
+    if (fk == FK_MASS) {
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      if (f < nc) {
-        acc[0][s] = cadd(acc[0][s], cmul(stokes_coef<T>(md, md.fk[f], 0, sig, kx, ke, il, is), v[f][s]));
-        acc[1][s] = cadd(acc[1][s], cmul(stokes_coef<T>(md, md.fk[f], 1, sig, kx, ke, il, is), v[f][s]));
-      }
+      for (int s = 0; s < RM; ++s) acc[s] = cadd(acc[s], cscale(v[s], gfac[s]));
+    } else if (fk == FK_DZ) {   // derivative along the line axis: k~ varies per element
+#pragma unroll
+      for (int s = 0; s < RM; ++s) acc[s] = cadd(acc[s], mul_ir(v[s], gfac[s] * ktl_[i + s * TT]));
+    } else {                 // derivative across lines: k~ is constant on the line
+      const T kc = ktl[fk];
+#pragma unroll
+      for (int s = 0; s < RM; ++s) acc[s] = cadd(acc[s], mul_ir(v[s], gfac[s] * kc));
     }
   }
-  fft_lines_multi<N, true, 2, RM>(acc, 2, i, lds + c, W, N * W, twg, tws);
-#pragma unroll
-  for (int o = 0; o < 2; ++o) {
-    if constexpr (SPLIT) split_twiddle<RM, TT>(acc[o], i, lg.k1, twg, true);
-    line_gstore<N, RM>(acc[o], data, (unsigned)(o * FS + lg.base), lg.es, i, valid, rm);
-  }
+  fft_line<N, true, !TC::TWL, RM>(acc, i, lds + c, W, tw, 1);
+  line_gstore<N, RM>(acc, data, l, (unsigned)P, i, valid, rm);
 }
 
 // Single scalar field (the finite-difference operator and the scalar grid solve): forward FFT,
 // multiply by the real factor alpha*sc / (c2 sigma - c0) in registers, inverse FFT.
-template <typename T, int N, bool SPLIT, int RX = rmax_t<T>(N)>
+template <typename T, int N, int RX = rmax_t<T>(N)>
 __global__ __launch_bounds__(kLineBlock) void k_fused1(cplx<T>* __restrict__ data, int64_t P, MultDesc md,
                                                        const cplx<T>* __restrict__ twg, int W, int64_t bstride,
                                                        RowMask rm) {
@@ -852,101 +446,69 @@ __global__ __launch_bounds__(kLineBlock) void k_fused1(cplx<T>* __restrict__ dat
   C* lds = reinterpret_cast<C*>(smem);
   data += (int64_t)blockIdx.y * bstride;   // problem of a batch
   const int tid = threadIdx.x;
-  const int tws = SPLIT ? md.split : 1;
-  const C* tw = TC::TWL ? stage_table(lds + N * W, twg, N, tid, W * TC::T_, tws) : twg;
-  const int ltws = TC::TWL ? 1 : tws;
+  const C* tw = TC::TWL ? stage_table(lds + N * W, twg, N, tid, W * TC::T_) : twg;
   const int c = tid & (W - 1), i = tid / W;
   unsigned lq_, li_;   // row and x mode of this thread's line; padding lines are skipped
   const bool valid = tile_lines(md.map, tile_of_block<C>(W), c, W, (unsigned)md.nxp, (unsigned)md.nxh, P, lq_, li_);
-  const int l = (int)(lq_ * (unsigned)md.nxp + li_);
+  const unsigned l = lq_ * (unsigned)md.nxp + li_;
   const int jx = (int)(valid ? li_ : 0u);
-  const int jy2 = (int)(valid ? lq_ : 0u);
-  const bool d3 = md.dim == 3;
-  const LineGeo<N, SPLIT> lg(md, l, P, jx, jy2);
-  const T* sgl = static_cast<const T*>(md.sig[d3 ? 2 : 1]);
-  T sig_l = static_cast<const T*>(md.sig[0])[jx];
-  if (d3) sig_l += static_cast<const T*>(md.sig[1])[jy2];
+  const int jy = (int)(valid ? lq_ : 0u);
+  const T* sgl = static_cast<const T*>(md.sig[2]);
+  const T sig_l = static_cast<const T*>(md.sig[0])[jx] + static_cast<const T*>(md.sig[1])[jy];
   C v[RM];
-  line_gload<N, RM>(v, data, lg.base, lg.es, i, valid, rm);
-  if constexpr (SPLIT) split_twiddle<RM, TT>(v, i, lg.k1, twg, false);
-  fft_line<N, false, !TC::TWL, RM>(v, i, lds + c, W, tw, ltws);
+  line_gload<N, RM>(v, data, l, (unsigned)P, i, valid, rm);
+  fft_line<N, false, !TC::TWL, RM>(v, i, lds + c, W, tw, 1);
   const T num = (T)(md.alpha * md.sc), c2 = (T)md.c2, c0 = (T)md.c0;
 #pragma unroll
   for (int s = 0; s < RM; ++s) {
-    const T den = c2 * (sig_l + sgl[lg.mode(i + s * TT)]) - c0;
+    const T den = c2 * (sig_l + sgl[i + s * TT]) - c0;
     v[s] = cscale(v[s], den == (T)0 ? (T)0 : num * recip(den));
   }
-  fft_line<N, true, !TC::TWL, RM>(v, i, lds + c, W, tw, ltws);
-  if constexpr (SPLIT) split_twiddle<RM, TT>(v, i, lg.k1, twg, true);
-  line_gstore<N, RM>(v, data, lg.base, lg.es, i, valid, rm);
+  fft_line<N, true, !TC::TWL, RM>(v, i, lds + c, W, tw, 1);
+  line_gstore<N, RM>(v, data, l, (unsigned)P, i, valid, rm);
 }
 
-// Transposed / multi-output pass: the NI input spectra stay in registers after their forward
-// FFTs and the no outputs are formed, inverse transformed and stored one at a time (inputs are
-// all read before the first store, and each workgroup owns its lines in every field).
-template <typename T, int N, int NI, int MODE, bool SPLIT>
-__global__ __launch_bounds__(kBlock) void k_fused_adj(cplx<T>* __restrict__ data, int64_t P, int no, MultDesc md,
-                                                      const cplx<T>* __restrict__ twg, int W, int64_t bstride, RowMask rm) {
+// Gradient outputs (mode 1): the input spectrum stays in registers after its forward FFT and the no
+// outputs i k~_o g F^ (o < 3), g F^ are formed, inverse transformed and stored one at a time (the
+// input is read before the first store, and each workgroup owns its lines in every field).
+template <typename T, int N>
+__global__ __launch_bounds__(kBlock) void k_fused_grad(cplx<T>* __restrict__ data, int64_t P, int no, MultDesc md,
+                                                       const cplx<T>* __restrict__ twg, int W, int64_t bstride,
+                                                       RowMask rm) {
   using C = cplx<T>;
-  using TC = TileCfg<T, N, fused_rmax<T>(N, NI)>;
+  using TC = TileCfg<T, N, fused_rmax<T>(N)>;
   constexpr int RM = TC::RMX, TT = TC::T_;
   extern __shared__ __align__(16) unsigned char smem[];
   C* lds = reinterpret_cast<C*>(smem);
   data += (int64_t)blockIdx.y * bstride;   // problem of a batch
   const int tid = threadIdx.x;
-  const int tws = SPLIT ? md.split : 1;
-  const C* tw = TC::TWL ? stage_table(lds + N * W, twg, N, tid, W * TC::T_, tws) : twg;
-  const int ltws = TC::TWL ? 1 : tws;
+  const C* tw = TC::TWL ? stage_table(lds + N * W, twg, N, tid, W * TC::T_) : twg;
   const int c = tid & (W - 1), i = tid / W;
   unsigned lq_, li_;   // row and x mode of this thread's line; padding lines are skipped
   const bool valid = tile_lines(md.map, tile_of_block<C>(W), c, W, (unsigned)md.nxp, (unsigned)md.nxh, P, lq_, li_);
-  const int l = (int)(lq_ * (unsigned)md.nxp + li_);
+  const unsigned l = lq_ * (unsigned)md.nxp + li_;
   const int64_t FS = P * N;
   const int jx = (int)(valid ? li_ : 0u);
-  const int jy2 = (int)(valid ? lq_ : 0u);
-  const bool d3 = md.dim == 3;
-  const LineGeo<N, SPLIT> lg(md, l, P, jx, jy2);
-  const T* sgl = static_cast<const T*>(md.sig[d3 ? 2 : 1]);
-  const T* ktl_ = static_cast<const T*>(md.kt[d3 ? 2 : 1]);
-  T sig_l = static_cast<const T*>(md.sig[0])[jx];
-  T ktl[3];
-  ktl[0] = static_cast<const T*>(md.kt[0])[jx];
-  ktl[1] = 0;
-  ktl[2] = 0;
-  if (d3) {
-    sig_l += static_cast<const T*>(md.sig[1])[jy2];
-    ktl[1] = static_cast<const T*>(md.kt[1])[jy2];
-  }
-  const int la = d3 ? 2 : 1;
-  C v[NI][RM];
-#pragma unroll
-  for (int f = 0; f < NI; ++f) {
-    line_gload<N, RM>(v[f], data, (unsigned)(f * FS + lg.base), lg.es, i, valid, rm);
-    if constexpr (SPLIT) split_twiddle<RM, TT>(v[f], i, lg.k1, twg, false);
-    fft_line<N, false, !TC::TWL, RM>(v[f], i, lds + c, W, tw, ltws);
-  }
+  const int jy = (int)(valid ? lq_ : 0u);
+  const T* sgl = static_cast<const T*>(md.sig[2]);
+  const T* ktl_ = static_cast<const T*>(md.kt[2]);
+  const T sig_l = static_cast<const T*>(md.sig[0])[jx] + static_cast<const T*>(md.sig[1])[jy];
+  const T k0 = static_cast<const T*>(md.kt[0])[jx], k1 = static_cast<const T*>(md.kt[1])[jy];
+  C v[RM];
+  line_gload<N, RM>(v, data, l, (unsigned)P, i, valid, rm);
+  fft_line<N, false, !TC::TWL, RM>(v, i, lds + c, W, tw, 1);
   for (int o = 0; o < no; ++o) {
     C acc[RM];
 #pragma unroll
     for (int s = 0; s < RM; ++s) {
-      const int e = lg.mode(i + s * TT);
-      T kt[3] = {ktl[0], ktl[1], ktl[2]};
-      kt[la] = ktl_[e];
-      const T sig = sig_l + sgl[e];
-      if constexpr (MODE == 1) {
-        const T den = (T)md.c2 * sig - (T)md.c0;
-        const T g = den == (T)0 ? (T)0 : (T)(md.alpha * md.sc) * recip(den);
-        const T ko = o == 0 ? kt[0] : (o == 1 ? kt[1] : kt[2]);
-        acc[s] = o < md.dim ? mul_ir(v[0][s], g * ko) : cscale(v[0][s], g);
-      } else {
-        acc[s] = mk<C>(0, 0);
-#pragma unroll
-        for (int f = 0; f < NI; ++f) acc[s] = cadd(acc[s], cmul(cconj(mult_coef<T>(md, md.fk[o], f, sig, kt)), v[f][s]));
-      }
+      const int e = i + s * TT;
+      const T den = (T)md.c2 * (sig_l + sgl[e]) - (T)md.c0;
+      const T g = den == (T)0 ? (T)0 : (T)(md.alpha * md.sc) * recip(den);
+      const T ko = o == 0 ? k0 : (o == 1 ? k1 : ktl_[e]);
+      acc[s] = o < 3 ? mul_ir(v[s], g * ko) : cscale(v[s], g);
     }
-    fft_line<N, true, !TC::TWL, RM>(acc, i, lds + c, W, tw, ltws);
-    if constexpr (SPLIT) split_twiddle<RM, TT>(acc, i, lg.k1, twg, true);
-    line_gstore<N, RM>(acc, data, (unsigned)(o * FS + lg.base), lg.es, i, valid, rm);
+    fft_line<N, true, !TC::TWL, RM>(acc, i, lds + c, W, tw, 1);
+    line_gstore<N, RM>(acc, data, (unsigned)(o * FS + l), (unsigned)P, i, valid, rm);
   }
 }
 
@@ -964,20 +526,6 @@ template <typename F> void dispatch_n(int n, F&& f) {
     default: throw Error(-2, "unsupported FFT length " + std::to_string(n));
   }
 }
-// x-pass rows: M = nx / 2 up to kMaxRow
-template <typename F> void dispatch_row(int m, F&& f) {
-  switch (m) {
-    case 2048: f(std::integral_constant<int, 2048>{}); break;
-    case 4096: f(std::integral_constant<int, 4096>{}); break;
-    default: dispatch_n(m, f);
-  }
-}
-
-// Lines longer than kMaxLine (2-D y axis of 2048 to 8192 points) run as a four-step transform
-// n = kSplit * (n / kSplit): see fft_fused_last.
-constexpr int kMaxLine = 1024;
-constexpr int kSplit = 8;
-
 }  // namespace
 
 int fft_supported(int n) { return n >= 16 && n <= 1024 && (n & (n - 1)) == 0; }
@@ -985,14 +533,14 @@ int fft_supported(int n) { return n >= 16 && n <= 1024 && (n & (n - 1)) == 0; }
 template <typename T>
 int fft_x_rpb_max(int nx) {
   int r = 0;
-  dispatch_row(nx / 2, [&](auto Mc) { r = RowCfg<T, decltype(Mc)::value>::RPB; });
+  dispatch_n(nx / 2, [&](auto Mc) { r = RowCfg<T, decltype(Mc)::value>::RPB; });
   return r;
 }
 
 template <typename T>
 int fft_line_w_max(int n, int plan) {
   int r = 0;
-  dispatch_n(n > kMaxLine ? n / kSplit : n, [&](auto Nc) {
+  dispatch_n(n, [&](auto Nc) {
     constexpr int N = decltype(Nc)::value;
     r = plan == 1 ? LineCfg<T, N, plan_rx<T>(N, 1)>::W : LineCfg<T, N>::W;
   });
@@ -1002,7 +550,7 @@ int fft_line_w_max(int n, int plan) {
 template <typename T>
 int fft_line_plans(int n) {
   int r = 1;
-  dispatch_n(n > kMaxLine ? n / kSplit : n, [&](auto Nc) {
+  dispatch_n(n, [&](auto Nc) {
     constexpr int N = decltype(Nc)::value;
     r = plan_rx<T>(N, 1) != plan_rx<T>(N, 0) ? 2 : 1;
   });
@@ -1023,7 +571,7 @@ template <typename T, typename TI>
 void x_r2c_launch(const TI* in, cplx<T>* out, int nx, int64_t nrows, const cplx<T>* tw_x, hipStream_t s, int rpb,
                   const RowList& rl, int64_t pitch) {
   if (pitch <= 0) pitch = nx / 2 + 1;
-  dispatch_row(nx / 2, [&](auto Mc) {
+  dispatch_n(nx / 2, [&](auto Mc) {
     constexpr int M = decltype(Mc)::value;
     using RC = RowCfg<T, M>;
     const int R = pick(rpb, RC::RPB);
@@ -1052,7 +600,7 @@ template <typename T>
 void fft_x_c2r(const cplx<T>* in, T* out, int nx, int64_t nrows, const cplx<T>* tw_x, hipStream_t s, int rpb,
                const RowList& rl, int64_t pitch) {
   if (pitch <= 0) pitch = nx / 2 + 1;
-  dispatch_row(nx / 2, [&](auto Mc) {
+  dispatch_n(nx / 2, [&](auto Mc) {
     constexpr int M = decltype(Mc)::value;
     using RC = RowCfg<T, M>;
     const int R = pick(rpb, RC::RPB);
@@ -1103,28 +651,6 @@ template <typename T>
 void fft_fused_last(cplx<T>* data, int n, int64_t P, int no, const MultDesc& md, const cplx<T>* tw, hipStream_t s,
                     int batch, int64_t bstride, int w, const RowMask& rm, int plan) {
   if (batch < 1) return;
-  if (n > kMaxLine) {
-    // Four-step transform of the 2-D y lines, n = N1 N2 (N1 = kSplit): with y = j1 N2 + j2 and mode
-    // k = k1 + N1 k2, the n-point DFT is an N1-point DFT over j1 for each j2 (a strided pass whose
-    // result k1 stays at row k1 N2 + j2), the twiddles w_n^(j2 k1), and an N2-point DFT over j2 for
-    // each k1, which leaves mode k1 + N1 k2 at row k1 N2 + k2.  The fused pass runs on those N2-point
-    // lines (twiddles, transform, multiplier at the modes they hold, inverse, conjugate twiddles) and
-    // an inverse N1-point pass per output field restores natural order.  Row masks do not carry over
-    // to the split lines: the caller provides dense fields (every row valid) and takes every row back.
-    if (md.dim != 2 || batch != 1 || n % kSplit != 0 || n / kSplit > kMaxLine)
-      throw Error(-2, "fused FFT pass: lines over 1024 points are supported for single 2-D problems up to 8192");
-    const int N2 = n / kSplit;
-    const int64_t FS = P * n;
-    const int64_t nin = std::max(md.nc, 1);
-    for (int64_t f = 0; f < nin; ++f)
-      fft_strided<T>(data + f * FS, kSplit, P * N2, P, P, (int64_t)N2 * P, false, tw, s, 0, RowMask(), md.nxh);
-    MultDesc m2 = md;
-    m2.split = kSplit;
-    fft_fused_last<T>(data, N2, P * kSplit, no, m2, tw, s, 1, 0, w, RowMask(), plan);
-    for (int o = 0; o < no; ++o)
-      fft_strided<T>(data + o * FS, kSplit, P * N2, P, P, (int64_t)N2 * P, true, tw, s, 0, RowMask(), md.nxh);
-    return;
-  }
   const int64_t nf = std::max<int64_t>(std::max(md.nc, no), 1);
   if (nf * P * n * (int64_t)sizeof(cplx<T>) > (int64_t)UINT32_MAX || P > INT32_MAX)
     throw Error(-2, "fused FFT pass: one problem's fields may not span 4 GiB");
@@ -1144,59 +670,27 @@ void fft_fused_last(cplx<T>* data, int n, int64_t P, int no, const MultDesc& md,
       blk = dim3(W * TC::T_);
       lds = sizeof(cplx<T>) * (N * W + (TC::TWL ? N : 0));
     };
-    auto run = [&](auto splitc) {
-      constexpr bool SP = decltype(splitc)::value;
-      int W = 0;
-      dim3 grid, blk;
-      size_t lds = 0;
-      const MultDesc& md = mdl;
-      if (md.mode == 1 && md.nc == 1 && no >= 1 && no <= md.dim + 1) {
-        shape(TileCfg<T, N, fused_rmax<T>(N, 1)>{}, W, grid, blk, lds);
-        hipLaunchKernelGGL((k_fused_adj<T, N, 1, 1, SP>), grid, blk, lds, s, data, P, no, md, tw, W, bstride, rm);
-      } else if (md.mode == 2 && md.stokes && md.nc == 2 && no >= 1 && no <= 5) {
-        shape(TileCfg<T, N, fused_rmax<T>(N, 2)>{}, W, grid, blk, lds);
-        hipLaunchKernelGGL((k_fused_adj<T, N, 2, 2, SP>), grid, blk, lds, s, data, P, no, md, tw, W, bstride, rm);
-      } else if (md.mode == 3 && md.stokes && md.dim == 2 && no == 1) {
-        shape(TileCfg<T, N, fused_rmax<T>(N, 1)>{}, W, grid, blk, lds);
-        hipLaunchKernelGGL((k_fused<T, N, 1, true, SP>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
-      } else if (md.mode != 0) {
-        throw Error(-2, "fused pass: unsupported transposed multiplier");
-      } else if (!md.stokes && no == 1 && md.nc == 1 && md.fk[0] == FK_MASS) {
-        if (plan == 1 && plan_rx<T>(N, 1) != plan_rx<T>(N, 0)) {
-          constexpr int RX = plan_rx<T>(N, 1);
-          shape(LineCfg<T, N, RX>{}, W, grid, blk, lds);
-          hipLaunchKernelGGL((k_fused1<T, N, SP, RX>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
-        } else {
-          shape(LineCfg<T, N>{}, W, grid, blk, lds);
-          hipLaunchKernelGGL((k_fused1<T, N, SP>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
-        }
-      } else if (!md.stokes && no == 1) {
-        shape(TileCfg<T, N, fused_rmax<T>(N, 1)>{}, W, grid, blk, lds);
-        hipLaunchKernelGGL((k_fused<T, N, 1, false, SP>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
-      } else if (md.stokes && no == 2 && md.dim == 2 && md.nc <= kStokesFields) {
-        using SC = StokesCfg<T, N>;
-        W = pick(w, SC::W);
-        grid = tiles(W);
-        blk = dim3(W * SC::T_);
-        lds = sizeof(cplx<T>) * (size_t)kStokesFields * N * W;
-        hipLaunchKernelGGL((k_fused_stokes2<T, N, SP>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
-      } else if (md.stokes && no == 2) {
-        shape(TileCfg<T, N, fused_rmax<T>(N, 2)>{}, W, grid, blk, lds);
-        hipLaunchKernelGGL((k_fused<T, N, 2, true, SP>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
+    int W = 0;
+    dim3 grid, blk;
+    size_t lds = 0;
+    const MultDesc& md = mdl;
+    if (md.mode == 1 && md.nc == 1 && no >= 1 && no <= 4) {
+      shape(TileCfg<T, N, fused_rmax<T>(N)>{}, W, grid, blk, lds);
+      hipLaunchKernelGGL((k_fused_grad<T, N>), grid, blk, lds, s, data, P, no, md, tw, W, bstride, rm);
+    } else if (md.mode != 0 || md.stokes || no != 1) {
+      throw Error(-2, "fused pass: unsupported multiplier / output count");
+    } else if (md.nc == 1 && md.fk[0] == FK_MASS) {
+      if (plan == 1 && plan_rx<T>(N, 1) != plan_rx<T>(N, 0)) {
+        constexpr int RX = plan_rx<T>(N, 1);
+        shape(LineCfg<T, N, RX>{}, W, grid, blk, lds);
+        hipLaunchKernelGGL((k_fused1<T, N, RX>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
       } else {
-        throw Error(-2, "fused pass: unsupported multiplier / output count");
-      }
-    };
-    if (md.split > 1) {
-      // the factor lines of 2048- to 8192-point y axes
-      if constexpr (N >= kMaxLine * 2 / kSplit) {
-        if (md.dim != 2 || batch != 1) throw Error(-2, "fused pass: four-step lines are single 2-D problems");
-        run(std::true_type{});
-      } else {
-        throw Error(-2, "fused pass: four-step lines of " + std::to_string(N) + " points are not built");
+        shape(LineCfg<T, N>{}, W, grid, blk, lds);
+        hipLaunchKernelGGL((k_fused1<T, N>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
       }
     } else {
-      run(std::false_type{});
+      shape(TileCfg<T, N, fused_rmax<T>(N)>{}, W, grid, blk, lds);
+      hipLaunchKernelGGL((k_fused<T, N>), grid, blk, lds, s, data, P, md, tw, W, bstride, rm);
     }
   });
   IBDL_LAUNCH_CHECK();

@@ -164,23 +164,25 @@ __global__ void k_wtab(const double* __restrict__ wt, int64_t n_ib, cplx<T>* __r
   tab[e] = t < 6 ? mk<cplx<T>>((T)wt[r * 12 + t], (T)wt[r * 12 + 6 + t]) : mk<cplx<T>>((T)0, (T)0);
 }
 
-// busy tiles along x of each listed row as a bit mask: bit t >> seg_group_log2 for tile (t, strip of
-// the row), t < ntx
+// busy tiles along x of each listed row as a bit mask of seg_row_words words: bit t & 63 of word t >> 6
+// for tile (t, strip of the row), t < ntx; one thread per row and word
 __global__ void k_row_segments(MarkerGeom g, const int* __restrict__ tile_off, const int* __restrict__ rows,
                                int64_t nact, unsigned long long* __restrict__ seg) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nact) return;
+  const int nw = seg_row_words(g);
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= nact * nw) return;
+  const int64_t r = e / nw;
+  const int t0 = 64 * (int)(e - r * nw);
   const int w = rows ? rows[r] : (int)r, y = w % g.n[1], z = w / g.n[1];
   // z counts planes, or problems of a batch in 2-D (tile[2] = 1 there): tiles are numbered
   // problem-major, so the strip index runs on across a batch's problems
   const int64_t strip = y / g.tile[1] + (int64_t)g.ntile[1] * (z / g.tile[2]);
-  const int gs = seg_group_log2(g);
+  const int nt = g.ntile[0] - t0 < 64 ? g.ntile[0] - t0 : 64;
+  const int* off = tile_off + strip * g.ntile[0] + t0;
   unsigned long long m = 0;
-  for (int t = 0; t < g.ntile[0]; ++t) {
-    const int64_t id = strip * g.ntile[0] + t;
-    if (tile_off[id + 1] > tile_off[id]) m |= 1ull << (t >> gs);
-  }
-  seg[r] = m;
+  for (int t = 0; t < nt; ++t)
+    if (off[t + 1] > off[t]) m |= 1ull << t;
+  seg[e] = m;
 }
 
 // ids of the tiles with at least one candidate, in increasing order (off is the exclusive scan of
@@ -1163,8 +1165,8 @@ void exclusive_scan(const int* cnt, int* off, int n, hipStream_t st) {
 void markers_row_segments(const MarkerGeom& g, const int* tile_off, const int* rows, int64_t nact,
                           unsigned long long* seg, hipStream_t st) {
   if (nact <= 0) return;
-  hipLaunchKernelGGL(k_row_segments, dim3((unsigned)((nact + 255) / 256)), dim3(256), 0, st, g, tile_off, rows, nact,
-                     seg);
+  hipLaunchKernelGGL(k_row_segments, dim3((unsigned)((nact * seg_row_words(g) + 255) / 256)), dim3(256), 0, st, g,
+                     tile_off, rows, nact, seg);
   IBDL_LAUNCH_CHECK();
 }
 

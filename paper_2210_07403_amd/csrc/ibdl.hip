@@ -29,6 +29,7 @@ constexpr int kYSlot = 256;
 
 template <typename T> struct GridWork {
   cplx<T>* tw[3] = {nullptr, nullptr, nullptr};
+  Tw2<T> tw2;                // 2-D: the tables of the passes
   T* sig[3] = {nullptr, nullptr, nullptr};
   T* kt[3] = {nullptr, nullptr, nullptr};
   T* real = nullptr;
@@ -53,7 +54,8 @@ struct ibdl_s {
   int dim = 2;
   int n[3] = {1, 1, 1};
   double h = 0;
-  int64_t ntot = 0, nxh = 0, nxp = 0, nspec = 0;   // nxp: half-spectrum row pitch (128-byte rows)
+  // half spectra of one field: 3-D [z][y][nxp] (rows padded to 128 bytes), 2-D transposed (spec2_size)
+  int64_t ntot = 0, nxh = 0, nxp = 0;
   int64_t n_ib = 0;
   int nq = 1;
   bool has_ubar = false;
@@ -81,8 +83,9 @@ struct ibdl_s {
   int4* busy_tmp = nullptr;
   int* busy_off = nullptr;
   int nbusy = 0;
-  unsigned long long* seg = nullptr;       // busy x-segments of each active row (RowList::seg)
+  unsigned long long* seg = nullptr;       // 3-D: busy x-segments of each active row (RowList::seg)
   unsigned long long* seg_all = nullptr;   // busy x-segments of every row of a field
+  int seg_words = 1;                       // 64-bit words of a row's segments
   // active rows (rows of the markers' windows): list for the x passes, per-plane limits for y
   int *row_lo = nullptr, *row_hi = nullptr, *row_cnt = nullptr, *row_off = nullptr, *rows = nullptr;
   int2* row_lim = nullptr;
@@ -222,6 +225,9 @@ struct ibdl_s {
     return dim + 1;
   }
   template <typename T> GridWork<T>& work();
+  template <typename T> int64_t nspec() const {   // half-spectrum values of one field
+    return dim == 2 ? spec2_size<T>(n[0], n[1]) : nxp * n[1] * n[2];
+  }
 };
 
 template <> GridWork<float>& ibdl_s::work<float>() {
@@ -264,7 +270,7 @@ template <typename T> GridWork<T>& ensure_work(ibdl_s* h) {
   const int nf = h->fields_needed();
   W.nfields = nf;
   W.real = (T*)h->dalloc<T>(sizeof(T) * h->ntot * nf);
-  W.spec = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * h->nspec * nf);
+  W.spec = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * h->nspec<T>() * nf);
   W.wtab = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * h->n_ib * 24);
   weight_table<T>(h->wt, h->n_ib, W.wtab, h->st);
   GridTables<T> G = make_grid_tables<T>(h->dim, h->n, h->cfg.L, h->h, h->fd(),
@@ -273,6 +279,10 @@ template <typename T> GridWork<T>& ensure_work(ibdl_s* h) {
     W.tw[d] = G.tw[d];
     W.sig[d] = G.sig[d];
     W.kt[d] = G.kt[d];
+  }
+  if (h->dim == 2) {
+    cplx<T>* st = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * fft2_table_len<T>(h->n[0], h->n[1]));
+    W.tw2 = fft2_tables<T>(h->n[0], h->n[1], W.tw[0], W.tw[1], st, h->st);
   }
   return W;
 }
@@ -283,7 +293,7 @@ template <typename T> GridWork<T>& ensure_fields(ibdl_s* h, int nf) {
   h->dfree(W.real);
   h->dfree(W.spec);
   W.real = (T*)h->dalloc<T>(sizeof(T) * h->ntot * nf);
-  W.spec = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * h->nspec * nf);
+  W.spec = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * h->nspec<T>() * nf);
   W.nfields = nf;
   return W;
 }
@@ -293,6 +303,7 @@ template <typename T> MultDesc base_desc(ibdl_s* h, GridWork<T>& W) {
   md.dim = h->dim;
   md.nxh = (int)h->nxh;
   md.nxp = (int)h->nxp;
+  md.nyp = (int)spec2_pitch<T>(h->n[1]);
   md.sc = 1.0 / (double)h->ntot;
   md.mu = h->cfg.mu;
   for (int d = 0; d < 3; ++d) {
@@ -318,23 +329,68 @@ template <typename T> MultDesc base_desc(ibdl_s* h, GridWork<T>& W) {
 // (a right-hand side that is interpolated next).
 enum RowsMode { ROWS_DENSE = 0, ROWS_SPARSE = 1, ROWS_OUT = 2 };
 
+// The 2-D form: the spectra are transposed (fft2d.hip) and the active rows are one interval.
+template <typename T>
+void pipeline2(ibdl_s* h, GridWork<T>& W, const T* src, int nin, T* dst, int nout, const MultDesc& md, int rows,
+               bool busy_only, const T* sub, int sub_f0, int nsub, const float* srcf) {
+  const int nx = h->n[0], ny = h->n[1];
+  const bool sin = rows == ROWS_SPARSE, sout = rows != ROWS_DENSE, tuned = rows == ROWS_SPARSE;
+  Rows2 rin, rout;
+  rin.lo = sin ? h->lim2d[0] : 0;
+  rin.hi = sin ? h->lim2d[1] : ny - 1;
+  rout.lo = sout ? h->lim2d[0] : 0;
+  rout.hi = sout ? h->lim2d[1] : ny - 1;
+  if (busy_only) {   // src holds a spread's output: only its busy tiles were written
+    rin.seg = h->seg_all;
+    rin.seg_words = h->seg_words;
+    rin.seg_log2 = __builtin_ctz((unsigned)h->geom.tile[0] / 2);
+  }
+  rin.sub = sub;   // minus a dense forcing on fields sub_f0 .. sub_f0 + nsub - 1
+  rin.sub_f0 = sub_f0;
+  rin.nsub = nsub;
+  RowMask mask;
+  mask.load = sin ? 1 : 0;
+  mask.store = sout ? 1 : 0;
+  mask.lo = h->lim2d[0];
+  mask.hi = h->lim2d[1];
+  {
+    StageTimer t(h, ST_FFT_X_FWD);
+    const int rpb = tuned ? W.shape.rpb : 0;
+    if constexpr (std::is_same<T, double>::value) {
+      if (srcf) fft2_x_r2c_widen(srcf, W.spec, nx, ny, nin, W.tw2, h->st, rpb, rin);
+      else fft2_x_r2c<T>(src, W.spec, nx, ny, nin, W.tw2, h->st, rpb, rin);
+    } else {
+      if (srcf) throw Error(IBDL_ERR_UNSUPPORTED, "float input fields are for the double pipeline");
+      fft2_x_r2c<T>(src, W.spec, nx, ny, nin, W.tw2, h->st, rpb, rin);
+    }
+  }
+  {
+    StageTimer t(h, ST_FUSED);
+    fft2_lines<T>(W.spec, ny, nout, md, W.tw2, h->st, 1, 0, tuned ? W.shape.wz : 0, mask);
+  }
+  {
+    StageTimer t(h, ST_FFT_X_INV);
+    fft2_x_c2r<T>(W.spec, dst, nx, ny, nout, W.tw2, h->st, tuned ? W.shape.rpb : 0, rout);
+  }
+}
+
 // srcf: float input fields for a double pipeline (widened as the forward x pass reads them; src unused)
 template <typename T>
 void pipeline(ibdl_s* h, GridWork<T>& W, const T* src, int nin, T* dst, int nout, const MultDesc& md,
               int rows = ROWS_DENSE, bool busy_only = false, const T* sub = nullptr, int sub_f0 = 0, int nsub = 0,
               const float* srcf = nullptr) {
+  if (h->dim == 2) {
+    pipeline2<T>(h, W, src, nin, dst, nout, md, rows, busy_only, sub, sub_f0, nsub, srcf);
+    return;
+  }
   const int64_t rows_per_field = h->ntot / h->n[0];
-  // 2-D grids of more than 1024 points along y: the last-axis pass is a four-step transform that
-  // reads and writes every row, so the forward x pass covers every row (those the markers do not
-  // reach come out zero without being read) and the y row limits are not applied
-  const bool split = h->dim == 2 && h->n[1] > 1024;
-  const bool sin = rows == ROWS_SPARSE && !split, sout = rows != ROWS_DENSE;
+  const bool sin = rows == ROWS_SPARSE, sout = rows != ROWS_DENSE;
   RowList rl_in, rl_out;
   RowMask fwd, inv, fused;
   rl_in.rpf = rows_per_field;
   if (busy_only) {   // src holds a spread's output: only its busy tiles were written
     rl_in.seg = sin ? h->seg : h->seg_all;
-    rl_in.seg_log2 = __builtin_ctz((unsigned)h->geom.tile[0] / 2) + seg_group_log2(h->geom);
+    rl_in.seg_log2 = __builtin_ctz((unsigned)h->geom.tile[0] / 2);
   }
   rl_in.sub = sub;   // minus a dense forcing on fields sub_f0 .. sub_f0 + nsub - 1
   rl_in.sub_f0 = sub_f0;
@@ -347,29 +403,22 @@ void pipeline(ibdl_s* h, GridWork<T>& W, const T* src, int nin, T* dst, int nout
       rl_in.rows = h->rows;
       rl_in.nact = h->nact;
     }
-    if (h->dim == 3) {
-      // only the planes with active rows matter on the way out (the inverse y pass and the
-      // last-axis stores), and on the way in when the input is zero elsewhere
-      fwd.lim = inv.lim = h->row_lim;
-      fwd.nplanes = inv.nplanes = h->n[2];
-      fwd.load = sin ? 1 : 0;
-      inv.store = 1;
-      inv.p0 = h->zlim[0];
-      inv.pspan = std::max(0, h->zlim[1] - h->zlim[0] + 1);
-      if (sin) {
-        fwd.p0 = inv.p0;
-        fwd.pspan = inv.pspan;
-      }
-      fused.load = sin ? 1 : 0;
-      fused.store = 1;
-      fused.lo = h->zlim[0];
-      fused.hi = h->zlim[1];
-    } else if (!split) {
-      fused.load = sin ? 1 : 0;
-      fused.store = 1;
-      fused.lo = h->lim2d[0];
-      fused.hi = h->lim2d[1];
+    // only the planes with active rows matter on the way out (the inverse y pass and the
+    // last-axis stores), and on the way in when the input is zero elsewhere
+    fwd.lim = inv.lim = h->row_lim;
+    fwd.nplanes = inv.nplanes = h->n[2];
+    fwd.load = sin ? 1 : 0;
+    inv.store = 1;
+    inv.p0 = h->zlim[0];
+    inv.pspan = std::max(0, h->zlim[1] - h->zlim[0] + 1);
+    if (sin) {
+      fwd.p0 = inv.p0;
+      fwd.pspan = inv.pspan;
     }
+    fused.load = sin ? 1 : 0;
+    fused.store = 1;
+    fused.lo = h->zlim[0];
+    fused.hi = h->zlim[1];
   }
   const bool tuned = rows == ROWS_SPARSE;   // the measured shapes are those of the apply
   const int64_t rin = sin ? h->nact * nin : rows_per_field * nin;
@@ -384,20 +433,18 @@ void pipeline(ibdl_s* h, GridWork<T>& W, const T* src, int nin, T* dst, int nout
       fft_x_r2c<T>(src, W.spec, h->n[0], rin, W.tw[0], h->st, tuned ? W.shape.rpb : 0, rl_in, h->nxp);
     }
   }
-  if (h->dim == 3) {
+  {
     StageTimer t(h, ST_FFT_Y_FWD);
     fft_strided<T>(W.spec, h->n[1], (int64_t)nin * (fwd.pspan ? fwd.pspan : h->n[2]) * h->nxp, h->nxp,
                    h->nxp * h->n[1], h->nxp, false, W.tw[1], h->st, tuned ? W.shape.wy : 0, fwd, h->nxh,
                    tuned ? W.shape.py : 0);
   }
-  const int last = h->dim - 1;
-  const int64_t P = h->nspec / h->n[last];
   {
     StageTimer t(h, ST_FUSED);
-    fft_fused_last<T>(W.spec, h->n[last], P, nout, md, W.tw[last], h->st, 1, 0, tuned ? W.shape.wz : 0, fused,
+    fft_fused_last<T>(W.spec, h->n[2], h->nxp * h->n[1], nout, md, W.tw[2], h->st, 1, 0, tuned ? W.shape.wz : 0, fused,
                       tuned ? W.shape.pz : 0);
   }
-  if (h->dim == 3 && !(sout && inv.pspan == 0)) {
+  if (!(sout && inv.pspan == 0)) {
     StageTimer t(h, ST_FFT_Y_INV);
     fft_strided<T>(W.spec, h->n[1], (int64_t)nout * (inv.pspan ? inv.pspan : h->n[2]) * h->nxp, h->nxp,
                    h->nxp * h->n[1], h->nxp, true, W.tw[1], h->st, tuned ? W.shape.wy : 0, inv, h->nxh,
@@ -433,11 +480,8 @@ SpreadArgs spread_args(ibdl_s* h, int mode, int nf, const double* q) {
   return a;
 }
 
-// the spread with this precision's tables and coefficient scratch.  Where a busy-segment bit covers
-// several x-tiles (2-D grids over 1024 points wide) the idle tiles of a busy segment are read too, so
-// the output fields are cleared first.
+// the spread with this precision's tables
 template <typename T> void spread_w(ibdl_s* h, SpreadArgs a, GridWork<T>& W, T* out) {
-  if (seg_group_log2(h->geom) > 0) grid_fill_zero<T>(out, (int64_t)a.nf * h->ntot, h->st);
   spread<T>(a, W.wtab, out, h->st);
 }
 
@@ -527,15 +571,18 @@ void density_to_grid(ibdl_s* h, const double* q, const double* m, const T* g, T*
 // Widths run from the largest that fits down to an eighth of it.
 template <typename T> void tune_apply(ibdl_s* h, GridWork<T>& W) {
   const DensityPlan pl = density_plan<T>(h, W, h->cfg.eta > 0);
-  const TuneKey key{0, h->dim, h->n[0], h->n[1], h->n[2], (int)sizeof(T), pl.nf, pow2_bucket(h->nact)};
+  const TuneKey key{h->dim == 2 ? 10 : 0, h->dim, h->n[0], h->n[1], h->n[2], (int)sizeof(T), pl.nf, pow2_bucket(h->nact)};
   if (tune_get(key, &W.shape)) return;
   grid_fill_zero<T>(W.real, h->ntot * W.nfields, h->st);
-  grid_fill_zero<T>(reinterpret_cast<T*>(W.spec), h->nspec * 2 * W.nfields, h->st);
+  grid_fill_zero<T>(reinterpret_cast<T*>(W.spec), h->nspec<T>() * 2 * W.nfields, h->st);
   const int64_t rpf = h->ntot / h->n[0];
   RowList rl;
   rl.rows = h->rows;
   rl.nact = h->nact;
   rl.rpf = rpf;
+  Rows2 rw;
+  rw.lo = h->lim2d[0];
+  rw.hi = h->lim2d[1];
   RowMask fwd, inv, fused;
   if (h->dim == 3) {
     fwd.lim = inv.lim = h->row_lim;
@@ -589,8 +636,13 @@ template <typename T> void tune_apply(ibdl_s* h, GridWork<T>& W) {
   LaunchShape sh;
   {
     std::vector<Cand> cand;
-    widths(0, fft_x_rpb_max<T>(h->n[0]), cand);
+    widths(0, h->dim == 2 ? fft2_rows_max<T>(h->n[0]) : fft_x_rpb_max<T>(h->n[0]), cand);
     sh.rpb = best_of(cand, [&](int, int r) {
+      if (h->dim == 2) {
+        fft2_x_r2c<T>(W.real, W.spec, h->n[0], h->n[1], pl.nf, W.tw2, h->st, r, rw);
+        fft2_x_c2r<T>(W.spec, W.real, h->n[0], h->n[1], pl.nout, W.tw2, h->st, r, rw);
+        return;
+      }
       fft_x_r2c<T>(W.real, W.spec, h->n[0], h->nact * pl.nf, W.tw[0], h->st, r, rl, h->nxp);
       fft_x_c2r<T>(W.spec, W.real, h->n[0], h->nact * pl.nout, W.tw[0], h->st, r, rl, h->nxp);
     }).second;
@@ -607,16 +659,20 @@ template <typename T> void tune_apply(ibdl_s* h, GridWork<T>& W) {
     sh.py = c.first;
     sh.wy = c.second;
   }
-  const int last = h->dim - 1;
-  {
-    // the second radix plan exists for the single-field scalar pass only
-    const bool single = !pl.md.stokes && pl.nout == 1 && pl.md.nc == 1 && pl.md.fk[0] == FK_MASS;
+  if (h->dim == 2) {
     std::vector<Cand> cand;
-    for (int p = 0; p < (single ? fft_line_plans<T>(h->n[last]) : 1); ++p)
-      widths(p, fft_line_w_max<T>(h->n[last], p), cand);
+    widths(0, fft2_lines_max<T>(h->n[1], std::max(pl.nf, pl.nout)), cand);
+    sh.wz = best_of(cand, [&](int, int w) {
+      fft2_lines<T>(W.spec, h->n[1], pl.nout, pl.md, W.tw2, h->st, 1, 0, w, fused);
+    }).second;
+  } else {
+    // the second radix plan exists for the single-field scalar pass only
+    const bool single = pl.nout == 1 && pl.md.nc == 1 && pl.md.fk[0] == FK_MASS;
+    std::vector<Cand> cand;
+    for (int p = 0; p < (single ? fft_line_plans<T>(h->n[2]) : 1); ++p)
+      widths(p, fft_line_w_max<T>(h->n[2], p), cand);
     const Cand c = best_of(cand, [&](int p, int w) {
-      fft_fused_last<T>(W.spec, h->n[last], h->nspec / h->n[last], pl.nout, pl.md, W.tw[last], h->st, 1, 0, w, fused,
-                        p);
+      fft_fused_last<T>(W.spec, h->n[2], h->nxp * h->n[1], pl.nout, pl.md, W.tw[2], h->st, 1, 0, w, fused, p);
     });
     sh.pz = c.first;
     sh.wz = c.second;
@@ -1127,8 +1183,7 @@ int backward_t(ibdl_s* h, const double* q, const T* u, const T* psi, double tol,
   return status;
 }
 
-// grid points per axis: powers of two from 16 to 1024, and in 2-D up to 8192 (lines over 1024
-// points run as four-step transforms)
+// grid points per axis: powers of two from 16 to 1024, and in 2-D up to 8192
 bool pow2_in_range(int64_t v, int dim) { return v >= 16 && v <= (dim == 2 ? 8192 : 1024) && (v & (v - 1)) == 0; }
 
 void validate(const ibdl_config_t* c, int64_t n_ib) {
@@ -1218,18 +1273,10 @@ void build_markers(ibdl_s* h) {
       h->zlim[0] = std::min(h->zlim[0], z);
       h->zlim[1] = std::max(h->zlim[1], z);
     }
-  {   // busy x-segments of the active rows; their count is reported by ibdl_spread_tiles
-    markers_row_segments(h->geom, h->tile_off, h->rows, na, h->seg, h->st);
-    markers_row_segments(h->geom, h->tile_off, nullptr, (int64_t)h->n[1] * (h->dim == 3 ? h->n[2] : 1), h->seg_all,
-                         h->st);
-    std::vector<unsigned long long> seg(na);
-    if (na > 0)
-      IBDL_HIP(hipMemcpyAsync(seg.data(), h->seg, sizeof(unsigned long long) * na, hipMemcpyDeviceToHost, h->st));
-    IBDL_HIP(hipStreamSynchronize(h->st));
-    int64_t cnt = 0;
-    for (unsigned long long m : seg) cnt += __builtin_popcountll(m);
-    h->seg_read = cnt;
-  }
+  // busy x-segments of the rows (of the active rows, too, where the x passes run over a list of them)
+  if (h->dim == 3) markers_row_segments(h->geom, h->tile_off, h->rows, na, h->seg, h->st);
+  markers_row_segments(h->geom, h->tile_off, nullptr, (int64_t)h->n[1] * nplanes, h->seg_all, h->st);
+  h->seg_read = -1;
   if (h->w32 && h->w32->wtab) weight_table<float>(h->wt, h->n_ib, h->w32->wtab, h->st);
   if (h->w64 && h->w64->wtab) weight_table<double>(h->wt, h->n_ib, h->w64->wtab, h->st);
 }
@@ -1440,7 +1487,6 @@ ibdl_status_t ibdl_create(const ibdl_config_t* cfg, int64_t n_ib, const double* 
     h->use_graph = h->ntot < ((int64_t)1 << 20);
     h->nxh = h->n[0] / 2 + 1;
     h->nxp = (h->nxh + 15) / 16 * 16;
-    h->nspec = h->nxp * h->n[1] * h->n[2];
     h->n_ib = n_ib;
     h->nq = h->stokes() ? h->dim : 1;
     h->has_ubar = h->cfg.eta > 0 && h->kappa() == 0.0;
@@ -1479,9 +1525,10 @@ ibdl_status_t ibdl_create(const ibdl_config_t* cfg, int64_t n_ib, const double* 
     h->row_off = (int*)h->dalloc<int>(sizeof(int) * (nplanes + 1));
     h->row_lim = (int2*)h->dalloc<int>(sizeof(int2) * nplanes);
     h->rows = (int*)h->dalloc<int>(sizeof(int) * (int64_t)h->n[1] * nplanes);
-    h->seg = (unsigned long long*)h->dalloc<unsigned long long>(sizeof(unsigned long long) * (int64_t)h->n[1] * nplanes);
-    h->seg_all =
-        (unsigned long long*)h->dalloc<unsigned long long>(sizeof(unsigned long long) * (int64_t)h->n[1] * nplanes);
+    const size_t nseg = sizeof(unsigned long long) * (size_t)h->n[1] * nplanes;
+    h->seg_words = seg_row_words(g);
+    if (h->dim == 3) h->seg = (unsigned long long*)h->dalloc<unsigned long long>(nseg);
+    h->seg_all = (unsigned long long*)h->dalloc<unsigned long long>(nseg * h->seg_words);
     h->small = (double*)h->dalloc<double>(sizeof(double) * 1024);
     h->vb = (double*)h->dalloc<double>(sizeof(double) * h->n_aug);
     h->vr = (double*)h->dalloc<double>(sizeof(double) * h->n_aug);
@@ -2000,11 +2047,25 @@ ibdl_status_t ibdl_active_span(ibdl_t h, int32_t* first, int32_t* last) {
 
 ibdl_status_t ibdl_spread_tiles(ibdl_t h, int64_t* nbusy, int64_t* segments_read, int32_t* tile) {
   if (!h) return IBDL_ERR_ARG;
-  if (nbusy) *nbusy = h->nbusy;
-  if (segments_read) *segments_read = h->seg_read;
-  if (tile)
-    for (int d = 0; d < 3; ++d) tile[d] = h->geom.tile[d];
-  return IBDL_OK;
+  return guarded(h, [&]() {
+    if (segments_read && h->seg_read < 0) {   // counted at the first question after the markers changed
+      const bool d3 = h->dim == 3;
+      const int64_t nw = d3 ? h->nact : h->nact * h->seg_words;
+      std::vector<unsigned long long> seg(nw);
+      if (nw > 0)
+        IBDL_HIP(hipMemcpyAsync(seg.data(), d3 ? h->seg : h->seg_all + (int64_t)h->lim2d[0] * h->seg_words,
+                                sizeof(unsigned long long) * nw, hipMemcpyDeviceToHost, h->st));
+      IBDL_HIP(hipStreamSynchronize(h->st));
+      int64_t cnt = 0;
+      for (unsigned long long m : seg) cnt += __builtin_popcountll(m);
+      h->seg_read = cnt;
+    }
+    if (nbusy) *nbusy = h->nbusy;
+    if (segments_read) *segments_read = h->seg_read;
+    if (tile)
+      for (int d = 0; d < 3; ++d) tile[d] = h->geom.tile[d];
+    return IBDL_OK;
+  });
 }
 
 ibdl_status_t ibdl_launch_shape(ibdl_t h, int32_t* rows_per_block, int32_t* lines_y, int32_t* lines_last) {

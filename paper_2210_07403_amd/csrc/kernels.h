@@ -1,4 +1,4 @@
-// Host-side launchers of the HIP kernels (implemented in fft.hip, ib.hip, krylov.hip).
+// Host-side launchers of the HIP kernels (implemented in fft.hip, fft2d.hip, ib.hip, krylov.hip).
 #pragma once
 
 #include "common.h"
@@ -69,6 +69,21 @@ struct RowMask {
   __device__ bool keep_out(int y) const { return !store || (y >= lo && y <= hi); }
 };
 
+// Rows of the 2-D x passes: lo .. hi of every field.  seg: busy x-segments of a row, seg_words 64-bit
+// words per row (bit t of the row: segment t, 2^seg_log2 complex values wide, holds data; NULL:
+// read everything), indexed by the row of a field, or by field and row with seg_per_field (a batch's
+// problems).  sub: a dense forcing [nsub][ny][nx] subtracted from fields sub_f0 .. sub_f0 + nsub - 1.
+struct Rows2 {
+  int lo = 0, hi = -1;
+  const unsigned long long* seg = nullptr;
+  int seg_words = 1, seg_log2 = 3, seg_per_field = 0;
+  const void* sub = nullptr;
+  int sub_f0 = 0, nsub = 0;
+};
+// 2-D half spectra: [field][nx / 2 + 1 x modes][spec2_pitch y values]
+template <typename T> constexpr int64_t spec2_pitch(int64_t ny) { return ny + 256 / (int64_t)sizeof(cplx<T>); }
+template <typename T> constexpr int64_t spec2_size(int64_t nx, int64_t ny) { return (nx / 2 + 1) * spec2_pitch<T>(ny); }
+
 // Assignment of tiles of W lines to the lines of a last-axis pass (set by fft_fused_last):
 // on = 0, tile t holds lines t W .. t W + W - 1; on = 1, the first nlast tiles hold the last x mode
 // of W consecutive rows (rows in all) and the others W consecutive x modes below the last of one row
@@ -83,7 +98,8 @@ struct MultDesc {
                     // 3: Stokes pressure
   int dim;          // 2 or 3
   int nxh;          // nx/2 + 1 modes along x
-  int nxp;          // row pitch of the half spectrum (>= nxh; lines with x index >= nxh are padding)
+  int nxp;          // 3-D: row pitch of the half spectrum (>= nxh; lines with x index >= nxh are padding)
+  int nyp;          // 2-D: line pitch of the transposed half spectrum (spec2_pitch)
   int stokes;       // 0: scalar multiplier, 1: Stokes multiplier
   int nc;           // input fields
   int fk[8];        // kind of each input field
@@ -93,7 +109,6 @@ struct MultDesc {
   double alpha;     // overall sign / factor
   const void* sig[3];  // per-axis Laplacian symbol components (grid type)
   const void* kt[3];   // per-axis derivative symbols k~ (grid type)
-  int split;           // 2-D lines of a four-step y transform: N1 > 1 (set by fft_fused_last); 0 or 1: none
   LineMap map;         // tiles -> lines (set by fft_fused_last)
 };
 
@@ -123,18 +138,50 @@ void fft_strided(cplx<T>* data, int n, int64_t nlines, int64_t inner, int64_t ou
                  int64_t vinner = 0, int plan = 0);
 // in-place fused pass along the last axis (length n, plane size P): forward FFT of the nc input
 // fields, multiplier, inverse FFT of the no output fields (written to fields 0..no-1).
-// mode 1 (one scalar input F): outputs i k~_o g F^ for o < dim, then g F^, g = alpha sc/(c2 sigma - c0);
-// mode 2 (two Stokes components): output o = sum_c conj(m(fk[o], c)) F^_c, the transpose of the
-// forward Stokes multiplier m(kind, component).
+// mode 1 (one scalar input F): outputs i k~_o g F^ for o < dim, then g F^, g = alpha sc/(c2 sigma - c0).
+// 3-D grids (2-D: fft2_lines, which also takes the Stokes multipliers and modes 2 and 3: the transpose
+// of the forward Stokes multiplier, the Stokes pressure).
 // batch problems with the same multiplier: problem b's fields start bstride elements after b-1's.
-// 2-D lines of 2048 to 8192 points (one problem) run as a four-step transform in three passes; their
-// fields must be valid on every row (rm is not applied) and every output row is written.
 // plan: radix plan of the single-field scalar pass (fft_line_plans); the other passes keep theirs.
 template <typename T>
 void fft_fused_last(cplx<T>* data, int n, int64_t P, int no, const MultDesc& md, const cplx<T>* tw,
                     hipStream_t s, int batch = 1, int64_t bstride = 0, int w = 0,
                     const RowMask& rm = RowMask(), int plan = 0);
 int fft_supported(int n);
+
+// Twiddle tables of the 2-D passes: the plain table along x (exp(-2 pi i m / nx), for the even/odd
+// split) and, in the order the stages read them, those of the transforms along x and along y (y[1]:
+// passes that hold several fields at once).  fft2_tables fills dst (fft2_table_len values) from the
+// plain tables of both axes.
+template <typename T> struct Tw2 {
+  const cplx<T>* base = nullptr;
+  const cplx<T>* x = nullptr;
+  const cplx<T>* y[2] = {nullptr, nullptr};
+};
+template <typename T> size_t fft2_table_len(int nx, int ny);
+template <typename T>
+Tw2<T> fft2_tables(int nx, int ny, const cplx<T>* twx, const cplx<T>* twy, cplx<T>* dst, hipStream_t s);
+
+// 2-D passes (fft2d.hip) over the transposed half spectra.  rpb: rows per block of the x passes, w:
+// lines per block of the pass along y (powers of two; 0: a default that suits dense fields; above the
+// largest that fits: that).
+template <typename T>
+void fft2_x_r2c(const T* in, cplx<T>* out, int nx, int ny, int nf, const Tw2<T>& tw, hipStream_t s, int rpb,
+                const Rows2& rw);
+// the double forward x pass reading float rows (widened on load)
+void fft2_x_r2c_widen(const float* in, cplx<double>* out, int nx, int ny, int nf, const Tw2<double>& tw, hipStream_t s,
+                      int rpb, const Rows2& rw);
+template <typename T>
+void fft2_x_c2r(const cplx<T>* in, T* out, int nx, int ny, int nf, const Tw2<T>& tw, hipStream_t s, int rpb,
+                const Rows2& rw);
+// in-place pass along y: forward FFT of the md.nc input fields, multiplier (the modes of
+// fft_fused_last), inverse FFT of the no output fields; rm.lo .. rm.hi: the rows to load / store
+template <typename T>
+void fft2_lines(cplx<T>* data, int n, int no, const MultDesc& md, const Tw2<T>& tw, hipStream_t s, int batch,
+                int64_t bstride, int w, const RowMask& rm);
+template <typename T> int fft2_rows_max(int nx);
+// most lines per block along y, for passes holding nmax fields at once
+template <typename T> int fft2_lines_max(int n, int nmax);
 
 // ------------------------------------------------------------------ markers, spread, interp
 enum KernelId { KID_PESKIN4 = 0, KID_COS4 = 1, KID_BSPLINE6 = 2 };
@@ -147,13 +194,8 @@ struct MarkerGeom {
   int tile[3];         // tile edge per axis (2-D: 16 x 16; 3-D: 16 x 4 x 8)
   int ntile[3];        // tiles per axis
 };
-// log2 of the x-tiles per bit of the busy-segment masks (RowList::seg): 0 up to 64 tiles along x;
-// wider 2-D grids group 2, 4, ... tiles per bit, since a mask has 64 bits
-__host__ __device__ inline int seg_group_log2(const MarkerGeom& g) {
-  int s = 0;
-  while ((g.ntile[0] >> s) > 64) ++s;
-  return s;
-}
+// 64-bit words of a row's busy-segment mask, one bit per x-tile (RowList::seg, Rows2::seg)
+__host__ __device__ inline int seg_row_words(const MarkerGeom& g) { return (g.ntile[0] + 63) / 64; }
 
 // marker setup: window start s[i][3] (wrapped), fractional offset f[i][3], weight table
 // wt[i][3][12] (kernel weights W[0..5] and centred differences G[0..5] on the window), tile counts
@@ -178,8 +220,8 @@ void markers_list_offsets(const MarkerGeom& g, const int4* busy, int nbusy, cons
 // the count is off[planes].  planes = nz in 3-D, 1 in 2-D.
 void markers_rows(const MarkerGeom& g, int64_t n_ib, const int* s, int* lo, int* hi, int* cnt, int* off, int2* lim,
                   int* rows, hipStream_t st);
-// seg[r] = bit mask of the busy tiles along x that listed row r (rows[r], r < nact; row r itself
-// when rows is NULL) passes through, 2^seg_group_log2(g) tiles per bit
+// seg[r][seg_row_words(g)] = bit mask of the busy tiles along x that listed row r (rows[r], r < nact;
+// row r itself when rows is NULL) passes through
 void markers_row_segments(const MarkerGeom& g, const int* tile_off, const int* rows, int64_t nact,
                           unsigned long long* seg, hipStream_t st);
 

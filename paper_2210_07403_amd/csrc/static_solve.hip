@@ -76,7 +76,7 @@ __global__ void k_tables(int n, int len, int fd, double h, double L, cplx<T>* tw
 }
 
 struct Layout {
-  size_t tw[3], sig[3], kt[3], spec, total;
+  size_t tw[3], sig[3], kt[3], stages, spec, total;
 };
 
 template <typename T> Layout layout(int dim, const int* n, int nf, int64_t nspec) {
@@ -95,6 +95,8 @@ template <typename T> Layout layout(int dim, const int* n, int nf, int64_t nspec
     lo.kt[d] = off;
     off += align256(sizeof(T) * (size_t)len);
   }
+  lo.stages = off;
+  if (dim == 2) off += align256(sizeof(cplx<T>) * fft2_table_len<T>(n[0], n[1]));
   lo.spec = off;
   off += align256(sizeof(cplx<T>) * (size_t)nspec * (size_t)nf);
   lo.total = off;
@@ -107,7 +109,7 @@ template <typename T> void solve_t(const ibdl_config_t& c, const T* rhs, T* u) {
   for (int d = 0; d < dim; ++d) n[d] = (int)c.n[d];
   const int64_t ntot = (int64_t)n[0] * n[1] * n[2];
   const int nxh = n[0] / 2 + 1, nxp = (nxh + 15) / 16 * 16;
-  const int64_t nspec = (int64_t)nxp * n[1] * n[2];
+  const int64_t nspec = dim == 2 ? spec2_size<T>(n[0], n[1]) : (int64_t)nxp * n[1] * n[2];
   const bool stokes = c.pde == IBDL_PDE_STOKES;
   const int nf = stokes ? 2 : 1;
   const Layout lo = layout<T>(dim, n, nf, nspec);
@@ -134,6 +136,7 @@ template <typename T> void solve_t(const ibdl_config_t& c, const T* rhs, T* u) {
   md.dim = dim;
   md.nxh = nxh;
   md.nxp = nxp;
+  md.nyp = (int)spec2_pitch<T>(n[1]);
   md.sc = 1.0 / (double)ntot;
   md.mu = c.mu;
   for (int d = 0; d < 3; ++d) {
@@ -157,19 +160,23 @@ template <typename T> void solve_t(const ibdl_config_t& c, const T* rhs, T* u) {
     md.fk[0] = FK_MASS;
     md.alpha = 1.0;
   }
+  if (dim == 2) {
+    Rows2 rw;
+    rw.hi = n[1] - 1;
+    const Tw2<T> tw2 = fft2_tables<T>(n[0], n[1], tw[0], tw[1], (cplx<T>*)(base + lo.stages), st);
+    fft2_x_r2c<T>(rhs, spec, n[0], n[1], nf, tw2, st, 0, rw);
+    fft2_lines<T>(spec, n[1], nf, md, tw2, st, 1, 0, 0, RowMask());
+    fft2_x_c2r<T>(spec, u, n[0], n[1], nf, tw2, st, 0, rw);
+    return;
+  }
   const int64_t rpf = ntot / n[0];
   RowList rl;
   rl.rpf = rpf;
-  fft_x_r2c<T>(rhs, spec, n[0], rpf * nf, tw[0], st, 0, rl, nxp);
-  if (dim == 3)
-    fft_strided<T>(spec, n[1], (int64_t)nf * n[2] * nxp, nxp, (int64_t)nxp * n[1], nxp, false, tw[1], st, 0, RowMask(),
-                   nxh);
-  const int last = dim - 1;
-  fft_fused_last<T>(spec, n[last], nspec / n[last], nf, md, tw[last], st, 1, 0, 0, RowMask());
-  if (dim == 3)
-    fft_strided<T>(spec, n[1], (int64_t)nf * n[2] * nxp, nxp, (int64_t)nxp * n[1], nxp, true, tw[1], st, 0, RowMask(),
-                   nxh);
-  fft_x_c2r<T>(spec, u, n[0], rpf * nf, tw[0], st, 0, rl, nxp);
+  fft_x_r2c<T>(rhs, spec, n[0], rpf, tw[0], st, 0, rl, nxp);
+  fft_strided<T>(spec, n[1], (int64_t)n[2] * nxp, nxp, (int64_t)nxp * n[1], nxp, false, tw[1], st, 0, RowMask(), nxh);
+  fft_fused_last<T>(spec, n[2], nspec / n[2], 1, md, tw[2], st, 1, 0, 0, RowMask());
+  fft_strided<T>(spec, n[1], (int64_t)n[2] * nxp, nxp, (int64_t)nxp * n[1], nxp, true, tw[1], st, 0, RowMask(), nxh);
+  fft_x_c2r<T>(spec, u, n[0], rpf, tw[0], st, 0, rl, nxp);
 }
 
 bool pow2_ok(int64_t v) { return v >= 16 && v <= 1024 && (v & (v - 1)) == 0; }

@@ -16,7 +16,8 @@ struct LaunchShape {
   int pz = 0;    // radix plan of the single-field last-axis pass
 };
 
-// (kind, dim, n0, n1, n2, bytes per value, fields, size bucket)
+// (kind, dim, n0, n1, n2, bytes per value, fields, size bucket); kinds 10 and above: the passes over
+// transposed 2-D spectra
 using TuneKey = std::array<int, 8>;
 
 bool tune_get(const TuneKey& key, LaunchShape* out);
