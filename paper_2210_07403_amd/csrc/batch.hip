@@ -111,7 +111,7 @@ struct ibdl_batch_s {
   // pointer tables of the per-problem input and output arrays: pinned host staging, device copy
   const double** hptr = nullptr;
   const double** dptr = nullptr;
-  // host-mapped, coherent: two publication slots of [nprob][GM_PUB] doubles, then two tags
+  // host-mapped, coherent: the records of every problem for two steps in flight, [2][nprob][GM_REC]
   double* hmap = nullptr;
   double* hmap_dev = nullptr;
   unsigned seq = 0;
@@ -620,21 +620,22 @@ std::vector<double> seg_norms(ibdl_batch_s* B, const double* v) {
   return r;
 }
 
-// The publication slot of the device-driven batch GMRES: wait for its tag (poll 2 ms, then a stream
-// synchronisation, after which it must be there).
-const volatile double* batch_wait(ibdl_batch_s* B, int slot, unsigned seq) {
-  const size_t slot_doubles = (size_t)B->nprob * GM_PUB;
-  volatile unsigned* tag = reinterpret_cast<volatile unsigned*>(B->hmap + 2 * slot_doubles) + 16 * slot;
+// Wait for every problem's record of step number seq (poll 2 ms, then a stream synchronisation, after
+// which they must be there): out[p][GM_PUB].
+void batch_wait(ibdl_batch_s* B, int slot, unsigned seq, std::vector<double>& out) {
+  const volatile double* rec = B->hmap + (size_t)slot * B->nprob * GM_REC;
   const auto t0 = std::chrono::steady_clock::now();
-  while (*tag != seq) {
-    if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) {
+  bool synced = false;
+  for (int p = 0; p < B->nprob;) {
+    if (gm_pub_read(rec + (size_t)p * GM_REC, seq, &out[(size_t)p * GM_PUB])) {
+      ++p;
+    } else if (synced) {
+      throw Error(IBDL_ERR_HIP, "GMRES state did not reach the host");
+    } else if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) {
       IBDL_HIP(hipStreamSynchronize(B->st));
-      if (*tag != seq) throw Error(IBDL_ERR_HIP, "GMRES state did not reach the host");
-      break;
+      synced = true;
     }
   }
-  std::atomic_thread_fence(std::memory_order_acquire);
-  return B->hmap + slot * slot_doubles;
 }
 
 // GMRES per problem (x0 = 0, no restart, CGS2), all problems in lock step and all on the device:
@@ -651,17 +652,15 @@ void batch_gmres(ibdl_batch_s* B, double tol, int maxit, double* x, std::vector<
   kb_multidot(B->vb, n, 1, B->vb, B->sg, B->partial, 1, B->bn2, B->st);
   double* xin = B->use_graph ? (ensure_graph(B), B->xin) : nullptr;
   kb_gmres_start(B->vb, B->doff, B->dlen, np, B->bn2, B->V, xin, B->st);
-  const size_t slot_doubles = (size_t)np * GM_PUB;
-  unsigned* tag_dev = reinterpret_cast<unsigned*>(B->hmap_dev + 2 * slot_doubles);
   unsigned seq[2] = {0, 0};
+  std::vector<double> hv((size_t)np * GM_PUB);
   auto step = [&](int j) {
     if (B->use_graph) IBDL_HIP(hipGraphLaunch(B->gexec, B->st));
     else apply_any(B, B->V + (int64_t)j * n, B->yout, false);
-    kb_arnoldi(B->V, n, j, B->yout, B->doff, B->dlen, np, B->maxlen, B->bn2, B->gsb, B->gstride, mx, tol,
-               B->V + (int64_t)(j + 1) * n, xin, B->st);
     const int slot = j & 1;
     seq[slot] = ++B->seq;
-    kb_publish(B->gsb, B->gstride, np, B->hmap_dev + slot * slot_doubles, tag_dev + 16 * slot, seq[slot], B->st);
+    kb_arnoldi(B->V, n, j, B->yout, B->doff, B->dlen, np, B->maxlen, B->bn2, B->gsb, B->gstride, mx, tol,
+               B->V + (int64_t)(j + 1) * n, xin, B->hmap_dev + (size_t)slot * np * GM_REC, seq[slot], B->st);
   };
   iters.assign(np, 0);
   relres.assign(np, 0.0);
@@ -678,10 +677,10 @@ void batch_gmres(ibdl_batch_s* B, double tol, int maxit, double* x, std::vector<
     }
     ahead = ahead && j + 1 < maxit;
     if (ahead) step(j + 1);
-    const volatile double* hv = batch_wait(B, j & 1, seq[j & 1]);
+    batch_wait(B, j & 1, seq[j & 1], hv);
     bool all = true;
     for (int p = 0; p < np; ++p) {
-      const volatile double* v = hv + (size_t)p * GM_PUB;
+      const double* v = &hv[(size_t)p * GM_PUB];
       if (j == 0 && !std::isfinite((double)v[GM_BETA])) throw Error(IBDL_ERR_NONFINITE, "right-hand side is not finite");
       if (!std::isfinite((double)v[GM_HN]) || !std::isfinite((double)v[GM_RES]))
         throw Error(IBDL_ERR_NONFINITE, "non-finite value in the Arnoldi process");
@@ -955,13 +954,10 @@ ibdl_status_t ibdl_batch_create(int32_t nprob, const ibdl_config_t* cfgs, const 
       IBDL_HIP(hipMemcpy(B->dlen, hlen.data(), sizeof(int64_t) * nprob, hipMemcpyHostToDevice));
       IBDL_HIP(hipHostMalloc((void**)&B->hptr, sizeof(double*) * 2 * nprob, hipHostMallocDefault));
       B->dptr = (const double**)B->dalloc(sizeof(double*) * 2 * nprob);
-      const size_t slot_doubles = (size_t)nprob * GM_PUB;
-      IBDL_HIP(hipHostMalloc((void**)&B->hmap, sizeof(double) * (2 * slot_doubles + 32),
-                             hipHostMallocMapped | hipHostMallocCoherent));
+      const size_t bytes = sizeof(double) * 2 * nprob * GM_REC;
+      IBDL_HIP(hipHostMalloc((void**)&B->hmap, bytes, hipHostMallocMapped | hipHostMallocCoherent));
+      memset(B->hmap, 0, bytes);
       IBDL_HIP(hipHostGetDevicePointer((void**)&B->hmap_dev, B->hmap, 0));
-      unsigned* tags = reinterpret_cast<unsigned*>(B->hmap + 2 * slot_doubles);
-      tags[0] = 0;
-      tags[16] = 0;
     }
     B->vb = (double*)B->dalloc(sizeof(double) * B->N);
     B->vr = (double*)B->dalloc(sizeof(double) * B->N);

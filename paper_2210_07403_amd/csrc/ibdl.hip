@@ -23,9 +23,10 @@ using namespace ibdl;
 
 namespace {
 
-constexpr int kSlot = 1024;   // doubles per host-mapped Arnoldi slot (h1, h2 and the norm)
-constexpr int kYOff = 2 * kSlot + 128;   // host-mapped doubles before the GMRES solution y
-constexpr int kYSlot = 256;
+// host-mapped doubles of a handle: the records of two steps in flight, then the squared norms a solve
+// ends with
+constexpr int kYOff = 2 * GM_REC;
+constexpr int kHmap = kYOff + 2;
 
 template <typename T> struct GridWork {
   cplx<T>* tw[3] = {nullptr, nullptr, nullptr};
@@ -108,14 +109,10 @@ struct ibdl_s {
   double* vb = nullptr;       // right-hand side
   double* vr = nullptr;       // residual scratch
   double* hostbuf = nullptr;  // pinned host scratch (1024 doubles)
-  // host-mapped coherent memory for the per-iteration Arnoldi values: the GPU writes them and a
-  // sequence tag, the host polls the tag (no copy-engine transfer, no stream-sync wake-up)
-  // host-mapped Arnoldi values: two slots of kSlot doubles, then one 64-byte tag per slot, then
-  // the least-squares solution y of the last GMRES call (kYSlot doubles, read by the device)
+  // host-mapped coherent memory for the per-iteration Krylov state (two records, GM_REC): the GPU
+  // writes it and the host polls it (no copy-engine transfer, no stream-sync wake-up)
   double* hmap = nullptr;
   double* hmap_dev = nullptr;
-  volatile unsigned* htag = nullptr;
-  unsigned* htag_dev = nullptr;
   unsigned seq = 0;
   // the working-precision operator apply (and its transpose) captured in HIP graphs, replayed from
   // the fixed vectors gx -> gy inside GMRES (rebuilt when the markers change)
@@ -938,20 +935,18 @@ double host_norm(ibdl_s* h, const double* v, int64_t n) {
   return sqrt(h->hostbuf[0]);
 }
 
-// Wait for a publication: poll its tag for up to 2 ms (an iteration's GPU work is well below that),
-// then fall back to a stream synchronisation, after which the tag must be there.
-const volatile double* wait_published(ibdl_s* h, int slot, unsigned seq) {
-  volatile unsigned* tag = h->htag + 16 * slot;
+// Wait for step number seq's record: poll it for up to 2 ms (an iteration's GPU work is well below
+// that), then fall back to a stream synchronisation, after which it must be there.
+void wait_published(ibdl_s* h, int slot, unsigned seq, double* out) {
+  const volatile double* rec = h->hmap + slot * GM_REC;
   const auto t0 = std::chrono::steady_clock::now();
-  while (*tag != seq) {
+  while (!gm_pub_read(rec, seq, out)) {
     if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) {
       IBDL_HIP(hipStreamSynchronize(h->st));
-      if (*tag != seq) throw Error(IBDL_ERR_HIP, "Arnoldi values did not reach the host");
+      if (!gm_pub_read(rec, seq, out)) throw Error(IBDL_ERR_HIP, "Arnoldi values did not reach the host");
       break;
     }
   }
-  std::atomic_thread_fence(std::memory_order_acquire);
-  return h->hmap + slot * kSlot;
 }
 
 // GMRES applies the working-precision operator (transposed with trans) by replaying a HIP graph
@@ -1017,8 +1012,7 @@ int gmres(ibdl_s* h, const double* b, double tol, int maxit, double* x, ibdl_inf
   double* gin = graph ? h->gx : nullptr;
   // |b|^2 (small[GM_BNORM2_AT]) and V[0] = b / |b| (also the graph's input) on the device, so that
   // step 0 is queued without a host round trip; step 0's least-squares update takes |b| from there
-  kr_multidot(b, n, 1, b, n, h->partial, nblk, h->small + GM_BNORM2_AT, h->st);
-  kr_scale_norm(b, h->small + GM_BNORM2_AT, 0.0, h->V, gin, n, h->st);
+  kr_gmres_start(b, n, h->partial, nblk, h->small + GM_BNORM2_AT, h->V, gin, h->st);
   unsigned seq[2] = {0, 0};
   // queue Arnoldi step j (V[j] is in place, and in gx for the graph): apply, orthogonalise, update
   // the least-squares state, publish it and, in the same launch, normalise w into V[j+1] (and gx)
@@ -1033,15 +1027,8 @@ int gmres(ibdl_s* h, const double* b, double tol, int maxit, double* x, ibdl_inf
     }
     const int slot = j & 1;
     seq[slot] = ++h->seq;
-    if (n <= kSmallN) {   // one workgroup holds the vectors: the whole step in one launch
-      kr_arnoldi_small(h->V, n, j + 1, w, n, h->small, 512, h->gm, mx, tol, h->hmap_dev + slot * kSlot,
-                       h->htag_dev + 16 * slot, seq[slot], h->V + (int64_t)(j + 1) * n, gin, h->st);
-      return;
-    }
-    kr_arnoldi_step(h->V, n, j + 1, w, n, h->partial, anblk, h->small, h->st);
-    kr_publish_scale(h->small, h->partial + (int64_t)2 * (j + 1) * anblk, anblk, 512, h->gm, j, mx, tol,
-                     h->hmap_dev + slot * kSlot, h->htag_dev + 16 * slot, seq[slot], w, h->V + (int64_t)(j + 1) * n,
-                     gin, n, h->st);
+    kr_arnoldi_step(h->V, n, j + 1, w, n, h->partial, anblk, h->small, h->gm, mx, tol, h->hmap_dev + slot * GM_REC,
+                    seq[slot], h->V + (int64_t)(j + 1) * n, gin, h->st);
   };
   step(0);
   int k = 0;
@@ -1065,7 +1052,8 @@ int gmres(ibdl_s* h, const double* b, double tol, int maxit, double* x, ibdl_inf
       }
     }
     if (ahead) step(j + 1);
-    const volatile double* hv = wait_published(h, j & 1, seq[j & 1]);
+    double hv[GM_PUB];
+    wait_published(h, j & 1, seq[j & 1], hv);
     const double beta = hv[GM_BETA], hn = hv[GM_HN];
     if (j == 0 && beta_out) *beta_out = beta;
     // |b| already small enough for the caller: no solve (x is left alone)
@@ -1533,13 +1521,10 @@ ibdl_status_t ibdl_create(const ibdl_config_t* cfg, int64_t n_ib, const double* 
     h->vb = (double*)h->dalloc<double>(sizeof(double) * h->n_aug);
     h->vr = (double*)h->dalloc<double>(sizeof(double) * h->n_aug);
     IBDL_HIP(hipHostMalloc((void**)&h->hostbuf, sizeof(double) * 1024, hipHostMallocDefault));
-    IBDL_HIP(hipHostMalloc((void**)&h->hmap, sizeof(double) * (kYOff + kYSlot),
+    IBDL_HIP(hipHostMalloc((void**)&h->hmap, sizeof(double) * kHmap,
                            hipHostMallocMapped | hipHostMallocCoherent));
     IBDL_HIP(hipHostGetDevicePointer((void**)&h->hmap_dev, h->hmap, 0));
-    h->htag = reinterpret_cast<volatile unsigned*>(h->hmap + 2 * kSlot);
-    h->htag_dev = reinterpret_cast<unsigned*>(h->hmap_dev + 2 * kSlot);
-    h->htag[0] = 0;
-    h->htag[16] = 0;
+    memset(h->hmap, 0, sizeof(double) * kHmap);
     IBDL_HIP(hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
     IBDL_HIP(hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming));
     IBDL_HIP(hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming));
@@ -1780,8 +1765,9 @@ ibdl_status_t ibdl_solve(ibdl_t h, const double* data, const void* g_grid, doubl
     else rhs_t<double>(h, data, (const double*)g_grid, h->vb);
     int iters = 0;
     double relres = 0;
+    double bn = 0.0;
     const int status = h->sl ? minres(h, h->vb, tol, maxit, q, info, &iters, &relres)
-                             : gmres(h, h->vb, tol, maxit, q, info, &iters, &relres);
+                             : gmres(h, h->vb, tol, maxit, q, info, &iters, &relres, false, &bn);
     // True residual ||b - A q|| / ||b|| with a double-precision apply, queued on the handle's
     // stream right behind the solution.  On a mixed handle it uses the double work arrays and the
     // recovery the float ones, so the (shorter) recovery runs beside it on the second stream.
@@ -1792,12 +1778,10 @@ ibdl_status_t ibdl_solve(ibdl_t h, const double* data, const void* g_grid, doubl
       IBDL_HIP(hipStreamWaitEvent(h->aux, h->ev_fork, 0));
     }
     apply_any(h, q, h->vr, true);
-    kr_axpby(h->vr, 1.0, h->vb, -1.0, h->n_aug, h->st);
     const int nblk = kr_nblk(h->n_aug);
     ensure_partial(h, nblk);
-    kr_multidot(h->vr, h->n_aug, 1, h->vr, h->n_aug, h->partial, nblk, h->small + 600, h->st);
-    kr_multidot(h->vb, h->n_aug, 1, h->vb, h->n_aug, h->partial, nblk, h->small + 601, h->st);
-    IBDL_HIP(hipMemcpyAsync(h->hostbuf + 600, h->small + 600, 2 * sizeof(double), hipMemcpyDeviceToHost, h->st));
+    kr_resid_norm2(h->vb, h->vr, h->n_aug, h->partial, nblk, h->hmap_dev + kYOff, h->st);
+    if (h->sl) kr_multidot(h->vb, h->n_aug, 1, h->vb, h->n_aug, h->partial, nblk, h->hmap_dev + kYOff + 1, h->st);
     if (u_grid) {
       if (overlap) h->st = h->aux;
       try {
@@ -1814,7 +1798,9 @@ ibdl_status_t ibdl_solve(ibdl_t h, const double* data, const void* g_grid, doubl
       IBDL_HIP(hipStreamWaitEvent(main, h->ev_join, 0));
     }
     IBDL_HIP(hipStreamSynchronize(main));
-    const double rn = sqrt(std::max(h->hostbuf[600], 0.0)), bn = sqrt(std::max(h->hostbuf[601], 0.0));
+    const volatile double* hy = h->hmap + kYOff;
+    const double rn = sqrt(std::max((double)hy[0], 0.0));
+    if (h->sl) bn = sqrt(std::max((double)hy[1], 0.0));
     if (info) {
       info->iters = iters;
       info->status = status;

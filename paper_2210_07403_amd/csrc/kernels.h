@@ -339,8 +339,6 @@ template <typename T> void grid_sum(const T* x, int ncomp, int64_t n, double* pa
 // ------------------------------------------------------------------ Krylov vectors (double)
 void kr_multidot(const double* V, int64_t ldv, int k, const double* w, int64_t n, double* partial,
                  int nblk, double* out, hipStream_t st);
-void kr_gemv_sub(const double* V, int64_t ldv, int k, const double* h, double* w, int64_t n, hipStream_t st);
-void kr_lincomb(const double* V, int64_t ldv, int k, const double* y, double* x, int64_t n, hipStream_t st);
 void kr_scale(const double* src, double s, double* dst, int64_t n, hipStream_t st);
 // dst (and dst2 unless NULL) = src / sqrt(max(*nrm2, 0)) with the norm read on the device; zero
 // when the norm is not above floor or not finite
@@ -349,52 +347,50 @@ void kr_scale_norm(const double* src, const double* nrm2, double floor, double* 
 void kr_axpby(double* y, double a, const double* x, double b, int64_t n, hipStream_t st);
 void kr_border(const double* q, const double* ds, int64_t n_ib, int nq, double eta, double* out,
                double* partial, int nblk, hipStream_t st);
-void kr_add(double* dst, const double* a, const double* b, int n, hipStream_t st);
 int kr_nblk(int64_t n);
-// One Arnoldi step's vector work, classical Gram-Schmidt twice on w against V_0..V_{k-1}
-// (three launches; each reduces the previous one's block partial sums itself, in a fixed order):
-// h[j] = V_j . w, w -= V h; h[256 + j] = V_j . w, w -= V h[256..]; the block partial sums of w . w
-// are left at partial + 2 k nblk (reduced by kr_publish).  partial: (2 k + 1) * nblk doubles with
-// nblk = kr_arnoldi_nblk(n); k <= 256.
-void kr_arnoldi_step(const double* V, int64_t ldv, int k, double* w, int64_t n, double* partial, int nblk,
-                     double* h, hipStream_t st);
-int kr_arnoldi_nblk(int64_t n);
-// Copy src[0..n) to host_dst, with src[norm_at] first set to the sum of pnorm[0..nblk) unless pnorm
-// is NULL.  host_dst / host_tag: device addresses of host-mapped, coherent pinned memory; the tag is
-// written last, after a system-scope fence
-void kr_publish(double* src, int n, const double* pnorm, int nblk, int norm_at, double* host_dst,
-                unsigned* host_tag, unsigned seq, hipStream_t st);
 // GMRES least-squares state in device memory (kr_gmres_state_doubles(mx) doubles for at most mx
 // steps): scalars GM_BETA (|b|), GM_RES (Krylov residual estimate / |b|), GM_K (steps the solution
 // uses), GM_DONE (1 once res <= tol or the process broke down: later steps leave the state alone),
 // GM_HN (|w| of the last step), then the rotations, the rotated right-hand side, the solution y and
 // the rotated Hessenberg columns.  The first GM_PUB scalars are what a step publishes to the host.
 enum { GM_BETA = 0, GM_RES = 1, GM_K = 2, GM_DONE = 3, GM_HN = 4, GM_PUB = 5, GM_HDR = 16 };
-// the Arnoldi scratch h holds the first Gram-Schmidt pass at [0, 256), the second at [256, 512),
-// |w|^2 at 512 and |b|^2 at GM_BNORM2_AT
+// A published record: the GM_PUB scalars and a check word, the exclusive or of their bits and of a key
+// made of the step's sequence number.  The words may reach the host in any order: it takes the record
+// once the check word fits (a word of an earlier step fits only if it equals the new one), so the
+// device waits for no fence.
+constexpr int GM_REC = 8;   // doubles per record (64 bytes)
+__host__ __device__ inline unsigned long long gm_pub_key(unsigned seq) { return (seq + 1ull) * 0x9E3779B97F4A7C15ull; }
+inline bool gm_pub_read(const volatile double* rec, unsigned seq, double* out) {
+  unsigned long long c = gm_pub_key(seq), w;
+  for (int i = 0; i <= GM_PUB; ++i) {
+    const double v = rec[i];
+    __builtin_memcpy(&w, &v, 8);
+    c ^= w;
+    if (i < GM_PUB) out[i] = v;
+  }
+  return c == 0;
+}
+// the Arnoldi scratch h holds the first Gram-Schmidt pass at [0, 256) and |b|^2 at GM_BNORM2_AT
 constexpr int GM_BNORM2_AT = 520;
 size_t kr_gmres_state_doubles(int mx);
-// End of Arnoldi step j (w orthogonalised by kr_arnoldi_step, its norm partials at pnorm): h[norm_at]
-// = |w|^2, the least-squares update of step j in gs (tolerance tol, at most mx <= 256 steps), the
-// state's first GM_PUB scalars copied to the host slot, the tag; and, in the same launch, dst (and
-// dst2 if set) = w / |w| over nv entries (0 where the norm is 0 or not finite), every workgroup
-// reducing the partials itself in the same order.
-void kr_publish_scale(double* h, const double* pnorm, int nblk, int norm_at, double* gs, int j, int mx, double tol,
-                      double* host_dst, unsigned* host_tag, unsigned seq, const double* w, double* dst, double* dst2,
-                      int64_t nv, hipStream_t st);
-// kr_arnoldi_step and kr_publish_scale in one workgroup and one launch for n <= kSmallN (step k - 1,
-// k basis vectors); deterministic, its sums group the entries differently from the blocked path
-constexpr int kSmallN = 256;
-void kr_arnoldi_small(const double* V, int64_t ldv, int k, double* w, int64_t n, double* h, int norm_at, double* gs,
-                      int mx, double tol, double* host_dst, unsigned* host_tag, unsigned seq, double* dst,
-                      double* dst2, hipStream_t st);
-// y = R^-1 g of the state's GM_K steps, in device memory at kr_gmres_ydev(gs, mx)
-void kr_gmres_y(double* gs, int mx, hipStream_t st);
-const double* kr_gmres_ydev(double* gs, int mx);
-// y = R^-1 g and x = V y over the state's GM_K steps; gate: only if the state's convergence flag is
-// set when the kernels run (queued behind a step predicted to be the last)
-void kr_gmres_finish(double* gs, int mx, const double* V, int64_t ldv, double* x, int64_t n, bool gate,
+int kr_arnoldi_nblk(int64_t n);
+constexpr int kArnoldiOne = 1024;   // longest vectors whose Arnoldi step one workgroup does
+// One Arnoldi step, step k - 1: classical Gram-Schmidt twice on w against V_0..V_{k-1} (w is scratch
+// afterwards unless it is vdst), |w|, the least-squares update in gs (tolerance tol, at most mx <= 256
+// steps), vdst (and vdst2 if set) = w / |w| (0 where that is 0 or not finite), the state's record of
+// step number seq to host_dst (device address of host-mapped, coherent pinned memory).  partial: (2 k + 1) * nblk doubles with nblk = kr_arnoldi_nblk(n).
+void kr_arnoldi_step(const double* V, int64_t ldv, int k, double* w, int64_t n, double* partial, int nblk, double* h,
+                     double* gs, int mx, double tol, double* host_dst, unsigned seq, double* vdst, double* vdst2,
                      hipStream_t st);
+// *bn2 = |b|^2, v0 (and v02 if set) = b / |b| (0 where |b| is 0 or not finite)
+void kr_gmres_start(const double* b, int64_t n, double* partial, int nblk, double* bn2, double* v0, double* v02,
+                    hipStream_t st);
+// x = V y, y = R^-1 g over the state's GM_K steps; gate: only if the state's convergence flag is set
+// when the kernel runs (queued behind a step predicted to be the last)
+void kr_gmres_finish(const double* gs, int mx, const double* V, int64_t ldv, double* x, int64_t n, bool gate,
+                     hipStream_t st);
+// *out = |b - a|^2 (partial: nblk = kr_nblk(n) doubles)
+void kr_resid_norm2(const double* b, const double* a, int64_t n, double* partial, int nblk, double* out, hipStream_t st);
 
 // ------------------------------------------------------------------ batched Krylov vectors
 // Concatenated per-problem vectors of total length n: seg[e] is element e's problem; dot-product
@@ -411,11 +407,8 @@ struct KrylovSegments {
 // out[p * ostride + j] = <V_j, w> over problem p's segment, j < k
 void kb_multidot(const double* V, int64_t ldv, int k, const double* w, const KrylovSegments& sg, double* partial,
                  int ostride, double* out, hipStream_t st);
-void kb_gemv_sub(const double* V, int64_t ldv, int k, const double* H, int hs, const KrylovSegments& sg, double* w,
-                 hipStream_t st);
 void kb_lincomb(const double* V, int64_t ldv, int k, const double* Y, int ys, const KrylovSegments& sg, double* x,
                 hipStream_t st);
-void kb_scale(const double* src, const double* sc, const KrylovSegments& sg, double* dst, hipStream_t st);
 // Batched GMRES on the device, one workgroup per problem; off[p], len[p] (device) locate problem p's
 // segment of the batch vectors, bn2[p] = |b_p|^2, gsb + p * gstride its least-squares state
 // (kr_gmres_state_doubles(mx) doubles each).
@@ -428,13 +421,11 @@ void kb_gmres_start(const double* b, const int64_t* off, const int64_t* len, int
                     double* xin, hipStream_t st);
 // Arnoldi step j of every problem (w = A V_j): CGS2, |w|, the least-squares update, then vnext (and
 // xin) = w / |w|; problems already converged write zeros and keep their state.
-// maxlen: the largest len[p] (problems of at most 4096 unknowns keep w in registers).
+// maxlen: the largest len[p] (problems of at most 4096 unknowns keep w in registers).  Every problem's
+// record goes to host_dst + p GM_REC.
 void kb_arnoldi(const double* V, int64_t ldv, int j, double* w, const int64_t* off, const int64_t* len, int np,
                 int64_t maxlen, const double* bn2, double* gsb, int64_t gstride, int mx, double tol, double* vnext,
-                double* xin, hipStream_t st);
-// every problem's first GM_PUB state scalars to the host slot ([np][GM_PUB]), then the tag
-void kb_publish(const double* gsb, int64_t gstride, int np, double* host_dst, unsigned* host_tag, unsigned seq,
-                hipStream_t st);
+                double* xin, double* host_dst, unsigned seq, hipStream_t st);
 // Y[p][0..kmax) = the least-squares solution of problem p (zeros beyond its step count)
 void kb_gmres_y(double* gsb, int64_t gstride, int np, int mx, int kmax, double* Y, int ys, hipStream_t st);
 

@@ -42,43 +42,6 @@ __global__ void k_reduce(const double* __restrict__ partial, int nblk, double* _
   }
 }
 
-__global__ void k_gemv_sub(const double* __restrict__ V, int64_t ldv, int k, const double* __restrict__ h,
-                           double* __restrict__ w, int64_t n) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    double s = w[e];
-    for (int j = 0; j < k; ++j) s -= V[j * ldv + e] * h[j];
-    w[e] = s;
-  }
-}
-
-// x = sum_j y_j V_j (k <= 256); y is read once per workgroup into LDS (it may live in host memory)
-__global__ void k_lincomb(const double* __restrict__ V, int64_t ldv, int k, const double* __restrict__ y,
-                          double* __restrict__ x, int64_t n) {
-  __shared__ double ys[256];
-  for (int j = threadIdx.x; j < k; j += blockDim.x) ys[j] = y[j];
-  __syncthreads();
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0.0;
-    for (int j = 0; j < k; ++j) s += V[j * ldv + e] * ys[j];
-    x[e] = s;
-  }
-}
-
-// x = V y over the k = gs[GM_K] steps of a GMRES state; gate as in k_gmres_y
-__global__ void k_lincomb_state(const double* __restrict__ V, int64_t ldv, const double* __restrict__ gs,
-                                const double* __restrict__ y, double* __restrict__ x, int64_t n, int gate) {
-  __shared__ double ys[256];
-  if (gate && gs[GM_DONE] == 0.0) return;
-  const int k = (int)gs[GM_K];
-  for (int j = threadIdx.x; j < k; j += blockDim.x) ys[j] = y[j];
-  __syncthreads();
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0.0;
-    for (int j = 0; j < k; ++j) s += V[j * ldv + e] * ys[j];
-    x[e] = s;
-  }
-}
-
 __global__ void k_scale(const double* __restrict__ src, double s, double* __restrict__ dst, int64_t n) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
     dst[e] = src[e] * s;
@@ -102,10 +65,6 @@ __global__ void k_scale_norm(const double* src, const double* __restrict__ nrm2,
 __global__ void k_axpby_d(double* __restrict__ y, double a, const double* __restrict__ x, double b, int64_t n) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
     y[e] = a * x[e] + b * y[e];
-}
-
-__global__ void k_add_small(double* __restrict__ dst, const double* __restrict__ a, const double* __restrict__ b, int n) {
-  for (int e = threadIdx.x; e < n; e += blockDim.x) dst[e] = a[e] + b[e];
 }
 
 // partial sums of eta * ds_i * q[i][c] over markers, per component c (ds = NULL: unit weights)
@@ -208,76 +167,63 @@ __global__ void k_adj_coefs(int stokes, int dim, int64_t n_ib, int nc, double hD
   }
 }
 
-// One Arnoldi step's vector work.  MODE 0: d_j = V_j . w (j < k); MODE 1: w -= V h, then
-// d_j = V_j . w; MODE 2: w -= V h, then d_0 = w . w.  A block handles 256 elements, one per thread
-// (the thread updates its element and then reads it, so no barrier is needed between the update and
-// the dots); dot products are taken eight at a time, each thread keeping eight partial products and
-// the block adding them in a fixed tree.  The per-block partials are added by k_arnoldi_reduce, one
-// block per dot product, in a fixed order, so the sums do not depend on scheduling.  (A last-block
-// reduction inside the first kernel would need device-wide fences, which write back the per-XCD L2
-// caches and cost more than the second launch.)
-constexpr int kArnChunk = 256;
-constexpr int kArnGroup = 8;
-
-// Sum of p[0..nblk) by one wave: lane strides, then a butterfly.  Every wave and workgroup that
-// sums the same values gets the same bits (the butterfly's pairwise sums commute), so a dot product
-// reduced redundantly by each workgroup that needs it equals the copy the host receives.
-__device__ __forceinline__ double wave_sum(const double* __restrict__ p, int nblk, int lane) {
-  double s = 0.0;
-  for (int b = lane; b < nblk; b += 64) s += p[b];
+// ------------------------------------------------------------------ sums over a workgroup
+// KR per-thread values at once: each wave folds them so that a lane ends with the whole wave's sum of
+// one value (17 exchanges for 16 values, against 96 for a butterfly of each), then one wave adds the
+// waves' sums.  The order is fixed, so the sums do not depend on scheduling, and every workgroup that
+// sums the same values gets the same bits.
+template <int KR> __device__ __forceinline__ double wave_fold(double (&v)[KR], int lane) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  return s;
-}
-
-// Arnoldi vector work on 256-element blocks.  mode 0: pout[j][b] = block b's part of V_j . w.
-// mode 1 / 2: h_j = the sums of pin[j][*] (the previous mode's dots, reduced in every workgroup;
-// workgroup 0 also stores them to hout), w -= V h, then mode 1 pout[j][b] = V_j . w, mode 2
-// pout[0][b] = w . w; j < k <= 256.
-template <int MODE>
-__global__ __launch_bounds__(kB) void k_arnoldi(const double* __restrict__ V, int64_t ldv, int k, double* w,
-                                                const double* __restrict__ pin, double* __restrict__ hout,
-                                                int64_t n, int nblk, double* __restrict__ pout) {
-  __shared__ double red[kArnGroup][kB];
-  __shared__ double hs[256];
-  const int64_t e = (int64_t)blockIdx.x * kArnChunk + threadIdx.x;
-  const bool in = e < n;
-  double we = in ? w[e] : 0.0;
-  if (MODE > 0) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int j = wave; j < k; j += kB / 64) {
-      const double v = wave_sum(pin + (int64_t)j * nblk, nblk, lane);
-      if (lane == 0) hs[j] = v;
-    }
-    __syncthreads();
-    if (blockIdx.x == 0)
-      for (int j = threadIdx.x; j < k; j += kB) hout[j] = hs[j];
-    if (in) {
-      for (int j = 0; j < k; ++j) we -= V[j * ldv + e] * hs[j];
-      w[e] = we;
+  for (int h = KR / 2, off = 32; h >= 1; h /= 2, off /= 2) {
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int i = 0; i < h; ++i) {
+      const double a = v[i], b = v[i + h];   // (named: selecting between array elements is compiled as indexing)
+      const double keep = up ? b : a, send = up ? a : b;
+      v[i] = keep + __shfl_xor(send, off);
     }
   }
-  const int nd = MODE == 2 ? 1 : k;
-  for (int d0 = 0; d0 < nd; d0 += kArnGroup) {
 #pragma unroll
-    for (int g = 0; g < kArnGroup; ++g) {
-      const int d = d0 + g;
-      double p = 0.0;
-      if (in && d < nd) p = (MODE == 2 ? we : V[d * ldv + e]) * we;
-      red[g][threadIdx.x] = p;
-    }
-    __syncthreads();
-    for (int st = kB / 2; st > 0; st >>= 1) {
-      if (threadIdx.x < st) {
-#pragma unroll
-        for (int g = 0; g < kArnGroup; ++g) red[g][threadIdx.x] += red[g][threadIdx.x + st];
-      }
-      __syncthreads();
-    }
-    if (threadIdx.x < kArnGroup && d0 + threadIdx.x < nd) pout[(d0 + threadIdx.x) * nblk + blockIdx.x] = red[threadIdx.x][0];
-    __syncthreads();
-  }
+  for (int off = 32 / KR; off > 0; off /= 2) v[0] += __shfl_xor(v[0], off);
+  return v[0];   // the sum of value lane / (64 / KR)
 }
+
+// out[0..KR) (LDS) = the workgroup's sums; part: [NT / 64][KR] of LDS.  Ends with a barrier.
+template <int NT, int KR> __device__ __forceinline__ void block_fold(double (&v)[KR], double* part, double* out) {
+  constexpr int NW = NT / 64, G = 64 / KR;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double s = wave_fold<KR>(v, lane);
+  if (lane % G == 0) part[wave * KR + lane / G] = s;
+  __syncthreads();
+  if (wave == 0) {
+    const int g = lane % KR, q0 = lane / KR;
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; q += G)
+      if (q + q0 < NW) t += part[(q + q0) * KR + g];
+#pragma unroll
+    for (int off = KR; off < 64; off *= 2) t += __shfl_xor(t, off);
+    if (lane < KR) out[g] = t;
+  }
+  __syncthreads();
+}
+
+// out[j] (LDS) = the sum of p[j * nblk .. + nblk) for j < cnt, sixteen lanes per sum; ends with a barrier
+__device__ __forceinline__ void sum_partials(const double* __restrict__ p, int cnt, int nblk, double* out) {
+  const int l = threadIdx.x & 15;
+  for (int j = threadIdx.x >> 4; j < cnt; j += kB / 16) {
+    double s = 0.0;
+#pragma unroll 4
+    for (int b = l; b < nblk; b += 16) s += p[(int64_t)j * nblk + b];
+#pragma unroll
+    for (int off = 8; off > 0; off /= 2) s += __shfl_xor(s, off, 16);
+    if (l == 0) out[j] = s;
+  }
+  __syncthreads();
+}
+
+constexpr int kArnChunk = 256;   // entries per workgroup of the blocked Arnoldi kernels, one per thread
+constexpr int kArnK = 16;        // basis vectors a thread holds at a time
 
 // ------------------------------------------------------------------ batched (segmented) vectors
 // A batch vector is the concatenation of the problems' vectors; block b of a segmented dot covers
@@ -314,17 +260,6 @@ __global__ void k_breduce(const double* __restrict__ partial, int nblk, const in
   }
 }
 
-// w[e] -= sum_j V_j[e] H[seg(e)][j]
-__global__ void k_bgemv_sub(const double* __restrict__ V, int64_t ldv, int k, const double* __restrict__ H,
-                            int hs, const int* __restrict__ seg, double* __restrict__ w, int64_t n) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const double* hp = H + (int64_t)seg[e] * hs;
-    double s = w[e];
-    for (int j = 0; j < k; ++j) s -= V[j * ldv + e] * hp[j];
-    w[e] = s;
-  }
-}
-
 // x[e] = sum_j V_j[e] Y[seg(e)][j]
 __global__ void k_blincomb(const double* __restrict__ V, int64_t ldv, int k, const double* __restrict__ Y, int ys,
                            const int* __restrict__ seg, double* __restrict__ x, int64_t n) {
@@ -334,13 +269,6 @@ __global__ void k_blincomb(const double* __restrict__ V, int64_t ldv, int k, con
     for (int j = 0; j < k; ++j) s += V[j * ldv + e] * yp[j];
     x[e] = s;
   }
-}
-
-// dst[e] = src[e] * sc[seg(e)]
-__global__ void k_bscale(const double* __restrict__ src, const double* __restrict__ sc, const int* __restrict__ seg,
-                         double* __restrict__ dst, int64_t n) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
-    dst[e] = src[e] * sc[seg[e]];
 }
 
 // ------------------------------------------------------------------ GMRES least squares
@@ -357,53 +285,62 @@ __device__ __forceinline__ double* gm_g(double* gs, int mx) { return gs + GM_HDR
 __device__ __forceinline__ double* gm_y(double* gs, int mx) { return gs + GM_HDR + 3 * mx + 1; }
 __device__ __forceinline__ double* gm_R(double* gs, int mx) { return gs + GM_HDR + 4 * mx + 2; }
 
-// Run by a whole workgroup of kB threads (the sequential rotation sweep by thread 0 on values staged
-// in LDS).  bnorm2 = |b|^2 (read at step 0), nrm2 = |w|^2 of this step.
-__device__ void givens_step(const double* __restrict__ h1, const double* __restrict__ h2, double nrm2,
-                            double bnorm2, int j, int mx, double tol, double* gs) {
-  __shared__ double col[257], c_s[256], s_s[256];
-  __shared__ int frozen;
-  if (threadIdx.x == 0) frozen = j > 0 && gs[GM_DONE] != 0.0;
-  __syncthreads();
-  if (frozen) return;
-  const double* cs = gm_cs(gs);
-  const double* sn = gm_sn(gs, mx);
-  for (int i = threadIdx.x; i <= j; i += kB) {
-    col[i] = h1[i] + h2[i];
-    if (i < j) {
-      c_s[i] = cs[i];
-      s_s[i] = sn[i];
-    }
+// What a step's least-squares update reads of the state, staged in LDS when the step's kernel starts
+// (beside its first vector loads) so that the update waits for no memory.
+struct GivensLds {
+  double c[256], s[256], col[257];
+  double beta, g;   // |b|, g[j]
+  int frozen;
+};
+__device__ __forceinline__ void givens_stage(GivensLds& G, const double* gs, int mx, int j, double bnorm2) {
+  double* m = const_cast<double*>(gs);
+  for (int i = threadIdx.x; i < j; i += blockDim.x) {
+    G.c[i] = gm_cs(m)[i];
+    G.s[i] = gm_sn(m, mx)[i];
   }
-  __syncthreads();
   if (threadIdx.x == 0) {
+    G.frozen = j > 0 && gs[GM_DONE] != 0.0;
+    G.beta = j > 0 ? gs[GM_BETA] : sqrt(bnorm2 < 0.0 ? 0.0 : bnorm2);
+    G.g = j > 0 ? gm_g(m, mx)[j] : G.beta;
+  }
+}
+
+// Run by one wave, after a barrier behind givens_stage (the sequential rotation sweep by lane 0).
+// h1, h2: the two Gram-Schmidt passes' dots (LDS), nrm2 = |w|^2 of this step.
+__device__ __forceinline__ void givens_update(GivensLds& G, const double* h1, const double* h2, double nrm2, int j, int mx,
+                                              double tol, double* gs) {
+  const int lane = threadIdx.x & 63;
+  if (G.frozen) return;
+  for (int i = lane; i <= j; i += 64) G.col[i] = h1[i] + h2[i];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) {
     double* g = gm_g(gs, mx);
-    double beta;
+    const double beta = G.beta, hn = sqrt(nrm2 < 0.0 ? 0.0 : nrm2);
     if (j == 0) {
-      beta = sqrt(bnorm2 < 0.0 ? 0.0 : bnorm2);
       gs[GM_BETA] = beta;
       g[0] = beta;
-    } else {
-      beta = gs[GM_BETA];
     }
-    const double hn = sqrt(nrm2 < 0.0 ? 0.0 : nrm2);
-    col[j + 1] = hn;
+    double cur = G.col[0];
+#pragma unroll 4
     for (int i = 0; i < j; ++i) {
-      const double t = c_s[i] * col[i] + s_s[i] * col[i + 1];
-      col[i + 1] = -s_s[i] * col[i] + c_s[i] * col[i + 1];
-      col[i] = t;
+      const double nxt = G.col[i + 1], c = G.c[i], sv = G.s[i];
+      G.col[i] = c * cur + sv * nxt;
+      cur = -sv * cur + c * nxt;
     }
+    G.col[j] = cur;
     double res = 0.0;
     bool stop = true;
     if (beta > 0.0) {
-      const double r = hypot(col[j], col[j + 1]);
-      const double c = col[j] / r, sv = col[j + 1] / r;
+      const double r = hypot(cur, hn);
+      const double c = cur / r, sv = hn / r;
       gm_cs(gs)[j] = c;
       gm_sn(gs, mx)[j] = sv;
-      col[j] = r;
-      g[j + 1] = -sv * g[j];
-      g[j] = c * g[j];
-      res = fabs(g[j + 1]) / beta;
+      G.col[j] = r;
+      const double gn = -sv * G.g;
+      g[j + 1] = gn;
+      g[j] = c * G.g;
+      res = fabs(gn) / beta;
       const bool breakdown = !(hn > 1e-300 * beta);
       stop = res <= tol || breakdown || !(res == res);
       gs[GM_K] = (double)(j + 1);
@@ -414,167 +351,130 @@ __device__ void givens_step(const double* __restrict__ h1, const double* __restr
     gs[GM_HN] = hn;
     gs[GM_DONE] = stop ? 1.0 : 0.0;
   }
-  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
   double* R = gm_R(gs, mx) + (int64_t)j * (mx + 1);
-  for (int i = threadIdx.x; i <= j; i += kB) R[i] = col[i];
+  for (int i = lane; i <= j; i += 64) R[i] = G.col[i];
 }
 
-// The least-squares solution y = R^-1 g of the k = gs[GM_K] steps, by one workgroup: with k <= 64
-// the triangle is staged in LDS once, otherwise each column is read as the substitution reaches it.
-// gate: nothing unless the state's convergence flag is set (a finish queued behind a step that the
-// host predicts to be the last, before it has seen that step's result).
-__global__ __launch_bounds__(kB) void k_gmres_y(double* gs, int mx, int gate) {
-  __shared__ double tri[64 * 64];
-  __shared__ double gv[256];
-  __shared__ double yv;
-  if (gate && gs[GM_DONE] == 0.0) return;
-  const int k = (int)gs[GM_K];
-  const double* R = gm_R(gs, mx);
-  const double* g = gm_g(gs, mx);
-  for (int i = threadIdx.x; i < k; i += kB) gv[i] = g[i];
-  const bool staged = k <= 64;
-  if (staged)
-    for (int e = threadIdx.x; e < k * k; e += kB) {
-      const int c = e / k, i = e - c * k;
-      tri[c * 64 + i] = i <= c ? R[(int64_t)c * (mx + 1) + i] : 0.0;
-    }
-  __syncthreads();
-  double* y = gm_y(gs, mx);
-  for (int c = k - 1; c >= 0; --c) {
-    const double* rc = staged ? tri + c * 64 : R + (int64_t)c * (mx + 1);
-    if (threadIdx.x == 0) {
-      yv = gv[c] / rc[c];
-      y[c] = yv;
-    }
-    __syncthreads();
-    const double v = yv;
-    for (int i = threadIdx.x; i < c; i += kB) gv[i] -= rc[i] * v;
-    __syncthreads();
+// By the wave that ran givens_update: the state's record to host-mapped memory (see GM_REC)
+__device__ __forceinline__ void publish_state(const double* gs, double* dst, unsigned seq) {
+  __threadfence_block();
+  const int lane = threadIdx.x & 63;
+  unsigned long long w = 0;
+  if (lane < GM_PUB) {
+    const double v = *const_cast<const volatile double*>(gs + lane);
+    w = __builtin_bit_cast(unsigned long long, v);
   }
-}
-
-// Copy n doubles into host-mapped memory, then (after a system-scope fence) the sequence tag, so a
-// host that sees the tag sees the values.
-// With pnorm set, src[norm_at] is first set to the sum of pnorm[0..nblk) (as k_arnoldi reduces).
-__global__ __launch_bounds__(kB) void k_publish(double* src, int n, const double* __restrict__ pnorm, int nblk,
-                                                int norm_at, double* dst, unsigned* tag, unsigned seq) {
-  if (pnorm) {
-    if (threadIdx.x < 64) {
-      const double v = wave_sum(pnorm, nblk, threadIdx.x);
-      if (threadIdx.x == 0) src[norm_at] = v;
-    }
-    __syncthreads();
-  }
-  for (int i = threadIdx.x; i < n; i += kB) dst[i] = src[i];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence_system();
-    *reinterpret_cast<volatile unsigned*>(tag) = seq;
-  }
-}
-
-// The end of an Arnoldi step in one launch: every workgroup reduces the norm partials itself (in the
-// same order, so with the same bits) and scales its part of w into vdst (and vdst2) by 1/|w|, or by
-// 0 where |w| is 0 or not finite; workgroup 0 also stores |w|^2 at h[norm_at], runs the step's
-// least-squares update (givens_step) and copies the state's scalars (GM_PUB of them) to the host
-// slot, then writes the tag.
-__global__ __launch_bounds__(kB) void k_publish_scale(double* h, const double* __restrict__ pnorm, int nblk,
-                                                      int norm_at, double* gs, int j, int mx, double tol, double* dst,
-                                                      unsigned* tag, unsigned seq, const double* w, double* vdst,
-                                                      double* vdst2, int64_t nv) {
-  __shared__ double nrm2;
-  if (threadIdx.x < 64) {
-    const double v = wave_sum(pnorm, nblk, threadIdx.x);
-    if (threadIdx.x == 0) nrm2 = v;
-  }
-  __syncthreads();
-  const double v = nrm2;
-  if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) h[norm_at] = v;
-    givens_step(h, h + 256, v, h[GM_BNORM2_AT], j, mx, tol, gs);
-    __syncthreads();
-    if (threadIdx.x < GM_PUB) dst[threadIdx.x] = gs[threadIdx.x];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      __threadfence_system();
-      *reinterpret_cast<volatile unsigned*>(tag) = seq;
-    }
-  }
-  const double hh = sqrt(v < 0.0 ? 0.0 : v);
-  const double sc = (hh > 0.0 && hh < INFINITY) ? 1.0 / hh : 0.0;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nv; e += (int64_t)gridDim.x * blockDim.x) {
-    const double x = w[e] * sc;
-    vdst[e] = x;
-    if (vdst2) vdst2[e] = x;
-  }
-}
-
-// The Arnoldi step and its publication in one workgroup and one launch, for vectors of at most
-// kB entries (the marker systems of small problems, where the four launches of the blocked path
-// are mostly launch latency): thread t owns entry t and keeps it in a register; the dot products
-// are taken eight at a time, a butterfly in each wave and then the four waves' sums in order
-// (deterministic; the rounding differs from the blocked path's tree).
-__device__ __forceinline__ void wg_sum8(double (&v)[kArnGroup], double (*lds)[kArnGroup]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  unsigned long long c = w;
 #pragma unroll
-  for (int g = 0; g < kArnGroup; ++g)
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[g] += __shfl_xor(v[g], off);
-  if (lane == 0)
-#pragma unroll
-    for (int g = 0; g < kArnGroup; ++g) lds[wave][g] = v[g];
-  __syncthreads();
-#pragma unroll
-  for (int g = 0; g < kArnGroup; ++g) v[g] = ((lds[0][g] + lds[1][g]) + lds[2][g]) + lds[3][g];
-  __syncthreads();
+  for (int off = 1; off < 8; off *= 2) c ^= __shfl_xor(c, off);
+  if (lane == GM_PUB) w = c ^ gm_pub_key(seq);
+  if (lane <= GM_PUB)
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst) + lane, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-__global__ __launch_bounds__(kB) void k_arnoldi_small(const double* __restrict__ V, int64_t ldv, int k, double* w,
-                                                      int64_t n, double* h, int norm_at, double* gs, int mx,
-                                                      double tol, double* dst, unsigned* tag, unsigned seq,
-                                                      double* vdst, double* vdst2) {
-  __shared__ double lds[4][kArnGroup];
-  __shared__ double hs[256];
-  const int e = threadIdx.x;
+// ------------------------------------------------------------------ blocked Arnoldi step
+// Three launches over 256-entry blocks, one entry per thread, sixteen basis vectors in registers at a
+// time: their loads are issued first and serve the update and the dots.
+//   k_arn0  pout[j][b] = block b's part of V_j . w
+//   k_arn1  h1 = sums of pin (reduced in every workgroup, in the same order), w -= V h1,
+//           pout[j][b] = parts of V_j . w (j < k) and of w . w (j = k)
+//   k_arn2  h2 likewise, w -= V h2, |w|^2 = (w . w before the update) - |h2|^2 (the update takes the
+//           h2 components out of w, so this is its norm to rounding; h2 itself is of the size of the
+//           first pass's rounding), then V_k (and vdst2) = w / |w|; workgroup 0 runs the
+//           least-squares update and publishes the state.
+// What bounds a step at these lengths is the chain of each launch (read what the last launch wrote,
+// fold, write; a vector is a few tens of KB), so it has one launch and two folds fewer than with an LDS
+// tree per eight dots and a norm pass of its own: 20.4 -> 13.6 us a step at 4,096 unknowns (10 basis
+// vectors), 24 -> 14.5 at 2,050, 21 -> 15 at 18,492.
+__device__ __forceinline__ void arn_load(double (&v)[kArnK], const double* __restrict__ V, int64_t ldv, int c0, int k,
+                                         int64_t e, bool in) {
+  // (unconditional loads at clamped places, so that no branch stands between them)
+  const double* p = V + (in ? e : 0);
+#pragma unroll
+  for (int g = 0; g < kArnK; ++g) v[g] = p[(int64_t)(c0 + g < k ? c0 + g : k - 1) * ldv];
+#pragma unroll
+  for (int g = 0; g < kArnK; ++g) v[g] = in && c0 + g < k ? v[g] : 0.0;
+}
+
+__global__ __launch_bounds__(kB) void k_arn0(const double* __restrict__ V, int64_t ldv, int k,
+                                             const double* __restrict__ w, int64_t n, int nblk,
+                                             double* __restrict__ pout) {
+  __shared__ double part[kB / 64 * kArnK], out[kArnK];
+  const int64_t e = (int64_t)blockIdx.x * kArnChunk + threadIdx.x;
+  const bool in = e < n;
+  const double we = in ? w[e] : 0.0;
+  for (int c0 = 0; c0 < k; c0 += kArnK) {
+    double v[kArnK];
+    arn_load(v, V, ldv, c0, k, e, in);
+#pragma unroll
+    for (int g = 0; g < kArnK; ++g) v[g] *= we;
+    block_fold<kB, kArnK>(v, part, out);
+    if (threadIdx.x < kArnK && c0 + (int)threadIdx.x < k) pout[(int64_t)(c0 + threadIdx.x) * nblk + blockIdx.x] = out[threadIdx.x];
+  }
+}
+
+__global__ __launch_bounds__(kB) void k_arn1(const double* __restrict__ V, int64_t ldv, int k, double* __restrict__ w,
+                                             int64_t n, int nblk, const double* __restrict__ pin,
+                                             double* __restrict__ hout, double* __restrict__ pout) {
+  __shared__ double part[kB / 64 * kArnK], out[kArnK], hs[256 + kArnK];
+  const int64_t e = (int64_t)blockIdx.x * kArnChunk + threadIdx.x;
   const bool in = e < n;
   double we = in ? w[e] : 0.0;
-  // two Gram-Schmidt passes: h[j] = V_j . w, w -= V h; h[256 + j] = V_j . w, w -= V h[256..]
-  for (int pass = 0; pass < 2; ++pass) {
-    for (int d0 = 0; d0 < k; d0 += kArnGroup) {
-      double acc[kArnGroup];
+  double v[kArnK];
+  arn_load(v, V, ldv, 0, k, e, in);
+  sum_partials(pin, k, nblk, hs);
+  if (threadIdx.x < kArnK) hs[k + threadIdx.x] = 0.0;
+  if (blockIdx.x == 0)
+    for (int j = threadIdx.x; j < k; j += kB) hout[j] = hs[j];
+  __syncthreads();
+  for (int c0 = 0; c0 < k; c0 += kArnK) {
+    if (c0 > 0) arn_load(v, V, ldv, c0, k, e, in);
 #pragma unroll
-      for (int g = 0; g < kArnGroup; ++g) acc[g] = (in && d0 + g < k) ? V[(int64_t)(d0 + g) * ldv + e] * we : 0.0;
-      wg_sum8(acc, lds);
-      if (threadIdx.x == 0)
+    for (int g = 0; g < kArnK; ++g) we -= v[g] * hs[c0 + g];
+  }
+  if (in) w[e] = we;
+  for (int c0 = 0; c0 <= k; c0 += kArnK) {   // k dots, then w . w
+    if (k > kArnK) arn_load(v, V, ldv, c0, k, e, in);
+    double d[kArnK];
 #pragma unroll
-        for (int g = 0; g < kArnGroup; ++g)
-          if (d0 + g < k) hs[d0 + g] = acc[g];
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < k; j += kB) h[256 * pass + j] = hs[j];
-    if (in) {
-      for (int j = 0; j < k; ++j) we -= V[(int64_t)j * ldv + e] * hs[j];
-      w[e] = we;
-    }
-    __syncthreads();
+    for (int g = 0; g < kArnK; ++g) d[g] = (c0 + g == k ? we : (c0 + g < k ? v[g] : 0.0)) * we;
+    block_fold<kB, kArnK>(d, part, out);
+    if (threadIdx.x < kArnK && c0 + (int)threadIdx.x <= k) pout[(int64_t)(c0 + threadIdx.x) * nblk + blockIdx.x] = out[threadIdx.x];
   }
-  // |w|^2, the least-squares update, the publication (values, then the tag after a system-scope
-  // fence), w / |w|
-  double sq[kArnGroup] = {we * we, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  wg_sum8(sq, lds);
-  const double v = sq[0];
-  if (threadIdx.x == 0) h[norm_at] = v;
-  __syncthreads();
-  givens_step(h, h + 256, v, h[GM_BNORM2_AT], k - 1, mx, tol, gs);
-  __syncthreads();
-  if (threadIdx.x < GM_PUB) dst[threadIdx.x] = gs[threadIdx.x];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence_system();
-    *reinterpret_cast<volatile unsigned*>(tag) = seq;
+}
+
+__global__ __launch_bounds__(kB) void k_arn2(const double* __restrict__ V, int64_t ldv, int k, const double* w, int64_t n,
+                                             int nblk, const double* __restrict__ pin, const double* __restrict__ h1g,
+                                             const double* __restrict__ bn2, double* gs, int mx, double tol, double* dst,
+                                             unsigned seq, double* vdst, double* vdst2) {
+  __shared__ double hs[256 + kArnK], h1[256];
+  __shared__ GivensLds G;
+  const int64_t e = (int64_t)blockIdx.x * kArnChunk + threadIdx.x;
+  const bool in = e < n;
+  double we = in ? w[e] : 0.0;
+  double v[kArnK];
+  arn_load(v, V, ldv, 0, k, e, in);
+  if (blockIdx.x == 0) {
+    givens_stage(G, gs, mx, k - 1, *bn2);
+    for (int j = threadIdx.x; j < k; j += kB) h1[j] = h1g[j];
   }
-  const double nr = sqrt(v < 0.0 ? 0.0 : v);
-  const double sc = (nr > 0.0 && nr < INFINITY) ? 1.0 / nr : 0.0;
+  sum_partials(pin, k + 1, nblk, hs);
+  double nrm2 = hs[k];
+  for (int j = 0; j < k; ++j) nrm2 -= hs[j] * hs[j];
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    givens_update(G, h1, hs, nrm2, k - 1, mx, tol, gs);
+    publish_state(gs, dst, seq);
+  }
+  for (int c0 = 0; c0 < k; c0 += kArnK) {
+    if (c0 > 0) arn_load(v, V, ldv, c0, k, e, in);
+#pragma unroll
+    for (int g = 0; g < kArnK; ++g)
+      if (c0 + g < k) we -= v[g] * hs[c0 + g];
+  }
+  const double hn = sqrt(nrm2 < 0.0 ? 0.0 : nrm2);
+  const double sc = (hn > 0.0 && hn < INFINITY) ? 1.0 / hn : 0.0;
   if (in) {
     const double x = we * sc;
     vdst[e] = x;
@@ -582,39 +482,233 @@ __global__ __launch_bounds__(kB) void k_arnoldi_small(const double* __restrict__
   }
 }
 
-// ------------------------------------------------------------------ batched GMRES on the device
-// One workgroup per problem does a whole Arnoldi step of its problem: both classical Gram-Schmidt
-// passes over its segment [off[p], off[p] + len[p]) of the batch vectors (dot products eight at a
-// time, each a fixed tree over the workgroup), |w|^2, the least-squares update of its own state
-// gs + p * gstride (givens_step), and the normalisation of w into the next basis vector and the
-// apply's input xin.  A problem whose state was already frozen writes zeros there (its later
-// applies run on zeros) and changes nothing else.  The step number j comes from the host.
-__device__ __forceinline__ double wg_tree(double v, double* red) {
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int st = kB / 2; st > 0; st >>= 1) {
-    if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
+// ------------------------------------------------------------------ Arnoldi step by one workgroup
+// Both Gram-Schmidt passes, |w|, the least-squares update and the normalisation, for vectors of at
+// most NT R entries: thread t holds entries t + r NT of w and of KR basis vectors at a time in
+// registers (read once per step while k <= KR).  Returns false (and writes nothing) where the state
+// is frozen and SKIP is set.
+template <int NT, int R, int KR, bool SKIP>
+__device__ __forceinline__ bool arnoldi_wg(const double* __restrict__ V, int64_t ldv, int k, const double* w, int64_t n,
+                                           double bnorm2, double* gs, int mx, double tol, double* vdst, double* vdst2,
+                                           double floor_rel) {
+  __shared__ double part[NT / 64 * KR], hv[2][256 + KR], red[NT / 64];
+  __shared__ GivensLds G;
+  double we[R], v[KR][R];
+  auto load = [&](int c0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {   // (unconditional loads at clamped places, so that no branch stands between them)
+      const int64_t e = threadIdx.x + (int64_t)r * NT;
+      const double* p = V + (e < n ? e : 0);
+#pragma unroll
+      for (int g = 0; g < KR; ++g) v[g][r] = p[(int64_t)(c0 + g < k ? c0 + g : k - 1) * ldv];
+#pragma unroll
+      for (int g = 0; g < KR; ++g) v[g][r] = c0 + g < k && e < n ? v[g][r] : 0.0;
+    }
+  };
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t e = threadIdx.x + (int64_t)r * NT;
+    we[r] = e < n ? w[e] : 0.0;
   }
-  const double r = red[0];
+  load(0);
+  givens_stage(G, gs, mx, k - 1, bnorm2);
   __syncthreads();
-  return r;
+  if (SKIP && G.frozen) return false;
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int c0 = 0; c0 < k; c0 += KR) {
+      if (c0 > 0 || (pass > 0 && k > KR)) load(c0);
+      double d[KR];
+#pragma unroll
+      for (int g = 0; g < KR; ++g) {
+        d[g] = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) d[g] += v[g][r] * we[r];
+      }
+      block_fold<NT, KR>(d, part, hv[pass] + c0);
+    }
+    for (int c0 = 0; c0 < k; c0 += KR) {
+      if (k > KR) load(c0);
+#pragma unroll
+      for (int g = 0; g < KR; ++g) {
+        const double h = hv[pass][c0 + g];
+#pragma unroll
+        for (int r = 0; r < R; ++r) we[r] -= v[g][r] * h;
+      }
+    }
+  }
+  double sq = 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) sq += we[r] * we[r];
+#pragma unroll
+  for (int off = 32; off > 0; off /= 2) sq += __shfl_xor(sq, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sq;
+  __syncthreads();
+  double nrm2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < NT / 64; ++q) nrm2 += red[q];
+  if (threadIdx.x < 64) givens_update(G, hv[0], hv[1], nrm2, k - 1, mx, tol, gs);
+  const double hn = sqrt(nrm2 < 0.0 ? 0.0 : nrm2);
+  const double sc = (hn > floor_rel * G.beta && hn < INFINITY) ? 1.0 / hn : 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t e = threadIdx.x + (int64_t)r * NT;
+    if (e < n) {
+      const double x = we[r] * sc;
+      vdst[e] = x;
+      if (vdst2) vdst2[e] = x;
+    }
+  }
+  return true;
 }
 
+template <int NT, int R, int KR>
+__global__ __launch_bounds__(NT) void k_arnoldi_one(const double* __restrict__ V, int64_t ldv, int k, const double* w,
+                                                    int64_t n, const double* __restrict__ bn2, double* gs, int mx,
+                                                    double tol, double* dst, unsigned seq, double* vdst, double* vdst2) {
+  arnoldi_wg<NT, R, KR, false>(V, ldv, k, w, n, *bn2, gs, mx, tol, vdst, vdst2, 0.0);
+  if (threadIdx.x < 64) publish_state(gs, dst, seq);
+}
+
+// ------------------------------------------------------------------ start, finish, residual
+// |b|^2 and v0 (and v02) = b / |b| (0 where |b| is 0 or not finite), one workgroup, n <= 16 * 1024
+constexpr int kOneWg = 16 * 1024;
+__global__ __launch_bounds__(1024) void k_start_one(const double* __restrict__ b, int64_t n, double* bn2, double* v0,
+                                                    double* v02) {
+  __shared__ double red[16];
+  double x[16], s = 0.0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int64_t e = threadIdx.x + (int64_t)r * 1024;
+    x[r] = e < n ? b[e] : 0.0;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s += x[r] * x[r];
+#pragma unroll
+  for (int off = 32; off > 0; off /= 2) s += __shfl_xor(s, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  double v = 0.0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) v += red[q];
+  if (threadIdx.x == 0) *bn2 = v;
+  const double h = sqrt(v < 0.0 ? 0.0 : v);
+  const double sc = (h > 0.0 && h < INFINITY) ? 1.0 / h : 0.0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int64_t e = threadIdx.x + (int64_t)r * 1024;
+    if (e < n) {
+      v0[e] = x[r] * sc;
+      if (v02) v02[e] = x[r] * sc;
+    }
+  }
+}
+
+// partial[b] = block b's part of |b - a|^2
+__global__ __launch_bounds__(kB) void k_resid_partial(const double* __restrict__ b, const double* __restrict__ a,
+                                                      int64_t n, double* __restrict__ partial) {
+  __shared__ double red[kB / 64];
+  double s = 0.0;
+#pragma unroll
+  for (int r = 0; r < kElemsPerBlock / kB; ++r) {
+    const int64_t e = (int64_t)blockIdx.x * kElemsPerBlock + r * kB + threadIdx.x;
+    const double d = e < n ? b[e] - a[e] : 0.0;
+    s += d * d;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off /= 2) s += __shfl_xor(s, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) partial[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// x = V y with y = R^-1 g of the k = gs[GM_K] steps: every workgroup solves the triangle itself (k <= 64:
+// by its first wave, lane i holding g_i, from LDS; longer ones column by column) and forms its part of x.
+// gate: nothing unless the state's convergence flag is set (a finish queued behind a step that the
+// host predicts to be the last, before it has seen that step's result).
+__global__ __launch_bounds__(kB) void k_gmres_finish(const double* __restrict__ V, int64_t ldv, const double* gs, int mx,
+                                                     double* __restrict__ x, int64_t n, int gate) {
+  __shared__ double tri[64 * 64];
+  __shared__ double ys[256];
+  if (gate && gs[GM_DONE] == 0.0) return;
+  const int k = (int)gs[GM_K];
+  double* m = const_cast<double*>(gs);
+  const double* R = gm_R(m, mx);
+  const double* g = gm_g(m, mx);
+  if (k <= 64) {
+    for (int q = threadIdx.x; q < k * k; q += kB) {
+      const int c = q / k, i = q - c * k;
+      tri[c * 64 + i] = i <= c ? R[(int64_t)c * (mx + 1) + i] : 0.0;
+    }
+    double gi = (int)threadIdx.x < k ? g[threadIdx.x] : 0.0;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      for (int c = k - 1; c >= 0; --c) {
+        const double y = __shfl(gi, c) / tri[c * 64 + c];
+        if ((int)threadIdx.x == c) ys[c] = y;
+        else if ((int)threadIdx.x < c) gi -= tri[c * 64 + threadIdx.x] * y;
+      }
+    }
+    __syncthreads();
+  } else {
+    for (int i = threadIdx.x; i < k; i += kB) ys[i] = g[i];
+    __syncthreads();
+    for (int c = k - 1; c >= 0; --c) {
+      const double* rc = R + (int64_t)c * (mx + 1);
+      const double y = ys[c] / rc[c];
+      __syncthreads();
+      for (int i = threadIdx.x; i <= c; i += kB) ys[i] = i == c ? y : ys[i] - rc[i] * y;
+      __syncthreads();
+    }
+  }
+  for (int64_t e = (int64_t)blockIdx.x * kB + threadIdx.x; e < n; e += (int64_t)gridDim.x * kB) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int j = 0; j < k; ++j) s += V[j * ldv + e] * ys[j];
+    x[e] = s;
+  }
+}
+
+// ------------------------------------------------------------------ batched GMRES on the device
+// One workgroup per problem does a whole Arnoldi step of its problem on its segment
+// [off[p], off[p] + len[p]) of the batch vectors and its own state gs + p * gstride.  A problem whose
+// state was already frozen writes zeros there (its later applies run on zeros) and changes nothing
+// else.  The step number j comes from the host.
+template <int NT, int R, int KR>
+__global__ __launch_bounds__(NT) void k_batch_arnoldi_wg(const double* __restrict__ V, int64_t ldv, int j,
+                                                         const double* __restrict__ w, const int64_t* __restrict__ off,
+                                                         const int64_t* __restrict__ len,
+                                                         const double* __restrict__ bn2, double* gsb, int64_t gstride,
+                                                         int mx, double tol, double* __restrict__ vnext,
+                                                         double* __restrict__ xin, double* dst, unsigned seq) {
+  const int p = blockIdx.x;
+  const int64_t beg = off[p], n = len[p];
+  double* gs = gsb + (int64_t)p * gstride;
+  const bool ran = arnoldi_wg<NT, R, KR, true>(V + beg, ldv, j + 1, w + beg, n, bn2[p], gs, mx, tol, vnext + beg,
+                                               xin ? xin + beg : nullptr, 1e-300);
+  if (threadIdx.x < 64) publish_state(gs, dst + (int64_t)p * GM_REC, seq);
+  if (ran) return;
+  for (int64_t e = threadIdx.x; e < n; e += NT) {
+    vnext[beg + e] = 0.0;
+    if (xin) xin[beg + e] = 0.0;
+  }
+}
+
+// The same for problems of any length, w in memory
 __global__ __launch_bounds__(kB) void k_batch_arnoldi(const double* __restrict__ V, int64_t ldv, int j,
                                                       double* __restrict__ w, const int64_t* __restrict__ off,
                                                       const int64_t* __restrict__ len, const double* __restrict__ bn2,
                                                       double* gsb, int64_t gstride, int mx, double tol,
-                                                      double* __restrict__ vnext, double* __restrict__ xin) {
-  __shared__ double red[kArnGroup][kB];
-  __shared__ double hv[2][256];
-  __shared__ int frozen;
+                                                      double* __restrict__ vnext, double* __restrict__ xin, double* dst,
+                                                      unsigned seq) {
+  __shared__ double part[kB / 64 * kArnK], hv[2][256 + kArnK], out[kArnK];
+  __shared__ GivensLds G;
   const int p = blockIdx.x;
   const int64_t beg = off[p], n = len[p];
   double* gs = gsb + (int64_t)p * gstride;
-  if (threadIdx.x == 0) frozen = j > 0 && gs[GM_DONE] != 0.0;
+  givens_stage(G, gs, mx, j, bn2[p]);
   __syncthreads();
-  if (frozen) {
+  if (G.frozen) {
+    if (threadIdx.x < 64) publish_state(gs, dst + (int64_t)p * GM_REC, seq);
     for (int64_t e = threadIdx.x; e < n; e += kB) {
       vnext[beg + e] = 0.0;
       if (xin) xin[beg + e] = 0.0;
@@ -623,153 +717,47 @@ __global__ __launch_bounds__(kB) void k_batch_arnoldi(const double* __restrict__
   }
   const int k = j + 1;
   double* wp = w + beg;
+  const double* Vp = V + beg;
+  double nrm2 = 0.0;
   for (int pass = 0; pass < 2; ++pass) {
-    for (int d0 = 0; d0 < k; d0 += kArnGroup) {
-      double acc[kArnGroup];
+    for (int c0 = 0; c0 < k; c0 += kArnK) {
+      double d[kArnK];
 #pragma unroll
-      for (int g = 0; g < kArnGroup; ++g) acc[g] = 0.0;
+      for (int g = 0; g < kArnK; ++g) d[g] = 0.0;
       for (int64_t e = threadIdx.x; e < n; e += kB) {
         const double we = wp[e];
+        double v[kArnK];
+        arn_load(v, Vp, ldv, c0, k, e, true);
 #pragma unroll
-        for (int g = 0; g < kArnGroup; ++g)
-          if (d0 + g < k) acc[g] += V[(int64_t)(d0 + g) * ldv + beg + e] * we;
+        for (int g = 0; g < kArnK; ++g) d[g] += v[g] * we;
       }
-#pragma unroll
-      for (int g = 0; g < kArnGroup; ++g) red[g][threadIdx.x] = acc[g];
-      __syncthreads();
-      for (int st = kB / 2; st > 0; st >>= 1) {
-        if (threadIdx.x < st) {
-#pragma unroll
-          for (int g = 0; g < kArnGroup; ++g) red[g][threadIdx.x] += red[g][threadIdx.x + st];
-        }
-        __syncthreads();
-      }
-      if (threadIdx.x < kArnGroup && d0 + threadIdx.x < k) hv[pass][d0 + threadIdx.x] = red[threadIdx.x][0];
-      __syncthreads();
+      block_fold<kB, kArnK>(d, part, hv[pass] + c0);
     }
+    double sq[kArnK];
+#pragma unroll
+    for (int g = 0; g < kArnK; ++g) sq[g] = 0.0;
     for (int64_t e = threadIdx.x; e < n; e += kB) {
       double we = wp[e];
-      for (int i = 0; i < k; ++i) we -= V[(int64_t)i * ldv + beg + e] * hv[pass][i];
+      for (int i = 0; i < k; ++i) we -= Vp[(int64_t)i * ldv + e] * hv[pass][i];
       wp[e] = we;
+      sq[0] += we * we;
     }
     __syncthreads();
+    if (pass == 1) {
+      block_fold<kB, kArnK>(sq, part, out);
+      nrm2 = out[0];
+    }
   }
-  double sq = 0.0;
-  for (int64_t e = threadIdx.x; e < n; e += kB) sq += wp[e] * wp[e];
-  const double nrm2 = wg_tree(sq, &red[0][0]);
-  givens_step(hv[0], hv[1], nrm2, bn2[p], j, mx, tol, gs);
-  __syncthreads();
+  if (threadIdx.x < 64) {
+    givens_update(G, hv[0], hv[1], nrm2, j, mx, tol, gs);
+    publish_state(gs, dst + (int64_t)p * GM_REC, seq);
+  }
   const double hn = sqrt(nrm2 < 0.0 ? 0.0 : nrm2);
-  const double beta = gs[GM_BETA];
-  const double sc = (hn > 1e-300 * beta && hn < INFINITY) ? 1.0 / hn : 0.0;
+  const double sc = (hn > 1e-300 * G.beta && hn < INFINITY) ? 1.0 / hn : 0.0;
   for (int64_t e = threadIdx.x; e < n; e += kB) {
     const double x = wp[e] * sc;
     vnext[beg + e] = x;
     if (xin) xin[beg + e] = x;
-  }
-}
-
-// The same step for problems of at most 1024 R unknowns with 1024 threads per problem, each thread
-// keeping its R entries of w in registers: dot products eight at a time, a butterfly in each wave
-// and then the sixteen waves' sums in order (deterministic; grouped differently from the 256-thread
-// form above).  (Keeping the first eight basis vectors in registers as well, to read them once per
-// step, needs more than the 128 registers a thread has at this workgroup size: it spilled.)
-template <int R>
-__global__ __launch_bounds__(1024) void k_batch_arnoldi_r(const double* __restrict__ V, int64_t ldv, int j,
-                                                          double* __restrict__ w, const int64_t* __restrict__ off,
-                                                          const int64_t* __restrict__ len,
-                                                          const double* __restrict__ bn2, double* gsb, int64_t gstride,
-                                                          int mx, double tol, double* __restrict__ vnext,
-                                                          double* __restrict__ xin) {
-  constexpr int NT = 1024, NW = NT / 64;
-  __shared__ double part[NW][kArnGroup];
-  __shared__ double hv[2][256];
-  __shared__ int frozen;
-  const int p = blockIdx.x;
-  const int64_t beg = off[p], n = len[p];
-  double* gs = gsb + (int64_t)p * gstride;
-  if (threadIdx.x == 0) frozen = j > 0 && gs[GM_DONE] != 0.0;
-  __syncthreads();
-  if (frozen) {
-    for (int64_t e = threadIdx.x; e < n; e += NT) {
-      vnext[beg + e] = 0.0;
-      if (xin) xin[beg + e] = 0.0;
-    }
-    return;
-  }
-  const int k = j + 1;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const double* vb = V + beg;
-  double we[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int64_t e = threadIdx.x + (int64_t)r * NT;
-    we[r] = e < n ? w[beg + e] : 0.0;
-  }
-  auto block_sum8 = [&](double (&v)[kArnGroup]) {
-#pragma unroll
-    for (int g = 0; g < kArnGroup; ++g)
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v[g] += __shfl_xor(v[g], o);
-    if (lane == 0)
-#pragma unroll
-      for (int g = 0; g < kArnGroup; ++g) part[wave][g] = v[g];
-    __syncthreads();
-#pragma unroll
-    for (int g = 0; g < kArnGroup; ++g) {
-      double t = part[0][g];
-      for (int q = 1; q < NW; ++q) t += part[q][g];
-      v[g] = t;
-    }
-    __syncthreads();
-  };
-  for (int pass = 0; pass < 2; ++pass) {
-    for (int d0 = 0; d0 < k; d0 += kArnGroup) {
-      double acc[kArnGroup];
-#pragma unroll
-      for (int g = 0; g < kArnGroup; ++g) {
-        acc[g] = 0.0;
-        if (d0 + g < k)
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const int64_t e = threadIdx.x + (int64_t)r * NT;
-            if (e < n) acc[g] += vb[(int64_t)(d0 + g) * ldv + e] * we[r];
-          }
-      }
-      block_sum8(acc);
-      if (threadIdx.x == 0)
-#pragma unroll
-        for (int g = 0; g < kArnGroup; ++g)
-          if (d0 + g < k) hv[pass][d0 + g] = acc[g];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int64_t e = threadIdx.x + (int64_t)r * NT;
-      double x = we[r];
-      if (e < n)
-        for (int i = 0; i < k; ++i) x -= vb[(int64_t)i * ldv + e] * hv[pass][i];
-      we[r] = e < n ? x : 0.0;
-    }
-  }
-  double sq[kArnGroup] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int r = 0; r < R; ++r) sq[0] += we[r] * we[r];
-  block_sum8(sq);
-  const double nrm2 = sq[0];
-  givens_step(hv[0], hv[1], nrm2, bn2[p], j, mx, tol, gs);
-  __syncthreads();
-  const double hn = sqrt(nrm2 < 0.0 ? 0.0 : nrm2);
-  const double beta = gs[GM_BETA];
-  const double sc = (hn > 1e-300 * beta && hn < INFINITY) ? 1.0 / hn : 0.0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int64_t e = threadIdx.x + (int64_t)r * NT;
-    if (e < n) {
-      const double x = we[r] * sc;
-      vnext[beg + e] = x;
-      if (xin) xin[beg + e] = x;
-    }
   }
 }
 
@@ -797,17 +785,6 @@ __global__ void k_batch_start(const double* __restrict__ b, const int64_t* __res
     const double x = b[off[p] + e] * sc;
     v0[off[p] + e] = x;
     if (xin) xin[off[p] + e] = x;
-  }
-}
-
-// The first GM_PUB scalars of every problem's state to the host slot, then the tag
-__global__ __launch_bounds__(kB) void k_batch_publish(const double* gsb, int64_t gstride, int np, double* dst,
-                                                      unsigned* tag, unsigned seq) {
-  for (int i = threadIdx.x; i < np * GM_PUB; i += kB) dst[i] = gsb[(int64_t)(i / GM_PUB) * gstride + i % GM_PUB];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence_system();
-    *reinterpret_cast<volatile unsigned*>(tag) = seq;
   }
 }
 
@@ -843,40 +820,30 @@ inline unsigned blocks_for(int64_t n) {
 
 }  // namespace
 
-void kr_publish_scale(double* h, const double* pnorm, int nblk, int norm_at, double* gs, int j, int mx, double tol,
-                      double* host_dst, unsigned* host_tag, unsigned seq, const double* w, double* dst, double* dst2,
-                      int64_t nv, hipStream_t st) {
-  if (j < 0 || j >= mx || mx > 256) throw Error(-2, "kr_publish_scale: 0 <= j < mx <= 256");
-  hipLaunchKernelGGL(k_publish_scale, dim3(blocks_for(nv)), dim3(kB), 0, st, h, pnorm, nblk, norm_at, gs, j, mx, tol,
-                     host_dst, host_tag, seq, w, dst, dst2, nv);
-  IBDL_LAUNCH_CHECK();
-}
-
-void kr_arnoldi_small(const double* V, int64_t ldv, int k, double* w, int64_t n, double* h, int norm_at, double* gs,
-                      int mx, double tol, double* host_dst, unsigned* host_tag, unsigned seq, double* dst,
-                      double* dst2, hipStream_t st) {
-  if (n > kSmallN || k < 1 || k > mx || mx > 256) throw Error(-2, "kr_arnoldi_small: n <= kSmallN and 1 <= k <= mx <= 256");
-  hipLaunchKernelGGL(k_arnoldi_small, dim3(1), dim3(kB), 0, st, V, ldv, k, w, n, h, norm_at, gs, mx, tol, host_dst,
-                     host_tag, seq, dst, dst2);
-  IBDL_LAUNCH_CHECK();
-}
-
 size_t kr_gmres_state_doubles(int mx) { return (size_t)GM_HDR + 4 * (size_t)mx + 2 + (size_t)mx * (mx + 1); }
 
-void kr_gmres_y(double* gs, int mx, hipStream_t st) {
-  hipLaunchKernelGGL(k_gmres_y, dim3(1), dim3(kB), 0, st, gs, mx, 0);
+void kr_gmres_finish(const double* gs, int mx, const double* V, int64_t ldv, double* x, int64_t n, bool gate,
+                     hipStream_t st) {
+  if (mx > 256) throw Error(-1, "kr_gmres_finish: at most 256 basis vectors");
+  hipLaunchKernelGGL(k_gmres_finish, dim3(blocks_for(n)), dim3(kB), 0, st, V, ldv, gs, mx, x, n, gate ? 1 : 0);
   IBDL_LAUNCH_CHECK();
 }
 
-const double* kr_gmres_ydev(double* gs, int mx) { return gs + GM_HDR + 3 * mx + 1; }
+void kr_gmres_start(const double* b, int64_t n, double* partial, int nblk, double* bn2, double* v0, double* v02,
+                    hipStream_t st) {
+  if (n <= kOneWg) {
+    hipLaunchKernelGGL(k_start_one, dim3(1), dim3(1024), 0, st, b, n, bn2, v0, v02);
+    IBDL_LAUNCH_CHECK();
+    return;
+  }
+  kr_multidot(b, n, 1, b, n, partial, nblk, bn2, st);
+  kr_scale_norm(b, bn2, 0.0, v0, v02, n, st);
+}
 
-void kr_gmres_finish(double* gs, int mx, const double* V, int64_t ldv, double* x, int64_t n, bool gate,
-                     hipStream_t st) {
-  if (mx > 256) throw Error(-1, "kr_gmres_finish: at most 256 basis vectors");
-  hipLaunchKernelGGL(k_gmres_y, dim3(1), dim3(kB), 0, st, gs, mx, gate ? 1 : 0);
+void kr_resid_norm2(const double* b, const double* a, int64_t n, double* partial, int nblk, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_resid_partial, dim3(nblk), dim3(kB), 0, st, b, a, n, partial);
   IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_lincomb_state, dim3(blocks_for(n)), dim3(256), 0, st, V, ldv, (const double*)gs,
-                     kr_gmres_ydev(gs, mx), x, n, gate ? 1 : 0);
+  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(64), 0, st, partial, nblk, out);
   IBDL_LAUNCH_CHECK();
 }
 
@@ -887,17 +854,6 @@ void kr_multidot(const double* V, int64_t ldv, int k, const double* w, int64_t n
   hipLaunchKernelGGL(k_multidot, dim3(nblk), dim3(kB), 0, st, V, ldv, k, w, n, nblk, partial);
   IBDL_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_reduce, dim3(k), dim3(64), 0, st, partial, nblk, out);
-  IBDL_LAUNCH_CHECK();
-}
-
-void kr_gemv_sub(const double* V, int64_t ldv, int k, const double* h, double* w, int64_t n, hipStream_t st) {
-  hipLaunchKernelGGL(k_gemv_sub, dim3(blocks_for(n)), dim3(256), 0, st, V, ldv, k, h, w, n);
-  IBDL_LAUNCH_CHECK();
-}
-
-void kr_lincomb(const double* V, int64_t ldv, int k, const double* y, double* x, int64_t n, hipStream_t st) {
-  if (k > 256) throw Error(-1, "kr_lincomb: at most 256 basis vectors");
-  hipLaunchKernelGGL(k_lincomb, dim3(blocks_for(n)), dim3(256), 0, st, V, ldv, k, y, x, n);
   IBDL_LAUNCH_CHECK();
 }
 
@@ -917,11 +873,6 @@ void kr_axpby(double* y, double a, const double* x, double b, int64_t n, hipStre
   IBDL_LAUNCH_CHECK();
 }
 
-void kr_add(double* dst, const double* a, const double* b, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_add_small, dim3(1), dim3(256), 0, st, dst, a, b, n);
-  IBDL_LAUNCH_CHECK();
-}
-
 void kr_border(const double* q, const double* ds, int64_t n_ib, int nq, double eta, double* out, double* partial,
                int nblk, hipStream_t st) {
   hipLaunchKernelGGL(k_border_partial, dim3(nblk, nq), dim3(kB), 0, st, q, ds, n_ib, nq, nblk, partial);
@@ -932,23 +883,29 @@ void kr_border(const double* q, const double* ds, int64_t n_ib, int nq, double e
 
 int kr_arnoldi_nblk(int64_t n) { return (int)((n + kArnChunk - 1) / kArnChunk) > 0 ? (int)((n + kArnChunk - 1) / kArnChunk) : 1; }
 
-void kr_arnoldi_step(const double* V, int64_t ldv, int k, double* w, int64_t n, double* partial, int nblk,
-                     double* h, hipStream_t st) {
-  if (k < 1 || k > 256) throw Error(-2, "Arnoldi step: 1 <= k <= 256");
-  double* p0 = partial;
-  double* p1 = partial + (int64_t)k * nblk;
-  double* p2 = p1 + (int64_t)k * nblk;
-  hipLaunchKernelGGL(k_arnoldi<0>, dim3(nblk), dim3(kB), 0, st, V, ldv, k, w, nullptr, nullptr, n, nblk, p0);
-  IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_arnoldi<1>, dim3(nblk), dim3(kB), 0, st, V, ldv, k, w, p0, h, n, nblk, p1);
-  IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_arnoldi<2>, dim3(nblk), dim3(kB), 0, st, V, ldv, k, w, p1, h + 256, n, nblk, p2);
-  IBDL_LAUNCH_CHECK();
-}
-
-void kr_publish(double* src, int n, const double* pnorm, int nblk, int norm_at, double* host_dst,
-                unsigned* host_tag, unsigned seq, hipStream_t st) {
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(kB), 0, st, src, n, pnorm, nblk, norm_at, host_dst, host_tag, seq);
+void kr_arnoldi_step(const double* V, int64_t ldv, int k, double* w, int64_t n, double* partial, int nblk, double* h,
+                     double* gs, int mx, double tol, double* host_dst, unsigned seq, double* vdst, double* vdst2,
+                     hipStream_t st) {
+  if (k < 1 || k > mx || mx > 256) throw Error(-2, "Arnoldi step: 1 <= k <= mx <= 256");
+  const double* bn2 = h + GM_BNORM2_AT;
+  // One workgroup while two entries per thread hold the vectors (9.4 us a step at 269 unknowns, 13.6 for
+  // the three launches); beyond that the basis vectors' reads want more than one CU.
+  if (n <= 256)
+    hipLaunchKernelGGL((k_arnoldi_one<256, 1, 16>), dim3(1), dim3(256), 0, st, V, ldv, k, w, n, bn2, gs, mx, tol, host_dst,
+                       seq, vdst, vdst2);
+  else if (n <= kArnoldiOne)
+    hipLaunchKernelGGL((k_arnoldi_one<512, 2, 16>), dim3(1), dim3(512), 0, st, V, ldv, k, w, n, bn2, gs, mx, tol,
+                       host_dst, seq, vdst, vdst2);
+  else {
+    double* p0 = partial;
+    double* p1 = partial + (int64_t)k * nblk;
+    hipLaunchKernelGGL(k_arn0, dim3(nblk), dim3(kB), 0, st, V, ldv, k, w, n, nblk, p0);
+    IBDL_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_arn1, dim3(nblk), dim3(kB), 0, st, V, ldv, k, w, n, nblk, p0, h, p1);
+    IBDL_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_arn2, dim3(nblk), dim3(kB), 0, st, V, ldv, k, w, n, nblk, p1, h, bn2, gs, mx, tol, host_dst,
+                       seq, vdst, vdst2);
+  }
   IBDL_LAUNCH_CHECK();
 }
 
@@ -960,20 +917,9 @@ void kb_multidot(const double* V, int64_t ldv, int k, const double* w, const Kry
   IBDL_LAUNCH_CHECK();
 }
 
-void kb_gemv_sub(const double* V, int64_t ldv, int k, const double* H, int hs, const KrylovSegments& sg, double* w,
-                 hipStream_t st) {
-  hipLaunchKernelGGL(k_bgemv_sub, dim3(blocks_for(sg.n)), dim3(256), 0, st, V, ldv, k, H, hs, sg.seg, w, sg.n);
-  IBDL_LAUNCH_CHECK();
-}
-
 void kb_lincomb(const double* V, int64_t ldv, int k, const double* Y, int ys, const KrylovSegments& sg, double* x,
                 hipStream_t st) {
   hipLaunchKernelGGL(k_blincomb, dim3(blocks_for(sg.n)), dim3(256), 0, st, V, ldv, k, Y, ys, sg.seg, x, sg.n);
-  IBDL_LAUNCH_CHECK();
-}
-
-void kb_scale(const double* src, const double* sc, const KrylovSegments& sg, double* dst, hipStream_t st) {
-  hipLaunchKernelGGL(k_bscale, dim3(blocks_for(sg.n)), dim3(256), 0, st, src, sc, sg.seg, dst, sg.n);
   IBDL_LAUNCH_CHECK();
 }
 
@@ -992,26 +938,20 @@ void kb_gmres_start(const double* b, const int64_t* off, const int64_t* len, int
 
 void kb_arnoldi(const double* V, int64_t ldv, int j, double* w, const int64_t* off, const int64_t* len, int np,
                 int64_t maxlen, const double* bn2, double* gsb, int64_t gstride, int mx, double tol, double* vnext,
-                double* xin, hipStream_t st) {
+                double* xin, double* host_dst, unsigned seq, hipStream_t st) {
   if (j < 0 || j >= mx || mx > 256) throw Error(-2, "kb_arnoldi: 0 <= j < mx <= 256");
-  if (maxlen <= 1024)
-    hipLaunchKernelGGL(k_batch_arnoldi_r<1>, dim3(np), dim3(1024), 0, st, V, ldv, j, w, off, len, bn2, gsb, gstride,
-                       mx, tol, vnext, xin);
-  else if (maxlen <= 2048)
-    hipLaunchKernelGGL(k_batch_arnoldi_r<2>, dim3(np), dim3(1024), 0, st, V, ldv, j, w, off, len, bn2, gsb, gstride,
-                       mx, tol, vnext, xin);
-  else if (maxlen <= 4096)
-    hipLaunchKernelGGL(k_batch_arnoldi_r<4>, dim3(np), dim3(1024), 0, st, V, ldv, j, w, off, len, bn2, gsb, gstride,
-                       mx, tol, vnext, xin);
+  auto wg = [&](auto tc, auto rc, auto kc) {
+    constexpr int NT = decltype(tc)::value;
+    hipLaunchKernelGGL((k_batch_arnoldi_wg<NT, decltype(rc)::value, decltype(kc)::value>), dim3(np), dim3(NT), 0, st, V,
+                       ldv, j, w, off, len, bn2, gsb, gstride, mx, tol, vnext, xin, host_dst, seq);
+  };
+  using std::integral_constant;
+  if (maxlen <= 1024) wg(integral_constant<int, 512>{}, integral_constant<int, 2>{}, integral_constant<int, 16>{});
+  else if (maxlen <= 2048) wg(integral_constant<int, 1024>{}, integral_constant<int, 2>{}, integral_constant<int, 8>{});
+  else if (maxlen <= 4096) wg(integral_constant<int, 1024>{}, integral_constant<int, 4>{}, integral_constant<int, 4>{});
   else
     hipLaunchKernelGGL(k_batch_arnoldi, dim3(np), dim3(kB), 0, st, V, ldv, j, w, off, len, bn2, gsb, gstride, mx, tol,
-                       vnext, xin);
-  IBDL_LAUNCH_CHECK();
-}
-
-void kb_publish(const double* gsb, int64_t gstride, int np, double* host_dst, unsigned* host_tag, unsigned seq,
-                hipStream_t st) {
-  hipLaunchKernelGGL(k_batch_publish, dim3(1), dim3(kB), 0, st, gsb, gstride, np, host_dst, host_tag, seq);
+                       vnext, xin, host_dst, seq);
   IBDL_LAUNCH_CHECK();
 }
 
