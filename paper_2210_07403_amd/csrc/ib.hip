@@ -263,10 +263,6 @@ __global__ __launch_bounds__(256) void k_sort_tiles(const int* __restrict__ off,
 constexpr int kT3X = 16, kT3Y = 4, kT3Z = 8;   // 3-D tile; lane (x, y) owns a z-column of 8
 constexpr int kT2X = 16, kT2Y = 16;            // 2-D tile; lane (x, y-group) owns 4 consecutive y
 
-template <typename T> struct Pack4;
-template <> struct Pack4<float> { using type = float4; };
-template <> struct Pack4<double> { using type = double4; };
-
 // per-marker coefficients of the spread fields (times ds / h^D)
 __device__ __forceinline__ void spread_coefs(const SpreadArgs& a, int m, int D, double base, double* cf) {
   for (int c = 0; c < 8; ++c) cf[c] = 0.0;
@@ -300,7 +296,7 @@ __device__ __forceinline__ double spread_coef(const SpreadArgs& a, int m, int D,
 }
 
 
-// Lanes used per wave for candidates in one pass (LDS budget: 32 KiB / 48 KiB per block).
+// Lanes used per wave for candidates in one pass of the 2-D spread (32 KiB of LDS per block).
 template <typename T> constexpr int spread_lanes() { return sizeof(T) == 4 ? 64 : 32; }
 
 // broadcast a lane's value to the whole wave (scalar register), any 32/64-bit type
@@ -606,17 +602,22 @@ __global__ __launch_bounds__(64 * NW, 8) void k_spread3f(SpreadArgs a, const cpl
 }
 
 // 2-D: a tile of TX x TY nodes (TX TY = 256, TY = 4 (64 / TX) rows); lane (x, y-group) owns
-// y = 4 yg + j' (j' < 4); the owning lane of a candidate writes its x row and its tile-aligned y
-// column (TY pairs) to LDS; coefficients and the x window start are broadcast.  s_x and s_y are the
-// caller's LDS: [4][LW][8] and [4][LW][TY] (T, T) pairs.
+// y = 4 yg + j' (j' < 4).  Wave w takes candidates w, w + 4, ... of the tile's list, LW at a time: the
+// lane of a candidate copies its x and y weight rows to LDS and keeps its window start and
+// coefficients, which are broadcast; a node's taps are picked by index (6 and 7 are zero).  The rows
+// are copied as they are, so everything a candidate needs is loaded at once behind its list entry:
+// the launch is a chain of dependent loads (tile, list entry, marker), a few candidates' work per wave,
+// and the sum over the waves.  (The y rows had been aligned to the tile as they were staged, one more
+// dependent load and 48 KiB of LDS in double: five Stokes fields on 199 tiles 7.6 -> 6.6 us, the 1,833
+// tiles of a 30-problem batch 22.2 -> 17.8 us.)  s_w is the caller's LDS, [4][LW][17] (T, T) pairs (one
+// of padding, so that the lanes' copies fall into different banks).
 template <typename T, int NF, int TX>
 __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>* __restrict__ wtab, T* __restrict__ out,
-                                             const int4 bt, cplx<T> (*s_x)[spread_lanes<T>()][8], cplx<T>* s_yraw) {
+                                             const int4 bt, cplx<T> (*s_w)[spread_lanes<T>()][17]) {
   using T2 = cplx<T>;
   constexpr int LW = spread_lanes<T>();
   constexpr int TY = 256 / TX;
   static_assert(TX * TY == 256 && TX >= 4 && TX <= 64, "2-D tile of 256 nodes, 64 lanes of 4 rows");
-  auto s_y = reinterpret_cast<T2 (*)[LW][TY]>(s_yraw);
   const MarkerGeom& g = a.g;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -639,31 +640,34 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
   for (int c0 = beg; c0 < end; c0 += 4 * LW) {
     const int left = end - c0 - wave;
     const int cnt = left <= 0 ? 0 : ((left + 3) / 4 < LW ? (left + 3) / 4 : LW);
-    int sx = 0;
+    int sx = 0, sy = 0;
     T cf[5];
 #pragma unroll
     for (int c = 0; c < 5; ++c) cf[c] = 0;
     if (lane < cnt) {
       const int m = a.list[c0 + 4 * lane + wave];
       const T2* row = wtab + (int64_t)m * 24;
+      T2 w[16];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) s_x[wave][lane][t] = row[t];
+      for (int t = 0; t < 16; ++t) w[t] = row[t];
       sx = a.s[m * 3 + 0];
-      const int sy = a.s[m * 3 + 1];
-#pragma unroll
-      for (int y = 0; y < TY; ++y) s_y[wave][lane][y] = row[8 + min((y0 + y - sy) & my, 6)];
+      sy = a.s[m * 3 + 1];
       double c8[8];
       spread_coefs(a, m, 2, a.raw ? 1.0 : a.ds[m] / hD, c8);
 #pragma unroll
       for (int c = 0; c < 5; ++c) cf[c] = (T)c8[c];
+#pragma unroll
+      for (int t = 0; t < 16; ++t) s_w[wave][lane][t] = w[t];
     }
-    __syncthreads();
+    // (each wave reads its own rows only)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     for (int j = 0; j < cnt; ++j) {
-      const int bx = bcast(sx, j);
-      const T2 xv = s_x[wave][j][min((x0 + lx - bx) & mx, 6)];
+      const int bx = bcast(sx, j), by = y0 + 4 * yg - bcast(sy, j);
+      const T2 xv = s_w[wave][j][min((x0 + lx - bx) & mx, 6)];
       T2 yv[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) yv[q] = s_y[wave][j][4 * yg + q];
+      for (int q = 0; q < 4; ++q) yv[q] = s_w[wave][j][8 + min((by + q) & my, 6)];
       if (fddiv) {
         // v = c_x G_x W_y + c_y W_x G_y + c_mass W_x W_y
         const T ax = bcast(cf[0], j) * xv.y + bcast(cf[3], j) * xv.x, ay = bcast(cf[1], j) * xv.x;
@@ -680,35 +684,38 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
         }
       }
     }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
   }
-  T* red = reinterpret_cast<T*>(s_yraw);   // needs 4 * 4 * 64 values: [4][LW][TY] pairs hold them
+  // sum of the waves' parts in wave order, as many fields at a time as the LDS holds
+  T* red = reinterpret_cast<T*>(&s_w[0][0][0]);
+  constexpr int FR = 4 * LW * 16 * 2 / 1024;   // fields of [4][4][64] values
+  static_assert(FR >= 1, "spread: LDS holds a field's partial tiles");
   const int64_t ntot = (int64_t)g.n[0] * g.n[1];
   out += (int64_t)prob * a.nf * ntot;
+  const int q = tid >> 6, l = lane;   // 256 tile nodes, one per thread: l (x, y-group), q: y within the group
+  T* dst = out + (int64_t)(y0 + 4 * (l / TX) + q) * g.n[0] + x0 + l % TX;
 #pragma unroll
-  for (int c = 0; c < NF; ++c) {
-    if (c >= a.nf) break;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) red[(wave * 4 + q) * 64 + lane] = acc[q][c];
+  for (int c0 = 0; c0 < NF; c0 += FR) {
+    if (c0 >= a.nf) break;
     __syncthreads();
-    {
-      const int o = tid;                // 256 tile nodes, one per thread
-      const int q = o >> 6, l = o & 63; // l: (x, y-group), q: y within the group
-      const T v = ((red[(0 * 4 + q) * 64 + l] + red[(1 * 4 + q) * 64 + l]) + red[(2 * 4 + q) * 64 + l]) +
-                  red[(3 * 4 + q) * 64 + l];
-      const int x = l % TX, y = 4 * (l / TX) + q;
-      out[c * ntot + (int64_t)(y0 + y) * g.n[0] + x0 + x] = v;
+#pragma unroll
+    for (int c = c0; c < NF && c < c0 + FR; ++c)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) red[((c - c0) * 16 + wave * 4 + k) * 64 + lane] = acc[k][c];
+    __syncthreads();
+#pragma unroll
+    for (int c = c0; c < NF && c < c0 + FR; ++c) {
+      if (c >= a.nf) break;
+      const T* r = red + (c - c0) * 1024 + l;
+      dst[c * ntot] = ((r[q * 64] + r[(4 + q) * 64]) + r[(8 + q) * 64]) + r[(12 + q) * 64];
     }
-    __syncthreads();
   }
 }
 
 template <typename T, int NF>
 __global__ __launch_bounds__(256) void k_spread2(SpreadArgs a, const cplx<T>* __restrict__ wtab, T* __restrict__ out) {
-  constexpr int LW = spread_lanes<T>();
-  __shared__ cplx<T> s_x[4][LW][8];
-  __shared__ cplx<T> s_y[4 * LW * kT2Y];
-  spread2_tile<T, NF, kT2X>(a, wtab, out, a.busy[blockIdx.x], s_x, s_y);
+  __shared__ cplx<T> s_w[4][spread_lanes<T>()][17];
+  spread2_tile<T, NF, kT2X>(a, wtab, out, a.busy[blockIdx.x], s_w);
 }
 
 // The spread of several grid groups (a batch) in one persistent launch over a single work list,
@@ -720,9 +727,7 @@ __global__ __launch_bounds__(256) void k_spread2(SpreadArgs a, const cplx<T>* __
 template <typename T>
 __global__ __launch_bounds__(256) void k_spread2_queue(const SpreadGroup* __restrict__ gd, const int2* __restrict__ items,
                                                        int nitems, const double* __restrict__ qbase) {
-  constexpr int LW = spread_lanes<T>();
-  __shared__ cplx<T> s_x[4][LW][8];
-  __shared__ cplx<T> s_y[4 * LW * 16];
+  __shared__ cplx<T> s_w[4][spread_lanes<T>()][17];
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 gi = items[it];
     const int gsel = __builtin_amdgcn_readfirstlane(gi.x);
@@ -732,15 +737,68 @@ __global__ __launch_bounds__(256) void k_spread2_queue(const SpreadGroup* __rest
     const cplx<T>* wt = reinterpret_cast<const cplx<T>*>(gd[gsel].wtab);
     T* out = reinterpret_cast<T*>(gd[gsel].out);
     const int tw = gd[gsel].tx;
-    if (tw == 32) spread2_tile<T, 1, 32>(a, wt, out, bt, s_x, s_y);
-    else if (tw == 64) spread2_tile<T, 1, 64>(a, wt, out, bt, s_x, s_y);
-    else spread2_tile<T, 1, 16>(a, wt, out, bt, s_x, s_y);
+    if (it != (int)blockIdx.x) __syncthreads();   // the last tile's sums are read
+    if (tw == 32) spread2_tile<T, 1, 32>(a, wt, out, bt, s_w);
+    else if (tw == 64) spread2_tile<T, 1, 64>(a, wt, out, bt, s_w);
+    else spread2_tile<T, 1, 16>(a, wt, out, bt, s_w);
   }
 }
 
 // ------------------------------------------------------------------ interpolation
+// Workgroup c of the border workgroups behind the nmain of an interpolation (BorderArgs)
+__device__ __forceinline__ void border_block(const BorderArgs& bd, int c) {
+  __shared__ double red[4];
+  double s = 0.0;
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < bd.n; i += 256) s += (bd.w ? bd.w[i] : 1.0) * bd.q[i * bd.nq + c];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) bd.out[c] = bd.scale * (((red[0] + red[1]) + red[2]) + red[3]);
+}
+
+// y of marker i from its interpolated adjoint fields G (see k_adj_combine)
+__device__ __forceinline__ void adj_marker(const AdjArgs& ad, int64_t i, int ng, const double* G, double* __restrict__ y) {
+  const double w = ad.hDinv * ad.ds[i];
+  if (!ad.stokes) {
+    double s = 0.0;
+    if (ad.dim == 2) s = ad.nrm[2 * i] * G[0] + ad.nrm[2 * i + 1] * G[1] - (ng > 2 ? ad.eta * G[2] : 0.0);
+    else
+      s = ad.nrm[3 * i] * G[0] + ad.nrm[3 * i + 1] * G[1] + ad.nrm[3 * i + 2] * G[2] - (ng > 3 ? ad.eta * G[3] : 0.0);
+    double v = w * s;
+    if (ad.p) v += ad.b * ad.p[i];
+    if (ad.pu) v += ad.eta * ad.ds[i] * ad.pu[0];
+    y[i] = v;
+    return;
+  }
+  const double n1 = ad.nrm[2 * i], n2 = ad.nrm[2 * i + 1];
+  double s1 = 2.0 * n1 * G[0] + n2 * G[1];
+  double s2 = n1 * G[1] + 2.0 * n2 * G[2];
+  if (ng > 3) {
+    s1 += ad.eta * G[3];
+    s2 += ad.eta * G[4];
+  }
+  double v1 = w * s1, v2 = w * s2;
+  if (ad.p) {
+    v1 += ad.b * ad.p[2 * i];
+    v2 += ad.b * ad.p[2 * i + 1];
+  }
+  if (ad.pu) {
+    v1 += ad.eta * ad.ds[i] * ad.pu[0];
+    v2 += ad.eta * ad.ds[i] * ad.pu[1];
+  }
+  y[2 * i] = v1;
+  y[2 * i + 1] = v2;
+}
+
 template <typename T, int D, int K>
-__global__ __launch_bounds__(256) void k_interp(InterpArgs a, const T* __restrict__ u, double* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_interp(InterpArgs a, const T* __restrict__ u, double* __restrict__ out,
+                                                int nmain, BorderArgs bd) {
+  if ((int)blockIdx.x >= nmain) {
+    border_block(bd, (int)blockIdx.x - nmain);
+    return;
+  }
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n_ib) return;
   const MarkerGeom& g = a.g;
@@ -783,13 +841,22 @@ __global__ __launch_bounds__(256) void k_interp(InterpArgs a, const T* __restric
 }
 
 // 4-point kernels: a group of RL = 4^(D-1) lanes per marker, lane r of the group sums the 4 x-taps of
-// stencil row r; the row sums are reduced across the group by a fixed butterfly (deterministic).
-template <typename T, int D>
-__global__ __launch_bounds__(256) void k_interp4(InterpArgs a, const cplx<T>* __restrict__ wtab, const T* __restrict__ u,
-                                                 double* __restrict__ out) {
+// stencil row r of each of the nf <= NF fields (every field's loads issued before the first sum); the
+// row sums are reduced across the group by a fixed butterfly (deterministic).  ADJ: lane 0 combines the
+// fields into the transposed operator's marker values instead of storing them.  (Latency-bound: with the
+// border sums and the combination in its launch, a 1024^2 Stokes apply went from 56.3 to 50.6 us and a
+// 512^2 Stokes adjoint step lost three launches of 1.8 to 4.6 us.)
+template <typename T, int D, int NF, bool ADJ>
+__global__ __launch_bounds__(256) void k_interp4(InterpArgs a, AdjArgs ad, const cplx<T>* __restrict__ wtab,
+                                                 const T* __restrict__ u, double* __restrict__ out, int nmain,
+                                                 BorderArgs bd) {
   constexpr int RL = (D == 3) ? 16 : 4;
+  if ((int)blockIdx.x >= nmain) {
+    border_block(bd, (int)blockIdx.x - nmain);
+    return;
+  }
   // XCD-contiguous marker ranges: markers close in index share grid lines, so they share an L2
-  const int64_t gid = (int64_t)xcd_chunk(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  const int64_t gid = (int64_t)xcd_chunk(blockIdx.x, nmain) * blockDim.x + threadIdx.x;
   const int64_t i = gid / RL;
   const int r = (int)(gid % RL);
   const bool valid = i < a.n_ib;
@@ -810,16 +877,31 @@ __global__ __launch_bounds__(256) void k_interp4(InterpArgs a, const cplx<T>* __
   }
   const int64_t ntot = (int64_t)g.n[0] * g.n[1] * (D == 3 ? g.n[2] : 1);
   if (a.pid) u += (int64_t)a.pid[im] * a.nf * ntot;
-  for (int c = 0; c < a.nf; ++c) {
-    const T* uc = u + c * ntot + base;
-    T v = ((uc[ix[0]] * wx[0] + uc[ix[1]] * wx[1]) + uc[ix[2]] * wx[2] + uc[ix[3]] * wx[3]) * wyz;
+  T v[NF];
 #pragma unroll
-    for (int off = 1; off < RL; off <<= 1) v += __shfl_xor(v, off, RL);
-    if (valid && r == 0) {
-      double o = a.a * (double)v;
-      if (a.x) o += a.b * a.x[i * a.nf + c];
-      if (a.ub) o += a.ub[c];
-      out[i * a.nf + c] = o;
+  for (int c = 0; c < NF; ++c) {
+    const T* uc = u + (c < a.nf ? c : 0) * ntot + base;
+    v[c] = ((uc[ix[0]] * wx[0] + uc[ix[1]] * wx[1]) + uc[ix[2]] * wx[2] + uc[ix[3]] * wx[3]) * wyz;
+  }
+#pragma unroll
+  for (int c = 0; c < NF; ++c)
+#pragma unroll
+    for (int off = 1; off < RL; off <<= 1) v[c] += __shfl_xor(v[c], off, RL);
+  if (!valid || r != 0) return;
+  if constexpr (ADJ) {
+    double G[NF];
+#pragma unroll
+    for (int c = 0; c < NF; ++c) G[c] = (double)v[c];
+    adj_marker(ad, i, a.nf, G, out);
+  } else {
+#pragma unroll
+    for (int c = 0; c < NF; ++c) {
+      if (c < a.nf) {
+        double o = a.a * (double)v[c];
+        if (a.x) o += a.b * a.x[i * a.nf + c];
+        if (a.ub) o += a.ub[c];
+        out[i * a.nf + c] = o;
+      }
     }
   }
 }
@@ -878,9 +960,14 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void k_interp_div(InterpArgs a, const cplx<T>* __restrict__ wtab,
                                                     const T* __restrict__ u, const double* __restrict__ nrm,
                                                     const double* __restrict__ ds, double eta, double hDinv,
-                                                    const double* __restrict__ pu, double* __restrict__ y) {
+                                                    const double* __restrict__ pu, double* __restrict__ y, int nmain,
+                                                    BorderArgs bd) {
   constexpr int RL = (D == 3) ? 32 : 8;
-  const int64_t gid = (int64_t)xcd_chunk(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  if ((int)blockIdx.x >= nmain) {
+    border_block(bd, (int)blockIdx.x - nmain);
+    return;
+  }
+  const int64_t gid = (int64_t)xcd_chunk(blockIdx.x, nmain) * blockDim.x + threadIdx.x;
   const int64_t i = gid / RL;
   const int r = (int)(gid % RL);
   const bool valid = i < a.n_ib;
@@ -1250,32 +1337,51 @@ void weight_table(const double* wt, int64_t n_ib, cplx<T>* tab, hipStream_t st) 
 }
 
 template <typename T>
-void interp(const InterpArgs& a, const cplx<T>* wtab, const T* u, double* out, hipStream_t st) {
+void interp(const InterpArgs& a, const cplx<T>* wtab, const T* u, double* out, hipStream_t st, const BorderArgs& bd) {
   if (a.n_ib == 0) return;
+  if (a.nf < 1 || a.nf > 5) throw Error(-1, "interp: 1..5 fields");
   const bool six = a.kernel == KID_BSPLINE6;
+  const int64_t lanes = six ? a.n_ib : a.n_ib * (a.g.dim == 3 ? 16 : 4);
+  const int nm = (int)((lanes + 255) / 256);
+  const dim3 grid((unsigned)(nm + (bd.q ? bd.nq : 0)));
+  const AdjArgs ad;
   if (six) {
-    const dim3 grid((unsigned)((a.n_ib + 255) / 256));
-    if (a.g.dim == 2) hipLaunchKernelGGL((k_interp<T, 2, 6>), grid, dim3(256), 0, st, a, u, out);
-    else hipLaunchKernelGGL((k_interp<T, 3, 6>), grid, dim3(256), 0, st, a, u, out);
+    if (a.g.dim == 2) hipLaunchKernelGGL((k_interp<T, 2, 6>), grid, dim3(256), 0, st, a, u, out, nm, bd);
+    else hipLaunchKernelGGL((k_interp<T, 3, 6>), grid, dim3(256), 0, st, a, u, out, nm, bd);
+  } else if (a.g.dim == 2) {
+    if (a.nf == 1) hipLaunchKernelGGL((k_interp4<T, 2, 1, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
+    else if (a.nf == 2) hipLaunchKernelGGL((k_interp4<T, 2, 2, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
+    else hipLaunchKernelGGL((k_interp4<T, 2, 5, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
   } else {
-    const int64_t lanes = a.n_ib * (a.g.dim == 3 ? 16 : 4);
-    const dim3 grid((unsigned)((lanes + 255) / 256));
-    if (a.g.dim == 2) hipLaunchKernelGGL((k_interp4<T, 2>), grid, dim3(256), 0, st, a, wtab, u, out);
-    else hipLaunchKernelGGL((k_interp4<T, 3>), grid, dim3(256), 0, st, a, wtab, u, out);
+    if (a.nf == 1) hipLaunchKernelGGL((k_interp4<T, 3, 1, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
+    else hipLaunchKernelGGL((k_interp4<T, 3, 5, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
   }
   IBDL_LAUNCH_CHECK();
 }
 
 template <typename T>
+void interp_adj(const InterpArgs& a, const AdjArgs& ad, const cplx<T>* wtab, const T* u, double* y, hipStream_t st,
+                const BorderArgs& bd) {
+  if (a.n_ib == 0) return;
+  if (a.kernel == KID_BSPLINE6 || a.nf < 1 || a.nf > 5) throw Error(-2, "interp_adj: 4-point kernels, 1..5 fields");
+  const int nm = (int)((a.n_ib * (a.g.dim == 3 ? 16 : 4) + 255) / 256);
+  const dim3 grid((unsigned)(nm + (bd.q ? bd.nq : 0)));
+  if (a.g.dim == 2) hipLaunchKernelGGL((k_interp4<T, 2, 5, true>), grid, dim3(256), 0, st, a, ad, wtab, u, y, nm, bd);
+  else hipLaunchKernelGGL((k_interp4<T, 3, 5, true>), grid, dim3(256), 0, st, a, ad, wtab, u, y, nm, bd);
+  IBDL_LAUNCH_CHECK();
+}
+
+template <typename T>
 void interp_div(const InterpArgs& a, const cplx<T>* wtab, const T* u, const double* nrm, const double* ds, double eta,
-                double hDinv, const double* pu, double* y, hipStream_t st) {
+                double hDinv, const double* pu, double* y, hipStream_t st, const BorderArgs& bd) {
   if (a.n_ib == 0) return;
   if (a.kernel == KID_BSPLINE6) throw Error(-2, "interp_div: 4-point kernels only");
   const int64_t lanes = a.n_ib * (a.g.dim == 3 ? 32 : 8);
-  const dim3 grid((unsigned)((lanes + 255) / 256));
+  const int nm = (int)((lanes + 255) / 256);
+  const dim3 grid((unsigned)(nm + (bd.q ? bd.nq : 0)));
   if (a.g.dim == 2)
-    hipLaunchKernelGGL((k_interp_div<T, 2>), grid, dim3(256), 0, st, a, wtab, u, nrm, ds, eta, hDinv, pu, y);
-  else hipLaunchKernelGGL((k_interp_div<T, 3>), grid, dim3(256), 0, st, a, wtab, u, nrm, ds, eta, hDinv, pu, y);
+    hipLaunchKernelGGL((k_interp_div<T, 2>), grid, dim3(256), 0, st, a, wtab, u, nrm, ds, eta, hDinv, pu, y, nm, bd);
+  else hipLaunchKernelGGL((k_interp_div<T, 3>), grid, dim3(256), 0, st, a, wtab, u, nrm, ds, eta, hDinv, pu, y, nm, bd);
   IBDL_LAUNCH_CHECK();
 }
 
@@ -1326,9 +1432,11 @@ void grid_sum(const T* x, int ncomp, int64_t n, double* partial, int nblk, doubl
   template void weight_table<T>(const double*, int64_t, cplx<T>*, hipStream_t);           \
   template void grid_fill_zero<T>(T*, int64_t, hipStream_t);                              \
   template void nonfinite_flag<T>(const T*, int64_t, unsigned*, hipStream_t);             \
-  template void interp<T>(const InterpArgs&, const cplx<T>*, const T*, double*, hipStream_t); \
+  template void interp<T>(const InterpArgs&, const cplx<T>*, const T*, double*, hipStream_t, const BorderArgs&); \
+  template void interp_adj<T>(const InterpArgs&, const AdjArgs&, const cplx<T>*, const T*, double*, hipStream_t, \
+                              const BorderArgs&);                                          \
   template void interp_div<T>(const InterpArgs&, const cplx<T>*, const T*, const double*, const double*, double, \
-                              double, const double*, double*, hipStream_t);                \
+                              double, const double*, double*, hipStream_t, const BorderArgs&); \
   template void grid_axpby<T>(T*, double, const T*, double, int64_t, hipStream_t);        \
   template void gather_dx<T>(const GatherArgs&, hipStream_t);                             \
   template void grid_add_const<T>(T*, const double*, int, int64_t, hipStream_t);          \

@@ -498,10 +498,31 @@ InterpArgs interp_args(ibdl_s* h, int nf, double a, double b, const double* x, c
   return ia;
 }
 
+// The border rows' sum scale sum_i (w ? w[i] : 1) q[i] of an apply, beside its interpolation where it is
+// short enough (else border_after)
+BorderArgs border_args(ibdl_s* h, const double* q, const double* w, double scale, double* y) {
+  BorderArgs bd;
+  if (!h->has_ubar || h->n_ib > kBorderOne) return bd;
+  bd.q = q;
+  bd.w = w;
+  bd.out = y + h->n_ib * h->nq;
+  bd.scale = scale;
+  bd.n = h->n_ib;
+  bd.nq = h->nq;
+  return bd;
+}
+
 void ensure_partial(ibdl_s* h, int need) {
   if (h->pcap >= need) return;
   h->partial = (double*)h->dalloc<double>(sizeof(double) * need);
   h->pcap = need;
+}
+
+void border_after(ibdl_s* h, const double* q, const double* w, double scale, double* y) {
+  if (!h->has_ubar || h->n_ib <= kBorderOne) return;
+  const int nblk = kr_nblk(h->n_ib);
+  ensure_partial(h, nblk * h->nq);
+  kr_border(q, w, h->n_ib, h->nq, scale, y + h->n_ib * h->nq, h->partial, nblk, h->st);
 }
 
 // The spread fields and Fourier multiplier of the density-to-grid map: Stokes A11, A12, A22 (and
@@ -692,13 +713,9 @@ template <typename T> void apply_t(ibdl_s* h, const double* q, double* y) {
   InterpArgs ia = interp_args(h, h->nq, 1.0, h->half(), q, ub);
   {
     StageTimer t(h, ST_INTERP);
-    interp<T>(ia, W.wtab, W.real, y, h->st);
+    interp<T>(ia, W.wtab, W.real, y, h->st, border_args(h, q, h->ds, h->border_w(), y));
   }
-  if (h->has_ubar) {
-    const int nblk = kr_nblk(h->n_ib);
-    ensure_partial(h, nblk * h->nq);
-    kr_border(q, h->ds, h->n_ib, h->nq, h->border_w(), y + h->n_ib * h->nq, h->partial, nblk, h->st);
-  }
+  border_after(h, q, h->ds, h->border_w(), y);
 }
 
 // u = L^-1 rhs (scalar) or L^-1 P rhs (Stokes); rhsf: the right-hand side as float fields instead
@@ -813,7 +830,8 @@ template <typename T> void adj_markers_div(ibdl_s* h, GridWork<T>& W, const doub
                                            double* y) {
   InterpArgs ia = interp_args(h, 1, 1.0, b, p, nullptr);
   StageTimer t(h, ST_INTERP);
-  interp_div<T>(ia, W.wtab, W.real, h->nrm, h->ds, h->cfg.eta, 1.0 / pow(h->h, (double)h->dim), pu, y, h->st);
+  interp_div<T>(ia, W.wtab, W.real, h->nrm, h->ds, h->cfg.eta, 1.0 / pow(h->h, (double)h->dim), pu, y, h->st,
+                p ? border_args(h, p, nullptr, 1.0, y) : BorderArgs());
 }
 
 void ensure_adj(ibdl_s* h) {
@@ -827,11 +845,24 @@ template <typename T> void adj_markers(ibdl_s* h, GridWork<T>& W, const double* 
                                        double* y) {
   const int nout = adj_nout(h);
   InterpArgs ia = interp_args(h, nout, 1.0, 0.0, nullptr, nullptr);
-  {
-    StageTimer t(h, ST_INTERP);
-    interp<T>(ia, W.wtab, W.real, h->adj_m, h->st);
-  }
   const double hDinv = 1.0 / pow(h->h, (double)h->dim);
+  const BorderArgs bd = p ? border_args(h, p, nullptr, 1.0, y) : BorderArgs();
+  StageTimer t(h, ST_INTERP);
+  if (h->cfg.kernel != IBDL_K_BSPLINE6) {
+    AdjArgs ad;
+    ad.stokes = h->stokes() ? 1 : 0;
+    ad.dim = h->dim;
+    ad.hDinv = hDinv;
+    ad.eta = h->cfg.eta;
+    ad.b = b;
+    ad.nrm = h->nrm;
+    ad.ds = h->ds;
+    ad.p = p;
+    ad.pu = pu;
+    interp_adj<T>(ia, ad, W.wtab, W.real, y, h->st, bd);
+    return;
+  }
+  interp<T>(ia, W.wtab, W.real, h->adj_m, h->st, bd);
   adj_combine(h->stokes() ? 1 : 0, h->dim, h->n_ib, nout, hDinv, h->cfg.eta, h->adj_m, h->nrm, h->ds, p, b, pu, y,
               h->st);
 }
@@ -856,11 +887,7 @@ template <typename T> void apply_adj_t(ibdl_s* h, const double* p, double* y) {
     adj_grid<T>(h, W, W.real, W.real, ROWS_SPARSE, true);
     adj_markers<T>(h, W, p, half, pu, y);
   }
-  if (h->has_ubar) {
-    const int nblk = kr_nblk(h->n_ib);
-    ensure_partial(h, nblk * h->nq);
-    kr_border(p, nullptr, h->n_ib, h->nq, 1.0, y + h->n_ib * h->nq, h->partial, nblk, h->st);
-  }
+  border_after(h, p, nullptr, 1.0, y);
 }
 
 // right-hand side of the adjoint system: the gradient of <psi, u> with respect to q

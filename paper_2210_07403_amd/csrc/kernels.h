@@ -295,7 +295,32 @@ struct InterpArgs {
   const double* ub;    // [nf] or null
   const int* pid;      // batch: marker i reads fields at u + pid[i] * nf * (grid points); or null
 };
-template <typename T> void interp(const InterpArgs& a, const cplx<T>* wtab, const T* u, double* out, hipStream_t st);
+// A border row's sum beside an interpolation, by one extra workgroup per component of its launch:
+// out[c] = scale sum_i (w ? w[i] : 1) q[i][c], i < n <= kBorderOne (q NULL: none; longer sums:
+// kr_border).
+constexpr int64_t kBorderOne = 16384;
+struct BorderArgs {
+  const double* q = nullptr;
+  const double* w = nullptr;
+  double* out = nullptr;
+  double scale = 0.0;
+  int64_t n = 0;
+  int nq = 1;
+};
+// Marker side of the transposed operator, combined from the nf interpolated adjoint fields of a marker
+// instead of storing them (adj_combine's formulas and arguments).
+struct AdjArgs {
+  int stokes = 0, dim = 2;
+  double hDinv = 0.0, eta = 0.0, b = 0.0;
+  const double *nrm = nullptr, *ds = nullptr, *p = nullptr, *pu = nullptr;
+};
+template <typename T>
+void interp(const InterpArgs& a, const cplx<T>* wtab, const T* u, double* out, hipStream_t st,
+            const BorderArgs& bd = BorderArgs());
+// y = adj_combine of the interpolated fields in one launch (4-point kernels, a.nf <= 5)
+template <typename T>
+void interp_adj(const InterpArgs& a, const AdjArgs& ad, const cplx<T>* wtab, const T* u, double* y, hipStream_t st,
+                const BorderArgs& bd);
 // One grid group of a batch for the single-launch interpolation: arguments (a.pid set), weight table,
 // fields, and the index m0 of its first marker in the concatenation.
 struct InterpGroup {
@@ -312,7 +337,7 @@ void interp4_groups(const InterpGroup* gd, int ng, int64_t ntot_m, const double*
 // + eta W W W] + b p_i + eta ds_i pu, with p = a.x and b = a.b (p, pu may be null); one field w.
 template <typename T>
 void interp_div(const InterpArgs& a, const cplx<T>* wtab, const T* u, const double* nrm, const double* ds, double eta,
-                double hDinv, const double* pu, double* y, hipStream_t st);
+                double hDinv, const double* pu, double* y, hipStream_t st, const BorderArgs& bd = BorderArgs());
 
 // Kernel-derivative gather: out[i][e] = sum_x F_i(x) d/dX_ie prod_d phi((x_d - X_id)/h), with
 // F_i(x) = sum_k coef[i][k] field_k(x) (field_k of the grid type; at most 8 fields).
