@@ -43,6 +43,7 @@ using Tuned = LaunchShape;
 template <typename T> struct GroupWork {
   GridTables<T> tab;
   Tw2<T> tw2;                // 2-D: the tables of the passes
+  TwX<T> twx;                // 3-D: those of the x passes
   T* real = nullptr;          // [problem][grid]
   cplx<T>* spec = nullptr;    // [problem][half spectrum]
   cplx<T>* wtab = nullptr;    // weight table in this precision
@@ -206,13 +207,13 @@ template <typename T> void group_pipeline(ibdl_batch_s* B, Group& G, GroupWork<T
   rl.rpf = rows;
   rl.seg = G.seg_all;
   rl.seg_log2 = __builtin_ctz((unsigned)G.geom.tile[0] / 2);
-  fft_x_r2c<T>(W.real, W.spec, G.n[0], rows, W.tab.tw[0], B->st, tn.rpb, rl, G.nxp);
+  fft_x_r2c<T>(W.real, W.spec, G.n[0], rows, W.twx, B->st, tn.rpb, rl, G.nxp);
   fft_strided<T>(W.spec, G.n[1], (int64_t)np * G.n[2] * G.nxp, G.nxp, G.nxp * G.n[1], G.nxp, false, W.tab.tw[1], B->st,
                  0, RowMask(), G.nxh);
   fft_fused_last<T>(W.spec, G.n[2], G.nxp * G.n[1], 1, md, W.tab.tw[2], B->st, np, G.nspec<T>(3), tn.wz);
   fft_strided<T>(W.spec, G.n[1], (int64_t)np * G.n[2] * G.nxp, G.nxp, G.nxp * G.n[1], G.nxp, true, W.tab.tw[1], B->st,
                  0, RowMask(), G.nxh);
-  fft_x_c2r<T>(W.spec, W.real, G.n[0], rows, W.tab.tw[0], B->st, tn.rpb, RowList(), G.nxp);
+  fft_x_c2r<T>(W.spec, W.real, G.n[0], rows, W.twx, B->st, tn.rpb, RowList(), G.nxp);
 }
 
 // the group's density q (its slice of a batch vector) -> grid fields u[q] = -L^-1 S~ q per problem
@@ -386,6 +387,9 @@ template <typename T> GroupWork<T>& group_work(ibdl_batch_s* B, Group& G) {
   if (B->dim == 2) {
     cplx<T>* st = (cplx<T>*)B->dalloc(sizeof(cplx<T>) * fft2_table_len<T>(G.n[0], G.n[1]));
     W.tw2 = fft2_tables<T>(G.n[0], G.n[1], W.tab.tw[0], W.tab.tw[1], st, B->st);
+  } else {
+    cplx<T>* st = (cplx<T>*)B->dalloc(sizeof(cplx<T>) * fft_x_table_len<T>(G.n[0]));
+    W.twx = fft_x_table<T>(G.n[0], W.tab.tw[0], st, B->st);
   }
   W.real = (T*)B->dalloc(sizeof(T) * G.ntot * np);
   W.spec = (cplx<T>*)B->dalloc(sizeof(cplx<T>) * G.nspec<T>(B->dim) * np);

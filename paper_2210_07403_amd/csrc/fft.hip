@@ -2,8 +2,7 @@
 // (fft_core.h).
 //
 // Passes:  x axis  real <-> half spectrum, by an N/2-point complex FFT of (x_2n + i x_2n+1)
-//                  and the standard even/odd split; rows are staged in LDS with coalesced
-//                  cooperative loads and stores.
+//                  and the standard even/odd split; a row belongs to one wave.
 //          strided in-place C2C along y (the middle axis), tiles of W adjacent lines so each
 //                  row of the tile is one contiguous segment.
 //          fused   last axis: forward FFT of every input field, Fourier multiplier of the scalar
@@ -94,178 +93,118 @@ __device__ __forceinline__ const C* stage_table(C* dst, const C* __restrict__ tw
   return dst;
 }
 
-// Rows per block of the x-axis passes (rows of M = nx / 2 complex points): as many rows as fit 256
-// threads and 64 KiB of LDS beside the twiddle table.
-constexpr int xrmax(int M) { return plan_rmax(M) < 8 ? plan_rmax(M) : 8; }   // elements per thread, x passes
-template <typename TR, int M> struct RowCfg {
-  static constexpr int RMX = xrmax(M);
-  static constexpr int T = Plan<M, RMX>::T;
-  static constexpr int BLK = T > kBlock ? T : kBlock;   // launch bound
-  static constexpr bool TWL = M <= 1024;                 // twiddle table staged in LDS
-  static constexpr int SZ = (int)sizeof(cplx<TR>);
-  static constexpr int PAD = 3;      // line exchanges pad one slot every 8 elements
-  static constexpr int LS = M + (M >> PAD) + 1;  // LDS row stride (complex elements)
-  static constexpr int R0 = BLK / T;
-  static constexpr int RL = TWL ? pow2floor((kLdsBytes - 2 * M * SZ) / (LS * SZ)) : 1;
-  static constexpr int RPB = (R0 < RL ? R0 : RL) > 0 ? (R0 < RL ? R0 : RL) : 1;
-  static constexpr int NT = RPB * T;  // threads per block
-  static constexpr int LDSB = (RPB * LS + (TWL ? 2 * M : 0)) * SZ;
-  static_assert(TWL ? LDSB <= kLdsBytes : LDSB <= 163840, "x pass: LDS over budget");
+// ------------------------------------------------------------------ x axis
+// Rows of M = nx / 2 complex points, T = M / RMX <= 64 threads each, so that a row belongs to one wave
+// and its exchanges need no workgroup barrier: a thread loads its elements of the row from memory,
+// transforms, takes the mirrored mode of the even/odd split through LDS and stores (or the reverse).
+// Bound by HBM on a large grid (512^3 FP64, all rows: 412 and 425 us, 5.2 and 5.1 TB/s, a copy's rate)
+// and by the latency of one load - transform - store chain on a row list (256^3 sphere, 10k rows, FP32:
+// 9.7 and 10.5 us).  With rows staged in LDS by the whole block, the twiddles beside them and a workgroup
+// barrier per exchange these were 443 / 455 and 13 / 13 us.  Eight elements per thread: twice the waves
+// of sixteen to hide that chain.
+template <int M> struct RowCfg {
+  static constexpr int RMX = M < 8 ? M : 8;
+  static constexpr int T = M / RMX;
+  static constexpr int LS = pad_len(M) + 4;              // LDS row stride: an exchange line, or M + 1 modes
+  static constexpr int RPB = kBlock / T;                 // most rows per block
+  static_assert(T <= 64, "a row belongs to one wave");
 };
 
-// ------------------------------------------------------------------ x axis, forward R2C
-// TI: element type of the input rows (float rows widened on load for a double transform)
+// forward R2C; TI: element type of the input rows (float rows widened on load for a double transform)
 template <typename T, int M, typename TI = T>
-__global__ __launch_bounds__((RowCfg<T, M>::BLK)) void k_x_r2c(const TI* __restrict__ in, cplx<T>* __restrict__ out,
-                                                  int64_t nrows, const cplx<T>* __restrict__ twg, int RPB,
-                                                  RowList rl, int64_t pitch) {
+__global__ __launch_bounds__(kBlock) void k_x_r2c(const TI* __restrict__ in, cplx<T>* __restrict__ out, unsigned nrows,
+                                                  const cplx<T>* __restrict__ tw, const cplx<T>* __restrict__ st,
+                                                  RowList rl, int pitch) {
   using C = cplx<T>;
-  using RC = RowCfg<T, M>;
+  using RC = RowCfg<M>;
+  constexpr int RMX = RC::RMX, TT = RC::T;
   extern __shared__ __align__(16) unsigned char smem[];
-  C* lds = reinterpret_cast<C*>(smem);
-  const int tid = threadIdx.x;
-  const int NT = RPB * RC::T;
-  const C* tw = RC::TWL ? stage_table(lds + RPB * RC::LS, twg, 2 * M, tid, NT) : twg;
-  const int64_t row0 = (int64_t)blockIdx.x * RPB;
-  const int nvalid = (int)((nrows - row0) < RPB ? (nrows - row0) : RPB);
-  __shared__ int64_t rbase[kBlock];   // row index of each block row (active-row list or contiguous)
-  __shared__ unsigned long long rseg[kBlock];   // busy x-segments of each block row
-  __shared__ int64_t rsub[kBlock];              // forcing row to subtract, or -1
-  for (int r = tid; r < RPB; r += NT) {
-    rbase[r] = r < nvalid ? rl.row(row0 + r) : 0;
-    rseg[r] = r < nvalid ? rl.segmask(row0 + r) : 0ull;
-    rsub[r] = r < nvalid ? rl.sub_row(row0 + r) : -1;
-  }
-  __syncthreads();
-  const cplx<TI>* src = reinterpret_cast<const cplx<TI>*>(in);
-  const C* sub = static_cast<const C*>(rl.sub);
-  // every load of a thread is issued before the first LDS write (RPB * M values, M / T per thread)
-  constexpr int K = M / RC::T;
-  C ld[K];
+  const int tid = threadIdx.x, lrow = tid / TT, i = tid - lrow * TT;
+  const unsigned r = blockIdx.x * (blockDim.x / TT) + lrow;
+  const bool live = r < nrows;
+  const unsigned rc = live ? r : nrows - 1;
+  const int64_t row = rl.row(rc);
+  const unsigned long long seg = live ? rl.segmask(rc) : 0ull;
+  const int64_t srow = live ? rl.sub_row(rc) : -1;
+  const cplx<TI>* src = reinterpret_cast<const cplx<TI>*>(in) + row * M;
+  C v[1][RMX];
 #pragma unroll
-  for (int j = 0; j < K; ++j) {
-    const int e = tid + j * NT, r = e / M, c = e - r * M;
-    ld[j] = mk<C>(0, 0);
-    if ((rseg[r] >> (c >> rl.seg_log2)) & 1ull) {
-      const cplx<TI> x = src[rbase[r] * M + c];
-      ld[j] = mk<C>((T)x.x, (T)x.y);
-    }
-    if (rsub[r] >= 0) {
-      const C f = sub[rsub[r] * M + c];
-      ld[j] = mk<C>(ld[j].x - f.x, ld[j].y - f.y);
+  for (int s = 0; s < RMX; ++s) {
+    v[0][s] = mk<C>(0, 0);
+    if ((seg >> ((i + s * TT) >> rl.seg_log2)) & 1ull) {
+      const cplx<TI> x = src[i + s * TT];
+      v[0][s] = mk<C>((T)x.x, (T)x.y);
     }
   }
+  if (srow >= 0) {   // minus a dense forcing
+    const C* sub = static_cast<const C*>(rl.sub) + srow * M;
 #pragma unroll
-  for (int j = 0; j < K; ++j) {
-    const int e = tid + j * NT, r = e / M, c = e - r * M;
-    lds[r * RC::LS + c] = ld[j];
+    for (int s = 0; s < RMX; ++s) v[0][s] = csub(v[0][s], sub[i + s * TT]);
   }
-  __syncthreads();
-  const int row = tid / RC::T, i = tid - row * RC::T;
-  C v[RC::RMX];
-  if (row < RPB) line_load<M, RC::RMX>(v, i, lds + row * RC::LS, 1);
-  fft_line<M, false, !RC::TWL, RC::RMX, RC::PAD>(v, i, lds + (row < RPB ? row : 0) * RC::LS, 1, tw, 2);
-  __syncthreads();
-  if (row < RPB) {
+  C wk[RMX];
 #pragma unroll
-    for (int s = 0; s < RC::RMX; ++s) lds[row * RC::LS + i + s * RC::T] = v[s];
-  }
-  __syncthreads();
-  constexpr int KO = (M + 1 + RC::T - 1) / RC::T;   // M + 1 outputs per row
-  C wk_[KO];
+  for (int s = 0; s < RMX; ++s) wk[s] = tw[i + s * TT];
+  C* line = reinterpret_cast<C*>(smem) + lrow * RC::LS;
+  C w0[RMX];
+  int par = 0;
+  fft_multi<M, false, 1, RMX, 1>(v, i, line, 0, par, st, w0);
+  line_sync<TT>();
 #pragma unroll
-  for (int j = 0; j < KO; ++j) wk_[j] = tw[(tid + j * NT) % (M + 1)];   // twiddles first, loads together
+  for (int s = 0; s < RMX; ++s) line[i + s * TT] = v[0][s];
+  line_sync<TT>();
+  if (!live) return;
+  C* dst = out + row * pitch;
 #pragma unroll
-  for (int j = 0; j < KO; ++j) {
-    const int e = tid + j * NT;
-    if (e < nvalid * (M + 1)) {
-      const int r = e / (M + 1), k = e - r * (M + 1);
-      const C zk = lds[r * RC::LS + (k == M ? 0 : k)];
-      const C zm = lds[r * RC::LS + (k == 0 ? 0 : M - k)];
-      const C E = mk<C>((zk.x + zm.x) * (T)0.5, (zk.y - zm.y) * (T)0.5);
-      const C O = mk<C>((zk.y + zm.y) * (T)0.5, -(zk.x - zm.x) * (T)0.5);
-      out[rbase[r] * pitch + k] = cadd(E, cmul(wk_[j], O));
-    }
+  for (int s = 0; s < RMX; ++s) {
+    const int k = i + s * TT;
+    const C zk = v[0][s], zm = line[k == 0 ? 0 : M - k];
+    const C E = mk<C>((zk.x + zm.x) * (T)0.5, (zk.y - zm.y) * (T)0.5);
+    const C O = mk<C>((zk.y + zm.y) * (T)0.5, -(zk.x - zm.x) * (T)0.5);
+    dst[k] = cadd(E, cmul(wk[s], O));
+    if (k == 0) dst[M] = mk<C>(zk.x - zk.y, (T)0);
   }
 }
 
-// ------------------------------------------------------------------ x axis, inverse C2R
+// inverse C2R
 template <typename T, int M>
-__global__ __launch_bounds__((RowCfg<T, M>::BLK)) void k_x_c2r(const cplx<T>* __restrict__ in, T* __restrict__ out,
-                                                  int64_t nrows, const cplx<T>* __restrict__ twg, int RPB,
-                                                  RowList rl, int64_t pitch) {
+__global__ __launch_bounds__(kBlock) void k_x_c2r(const cplx<T>* __restrict__ in, T* __restrict__ out, unsigned nrows,
+                                                  const cplx<T>* __restrict__ tw, const cplx<T>* __restrict__ st,
+                                                  RowList rl, int pitch) {
   using C = cplx<T>;
-  using RC = RowCfg<T, M>;
+  using RC = RowCfg<M>;
+  constexpr int RMX = RC::RMX, TT = RC::T;
   extern __shared__ __align__(16) unsigned char smem[];
-  C* lds = reinterpret_cast<C*>(smem);
-  const int tid = threadIdx.x;
-  const int NT = RPB * RC::T;
-  const C* tw = RC::TWL ? stage_table(lds + RPB * RC::LS, twg, 2 * M, tid, NT) : twg;
-  const int64_t row0 = (int64_t)blockIdx.x * RPB;
-  const int nvalid = (int)((nrows - row0) < RPB ? (nrows - row0) : RPB);
-  __shared__ int64_t rbase[kBlock];
-  for (int r = tid; r < RPB; r += NT) rbase[r] = r < nvalid ? rl.row(row0 + r) : 0;
-  __syncthreads();
-  // every load of a thread is issued before the first LDS write
-  constexpr int KI = (M + 1 + RC::T - 1) / RC::T;
-  C ld[KI];
+  const int tid = threadIdx.x, lrow = tid / TT, i = tid - lrow * TT;
+  const unsigned r = blockIdx.x * (blockDim.x / TT) + lrow;
+  const bool live = r < nrows;
+  const int64_t row = rl.row(live ? r : nrows - 1);
+  const C* src = in + row * pitch;
+  C x[RMX], last = mk<C>(0, 0);
 #pragma unroll
-  for (int j = 0; j < KI; ++j) {
-    const int e = tid + j * NT, r = e / (M + 1), k = e - r * (M + 1);
-    ld[j] = mk<C>(0, 0);
-    if (e < RPB * (M + 1) && r < nvalid) ld[j] = in[rbase[r] * pitch + k];
-  }
+  for (int s = 0; s < RMX; ++s) x[s] = src[i + s * TT];
+  if (i == 0) last = src[M];
+  C wk[RMX];
 #pragma unroll
-  for (int j = 0; j < KI; ++j) {
-    const int e = tid + j * NT, r = e / (M + 1), k = e - r * (M + 1);
-    if (e < RPB * (M + 1)) lds[r * RC::LS + k] = ld[j];
-  }
-  __syncthreads();
-  // Z'_k = (X_k + conj X_{M-k}) + i conj(W^k) (X_k - conj X_{M-k}); each thread owns a pair (k, M-k)
-  constexpr int HP = M / 2 + 1, KP = (HP + RC::T - 1) / RC::T;
-  C wk_[KP], wm_[KP];
+  for (int s = 0; s < RMX; ++s) wk[s] = tw[i + s * TT];
+  C* line = reinterpret_cast<C*>(smem) + lrow * RC::LS;
 #pragma unroll
-  for (int j = 0; j < KP; ++j) {   // twiddles first: their loads are issued together
-    const int k = (tid + j * NT) % HP;
-    wk_[j] = cconj(tw[k]);
-    wm_[j] = cconj(tw[M - k]);
-  }
+  for (int s = 0; s < RMX; ++s) line[i + s * TT] = x[s];
+  if (i == 0) line[M] = last;
+  line_sync<TT>();
+  // Z'_k = (X_k + conj X_{M-k}) + i conj(W^k) (X_k - conj X_{M-k})
+  C v[1][RMX];
 #pragma unroll
-  for (int j = 0; j < KP; ++j) {
-    const int e = tid + j * NT;
-    if (e < nvalid * HP) {
-      const int r = e / HP, k = e - r * HP;
-      C* rowp = lds + r * RC::LS;
-      const C a = rowp[k], b = rowp[M - k];
-      const C wk = wk_[j], wm = wm_[j];
-      const C za = cadd(mk<C>(a.x + b.x, a.y - b.y), cmul(mk<C>(-wk.y, wk.x), mk<C>(a.x - b.x, a.y + b.y)));
-      rowp[k] = za;
-      if (k != 0 && 2 * k != M) {
-        const C zb = cadd(mk<C>(b.x + a.x, b.y - a.y), cmul(mk<C>(-wm.y, wm.x), mk<C>(b.x - a.x, b.y + a.y)));
-        rowp[M - k] = zb;
-      }
-    }
+  for (int s = 0; s < RMX; ++s) {
+    const C a = x[s], b = line[M - (i + s * TT)];
+    v[0][s] = cadd(mk<C>(a.x + b.x, a.y - b.y), cmul(mk<C>(wk[s].y, wk[s].x), mk<C>(a.x - b.x, a.y + b.y)));
   }
-  __syncthreads();
-  const int row = tid / RC::T, i = tid - row * RC::T;
-  C v[RC::RMX];
-  if (row < RPB) line_load<M, RC::RMX>(v, i, lds + row * RC::LS, 1);
-  fft_line<M, true, !RC::TWL, RC::RMX, RC::PAD>(v, i, lds + (row < RPB ? row : 0) * RC::LS, 1, tw, 2);
-  __syncthreads();
-  if (row < RPB) {
+  C w0[RMX];
+  int par = 0;
+  fft_multi<M, true, 1, RMX, 1>(v, i, line, 0, par, st, w0);
+  if (!live) return;
+  C* dst = reinterpret_cast<C*>(out) + row * M;
 #pragma unroll
-    for (int s = 0; s < RC::RMX; ++s) lds[row * RC::LS + i + s * RC::T] = v[s];
-  }
-  __syncthreads();
-  C* dst = reinterpret_cast<C*>(out);
-#pragma unroll
-  for (int j = 0; j < M / RC::T; ++j) {
-    const int e = tid + j * NT;
-    if (e < nvalid * M) {
-      const int r = e / M, c = e - r * M;
-      dst[rbase[r] * M + c] = lds[r * RC::LS + c];
-    }
-  }
+  for (int s = 0; s < RMX; ++s) dst[i + s * TT] = v[0][s];
 }
 
 // tile width (lines per block) for strided and fused passes
@@ -526,6 +465,14 @@ template <typename F> void dispatch_n(int n, F&& f) {
     default: throw Error(-2, "unsupported FFT length " + std::to_string(n));
   }
 }
+
+// the x passes' complex length, nx / 2
+template <typename F> void dispatch_m(int m, F&& f) {
+  if (m == 1024) throw Error(-2, "unsupported FFT length " + std::to_string(2 * m));
+  dispatch_n(m, [&](auto Mc) {
+    if constexpr (decltype(Mc)::value < 1024) f(Mc);
+  });
+}
 }  // namespace
 
 int fft_supported(int n) { return n >= 16 && n <= 1024 && (n & (n - 1)) == 0; }
@@ -533,8 +480,27 @@ int fft_supported(int n) { return n >= 16 && n <= 1024 && (n & (n - 1)) == 0; }
 template <typename T>
 int fft_x_rpb_max(int nx) {
   int r = 0;
-  dispatch_n(nx / 2, [&](auto Mc) { r = RowCfg<T, decltype(Mc)::value>::RPB; });
+  dispatch_m(nx / 2, [&](auto Mc) { r = RowCfg<decltype(Mc)::value>::RPB; });
   return r;
+}
+
+template <typename T> size_t fft_x_table_len(int nx) {
+  int r = 0;
+  dispatch_m(nx / 2, [&](auto Mc) { r = stage_len<decltype(Mc)::value, RowCfg<decltype(Mc)::value>::RMX>(); });
+  return (size_t)r + 1;
+}
+
+template <typename T> TwX<T> fft_x_table(int nx, const cplx<T>* twx, cplx<T>* dst, hipStream_t s) {
+  dispatch_m(nx / 2, [&](auto Mc) {
+    constexpr int M = decltype(Mc)::value, RMX = RowCfg<M>::RMX;
+    const int len = stage_len<M, RMX>();
+    if (len > 0) hipLaunchKernelGGL((k_stages<M, RMX, cplx<T>>), dim3((len + 255) / 256), dim3(256), 0, s, dst, twx, 2);
+  });
+  IBDL_LAUNCH_CHECK();
+  TwX<T> t;
+  t.base = twx;
+  t.x = dst;
+  return t;
 }
 
 template <typename T>
@@ -568,47 +534,43 @@ int pick(int want, int max) {
 
 namespace {
 template <typename T, typename TI>
-void x_r2c_launch(const TI* in, cplx<T>* out, int nx, int64_t nrows, const cplx<T>* tw_x, hipStream_t s, int rpb,
+void x_r2c_launch(const TI* in, cplx<T>* out, int nx, int64_t nrows, const TwX<T>& tw, hipStream_t s, int rpb,
                   const RowList& rl, int64_t pitch) {
-  if (pitch <= 0) pitch = nx / 2 + 1;
-  dispatch_n(nx / 2, [&](auto Mc) {
+  if (nrows <= 0) return;
+  if (nrows > INT32_MAX) throw Error(-2, "x FFT pass: too many rows");
+  dispatch_m(nx / 2, [&](auto Mc) {
     constexpr int M = decltype(Mc)::value;
-    using RC = RowCfg<T, M>;
+    using RC = RowCfg<M>;
     const int R = pick(rpb, RC::RPB);
-    const int64_t nb = (nrows + R - 1) / R;
-    const size_t lds = sizeof(cplx<T>) * (R * RC::LS + (RC::TWL ? 2 * M : 0));
-    if (nb > 0)
-      hipLaunchKernelGGL((k_x_r2c<T, M, TI>), dim3((unsigned)nb), dim3(R * RC::T), lds, s, in, out, nrows, tw_x, R, rl,
-                         pitch);
+    hipLaunchKernelGGL((k_x_r2c<T, M, TI>), dim3((unsigned)((nrows + R - 1) / R)), dim3(R * RC::T),
+                       sizeof(cplx<T>) * R * RC::LS, s, in, out, (unsigned)nrows, tw.base, tw.x, rl, (int)pitch);
   });
   IBDL_LAUNCH_CHECK();
 }
 }  // namespace
 
 template <typename T>
-void fft_x_r2c(const T* in, cplx<T>* out, int nx, int64_t nrows, const cplx<T>* tw_x, hipStream_t s, int rpb,
+void fft_x_r2c(const T* in, cplx<T>* out, int nx, int64_t nrows, const TwX<T>& tw, hipStream_t s, int rpb,
                const RowList& rl, int64_t pitch) {
-  x_r2c_launch<T, T>(in, out, nx, nrows, tw_x, s, rpb, rl, pitch);
+  x_r2c_launch<T, T>(in, out, nx, nrows, tw, s, rpb, rl, pitch);
 }
 
-void fft_x_r2c_widen(const float* in, cplx<double>* out, int nx, int64_t nrows, const cplx<double>* tw_x,
-                     hipStream_t s, int rpb, const RowList& rl, int64_t pitch) {
-  x_r2c_launch<double, float>(in, out, nx, nrows, tw_x, s, rpb, rl, pitch);
+void fft_x_r2c_widen(const float* in, cplx<double>* out, int nx, int64_t nrows, const TwX<double>& tw, hipStream_t s, int rpb,
+                     const RowList& rl, int64_t pitch) {
+  x_r2c_launch<double, float>(in, out, nx, nrows, tw, s, rpb, rl, pitch);
 }
 
 template <typename T>
-void fft_x_c2r(const cplx<T>* in, T* out, int nx, int64_t nrows, const cplx<T>* tw_x, hipStream_t s, int rpb,
+void fft_x_c2r(const cplx<T>* in, T* out, int nx, int64_t nrows, const TwX<T>& tw, hipStream_t s, int rpb,
                const RowList& rl, int64_t pitch) {
-  if (pitch <= 0) pitch = nx / 2 + 1;
-  dispatch_n(nx / 2, [&](auto Mc) {
+  if (nrows <= 0) return;
+  if (nrows > INT32_MAX) throw Error(-2, "x FFT pass: too many rows");
+  dispatch_m(nx / 2, [&](auto Mc) {
     constexpr int M = decltype(Mc)::value;
-    using RC = RowCfg<T, M>;
+    using RC = RowCfg<M>;
     const int R = pick(rpb, RC::RPB);
-    const int64_t nb = (nrows + R - 1) / R;
-    const size_t lds = sizeof(cplx<T>) * (R * RC::LS + (RC::TWL ? 2 * M : 0));
-    if (nb > 0)
-      hipLaunchKernelGGL((k_x_c2r<T, M>), dim3((unsigned)nb), dim3(R * RC::T), lds, s, in, out, nrows, tw_x, R, rl,
-                         pitch);
+    hipLaunchKernelGGL((k_x_c2r<T, M>), dim3((unsigned)((nrows + R - 1) / R)), dim3(R * RC::T),
+                       sizeof(cplx<T>) * R * RC::LS, s, in, out, (unsigned)nrows, tw.base, tw.x, rl, (int)pitch);
   });
   IBDL_LAUNCH_CHECK();
 }
@@ -697,10 +659,12 @@ void fft_fused_last(cplx<T>* data, int n, int64_t P, int no, const MultDesc& md,
 }
 
 #define IBDL_FFT_INST(T)                                                                                   \
-  template void fft_x_r2c<T>(const T*, cplx<T>*, int, int64_t, const cplx<T>*, hipStream_t, int,         \
+  template void fft_x_r2c<T>(const T*, cplx<T>*, int, int64_t, const TwX<T>&, hipStream_t, int,          \
                              const RowList&, int64_t);                                                     \
-  template void fft_x_c2r<T>(const cplx<T>*, T*, int, int64_t, const cplx<T>*, hipStream_t, int,         \
+  template void fft_x_c2r<T>(const cplx<T>*, T*, int, int64_t, const TwX<T>&, hipStream_t, int,          \
                              const RowList&, int64_t);                                                     \
+  template size_t fft_x_table_len<T>(int);                                                                 \
+  template TwX<T> fft_x_table<T>(int, const cplx<T>*, cplx<T>*, hipStream_t);                              \
   template void fft_strided<T>(cplx<T>*, int, int64_t, int64_t, int64_t, int64_t, bool, const cplx<T>*,   \
                                hipStream_t, int, const RowMask&, int64_t, int);                            \
   template void fft_fused_last<T>(cplx<T>*, int, int64_t, int, const MultDesc&, const cplx<T>*, hipStream_t, \

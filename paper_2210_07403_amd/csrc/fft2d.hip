@@ -34,134 +34,6 @@ namespace {
 constexpr int kLds = 163840;      // LDS of a gfx950 workgroup
 constexpr int kLdsHalf = 81920;   // two workgroups per CU
 
-// order a line's LDS accesses across its T threads
-template <int T> __device__ __forceinline__ void line_sync() {
-  if constexpr (T <= 64) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  } else {
-    __syncthreads();
-  }
-}
-
-// Twiddles are read from a table in stage order: stage S >= 1 of a transform holds w_N^(j k N / (PP R))
-// at stage_off + (j - 1) PP + k (1 <= j < R, k < PP), so that the lanes of a wave read consecutive
-// values; from the plain table w_N^m they would read N / (PP R) j values apart, a cache line per lane.
-template <int N, int RMX> constexpr int stage_off(int S) {
-  using P = Plan<N, RMX>;
-  int o = 0;
-  for (int q = 1; q < S; ++q) o += (P::radix(q) - 1) * P::pw(q);
-  return o;
-}
-template <int N, int RMX> constexpr int stage_len() { return stage_off<N, RMX>(Plan<N, RMX>::NST); }
-
-// the twiddles of stage S on this thread's elements: w[m * R + j] multiplies element m + j * NB
-template <int N, int S, int RMX, typename C>
-__device__ __forceinline__ void stage_twiddles(C (&w)[RMX], int i, const C* __restrict__ tab) {
-  using P = Plan<N, RMX>;
-  constexpr int R = P::radix(S), PP = P::pw(S), NB = RMX / R, TT = P::T, OFF = stage_off<N, RMX>(S);
-#pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    const int k = (i + m * TT) & (PP - 1);
-#pragma unroll
-    for (int j = 1; j < R; ++j) w[m * R + j] = tab[OFF + (j - 1) * PP + k];
-  }
-}
-
-// fills the stage-ordered table of an N-point transform from the plain one (w_N^m at tw[m * stride])
-template <int N, int RMX, typename C> __device__ void fill_stages(C* tab, const C* tw, int stride) {
-  using P = Plan<N, RMX>;
-  const int t0 = (int)(blockIdx.x * blockDim.x + threadIdx.x), nt = (int)(gridDim.x * blockDim.x);
-  for (int S = 1; S < P::NST; ++S) {
-    const int R = P::radix(S), PP = P::pw(S), off = stage_off<N, RMX>(S);
-    for (int e = t0; e < (R - 1) * PP; e += nt) {
-      const int j = 1 + e / PP, k = e - (j - 1) * PP;
-      tab[off + e] = tw[(int64_t)(j * k * (N / (PP * R))) * stride];
-    }
-  }
-}
-template <int N, int RMX, typename C> __global__ void k2_stages(C* tab, const C* tw, int stride) {
-  fill_stages<N, RMX, C>(tab, tw, stride);
-}
-
-template <int N, int S, bool INV, int RMX, typename C>
-__device__ __forceinline__ void stage_dft(C (&v)[RMX], const C (&w)[RMX]) {
-  using P = Plan<N, RMX>;
-  constexpr int R = P::radix(S), NB = RMX / R;
-#pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    C x[R];
-    x[0] = v[m];
-#pragma unroll
-    for (int j = 1; j < R; ++j) {
-      if constexpr (S > 0) x[j] = cmul(v[m + j * NB], INV ? cconj(w[m * R + j]) : w[m * R + j]);
-      else x[j] = v[m + j * NB];
-    }
-    dft<R, INV>(x);
-#pragma unroll
-    for (int j = 0; j < R; ++j) v[m + j * NB] = x[j];
-  }
-}
-
-constexpr int kPad = 3;   // one pad slot every 8 values of an exchange line
-constexpr int pad_len(int n) { return n + (n >> kPad); }
-
-// Exchange of stage S through a padded line: element e lives at pad_at(e) = e + e / 8.  Every address is
-// one base per stage plus a constant: (base + offset) / 8 = base / 8 + offset / 8 for the bases and
-// offsets that occur (a store's base is k < PP above a multiple of PP R, a load's i < T, and PP, T are
-// powers of two), which the compiler does not see by itself: it would keep an address register per
-// element and stage.
-__device__ __forceinline__ int pad_at(int e) { return e + (e >> kPad); }
-template <int N, int S, int RMX, typename C>
-__device__ __forceinline__ void put_stage(const C (&v)[RMX], int i, C* line) {
-  using P = Plan<N, RMX>;
-  constexpr int R = P::radix(S), PP = P::pw(S);
-  static_assert(R == RMX, "a stage that exchanges uses the full radix");
-  const int k = i & (PP - 1);
-  C* b = line + pad_at((i - k) * R + k);
-#pragma unroll
-  for (int j = 0; j < R; ++j) b[pad_len(j * PP)] = v[j];
-}
-template <int N, int RMX, typename C>
-__device__ __forceinline__ void get_line(C (&v)[RMX], int i, const C* line) {
-  const C* b = line + pad_at(i);
-#pragma unroll
-  for (int s = 0; s < RMX; ++s) v[s] = b[pad_len(s * Plan<N, RMX>::T)];
-}
-
-// Transforms of NF lines together (same line index of NF fields): stage by stage, each field in turn
-// exchanging through one of NBUF buffers of the line (bstr apart; par: the one to use next), so that
-// a field's LDS reads are in flight while the next one computes.  Each stage's twiddles serve every
-// field and are loaded a stage ahead.  All threads of the block call it.
-// LEAN: twiddles read when a stage begins, and the fields' work kept apart, for blocks whose threads
-// have few registers.
-template <int N, bool INV, int NF, int RMX, int NBUF, bool LEAN = false, int S = 0, typename C>
-__device__ __forceinline__ void fft_multi(C (&v)[NF][RMX], int i, C* lds, int bstr, int& par,
-                                          const C* __restrict__ tw, C (&w)[RMX]) {
-  using P = Plan<N, RMX>;
-  if constexpr (S < P::NST) {
-    C wn[RMX];
-    // (the scheduler would otherwise collect the loads of all stages at the top, for a register each)
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (LEAN && S > 0) stage_twiddles<N, S, RMX>(w, i, tw);
-    if constexpr (!LEAN && S + 1 < P::NST) stage_twiddles<N, S + 1, RMX>(wn, i, tw);
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      if constexpr (LEAN) __builtin_amdgcn_sched_barrier(0);
-      stage_dft<N, S, INV, RMX>(v[f], w);
-      if constexpr (S + 1 < P::NST) {
-        C* b = NBUF == 2 ? lds + par * bstr : lds;
-        if constexpr (NBUF == 1) line_sync<P::T>();
-        put_stage<N, S, RMX>(v[f], i, b);
-        line_sync<P::T>();
-        get_line<N, RMX>(v[f], i, b);
-        par ^= 1;
-      }
-    }
-    fft_multi<N, INV, NF, RMX, NBUF, LEAN, S + 1>(v, i, lds, bstr, par, tw, wn);
-  }
-}
-
 // ------------------------------------------------------------------ x axis
 // Rows of M = nx / 2 complex values, T = M / RMX threads each, R rows per block.  LDS row stride: at
 // least the padded exchange line and M + 1 modes, offset so that the R rows' accesses of one mode
@@ -711,12 +583,12 @@ Tw2<T> fft2_tables(int nx, int ny, const cplx<T>* twx, const cplx<T>* twy, cplx<
   auto blocks = [](int n) { return dim3((unsigned)((n + 255) / 256)); };
   dispatch2(nx / 2, [&](auto Mc) {
     constexpr int M = decltype(Mc)::value;
-    if (l.x > 0) hipLaunchKernelGGL((k2_stages<M, X2<T, M>::RMX, C>), blocks(l.x), dim3(256), 0, s, x, twx, 2);
+    if (l.x > 0) hipLaunchKernelGGL((k_stages<M, X2<T, M>::RMX, C>), blocks(l.x), dim3(256), 0, s, x, twx, 2);
   });
   dispatch2_line(ny, [&](auto Nc) {
     constexpr int N = decltype(Nc)::value;
-    if (l.y0 > 0) hipLaunchKernelGGL((k2_stages<N, line_rmx<T>(N, 1), C>), blocks(l.y0), dim3(256), 0, s, y[0], twy, 1);
-    if (l.y1 > 0) hipLaunchKernelGGL((k2_stages<N, line_rmx<T>(N, 2), C>), blocks(l.y1), dim3(256), 0, s, y[1], twy, 1);
+    if (l.y0 > 0) hipLaunchKernelGGL((k_stages<N, line_rmx<T>(N, 1), C>), blocks(l.y0), dim3(256), 0, s, y[0], twy, 1);
+    if (l.y1 > 0) hipLaunchKernelGGL((k_stages<N, line_rmx<T>(N, 2), C>), blocks(l.y1), dim3(256), 0, s, y[1], twy, 1);
   });
   IBDL_LAUNCH_CHECK();
   Tw2<T> t;

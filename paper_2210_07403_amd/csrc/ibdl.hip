@@ -31,6 +31,7 @@ constexpr int kHmap = kYOff + 2;
 template <typename T> struct GridWork {
   cplx<T>* tw[3] = {nullptr, nullptr, nullptr};
   Tw2<T> tw2;                // 2-D: the tables of the passes
+  TwX<T> twx;                // 3-D: those of the x passes
   T* sig[3] = {nullptr, nullptr, nullptr};
   T* kt[3] = {nullptr, nullptr, nullptr};
   T* real = nullptr;
@@ -280,6 +281,9 @@ template <typename T> GridWork<T>& ensure_work(ibdl_s* h) {
   if (h->dim == 2) {
     cplx<T>* st = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * fft2_table_len<T>(h->n[0], h->n[1]));
     W.tw2 = fft2_tables<T>(h->n[0], h->n[1], W.tw[0], W.tw[1], st, h->st);
+  } else {
+    cplx<T>* st = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * fft_x_table_len<T>(h->n[0]));
+    W.twx = fft_x_table<T>(h->n[0], W.tw[0], st, h->st);
   }
   return W;
 }
@@ -423,11 +427,11 @@ void pipeline(ibdl_s* h, GridWork<T>& W, const T* src, int nin, T* dst, int nout
   {
     StageTimer t(h, ST_FFT_X_FWD);
     if constexpr (std::is_same<T, double>::value) {
-      if (srcf) fft_x_r2c_widen(srcf, W.spec, h->n[0], rin, W.tw[0], h->st, tuned ? W.shape.rpb : 0, rl_in, h->nxp);
-      else fft_x_r2c<T>(src, W.spec, h->n[0], rin, W.tw[0], h->st, tuned ? W.shape.rpb : 0, rl_in, h->nxp);
+      if (srcf) fft_x_r2c_widen(srcf, W.spec, h->n[0], rin, W.twx, h->st, tuned ? W.shape.rpb : 0, rl_in, h->nxp);
+      else fft_x_r2c<T>(src, W.spec, h->n[0], rin, W.twx, h->st, tuned ? W.shape.rpb : 0, rl_in, h->nxp);
     } else {
       if (srcf) throw Error(IBDL_ERR_UNSUPPORTED, "float input fields are for the double pipeline");
-      fft_x_r2c<T>(src, W.spec, h->n[0], rin, W.tw[0], h->st, tuned ? W.shape.rpb : 0, rl_in, h->nxp);
+      fft_x_r2c<T>(src, W.spec, h->n[0], rin, W.twx, h->st, tuned ? W.shape.rpb : 0, rl_in, h->nxp);
     }
   }
   {
@@ -449,7 +453,7 @@ void pipeline(ibdl_s* h, GridWork<T>& W, const T* src, int nin, T* dst, int nout
   }
   {
     StageTimer t(h, ST_FFT_X_INV);
-    fft_x_c2r<T>(W.spec, dst, h->n[0], rout, W.tw[0], h->st, tuned ? W.shape.rpb : 0, rl_out, h->nxp);
+    fft_x_c2r<T>(W.spec, dst, h->n[0], rout, W.twx, h->st, tuned ? W.shape.rpb : 0, rl_out, h->nxp);
   }
 }
 
@@ -661,8 +665,8 @@ template <typename T> void tune_apply(ibdl_s* h, GridWork<T>& W) {
         fft2_x_c2r<T>(W.spec, W.real, h->n[0], h->n[1], pl.nout, W.tw2, h->st, r, rw);
         return;
       }
-      fft_x_r2c<T>(W.real, W.spec, h->n[0], h->nact * pl.nf, W.tw[0], h->st, r, rl, h->nxp);
-      fft_x_c2r<T>(W.spec, W.real, h->n[0], h->nact * pl.nout, W.tw[0], h->st, r, rl, h->nxp);
+      fft_x_r2c<T>(W.real, W.spec, h->n[0], h->nact * pl.nf, W.twx, h->st, r, rl, h->nxp);
+      fft_x_c2r<T>(W.spec, W.real, h->n[0], h->nact * pl.nout, W.twx, h->st, r, rl, h->nxp);
     }).second;
   }
   if (h->dim == 3) {

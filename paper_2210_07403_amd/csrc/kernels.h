@@ -31,14 +31,17 @@ struct RowList {
   int seg_log2 = 3;                          // list (NULL: read everything)
   const void* sub = nullptr;
   int sub_f0 = 0, nsub = 0;
-  __device__ int64_t row(int64_t r) const { return rows ? (int64_t)rows[r % nact] + (r / nact) * rpf : r; }
-  __device__ unsigned long long segmask(int64_t r) const {
-    return seg ? seg[rows ? r % nact : r % rpf] : ~0ull;
+  __device__ int64_t row(unsigned r) const {
+    const unsigned n = (unsigned)nact;
+    return rows ? (int64_t)rows[r % n] + (int64_t)(r / n) * rpf : (int64_t)r;
   }
-  __device__ int64_t sub_row(int64_t r) const {   // row of sub to subtract from listed row r, or -1
+  __device__ unsigned long long segmask(unsigned r) const {
+    return seg ? seg[rows ? r % (unsigned)nact : r % (unsigned)rpf] : ~0ull;
+  }
+  __device__ int64_t sub_row(unsigned r) const {   // row of sub to subtract from listed row r, or -1
     if (!sub) return -1;
-    const int64_t f = rows ? r / nact : r / rpf;
-    const int64_t w = rows ? (int64_t)rows[r % nact] : r % rpf;
+    const int64_t f = r / (unsigned)(rows ? nact : rpf);
+    const int64_t w = rows ? (int64_t)rows[r % (unsigned)nact] : r % (unsigned)rpf;
     return (f >= sub_f0 && f < sub_f0 + nsub) ? (f - sub_f0) * rpf + w : -1;
   }
 };
@@ -119,17 +122,25 @@ template <typename T> int fft_x_rpb_max(int nx);
 template <typename T> int fft_line_w_max(int n, int plan = 0);
 // radix plans of the single-field line passes of length n (1 or 2; plan 1 halves the elements per thread)
 template <typename T> int fft_line_plans(int n);
+// Twiddle tables of the x passes: the plain one (exp(-2 pi i m / nx), for the even/odd split) and that of
+// the transform in the order its stages read it, which fft_x_table fills into dst (fft_x_table_len values)
+template <typename T> struct TwX {
+  const cplx<T>* base = nullptr;
+  const cplx<T>* x = nullptr;
+};
+template <typename T> size_t fft_x_table_len(int nx);
+template <typename T> TwX<T> fft_x_table(int nx, const cplx<T>* twx, cplx<T>* dst, hipStream_t s);
 // x passes over nrows rows (with a row list: nrows = active rows per field x fields)
-// pitch: spectrum row pitch in complex values (0: nx/2 + 1)
+// pitch: spectrum row pitch in complex values
 template <typename T>
-void fft_x_r2c(const T* in, cplx<T>* out, int nx, int64_t nrows, const cplx<T>* tw_x, hipStream_t s, int rpb = 0,
-               const RowList& rl = RowList(), int64_t pitch = 0);
+void fft_x_r2c(const T* in, cplx<T>* out, int nx, int64_t nrows, const TwX<T>& tw, hipStream_t s, int rpb,
+               const RowList& rl, int64_t pitch);
 // the double forward x pass reading float rows (widened on load)
-void fft_x_r2c_widen(const float* in, cplx<double>* out, int nx, int64_t nrows, const cplx<double>* tw_x,
-                     hipStream_t s, int rpb = 0, const RowList& rl = RowList(), int64_t pitch = 0);
+void fft_x_r2c_widen(const float* in, cplx<double>* out, int nx, int64_t nrows, const TwX<double>& tw, hipStream_t s,
+                     int rpb, const RowList& rl, int64_t pitch);
 template <typename T>
-void fft_x_c2r(const cplx<T>* in, T* out, int nx, int64_t nrows, const cplx<T>* tw_x, hipStream_t s, int rpb = 0,
-               const RowList& rl = RowList(), int64_t pitch = 0);
+void fft_x_c2r(const cplx<T>* in, T* out, int nx, int64_t nrows, const TwX<T>& tw, hipStream_t s, int rpb,
+               const RowList& rl, int64_t pitch);
 // in-place strided C2C pass: line l starts at (l / inner) * outer + (l % inner), element stride es;
 // lines with l % inner >= vinner are padding and skipped (vinner 0: none)
 template <typename T>

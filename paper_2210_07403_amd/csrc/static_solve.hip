@@ -96,7 +96,7 @@ template <typename T> Layout layout(int dim, const int* n, int nf, int64_t nspec
     off += align256(sizeof(T) * (size_t)len);
   }
   lo.stages = off;
-  if (dim == 2) off += align256(sizeof(cplx<T>) * fft2_table_len<T>(n[0], n[1]));
+  off += align256(sizeof(cplx<T>) * (dim == 2 ? fft2_table_len<T>(n[0], n[1]) : fft_x_table_len<T>(n[0])));
   lo.spec = off;
   off += align256(sizeof(cplx<T>) * (size_t)nspec * (size_t)nf);
   lo.total = off;
@@ -172,11 +172,12 @@ template <typename T> void solve_t(const ibdl_config_t& c, const T* rhs, T* u) {
   const int64_t rpf = ntot / n[0];
   RowList rl;
   rl.rpf = rpf;
-  fft_x_r2c<T>(rhs, spec, n[0], rpf, tw[0], st, 0, rl, nxp);
+  const TwX<T> twx = fft_x_table<T>(n[0], tw[0], (cplx<T>*)(base + lo.stages), st);
+  fft_x_r2c<T>(rhs, spec, n[0], rpf, twx, st, 0, rl, nxp);
   fft_strided<T>(spec, n[1], (int64_t)n[2] * nxp, nxp, (int64_t)nxp * n[1], nxp, false, tw[1], st, 0, RowMask(), nxh);
   fft_fused_last<T>(spec, n[2], nspec / n[2], 1, md, tw[2], st, 1, 0, 0, RowMask());
   fft_strided<T>(spec, n[1], (int64_t)n[2] * nxp, nxp, (int64_t)nxp * n[1], nxp, true, tw[1], st, 0, RowMask(), nxh);
-  fft_x_c2r<T>(spec, u, n[0], rpf, tw[0], st, 0, rl, nxp);
+  fft_x_c2r<T>(spec, u, n[0], rpf, twx, st, 0, rl, nxp);
 }
 
 bool pow2_ok(int64_t v) { return v >= 16 && v <= 1024 && (v & (v - 1)) == 0; }
