@@ -69,89 +69,156 @@ __device__ __forceinline__ int tile_id(const MarkerGeom& g, const int (&j0)[3], 
   return (tz * g.ntile[1] + ty) * g.ntile[0] + tx;
 }
 
-__global__ void k_marker_setup(MarkerGeom g, int kernel, int64_t n_ib, const double* __restrict__ X,
-                               int* __restrict__ s, double* __restrict__ f, double* __restrict__ wt,
-                               int* __restrict__ tile_count, const int* __restrict__ pid) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_ib) return;
-  int si[3] = {0, 0, 0};
-  for (int d = 0; d < g.dim; ++d) {
-    const double n = (double)g.n[d];
-    double xi = (X[i * g.dim + d] - g.origin[d]) / g.h;
-    xi = xi - n * floor(xi / n);                 // wrap into [0, n)
-    if (!(xi >= 0.0 && xi < n)) xi = 0.0;        // non-finite input: keep indices in range
-    const double b = floor(xi);
-    int bi = (int)b;
-    if (bi >= g.n[d]) bi = g.n[d] - 1;
-    f[i * 3 + d] = xi - (double)bi;
-    si[d] = (bi - 2 + 2 * g.n[d]) & (g.n[d] - 1);
-    s[i * 3 + d] = si[d];
-  }
-  for (int d = g.dim; d < 3; ++d) {
-    s[i * 3 + d] = 0;
-    f[i * 3 + d] = 0.0;
-  }
-  // kernel weights W[t] = phi((s + t) - X/h) on the 6-node window and centred differences
-  // G[t] = (W[t+1] - W[t-1]) / 2h (W = 0 outside the window), per axis; unit weight off-dimension
-  for (int d = 0; d < 3; ++d) {
+// Four lanes per marker: lane d < 3 places the marker along axis d and evaluates that axis's weights (a
+// chain which one thread per marker ran three times over on a few waves: 31 us at 18,500 markers in 3-D,
+// now 21); all four then count the tiles.
+__global__ __launch_bounds__(256) void k_marker_setup(MarkerGeom g, int kernel, int64_t n_ib,
+                                                      const double* __restrict__ X, int* __restrict__ s,
+                                                      double* __restrict__ f, double* __restrict__ wt,
+                                                      int* __restrict__ tile_count, const int* __restrict__ pid) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = e >> 2;
+  const int d = (int)(e & 3);
+  const bool live = i < n_ib;
+  int sd = 0;
+  if (live && d < 3) {
+    double fr = 0.0;
+    if (d < g.dim) {
+      const double n = (double)g.n[d];
+      double xi = (X[i * g.dim + d] - g.origin[d]) / g.h;
+      xi = xi - n * floor(xi / n);                 // wrap into [0, n)
+      if (!(xi >= 0.0 && xi < n)) xi = 0.0;        // non-finite input: keep indices in range
+      int bi = (int)floor(xi);
+      if (bi >= g.n[d]) bi = g.n[d] - 1;
+      fr = xi - (double)bi;
+      sd = (bi - 2 + 2 * g.n[d]) & (g.n[d] - 1);
+    }
+    s[i * 3 + d] = sd;
+    f[i * 3 + d] = fr;
+    // kernel weights W[t] = phi((s + t) - X/h) on the 6-node window and centred differences
+    // G[t] = (W[t+1] - W[t-1]) / 2h (W = 0 outside the window), per axis; unit weight off-dimension
     double w[8];
     w[0] = w[7] = 0.0;
-    for (int t = 0; t < 6; ++t)
-      w[t + 1] = d < g.dim ? phi_eval(kernel, (double)(t - 2) - f[i * 3 + d]) : (t == 2 ? 1.0 : 0.0);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) w[t + 1] = d < g.dim ? phi_eval(kernel, (double)(t - 2) - fr) : (t == 2 ? 1.0 : 0.0);
     double* row = wt + (i * 3 + d) * 12;
+#pragma unroll
     for (int t = 0; t < 6; ++t) {
       row[t] = w[t + 1];
       row[6 + t] = d < g.dim ? (w[t + 2] - w[t]) * (0.5 / g.h) : 0.0;
     }
   }
+  const int l0 = (int)(threadIdx.x & 60);
+  const int si[3] = {__shfl(sd, l0), __shfl(sd, l0 + 1), __shfl(sd, l0 + 2)};
+  if (!live) return;
   int j0[3], nt[3];
   marker_tiles(g, si, j0, nt);
   const int toff = pid ? pid[i] * g.ntile[0] * g.ntile[1] * g.ntile[2] : 0;   // tiles of problem pid[i]
-  for (int a = 0; a < nt[2]; ++a)
-    for (int b = 0; b < nt[1]; ++b)
-      for (int c = 0; c < nt[0]; ++c) atomicAdd(&tile_count[toff + tile_id(g, j0, a, b, c)], 1);
+  for (int q = d; q < nt[0] * nt[1] * nt[2]; q += 4)
+    atomicAdd(&tile_count[toff + tile_id(g, j0, q / (nt[0] * nt[1]), q / nt[0] % nt[1], q % nt[0])], 1);
 }
 
-__global__ void k_fill(MarkerGeom g, int64_t n_ib, const int* __restrict__ s, const int* __restrict__ off,
-                       int* __restrict__ cur, int* __restrict__ list, const int* __restrict__ pid) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// eight lanes per marker, one tile each (an atomic's round trip per tile, not one after another: 23 us at
+// 18,500 markers in 3-D, now 19)
+__global__ __launch_bounds__(256) void k_fill(MarkerGeom g, int64_t n_ib, const int* __restrict__ s,
+                                              const int* __restrict__ off, int* __restrict__ cur,
+                                              int* __restrict__ list, const int* __restrict__ pid) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = e >> 3;
   if (i >= n_ib) return;
-  int si[3] = {s[i * 3], s[i * 3 + 1], s[i * 3 + 2]};
+  const int si[3] = {s[i * 3], s[i * 3 + 1], s[i * 3 + 2]};
   int j0[3], nt[3];
   marker_tiles(g, si, j0, nt);
   const int toff = pid ? pid[i] * g.ntile[0] * g.ntile[1] * g.ntile[2] : 0;
-  for (int a = 0; a < nt[2]; ++a)
-    for (int b = 0; b < nt[1]; ++b)
-      for (int c = 0; c < nt[0]; ++c) {
-        const int id = toff + tile_id(g, j0, a, b, c);
-        const int pos = off[id] + atomicAdd(&cur[id], 1);
-        list[pos] = (int)i;
-      }
+  for (int q = (int)(e & 7); q < nt[0] * nt[1] * nt[2]; q += 8) {
+    const int id = toff + tile_id(g, j0, q / (nt[0] * nt[1]), q / nt[0] % nt[1], q % nt[0]);
+    const int pos = off[id] + atomicAdd(&cur[id], 1);
+    list[pos] = (int)i;
+  }
 }
+
+// Exclusive prefix of v over a workgroup of 1024 threads; tot: the workgroup's sum.  Sixteen waves, each
+// by shuffles, and their sums through s_w[16]: two barriers, the first of which also ends the last use.
+template <typename V> __device__ __forceinline__ V block_scan(V v, V* s_w, V& tot) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  V x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const V t = __shfl_up(x, o);
+    if (lane >= o) x += t;
+  }
+  __syncthreads();
+  if (lane == 63) s_w[wave] = x;
+  __syncthreads();
+  V before = 0;
+  tot = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const V t = s_w[w];
+    before += w < wave ? t : 0;
+    tot += t;
+  }
+  return before + x - v;
+}
+
+constexpr int kScanItems = 4;   // consecutive items per thread and trip of the one-block scans
 
 // exclusive scan of cnt[0..n) into off[0..n]; one block of 1024 threads
 __global__ __launch_bounds__(1024) void k_scan(const int* __restrict__ cnt, int* __restrict__ off, int n) {
-  __shared__ int buf[1024];
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int base = 0; base < n; base += 1024) {
-    const int i = base + threadIdx.x;
-    const int v = i < n ? cnt[i] : 0;
-    buf[threadIdx.x] = v;
-    __syncthreads();
-    for (int st = 1; st < 1024; st <<= 1) {
-      const int t = threadIdx.x >= st ? buf[threadIdx.x - st] : 0;
-      __syncthreads();
-      buf[threadIdx.x] += t;
-      __syncthreads();
+  __shared__ int s_w[16];
+  int carry = 0;
+  for (int base = 0; base < n; base += 1024 * kScanItems) {
+    const int i0 = base + (int)threadIdx.x * kScanItems;
+    int v[kScanItems], sum = 0, tot;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) sum += v[k] = i0 + k < n ? cnt[i0 + k] : 0;
+    int o = carry + block_scan(sum, s_w, tot);
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+      if (i0 + k < n) off[i0 + k] = o;
+      o += v[k];
     }
-    if (i < n) off[i] = carry + buf[threadIdx.x] - v;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry += buf[1023];
-    __syncthreads();
+    carry += tot;
   }
   if (threadIdx.x == 0) off[n] = carry;
+}
+
+// The tile lists' offsets (exclusive scan of the candidate counts) and the tiles with at least one
+// candidate, in increasing order, with their list ranges; foff[n]: their number; cur cleared for k_fill.
+// One block of 1024 threads, both scans in one 64-bit sum (number of busy tiles above, candidates below):
+// 4,096 tiles in 5 us, where a kernel for the flags, two scans with two barriers a doubling, the list and
+// a clearing took 26.
+__global__ __launch_bounds__(1024) void k_bin_scan(const int* __restrict__ cnt, int* __restrict__ off,
+                                                   int* __restrict__ foff, int4* __restrict__ busy,
+                                                   int* __restrict__ cur, int n) {
+  __shared__ unsigned long long s_w[16];
+  unsigned long long carry = 0;
+  for (int base = 0; base < n; base += 1024 * kScanItems) {
+    const int i0 = base + (int)threadIdx.x * kScanItems;
+    int v[kScanItems];
+    unsigned long long sum = 0, tot;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+      v[k] = i0 + k < n ? cnt[i0 + k] : 0;
+      sum += ((unsigned long long)(v[k] > 0) << 32) + (unsigned)v[k];
+    }
+    const unsigned long long o = carry + block_scan(sum, s_w, tot);
+    int fo = (int)(o >> 32), co = (int)(o & 0xffffffffu);
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+      if (i0 + k < n) {
+        off[i0 + k] = co;
+        cur[i0 + k] = 0;
+        if (v[k] > 0) busy[fo++] = make_int4(i0 + k, co, co + v[k], 0);
+      }
+      co += v[k];
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) {
+    off[n] = (int)(carry & 0xffffffffu);
+    foff[n] = (int)(carry >> 32);
+  }
 }
 
 // per-precision weight table: (W[t], G[t]) pairs, t < 6, padded with zeros at t = 6, 7
@@ -185,21 +252,11 @@ __global__ void k_row_segments(MarkerGeom g, const int* __restrict__ tile_off, c
   seg[e] = m;
 }
 
-// ids of the tiles with at least one candidate, in increasing order (off is the exclusive scan of
-// the 0/1 flags computed by k_busy_flags)
-__global__ void k_busy_flags(const int* __restrict__ cnt, int* __restrict__ flag, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) flag[i] = cnt[i] > 0 ? 1 : 0;
-}
-__global__ void k_busy_ids(const int* __restrict__ cnt, const int* __restrict__ foff, const int* __restrict__ off,
-                           int4* __restrict__ busy, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && cnt[i] > 0) busy[foff[i]] = make_int4(i, off[i], off[i + 1], 0);
-}
-
 // The busy tiles in decreasing order of their candidate count (ties by tile id): the spread's
 // workgroups then start with the longest tiles and end with the shortest, which evens out the
-// CUs' finishing times.  Rank sort; *nptr = number of busy tiles.
+// CUs' finishing times.  Rank sort; *nptr = number of busy tiles.  A workgroup ranks kOrder tiles: its
+// threads count over the tiles' list side by side, each against all kOrder (one thread per tile, the list
+// staged in LDS: 42 us at 784 tiles, a serial chain of 784 reads on four workgroups; now 7).
 // groups: the tiles (in tile-id order, i.e. in slabs) are first cut into the 8 XCD-contiguous
 // ranges of xcd_chunk, and each range is ordered on its own, so that a spread reading entry
 // xcd_chunk(b, n) gives each XCD one slab of neighbouring tiles, longest first; their markers'
@@ -208,48 +265,71 @@ __device__ __forceinline__ int xcd_range_lo(int x, int n) {   // first index of 
   const int q = n / 8, r = n % 8;
   return x * q + (x < r ? x : r);
 }
+constexpr int kOrder = 8;
 __global__ __launch_bounds__(256) void k_busy_order(const int4* __restrict__ in, const int* __restrict__ nptr,
                                                     int4* __restrict__ out, int groups) {
-  __shared__ int sc[256];
+  __shared__ int s_rk[4][kOrder];
   const int n = *nptr;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int4 v = i < n ? in[i] : make_int4(0, 0, 0, 0);
-  const int c = v.z - v.y;
-  int lo = 0, hi = n;
-  if (groups) {
-    const int q = n / 8, r = n % 8;
-    const int x = i < r * (q + 1) ? i / (q + 1) : r + (q > 0 ? (i - r * (q + 1)) / q : 0);
-    lo = xcd_range_lo(x, n);
-    hi = xcd_range_lo(x + 1, n);
-  }
-  int rk = 0;
-  for (int k0 = 0; k0 < n; k0 += 256) {
-    __syncthreads();
-    if (k0 + (int)threadIdx.x < n) {
-      const int4 u = in[k0 + threadIdx.x];
-      sc[threadIdx.x] = u.z - u.y;
-    }
-    __syncthreads();
-    const int kn = n - k0 < 256 ? n - k0 : 256;
-    for (int k = 0; k < kn; ++k) {
-      const int ck = sc[k];
-      const int kk = k0 + k;
-      rk += (kk >= lo && kk < hi) && ((ck > c) || (ck == c && kk < i));
+  const int i0 = (int)blockIdx.x * kOrder;
+  if (i0 >= n) return;
+  int c[kOrder], lo[kOrder], hi[kOrder], rk[kOrder];
+#pragma unroll
+  for (int e = 0; e < kOrder; ++e) {
+    const int i = i0 + e < n ? i0 + e : n - 1;
+    const int4 v = in[i];
+    c[e] = v.z - v.y;
+    lo[e] = 0;
+    hi[e] = n;
+    rk[e] = 0;
+    if (groups) {
+      const int q = n / 8, r = n % 8;
+      const int x = i < r * (q + 1) ? i / (q + 1) : r + (q > 0 ? (i - r * (q + 1)) / q : 0);
+      lo[e] = xcd_range_lo(x, n);
+      hi[e] = xcd_range_lo(x + 1, n);
     }
   }
-  if (i < n) out[lo + rk] = v;
+  for (int k = lo[0] + (int)threadIdx.x; k < hi[kOrder - 1]; k += 256) {
+    const int4 u = in[k];
+    const int ck = u.z - u.y;
+#pragma unroll
+    for (int e = 0; e < kOrder; ++e)
+      rk[e] += (k >= lo[e] && k < hi[e]) && ((ck > c[e]) || (ck == c[e] && k < i0 + e));
+  }
+#pragma unroll
+  for (int e = 0; e < kOrder; ++e) {
+    for (int o = 32; o > 0; o >>= 1) rk[e] += __shfl_xor(rk[e], o);
+    if ((threadIdx.x & 63) == 0) s_rk[threadIdx.x >> 6][e] = rk[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kOrder; ++e)
+    if ((int)threadIdx.x == e && i0 + e < n)
+      out[lo[e] + s_rk[0][e] + s_rk[1][e] + s_rk[2][e] + s_rk[3][e]] = in[i0 + e];
 }
 
-// sort each tile's marker list ascending (rank sort; marker indices in a tile are unique)
+// Sort each tile's marker list ascending (rank sort; marker indices in a tile are unique).  The list goes
+// through LDS 256 entries at a time, four a read: the ranks come from broadcasts, not from memory (4,096
+// tiles, 784 of them busy: 26 us with one load from memory per compared entry, now 15).
 __global__ __launch_bounds__(256) void k_sort_tiles(const int* __restrict__ off, const int* __restrict__ tmp,
                                                     int* __restrict__ list) {
-  const int t = blockIdx.x;
-  const int b = off[t], e = off[t + 1], L = e - b;
-  for (int a = threadIdx.x; a < L; a += blockDim.x) {
-    const int v = tmp[b + a];
+  __shared__ int4 s_v[64];
+  const int b = off[blockIdx.x], L = off[blockIdx.x + 1] - b;
+  for (int a0 = 0; a0 < L; a0 += 256) {
+    const int a = a0 + (int)threadIdx.x;
+    const int v = a < L ? tmp[b + a] : 0;
     int r = 0;
-    for (int k = 0; k < L; ++k) r += tmp[b + k] < v;
-    list[b + r] = v;
+    for (int k0 = 0; k0 < L; k0 += 256) {
+      const int k = k0 + (int)threadIdx.x;
+      __syncthreads();
+      reinterpret_cast<int*>(s_v)[threadIdx.x] = k < L ? tmp[b + k] : 0x7fffffff;
+      __syncthreads();
+      const int kn = ((L - k0 < 256 ? L - k0 : 256) + 3) / 4;
+      for (int q = 0; q < kn; ++q) {
+        const int4 u = s_v[q];
+        r += (u.x < v) + (u.y < v) + (u.z < v) + (u.w < v);
+      }
+    }
+    if (a < L) list[b + r] = v;
   }
 }
 
@@ -1052,14 +1132,35 @@ __global__ __launch_bounds__(256) void k_rows_mark(MarkerGeom g, int64_t n_ib, c
   }
 }
 
-// per-plane row counts, the (lo, hi) pairs used by the y-pass masks, and then the row list
-__global__ void k_rows_count(const int* __restrict__ lo, const int* __restrict__ hi, int nplanes,
-                             int* __restrict__ cnt, int2* __restrict__ lim) {
-  const int z = blockIdx.x * blockDim.x + threadIdx.x;
-  if (z >= nplanes) return;
-  const bool any = hi[z] >= lo[z];
-  cnt[z] = any ? hi[z] - lo[z] + 1 : 0;
-  lim[z] = any ? make_int2(lo[z], hi[z]) : make_int2(1, 0);
+// Per-plane row counts, their scan, and the (lo, hi) pairs used by the y-pass masks; one block of 1024
+// threads.  host (pinned): the number of busy tiles, of active rows, and the pairs, for the caller to
+// read after a wait on the stream.
+__global__ __launch_bounds__(1024) void k_rows_count(const int* __restrict__ lo, const int* __restrict__ hi, int nplanes,
+                                                     int* __restrict__ cnt, int* __restrict__ off, int2* __restrict__ lim,
+                                                     const int* __restrict__ nbusy, int* __restrict__ host) {
+  __shared__ int s_w[16];
+  int carry = 0;
+  for (int base = 0; base < nplanes; base += 1024) {
+    const int z = base + (int)threadIdx.x;
+    int2 l = make_int2(1, 0);
+    if (z < nplanes && hi[z] >= lo[z]) l = make_int2(lo[z], hi[z]);
+    const int c = l.y - l.x + 1;
+    int tot;
+    const int o = carry + block_scan(c, s_w, tot);
+    if (z < nplanes) {
+      cnt[z] = c;
+      off[z] = o;
+      lim[z] = l;
+      host[2 + 2 * z] = l.x;
+      host[3 + 2 * z] = l.y;
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) {
+    off[nplanes] = carry;
+    host[0] = *nbusy;
+    host[1] = carry;
+  }
 }
 
 __global__ void k_rows_list(const int* __restrict__ lo, const int* __restrict__ cnt, const int* __restrict__ off,
@@ -1071,49 +1172,91 @@ __global__ void k_rows_list(const int* __restrict__ lo, const int* __restrict__ 
 
 
 // ------------------------------------------------------------------ kernel-derivative gather
-// One thread per marker over its K^D window (K = 4: taps 1..4 of the 6-node window; K = 6: all),
-// in double: out[i][e] = sum_x F_i(x) (-phi'(r_e)/h) prod_{d != e} phi(r_d), r_d = (x_d - X_id)/h.
+// Sixteen lanes per marker over its K^D window (K = 4: taps 1..4 of the 6-node window; K = 6: all), in
+// double: out[i][e] = sum_x F_i(x) (-phi'(r_e)/h) prod_{d != e} phi(r_d), r_d = (x_d - X_id)/h.  A lane
+// takes a row of the window (in 2-D a node), its weights staged in LDS by the whole block.  Bound by the
+// latency of scattered loads, so lanes: with one thread per marker the 64 nodes x fields of a window were
+// one chain on a few waves (18,500 markers, 3-D, FP64: 94 us on 73 workgroups, now 14; 1,024 markers,
+// 2-D, 5 fields: 41 us, now 8).
+constexpr int kGatherLanes = 16;
 template <typename T, int D, int K>
 __global__ __launch_bounds__(256) void k_gather_dx(GatherArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n_ib) return;
+  constexpr int LN = kGatherLanes, MPB = 256 / LN, T0 = (K == 4) ? 1 : 0, NF = 8;
+  __shared__ double s_w[MPB][3][K], s_dw[MPB][3][K], s_cf[MPB][NF];
+  __shared__ int s_ix[MPB][3][K];
   const MarkerGeom& g = a.g;
-  constexpr int T0 = (K == 4) ? 1 : 0;
-  double w[3][K], dw[3][K];
-  int ix[3][K];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const int s = a.s[i * 3 + d];
-    const double fr = a.f[i * 3 + d];
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-      const double r = (double)(t + T0 - 2) - fr;
-      w[d][t] = d < D ? phi_eval(a.kernel, r) : (t == 0 ? 1.0 : 0.0);
-      dw[d][t] = d < D ? -dphi_eval(a.kernel, r) / g.h : 0.0;
-      ix[d][t] = d < D ? ((s + t + T0) & (g.n[d] - 1)) : 0;
+  const int64_t i0 = (int64_t)blockIdx.x * MPB;
+  for (int t = threadIdx.x; t < MPB * 3 * K; t += 256) {
+    const int m = t / (3 * K), d = t / K % 3, k = t % K;
+    const int64_t i = i0 + m;
+    double w = (D == 2 && d == 2) ? 1.0 : 0.0, dw = 0.0;
+    int ix = 0;
+    if (d < D && i < a.n_ib) {
+      const double r = (double)(k + T0 - 2) - a.f[i * 3 + d];
+      w = phi_eval(a.kernel, r);
+      dw = -dphi_eval(a.kernel, r) / g.h;
+      ix = (a.s[i * 3 + d] + k + T0) & (g.n[d] - 1);
     }
+    s_w[m][d][k] = w;
+    s_dw[m][d][k] = dw;
+    s_ix[m][d][k] = ix;
   }
-  double cf[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) cf[k] = k < a.nfield ? a.coef[i * a.nfield + k] : 0.0;
+  if (threadIdx.x < MPB * NF) {
+    const int m = threadIdx.x / NF, k = threadIdx.x % NF;
+    s_cf[m][k] = (k < a.nfield && i0 + m < a.n_ib) ? a.coef[(i0 + m) * a.nfield + k] : 0.0;
+  }
+  __syncthreads();
+  const int m = threadIdx.x / LN, lane = threadIdx.x % LN;
+  constexpr int NX = D == 3 ? K : 1;   // nodes of a lane's item
   double acc[3] = {0.0, 0.0, 0.0};
-  constexpr int KZ = (D == 3) ? K : 1;
-  for (int tz = 0; tz < KZ; ++tz) {
-    for (int ty = 0; ty < K; ++ty) {
-      const int64_t row = ((int64_t)(D == 3 ? ix[2][tz] : 0) * g.n[1] + ix[1][ty]) * g.n[0];
-      const double wz = D == 3 ? w[2][tz] : 1.0, dwz = D == 3 ? dw[2][tz] : 0.0;
-      for (int tx = 0; tx < K; ++tx) {
-        const int64_t idx = row + ix[0][tx];
-        double F = 0.0;
-        for (int k = 0; k < a.nfield; ++k) F += cf[k] * (double)static_cast<const T*>(a.field[k])[idx];
-        acc[0] += F * dw[0][tx] * w[1][ty] * wz;
-        acc[1] += F * w[0][tx] * dw[1][ty] * wz;
-        if (D == 3) acc[2] += F * w[0][tx] * w[1][ty] * dwz;
+  if (i0 + m < a.n_ib) {
+    for (int q = lane; q < K * K; q += LN) {
+      const int t1 = q / K, t0 = q % K;
+      // item q: the x row at (y, z) = (t0, t1) in 3-D, the node (x, y) = (t0, t1) in 2-D
+      const int64_t row = D == 3 ? ((int64_t)s_ix[m][2][t1] * g.n[1] + s_ix[m][1][t0]) * g.n[0]
+                                 : (int64_t)s_ix[m][1][t1] * g.n[0] + s_ix[m][0][t0];
+      double F[NX];
+#pragma unroll
+      for (int x = 0; x < NX; ++x) F[x] = 0.0;
+      for (int k0 = 0; k0 < a.nfield; k0 += 4) {
+        T v[4][NX];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {   // fields beyond the last: loaded again and not used
+          const T* fld = static_cast<const T*>(a.field[k0 + k < a.nfield ? k0 + k : 0]) + row;
+#pragma unroll
+          for (int x = 0; x < NX; ++x) v[k][x] = fld[D == 3 ? s_ix[m][0][x] : 0];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (k0 + k >= a.nfield) break;
+#pragma unroll
+          for (int x = 0; x < NX; ++x) F[x] += s_cf[m][k0 + k] * (double)v[k][x];
+        }
+      }
+      if constexpr (D == 3) {
+        double fw = 0.0, fd = 0.0;
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+          fw += F[x] * s_w[m][0][x];
+          fd += F[x] * s_dw[m][0][x];
+        }
+        acc[0] += fd * s_w[m][1][t0] * s_w[m][2][t1];
+        acc[1] += fw * s_dw[m][1][t0] * s_w[m][2][t1];
+        acc[2] += fw * s_w[m][1][t0] * s_dw[m][2][t1];
+      } else {
+        acc[0] += F[0] * s_dw[m][0][t0] * s_w[m][1][t1];
+        acc[1] += F[0] * s_w[m][0][t0] * s_dw[m][1][t1];
       }
     }
   }
 #pragma unroll
-  for (int e = 0; e < D; ++e) a.out[i * D + e] = acc[e];
+  for (int e = 0; e < D; ++e) {
+    for (int o = LN / 2; o > 0; o >>= 1) acc[e] += __shfl_xor(acc[e], o);
+  }
+  if (i0 + m < a.n_ib && lane == 0) {
+#pragma unroll
+    for (int e = 0; e < D; ++e) a.out[(i0 + m) * D + e] = acc[e];
+  }
 }
 
 // ------------------------------------------------------------------ grid elementwise
@@ -1188,7 +1331,7 @@ void markers_setup(const MarkerGeom& g, int kernel, int64_t n_ib, const double* 
   const int64_t ntile = (int64_t)g.ntile[0] * g.ntile[1] * g.ntile[2] * nprob;
   IBDL_HIP(hipMemsetAsync(tile_count, 0, sizeof(int) * ntile, st));
   if (n_ib > 0)
-    hipLaunchKernelGGL(k_marker_setup, dim3((unsigned)((n_ib + 255) / 256)), dim3(256), 0, st, g, kernel, n_ib, X,
+    hipLaunchKernelGGL(k_marker_setup, dim3((unsigned)((4 * n_ib + 255) / 256)), dim3(256), 0, st, g, kernel, n_ib, X,
                        s, f, wt, tile_count, pid);
   IBDL_LAUNCH_CHECK();
 }
@@ -1223,21 +1366,13 @@ void markers_bin(const MarkerGeom& g, int64_t n_ib, const int* s, const int* til
                  int* tile_cur, int* list, int* list_tmp, int4* busy, int4* busy_tmp, int* busy_off, hipStream_t st,
                  const int* pid, int nprob, int xcd_groups) {
   const int ntile = g.ntile[0] * g.ntile[1] * g.ntile[2] * nprob;
-  hipLaunchKernelGGL(k_busy_flags, dim3((ntile + 255) / 256), dim3(256), 0, st, tile_count, tile_cur, ntile);
+  hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(1024), 0, st, tile_count, tile_off, busy_off, busy_tmp, tile_cur, ntile);
   IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, tile_cur, busy_off, ntile);
+  hipLaunchKernelGGL(k_busy_order, dim3((ntile + kOrder - 1) / kOrder), dim3(256), 0, st, busy_tmp, busy_off + ntile,
+                     busy, xcd_groups);
   IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, tile_count, tile_off, ntile);
-  IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_busy_ids, dim3((ntile + 255) / 256), dim3(256), 0, st, tile_count, busy_off, tile_off,
-                     busy_tmp, ntile);
-  IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_busy_order, dim3((ntile + 255) / 256), dim3(256), 0, st, busy_tmp, busy_off + ntile, busy,
-                     xcd_groups);
-  IBDL_LAUNCH_CHECK();
-  IBDL_HIP(hipMemsetAsync(tile_cur, 0, sizeof(int) * ntile, st));
   if (n_ib > 0)
-    hipLaunchKernelGGL(k_fill, dim3((unsigned)((n_ib + 255) / 256)), dim3(256), 0, st, g, n_ib, s, tile_off,
+    hipLaunchKernelGGL(k_fill, dim3((unsigned)((8 * n_ib + 255) / 256)), dim3(256), 0, st, g, n_ib, s, tile_off,
                        tile_cur, list_tmp, pid);
   IBDL_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_sort_tiles, dim3(ntile), dim3(256), 0, st, tile_off, list_tmp, list);
@@ -1258,7 +1393,7 @@ void markers_row_segments(const MarkerGeom& g, const int* tile_off, const int* r
 }
 
 void markers_rows(const MarkerGeom& g, int64_t n_ib, const int* s, int* lo, int* hi, int* cnt, int* off, int2* lim,
-                  int* rows, hipStream_t st) {
+                  int* rows, const int* nbusy, int* host, hipStream_t st) {
   const int nplanes = g.dim == 3 ? g.n[2] : 1;
   hipLaunchKernelGGL(k_rows_init, dim3((nplanes + 255) / 256), dim3(256), 0, st, lo, hi, nplanes, g.n[1]);
   IBDL_LAUNCH_CHECK();
@@ -1266,9 +1401,7 @@ void markers_rows(const MarkerGeom& g, int64_t n_ib, const int* s, int* lo, int*
     hipLaunchKernelGGL(k_rows_mark, dim3((unsigned)((n_ib + 255) / 256)), dim3(256), sizeof(int) * 2 * nplanes, st,
                        g, n_ib, s, lo, hi);
   IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_rows_count, dim3((nplanes + 255) / 256), dim3(256), 0, st, lo, hi, nplanes, cnt, lim);
-  IBDL_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, cnt, off, nplanes);
+  hipLaunchKernelGGL(k_rows_count, dim3(1), dim3(1024), 0, st, lo, hi, nplanes, cnt, off, lim, nbusy, host);
   IBDL_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_rows_list, dim3(nplanes), dim3(256), 0, st, lo, cnt, off, nplanes, g.n[1], rows);
   IBDL_LAUNCH_CHECK();
@@ -1389,7 +1522,7 @@ template <typename T>
 void gather_dx(const GatherArgs& a, hipStream_t st) {
   if (a.n_ib == 0) return;
   if (a.nfield < 1 || a.nfield > 8) throw Error(-1, "gather_dx: 1..8 fields");
-  const dim3 grid((unsigned)((a.n_ib + 255) / 256));
+  const dim3 grid((unsigned)((a.n_ib * kGatherLanes + 255) / 256));
   const bool six = a.kernel == KID_BSPLINE6;
   if (a.g.dim == 2) {
     if (six) hipLaunchKernelGGL((k_gather_dx<T, 2, 6>), grid, dim3(256), 0, st, a);

@@ -110,6 +110,7 @@ struct ibdl_s {
   double* vb = nullptr;       // right-hand side
   double* vr = nullptr;       // residual scratch
   double* hostbuf = nullptr;  // pinned host scratch (1024 doubles)
+  int* minfo = nullptr;       // pinned: what markers_rows reports to the host
   // host-mapped coherent memory for the per-iteration Krylov state (two records, GM_REC): the GPU
   // writes it and the host polls it (no copy-engine transfer, no stream-sync wake-up)
   double* hmap = nullptr;
@@ -197,6 +198,7 @@ struct ibdl_s {
     drop_graphs();
     if (hostbuf) (void)hipHostFree(hostbuf);
     if (hmap) (void)hipHostFree(hmap);
+    if (minfo) (void)hipHostFree(minfo);
     for (auto& p : pending) {
       (void)hipEventDestroy(p.second.first);
       (void)hipEventDestroy(p.second.second);
@@ -1269,15 +1271,13 @@ void build_markers(ibdl_s* h) {
   markers_setup(h->geom, h->cfg.kernel, h->n_ib, h->X, h->s, h->f, h->wt, h->tile_count, h->st);
   markers_bin(h->geom, h->n_ib, h->s, h->tile_count, h->tile_off, h->tile_cur, h->list, h->list_tmp, h->busy,
               h->busy_tmp, h->busy_off, h->st, nullptr, 1, h->dim == 3 ? 1 : 0);
-  markers_rows(h->geom, h->n_ib, h->s, h->row_lo, h->row_hi, h->row_cnt, h->row_off, h->row_lim, h->rows, h->st);
   const int ntile = h->geom.ntile[0] * h->geom.ntile[1] * h->geom.ntile[2];
   const int nplanes = h->dim == 3 ? h->n[2] : 1;
-  int nb = 0, na = 0;
-  std::vector<int2> lim(nplanes);
-  IBDL_HIP(hipMemcpyAsync(&nb, h->busy_off + ntile, sizeof(int), hipMemcpyDeviceToHost, h->st));
-  IBDL_HIP(hipMemcpyAsync(&na, h->row_off + nplanes, sizeof(int), hipMemcpyDeviceToHost, h->st));
-  IBDL_HIP(hipMemcpyAsync(lim.data(), h->row_lim, sizeof(int2) * nplanes, hipMemcpyDeviceToHost, h->st));
+  markers_rows(h->geom, h->n_ib, h->s, h->row_lo, h->row_hi, h->row_cnt, h->row_off, h->row_lim, h->rows,
+               h->busy_off + ntile, h->minfo, h->st);
   IBDL_HIP(hipStreamSynchronize(h->st));
+  const int nb = h->minfo[0], na = h->minfo[1];
+  const int2* lim = reinterpret_cast<const int2*>(h->minfo + 2);
   h->nbusy = nb;
   h->nact = na;
   if (h->lofs) markers_list_offsets(h->geom, h->busy, nb, h->list, h->s, h->lofs, h->st);
@@ -1556,6 +1556,7 @@ ibdl_status_t ibdl_create(const ibdl_config_t* cfg, int64_t n_ib, const double* 
                            hipHostMallocMapped | hipHostMallocCoherent));
     IBDL_HIP(hipHostGetDevicePointer((void**)&h->hmap_dev, h->hmap, 0));
     memset(h->hmap, 0, sizeof(double) * kHmap);
+    IBDL_HIP(hipHostMalloc((void**)&h->minfo, sizeof(int) * (2 + 2 * nplanes), hipHostMallocMapped | hipHostMallocCoherent));
     IBDL_HIP(hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
     IBDL_HIP(hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming));
     IBDL_HIP(hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming));
