@@ -380,8 +380,9 @@ ibdl_status_t ibdl_launch_shape(ibdl_t h, int32_t* rows_per_block, int32_t* line
 
 /* GMRES and MINRES in ibdl_solve, ibdl_solve_refined, ibdl_backward and ibdl_ns_step replay each
  * operator apply from a HIP graph captured at the first apply (1) or launch its kernels directly
- * (0).  The default is 1 below 2^20 grid points, where an apply is shorter than its launches, and
- * 0 from there on.  Both give the same bits.  Disabling drops the captured graphs. */
+ * (0).  The default replays a graph up to 2^14 grid points, from the second solve with the same
+ * markers on, and launches directly otherwise: from there on the device, not the host, sets the
+ * pace.  Both give the same bits.  Disabling drops the captured graphs. */
 ibdl_status_t ibdl_set_graph(ibdl_t h, int32_t enable);
 
 /* Profiling: enable (1) or disable (0) per-stage timing with HIP events recorded on the handle's

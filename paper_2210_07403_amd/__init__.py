@@ -321,7 +321,8 @@ class Problem:
 
     def set_graph(self, enable=True):
         """Replay the Krylov solvers' operator applies from a captured HIP graph or launch them
-        directly (the default is the graph below 2^20 grid points)."""
+        directly (the default is the graph up to 2^14 grid points, from the second solve with the
+        same markers on)."""
         B.check(B.load().ibdl_set_graph(self._h, 1 if enable else 0), self._h)
 
     def set_timing(self, enable=True):

@@ -121,9 +121,11 @@ struct ibdl_s {
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
   double *gx = nullptr, *gy = nullptr;
-  bool use_graph = true;
+  enum { GRAPH_OFF, GRAPH_SECOND, GRAPH_ON } graph_mode = GRAPH_OFF;   // SECOND: from the second solve with the same markers
+  bool graph_seen[2] = {false, false};   // GRAPH_SECOND: a solve has run with these markers
   void drop_graphs() {
     for (int k = 0; k < 2; ++k) {
+      graph_seen[k] = false;
       if (gexec[k]) (void)hipGraphExecDestroy(gexec[k]);
       if (graph[k]) (void)hipGraphDestroy(graph[k]);
       gexec[k] = nullptr;
@@ -983,16 +985,20 @@ void wait_published(ibdl_s* h, int slot, unsigned seq, double* out) {
 }
 
 // GMRES applies the working-precision operator (transposed with trans) by replaying a HIP graph
-// captured from direct launches, reading gx and writing gy.  Captures it on first use; returns
-// false when applies are launched directly instead (stage timing on, or graphs disabled).
+// captured from direct launches, reading gx and writing gy.  Captures it on first use (or on the
+// second, by graph_mode); returns false when applies are launched directly instead.
 bool ensure_graph(ibdl_s* h, bool trans) {
-  if (h->timing || !h->use_graph) return false;
+  if (h->timing || h->graph_mode == ibdl_s::GRAPH_OFF) return false;
   const int64_t n = h->n_aug;
   const int k = trans ? 1 : 0;
   if (h->gexec[k]) return true;
   if (!h->gx) {
     h->gx = (double*)h->dalloc<double>(sizeof(double) * n);
     h->gy = (double*)h->dalloc<double>(sizeof(double) * n);
+  }
+  if (h->graph_mode == ibdl_s::GRAPH_SECOND && !h->graph_seen[k]) {
+    h->graph_seen[k] = true;
+    return false;
   }
   // a direct run first allocates every workspace and measures the launch shapes
   IBDL_HIP(hipMemsetAsync(h->gx, 0, sizeof(double) * n, h->st));
@@ -1500,10 +1506,14 @@ ibdl_status_t ibdl_create(const ibdl_config_t* cfg, int64_t n_ib, const double* 
     for (int d = 0; d < 3; ++d) h->n[d] = d < h->dim ? (int)cfg->n[d] : 1;
     h->h = cfg->L[0] / (double)cfg->n[0];
     h->ntot = (int64_t)h->n[0] * h->n[1] * h->n[2];
-    // Krylov solvers replay the apply from a graph on small grids, where an apply is shorter than
-    // the host's launches; on large grids the host queues a step ahead anyway and direct launches
-    // avoid the idle gap after each graph (measured 1.7 % faster at 256^3, 3 % at 1024^2)
-    h->use_graph = h->ntot < ((int64_t)1 << 20);
+    // Krylov solvers launch the apply's kernels one by one: a handful, which the host queues a step
+    // ahead.  A graph of them only pays where the device finishes them about as fast as the host can
+    // launch them, and only once it is there: its capture, with the direct apply before it, the wait
+    // and the instantiation, is 0.2 ms for each of A and A^T after every change of markers.  Solves
+    // replayed and launched: 64^2 Stokes 700 and 715 us, 128^2 471 and 481, 256^2 and 512^2 scalar
+    // 412 and 417, 428 and 427; 512^2 Stokes 983 and 953, 1024^2 572 and 562, Stokes 1520 and 1413;
+    // a 512^2 training step 2480 and 2100.  So up to 2^14 points, from a marker set's second solve on.
+    h->graph_mode = h->ntot <= ((int64_t)1 << 14) ? ibdl_s::GRAPH_SECOND : ibdl_s::GRAPH_OFF;
     h->nxh = h->n[0] / 2 + 1;
     h->nxp = (h->nxh + 15) / 16 * 16;
     h->n_ib = n_ib;
@@ -2006,8 +2016,8 @@ ibdl_status_t ibdl_solve_refined(ibdl_t h, const double* data, const void* g_gri
 ibdl_status_t ibdl_set_graph(ibdl_t h, int32_t enable) {
   return guarded(h, [&]() {
     IBDL_HIP(hipStreamSynchronize(h->st));
-    h->use_graph = enable != 0;
-    if (!h->use_graph) h->drop_graphs();
+    h->graph_mode = enable ? ibdl_s::GRAPH_ON : ibdl_s::GRAPH_OFF;
+    if (!enable) h->drop_graphs();
     return IBDL_OK;
   });
 }
