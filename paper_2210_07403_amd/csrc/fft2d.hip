@@ -15,12 +15,11 @@
 //                  output fields, in one kernel: the spectra never go back to memory in between.
 //
 // Measured against the row-major spectra (double precision, kernel medians): the 1024^2 Stokes pass along
-// y 41 -> 22 us and its forward x pass 20.9 -> 12.0 us; the scalar pass 12.5 -> 8.6 us; on 4096^2 the
-// three passes along y of one Stokes apply (five strided, the fused one, two strided) 968 -> 275 us,
-// the forward x pass 295 -> 154 us over the active rows only.  A whole 4096^2 cylinder-array solve:
-// 33.8 -> 13.3 ms.  What bounds them now: at 1024^2 and below the latency of the chain load, radix
-// stages and their LDS exchanges, store, with 513 lines for 256 CUs; at 4096 the exchanges and the
-// FP64 arithmetic of a block that has its CU to itself (2.0 TB/s).
+// y 41 -> 17 us and its forward x pass 20.9 -> 12.0 us; the scalar pass 12.5 -> 8.6 us; on 4096^2 the
+// three passes along y of one Stokes apply (five strided, the fused one, two strided) 968 -> 267 us,
+// the forward x pass 295 -> 154 us over the active rows only.  What bounds them now: at 1024^2 and below
+// the latency of the chain load, radix stages and their LDS exchanges, store, two lines to a CU; at 4096
+// the same chain in a block that has its CU to itself (2.0 TB/s).
 //
 // Transforms whose lines are owned by at most one wave (T <= 64 threads) exchange through LDS
 // without a workgroup barrier; longer ones alternate between two LDS buffers where they fit, one
@@ -286,12 +285,15 @@ __device__ __forceinline__ void mode_mult(const MultDesc& md, const Mode<T>& m, 
 
 // Elements per thread of a y line: 8 for one field.  Passes that hold several fields at once take 4 in
 // double (five fields at 4 take 80 registers), in float from 2048 points on, where a block of 512 or
-// 1024 threads leaves 128 registers.  Lines of 8192 points need 8 to fit 1024 threads.
+// 1024 threads leaves 128 registers.  Double lines of 2048 and 4096 points take 8: 2048 lines of 2048
+// points, five fields and two: 82 us with 4 on 512 threads (which spill), 62 with 8 on 256 threads and
+// twiddles read as they are used; lines of 1024 with 8: 24 us, with 4: 17.
+// Lines of 8192 points need 8 to fit 1024 threads.
 template <typename T> constexpr int line_rmx(int N, int nmax) {
   if (N <= 8) return N;
   if (nmax == 1 || N < 64) return 8;
   if (N == 8192) return 8;
-  if (sizeof(T) == 8 && N == 4096) return 8;
+  if (sizeof(T) == 8 && N >= 2048) return 8;
   return sizeof(T) == 8 || N >= 2048 ? 4 : 8;
 }
 template <typename T, int N, int NI, int NO> struct LineShape {
@@ -302,13 +304,14 @@ template <typename T, int N, int NI, int NO> struct LineShape {
   static constexpr int LP = pad_len(N);
   // waves per SIMD that the register bound aims at: the five-field 4096-point double pass keeps its 160
   // registers of data and one block per CU (measured 275 us a launch on 4096^2 with two exchange
-  // buffers, 312 with one; 4 elements per thread on 1024 threads of 128 registers: 355)
+  // buffers, 312 with one; 4 elements per thread on 1024 threads of 128 registers: 355; 16 on 256: 472)
   static constexpr bool ALONE = sizeof(T) == 8 && N == 4096 && NM > 3;
   // Blocks of 512 threads or more: registers are what bounds the waves per SIMD, so the second
   // transform reads its twiddles again (from cache) instead of keeping the first one's, and the
   // symbols are read as they are used.
-  static constexpr bool LEAN = T_ >= 512;
-  static constexpr int MINW = !LEAN ? 1 : ALONE ? 2 : 4;
+  static constexpr bool D2048 = sizeof(T) == 8 && N == 2048 && NM > 1;   // 8 elements on 256 threads
+  static constexpr bool LEAN = T_ >= 512 || D2048;
+  static constexpr int MINW = D2048 ? 2 : !LEAN ? 1 : ALONE ? 2 : 4;
   // two exchange buffers per line where two blocks then still share a CU, or where the block has
   // the CU to itself anyway
   static constexpr int NBUF =
@@ -322,10 +325,39 @@ template <typename T, int N, int NI, int NO> struct LineShape {
   static_assert(LP * NBUF * SZ <= kLds, "y line: LDS over budget");
 };
 
-template <typename T, int N, int NI, int NO, int KIND>
-__global__ __launch_bounds__((LineShape<T, N, NI, NO>::BLK), (LineShape<T, N, NI, NO>::MINW)) void k2_lines(cplx<T>* __restrict__ data, MultDesc md,
-                                                                         const cplx<T>* __restrict__ tw, int W,
-                                                                         int64_t bstride, RowMask rm) {
+// The lines kx = 0 and kx = nx / 2 are spectra of real data: real along y, like every product with the
+// symbols (k~ vanishes at 0 and at the half), so one complex line a + i b carries both, and nx / 2 lines
+// are left of nx / 2 + 1.  That line more was a block more than the CUs hold at once, a whole round for
+// itself: five fields and two, FP64, 513 lines of 1024 points 22.4 us, 2049 of 4096 275 us, with the two
+// packed 17.2 and 267; one field, 2049 of 4096, 67 and 63.  Where a line has 256 threads or more; with
+// fewer a CU holds enough blocks.
+//
+// half_swap: the transform Z of a + i b, in place, to a^ in slots 0 < k < N/2 and b^ in the slots N - k
+// (a^ + i b^ of the real modes stays in slots 0 and N/2); with JOIN back.
+template <int N, int RMX, bool JOIN, typename C>
+__device__ __forceinline__ void half_swap(C (&v)[RMX], int i, C* lds) {
+  constexpr int TT = N / RMX;
+  __builtin_amdgcn_sched_barrier(0);
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < RMX; ++s) lds[pad_at(i) + pad_len(s * TT)] = v[s];
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < RMX; ++s) {
+    if ((s == 0 || s == RMX / 2) && i == 0) continue;
+    const C a = v[s], m = lds[pad_at(N - (i + s * TT))];
+    if constexpr (JOIN) v[s] = s < RMX / 2 ? mk<C>(a.x - m.y, a.y + m.x) : mk<C>(m.x + a.y, a.x - m.y);
+    else v[s] = cscale(s < RMX / 2 ? mk<C>(a.x + m.x, a.y - m.y) : mk<C>(m.y + a.y, a.x - m.x), decltype(a.x)(0.5));
+  }
+}
+template <int N, int KIND, int T_> constexpr bool line_packs() {
+  return T_ >= 256 && KIND != L_FWD && KIND != L_INV;
+}
+
+// PACK: the block of lines 0 and jh
+template <typename T, int N, int NI, int NO, int KIND, bool PACK>
+__device__ __forceinline__ void lines_block(cplx<T>* __restrict__ data, const MultDesc& md,
+                                            const cplx<T>* __restrict__ tw, int W, int64_t bstride, const RowMask& rm) {
   using C = cplx<T>;
   using L = LineShape<T, N, NI, NO>;
   constexpr int RMX = L::RMX, TT = L::T_, NBUF = L::NBUF;
@@ -335,7 +367,7 @@ __global__ __launch_bounds__((LineShape<T, N, NI, NO>::BLK), (LineShape<T, N, NI
   C* lds = reinterpret_cast<C*>(smem) + c * (NBUF * L::LP);
   const int kx = (int)blockIdx.x * W + c;
   const bool valid = kx < md.nxh;
-  const int jx = valid ? kx : 0;
+  const int jx = valid ? kx : 0, jh = md.nxh - 1;
   const unsigned fs = (unsigned)md.nxh * (unsigned)md.nyp;
   const unsigned b0 = ((unsigned)jx * (unsigned)md.nyp + (unsigned)i) * (unsigned)sizeof(C);
   constexpr unsigned step = TT * (unsigned)sizeof(C);
@@ -343,19 +375,31 @@ __global__ __launch_bounds__((LineShape<T, N, NI, NO>::BLK), (LineShape<T, N, NI
   const T* sgl = static_cast<const T*>(md.sig[1]);
   const T* ktl = static_cast<const T*>(md.kt[1]);
   const T sigx = static_cast<const T*>(md.sig[0])[jx], kxs = static_cast<const T*>(md.kt[0])[jx];
+  const unsigned bh = ((unsigned)jh * (unsigned)md.nyp + (unsigned)i) * (unsigned)sizeof(C);
+  // a slot of the packed line that holds a mode of line jh (half_swap), and its y mode
+  auto half = [&](int s) { return PACK && s >= RMX / 2 && i + s * TT != N / 2; };
+  auto ymode = [&](int s) { return half(s) ? N - (i + s * TT) : i + s * TT; };
   auto load = [&](C (&v)[RMX], int f) {
 #pragma unroll
     for (int s = 0; s < RMX; ++s) {
       const int y = i + s * TT;
       const bool on = valid && (!rm.load || (y >= rm.lo && y <= rm.hi));
       v[s] = on ? at(data, (unsigned)f * fsb + b0 + s * step) : mk<C>(0, 0);
+      if constexpr (PACK) v[s].y = on ? at(data, (unsigned)f * fsb + bh + s * step).x : (T)0;
     }
   };
   auto store = [&](const C (&v)[RMX], int f) {
 #pragma unroll
     for (int s = 0; s < RMX; ++s) {
       const int y = i + s * TT;
-      if (valid && (!rm.store || (y >= rm.lo && y <= rm.hi))) at(data, (unsigned)f * fsb + b0 + s * step) = v[s];
+      if (valid && (!rm.store || (y >= rm.lo && y <= rm.hi))) {
+        C a = v[s];
+        if constexpr (PACK) {
+          at(data, (unsigned)f * fsb + bh + s * step) = mk<C>(a.y, (T)0);
+          a.y = (T)0;
+        }
+        at(data, (unsigned)f * fsb + b0 + s * step) = a;
+      }
     }
   };
   C w0[RMX];
@@ -373,32 +417,74 @@ __global__ __launch_bounds__((LineShape<T, N, NI, NO>::BLK), (LineShape<T, N, NI
     if constexpr (!L::LEAN) {
 #pragma unroll
       for (int s = 0; s < RMX; ++s) {
-        sg[s] = sgl[i + s * TT];
-        ks[s] = line_needs_k(KIND, NI) ? ktl[i + s * TT] : (T)0;
+        sg[s] = sgl[ymode(s)];
+        ks[s] = line_needs_k(KIND, NI) ? ktl[ymode(s)] : (T)0;
       }
     }
     fft_multi<N, false, NI, RMX, NBUF, L::LEAN>(v, i, lds, L::LP, par, tw, w0);
+    if constexpr (PACK) {
+#pragma unroll
+      for (int f = 0; f < NI; ++f) half_swap<N, RMX, false>(v[f], i, lds);
+      __syncthreads();
+    }
     __builtin_amdgcn_sched_barrier(0);
     C u[NO][RMX];
 #pragma unroll
     for (int s = 0; s < RMX; ++s) {
       if constexpr (L::LEAN) {
         __builtin_amdgcn_sched_barrier(0);
-        sg[s] = sgl[i + s * TT];
-        ks[s] = line_needs_k(KIND, NI) ? ktl[i + s * TT] : (T)0;
+        sg[s] = sgl[ymode(s)];
+        ks[s] = line_needs_k(KIND, NI) ? ktl[ymode(s)] : (T)0;
       }
-      const Mode<T> m{kxs, ks[s], sigx + sg[s]};
+      Mode<T> m{kxs, ks[s], sigx + sg[s]};
+      if constexpr (PACK) {
+        if (half(s)) {
+          m.kx = static_cast<const T*>(md.kt[0])[jh];
+          m.sig = static_cast<const T*>(md.sig[0])[jh] + sg[s];
+        }
+      }
       C x[NI], y[NO];
 #pragma unroll
       for (int f = 0; f < NI; ++f) x[f] = v[f][s];
       mode_mult<KIND, NI, NO, T>(md, m, x, y);
 #pragma unroll
       for (int o = 0; o < NO; ++o) u[o][s] = y[o];
+      if (PACK && (s == 0 || s == RMX / 2)) {
+        if (i == 0) {   // the packed real modes: real part from line 0's symbols, imaginary part from line jh's
+          m.kx = static_cast<const T*>(md.kt[0])[jh];
+          m.sig = static_cast<const T*>(md.sig[0])[jh] + sg[s];
+          mode_mult<KIND, NI, NO, T>(md, m, x, y);
+#pragma unroll
+          for (int o = 0; o < NO; ++o) u[o][s].y = y[o].y;
+        }
+      }
+    }
+    if constexpr (PACK) {
+#pragma unroll
+      for (int o = 0; o < NO; ++o) half_swap<N, RMX, true>(u[o], i, lds);
+      __syncthreads();
     }
     fft_multi<N, true, NO, RMX, NBUF, L::LEAN>(u, i, lds, L::LP, par, tw2, w0);
 #pragma unroll
     for (int o = 0; o < NO; ++o) store(u[o], o);
   }
+}
+
+template <typename T, int N, int NI, int NO, int KIND>
+__global__ __launch_bounds__((LineShape<T, N, NI, NO>::BLK), (LineShape<T, N, NI, NO>::MINW)) void k2_lines(cplx<T>* __restrict__ data, MultDesc md,
+                                                                         const cplx<T>* __restrict__ tw, int W,
+                                                                         int64_t bstride, RowMask rm) {
+  if constexpr (line_packs<N, KIND, LineShape<T, N, NI, NO>::T_>()) {
+    if (blockIdx.x == 0) {
+      // (own copies of the pointers: the compiler would otherwise hold what both paths load for both)
+      cplx<T>* d = data;
+      const cplx<T>* t = tw;
+      asm volatile("" : "+s"(d), "+s"(t));
+      lines_block<T, N, NI, NO, KIND, true>(d, md, t, W, bstride, rm);
+      return;
+    }
+  }
+  lines_block<T, N, NI, NO, KIND, false>(data, md, tw, W, bstride, rm);
 }
 
 // the multiplier by itself, on transformed fields (LineShape::SPLIT)
@@ -514,7 +600,8 @@ void fft2_lines(cplx<T>* data, int n, int no, const MultDesc& md, const Tw2<T>& 
         using L = LineShape<T, N, I, O>;
         int W = 1;
         while (2 * W <= (w <= 0 || w > L::W ? L::W : w)) W *= 2;
-        const dim3 grid((unsigned)((md.nxh + W - 1) / W), (unsigned)count);
+        const int nl = md.nxh - (line_packs<N, decltype(kc1)::value, L::T_>() ? 1 : 0);
+        const dim3 grid((unsigned)((nl + W - 1) / W), (unsigned)count);
         hipLaunchKernelGGL((k2_lines<T, N, I, O, decltype(kc1)::value>), grid, dim3(W * L::T_),
                            (size_t)W * L::NBUF * L::LP * sizeof(cplx<T>), s, data, md,
                            tw.y[L::NM > 1 ? 1 : 0], W, stride, mask);
