@@ -376,8 +376,10 @@ __device__ __forceinline__ double spread_coef(const SpreadArgs& a, int m, int D,
 }
 
 
-// Lanes used per wave for candidates in one pass of the 2-D spread (32 KiB of LDS per block).
-template <typename T> constexpr int spread_lanes() { return sizeof(T) == 4 ? 64 : 32; }
+// Candidates per wave in one pass of the 2-D spread (17 KiB of LDS per block, eight blocks per CU).
+// FP64, candidates 32 (two lanes each), 16 (four), 8 (eight): the tiles of a 30-problem batch 15.5, 14.2,
+// 15.9 us; 200 tiles of a 1024^2 scalar problem 6.7, 6.6, 7.0; 95 tiles with five fields 5.8, 5.4, 5.4.
+template <typename T> constexpr int spread_lanes() { return sizeof(T) == 4 ? 32 : 16; }
 
 // broadcast a lane's value to the whole wave (scalar register), any 32/64-bit type
 template <typename T> __device__ __forceinline__ T bcast(T v, int lane) {
@@ -682,14 +684,16 @@ __global__ __launch_bounds__(64 * NW, 8) void k_spread3f(SpreadArgs a, const cpl
 }
 
 // 2-D: a tile of TX x TY nodes (TX TY = 256, TY = 4 (64 / TX) rows); lane (x, y-group) owns
-// y = 4 yg + j' (j' < 4).  Wave w takes candidates w, w + 4, ... of the tile's list, LW at a time: the
-// lane of a candidate copies its x and y weight rows to LDS and keeps its window start and
+// y = 4 yg + j' (j' < 4).  Wave w takes candidates w, w + 4, ... of the tile's list, LW at a time: 64 / LW
+// lanes copy a candidate's x and y weight rows to LDS, the first of them keeps its window start and
 // coefficients, which are broadcast; a node's taps are picked by index (6 and 7 are zero).  The rows
 // are copied as they are, so everything a candidate needs is loaded at once behind its list entry:
 // the launch is a chain of dependent loads (tile, list entry, marker), a few candidates' work per wave,
 // and the sum over the waves.  (The y rows had been aligned to the tile as they were staged, one more
-// dependent load and 48 KiB of LDS in double: five Stokes fields on 199 tiles 7.6 -> 6.6 us, the 1,833
-// tiles of a 30-problem batch 22.2 -> 17.8 us.)  s_w is the caller's LDS, [4][LW][17] (T, T) pairs (one
+// dependent load and 48 KiB of LDS in double, then copied by one lane per candidate, sixteen loads each
+// and 34 KiB: five Stokes fields on 95 tiles 6.7 -> 5.4 us with several lanes and 17 KiB, on the 774 tiles
+// of a 4096^2 array 9.7 -> 7.8 us, the tiles of a 30-problem batch 22.2 -> 18.2 -> 14.2 us.)
+// s_w is the caller's LDS, [4][LW][17] (T, T) pairs (one
 // of padding, so that the lanes' copies fall into different banks).
 template <typename T, int NF, int TX>
 __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>* __restrict__ wtab, T* __restrict__ out,
@@ -724,12 +728,14 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
     T cf[5];
 #pragma unroll
     for (int c = 0; c < 5; ++c) cf[c] = 0;
-    if (lane < cnt) {
-      const int m = a.list[c0 + 4 * lane + wave];
-      const T2* row = wtab + (int64_t)m * 24;
-      T2 w[16];
+    constexpr int NP = 64 / LW, NW = 16 / NP;   // lanes per candidate, weights copied by each
+    const int cd = lane % LW, part = lane / LW;
+    if (cd < cnt) {
+      const int m = a.list[c0 + 4 * cd + wave];
+      const T2* row = wtab + (int64_t)m * 24 + part * NW;
+      T2 w[NW];
 #pragma unroll
-      for (int t = 0; t < 16; ++t) w[t] = row[t];
+      for (int t = 0; t < NW; ++t) w[t] = row[t];
       sx = a.s[m * 3 + 0];
       sy = a.s[m * 3 + 1];
       double c8[8];
@@ -737,7 +743,7 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
 #pragma unroll
       for (int c = 0; c < 5; ++c) cf[c] = (T)c8[c];
 #pragma unroll
-      for (int t = 0; t < 16; ++t) s_w[wave][lane][t] = w[t];
+      for (int t = 0; t < NW; ++t) s_w[wave][cd][part * NW + t] = w[t];
     }
     // (each wave reads its own rows only)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
