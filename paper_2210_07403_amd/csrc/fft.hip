@@ -100,10 +100,11 @@ __device__ __forceinline__ const C* stage_table(C* dst, const C* __restrict__ tw
 // Bound by HBM on a large grid (512^3 FP64, all rows: 412 and 425 us, 5.2 and 5.1 TB/s, a copy's rate)
 // and by the latency of one load - transform - store chain on a row list (256^3 sphere, 10k rows, FP32:
 // 9.7 and 10.5 us).  With rows staged in LDS by the whole block, the twiddles beside them and a workgroup
-// barrier per exchange these were 443 / 455 and 13 / 13 us.  Eight elements per thread: twice the waves
-// of sixteen to hide that chain.
-template <int M> struct RowCfg {
-  static constexpr int RMX = M < 8 ? M : 8;
+// barrier per exchange these were 458 / 464 and 13 / 13 us.  Eight elements per thread; single precision
+// rows of 128 values and more take sixteen, two stages instead of three (512^3, all rows: 248 and 272 us
+// with eight, 221 and 248 with sixteen; the 256^3 row list the same; double the same).
+template <typename TR, int M> struct RowCfg {
+  static constexpr int RMX = sizeof(TR) == 4 && M >= 128 ? 16 : 8;
   static constexpr int T = M / RMX;
   static constexpr int LS = pad_len(M) + 4;              // LDS row stride: an exchange line, or M + 1 modes
   static constexpr int RPB = kBlock / T;                 // most rows per block
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(kBlock) void k_x_r2c(const TI* __restrict__ in, cpl
                                                   const cplx<T>* __restrict__ tw, const cplx<T>* __restrict__ st,
                                                   RowList rl, int pitch) {
   using C = cplx<T>;
-  using RC = RowCfg<M>;
+  using RC = RowCfg<T, M>;
   constexpr int RMX = RC::RMX, TT = RC::T;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lrow = tid / TT, i = tid - lrow * TT;
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(kBlock) void k_x_c2r(const cplx<T>* __restrict__ in
                                                   const cplx<T>* __restrict__ tw, const cplx<T>* __restrict__ st,
                                                   RowList rl, int pitch) {
   using C = cplx<T>;
-  using RC = RowCfg<M>;
+  using RC = RowCfg<T, M>;
   constexpr int RMX = RC::RMX, TT = RC::T;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lrow = tid / TT, i = tid - lrow * TT;
@@ -480,19 +481,19 @@ int fft_supported(int n) { return n >= 16 && n <= 1024 && (n & (n - 1)) == 0; }
 template <typename T>
 int fft_x_rpb_max(int nx) {
   int r = 0;
-  dispatch_m(nx / 2, [&](auto Mc) { r = RowCfg<decltype(Mc)::value>::RPB; });
+  dispatch_m(nx / 2, [&](auto Mc) { r = RowCfg<T, decltype(Mc)::value>::RPB; });
   return r;
 }
 
 template <typename T> size_t fft_x_table_len(int nx) {
   int r = 0;
-  dispatch_m(nx / 2, [&](auto Mc) { r = stage_len<decltype(Mc)::value, RowCfg<decltype(Mc)::value>::RMX>(); });
+  dispatch_m(nx / 2, [&](auto Mc) { r = stage_len<decltype(Mc)::value, RowCfg<T, decltype(Mc)::value>::RMX>(); });
   return (size_t)r + 1;
 }
 
 template <typename T> TwX<T> fft_x_table(int nx, const cplx<T>* twx, cplx<T>* dst, hipStream_t s) {
   dispatch_m(nx / 2, [&](auto Mc) {
-    constexpr int M = decltype(Mc)::value, RMX = RowCfg<M>::RMX;
+    constexpr int M = decltype(Mc)::value, RMX = RowCfg<T, M>::RMX;
     const int len = stage_len<M, RMX>();
     if (len > 0) hipLaunchKernelGGL((k_stages<M, RMX, cplx<T>>), dim3((len + 255) / 256), dim3(256), 0, s, dst, twx, 2);
   });
@@ -540,7 +541,7 @@ void x_r2c_launch(const TI* in, cplx<T>* out, int nx, int64_t nrows, const TwX<T
   if (nrows > INT32_MAX) throw Error(-2, "x FFT pass: too many rows");
   dispatch_m(nx / 2, [&](auto Mc) {
     constexpr int M = decltype(Mc)::value;
-    using RC = RowCfg<M>;
+    using RC = RowCfg<T, M>;
     const int R = pick(rpb, RC::RPB);
     hipLaunchKernelGGL((k_x_r2c<T, M, TI>), dim3((unsigned)((nrows + R - 1) / R)), dim3(R * RC::T),
                        sizeof(cplx<T>) * R * RC::LS, s, in, out, (unsigned)nrows, tw.base, tw.x, rl, (int)pitch);
@@ -567,7 +568,7 @@ void fft_x_c2r(const cplx<T>* in, T* out, int nx, int64_t nrows, const TwX<T>& t
   if (nrows > INT32_MAX) throw Error(-2, "x FFT pass: too many rows");
   dispatch_m(nx / 2, [&](auto Mc) {
     constexpr int M = decltype(Mc)::value;
-    using RC = RowCfg<M>;
+    using RC = RowCfg<T, M>;
     const int R = pick(rpb, RC::RPB);
     hipLaunchKernelGGL((k_x_c2r<T, M>), dim3((unsigned)((nrows + R - 1) / R)), dim3(R * RC::T),
                        sizeof(cplx<T>) * R * RC::LS, s, in, out, (unsigned)nrows, tw.base, tw.x, rl, (int)pitch);
