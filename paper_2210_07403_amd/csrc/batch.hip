@@ -128,6 +128,10 @@ struct ibdl_batch_s {
     int2* items = nullptr;
     int nitems = 0;
     int blocks = 0;             // workgroups of the persistent spread (0: one per tile)
+    std::vector<Fft2Group> fft; // merged FFT passes (empty: the passes run group by group)
+    Fft2Group* fft_dev = nullptr;
+    int2* fft_items = nullptr;
+    int fft_nx = 0, fft_ny = 0;
     bool ready = false;
   } queue[2];
   int spread_blocks = 0;        // workgroups of the persistent spread
@@ -184,23 +188,28 @@ template <typename T> MultDesc group_desc(const Group& G, const GroupWork<T>& W,
   return md;
 }
 
+// rows of a 2-D group in its x passes: the spread wrote the busy tiles only, so the forward pass reads
+// their row segments and takes the rest of each row as zero (no clearing of the fields)
+Rows2 group_rows(const Group& G, bool in) {
+  Rows2 rw;
+  rw.hi = G.n[1] - 1;
+  if (in) {
+    rw.seg = G.seg_all;
+    rw.seg_log2 = __builtin_ctz((unsigned)G.geom.tile[0] / 2);
+    rw.seg_per_field = 1;
+  }
+  return rw;
+}
+
 // the group's spread field -> -L^-1 (field), all problems of the group at once
 template <typename T> void group_pipeline(ibdl_batch_s* B, Group& G, GroupWork<T>& W, const Tuned& tn) {
   const int np = (int)G.probs.size();
   const int64_t rows = (int64_t)np * (G.ntot / G.n[0]);
   const MultDesc md = group_desc<T>(G, W, B->dim);
-  // the spread wrote the busy tiles only: the x pass reads their row segments and takes the rest
-  // of each row as zero (no clearing of the fields)
   if (B->dim == 2) {
-    Rows2 rw;
-    rw.hi = G.n[1] - 1;
-    const Rows2 out = rw;
-    rw.seg = G.seg_all;
-    rw.seg_log2 = __builtin_ctz((unsigned)G.geom.tile[0] / 2);
-    rw.seg_per_field = 1;
-    fft2_x_r2c<T>(W.real, W.spec, G.n[0], G.n[1], np, W.tw2, B->st, tn.rpb, rw);
+    fft2_x_r2c<T>(W.real, W.spec, G.n[0], G.n[1], np, W.tw2, B->st, tn.rpb, group_rows(G, true));
     fft2_lines<T>(W.spec, G.n[1], 1, md, W.tw2, B->st, np, G.nspec<T>(2), tn.wz, RowMask());
-    fft2_x_c2r<T>(W.spec, W.real, G.n[0], G.n[1], np, W.tw2, B->st, tn.rpb, out);
+    fft2_x_c2r<T>(W.spec, W.real, G.n[0], G.n[1], np, W.tw2, B->st, tn.rpb, group_rows(G, false));
     return;
   }
   RowList rl;
@@ -473,6 +482,34 @@ template <typename T> void build_queue(ibdl_batch_s* B) {
   IBDL_HIP(hipMemcpyAsync(Q.sg, sg.data(), sizeof(SpreadGroup) * ng, hipMemcpyHostToDevice, B->st));
   IBDL_HIP(hipMemcpyAsync(Q.ig, ig.data(), sizeof(InterpGroup) * ng, hipMemcpyHostToDevice, B->st));
   IBDL_HIP(hipMemcpyAsync(Q.items, it.data(), sizeof(int2) * it.size(), hipMemcpyHostToDevice, B->st));
+  // The FFT passes of all groups in one launch each where there is more than one group (30 problems in
+  // three groups: 45 us an apply, group by group 63); a single group's passes keep the launch shapes
+  // chosen by timing.
+  bool merge = ng > 1;
+  for (const Group& G : B->groups) merge = merge && fft2_groups_fit(G.n[0], G.n[1]);
+  std::vector<int2> fi, fl;
+  if (merge) {
+    Q.fft.resize(ng);
+    for (int gi = 0; gi < ng; ++gi) {
+      Group& G = B->groups[gi];
+      GroupWork<T>& W = G.work<T>();
+      Fft2Group& d = Q.fft[gi];
+      d = Fft2Group{};
+      fft2_group_set<T>(d, W.real, W.spec, G.n[0], G.n[1], (int)G.probs.size(), W.tw2);
+      d.in = group_rows(G, true);
+      d.out = group_rows(G, false);
+      d.md = group_desc<T>(G, W, B->dim);
+      for (int k = 0; k < d.np * d.nbx; ++k) fi.push_back(make_int2(gi, k));
+      for (int k = 0; k < d.np * d.nbl; ++k) fl.push_back(make_int2(gi, k));
+    }
+    Q.fft_nx = (int)fi.size();
+    Q.fft_ny = (int)fl.size();
+    fi.insert(fi.end(), fl.begin(), fl.end());
+    Q.fft_dev = (Fft2Group*)B->dalloc(sizeof(Fft2Group) * ng);
+    Q.fft_items = (int2*)B->dalloc(sizeof(int2) * fi.size());
+    IBDL_HIP(hipMemcpyAsync(Q.fft_dev, Q.fft.data(), sizeof(Fft2Group) * ng, hipMemcpyHostToDevice, B->st));
+    IBDL_HIP(hipMemcpyAsync(Q.fft_items, fi.data(), sizeof(int2) * fi.size(), hipMemcpyHostToDevice, B->st));
+  }
   IBDL_HIP(hipStreamSynchronize(B->st));
   Q.ready = true;
   // Workgroups of the persistent spread by measurement: 2, 4 or 8 per compute unit, or one per tile
@@ -515,16 +552,25 @@ template <typename T> void build_queue(ibdl_batch_s* B) {
   tune_put(key, put);
 }
 
+// every group's spread field -> -L^-1 (field) in 2-D
+template <typename T> void batch_pipelines(ibdl_batch_s* B) {
+  const ibdl_batch_s::Queue& Q = B->queue[prec_index(sizeof(T))];
+  if (!Q.fft.empty())
+    fft2_groups<T>(Q.fft.data(), Q.fft_dev, (int)Q.fft.size(), Q.fft_items, Q.fft_nx, Q.fft_ny, B->st);
+  else
+    for (Group& G : B->groups) group_pipeline<T>(B, G, G.work<T>(), G.work<T>().tune);
+}
+
 // y = A x for every problem of the batch (Dirichlet: y = S* u[x] + x/2).  2-D: the spread of every
-// group in one persistent launch over the merged tile queue, the FFT passes per group, and the
-// interpolation of every group in one launch.
+// group in one persistent launch over the merged tile queue, the FFT passes of every group in one
+// launch each, and the interpolation of every group in one launch.
 template <typename T> void batch_apply(ibdl_batch_s* B, const double* x, double* y) {
   if (queue_path(B)) {
     for (Group& G : B->groups) group_work<T>(B, G);
     build_queue<T>(B);
     ibdl_batch_s::Queue& Q = B->queue[prec_index(sizeof(T))];
     spread2_queue<T>(Q.sg, Q.items, Q.nitems, x, Q.blocks, B->st);
-    for (Group& G : B->groups) group_pipeline<T>(B, G, G.work<T>(), G.work<T>().tune);
+    batch_pipelines<T>(B);
     interp4_groups<T>(Q.ig, (int)B->groups.size(), B->N, x, y, B->st);
     return;
   }
@@ -715,11 +761,11 @@ template <typename T> void batch_recover(ibdl_batch_s* B, const double* q, void*
     build_queue<T>(B);
     ibdl_batch_s::Queue& Q = B->queue[prec_index(sizeof(T))];
     spread2_queue<T>(Q.sg, Q.items, Q.nitems, q, Q.blocks, B->st);
+    batch_pipelines<T>(B);
   }
   for (Group& G : B->groups) {
     GroupWork<T>& W = group_work<T>(B, G);
-    if (queue_path(B)) group_pipeline<T>(B, G, W, W.tune);
-    else group_density_to_grid<T>(B, G, W, q + G.aoff);
+    if (!queue_path(B)) group_density_to_grid<T>(B, G, W, q + G.aoff);
     for (size_t k = 0; k < G.probs.size(); ++k) {
       void* dst = u[G.probs[k]];
       if (dst)

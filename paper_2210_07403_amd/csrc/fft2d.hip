@@ -59,18 +59,15 @@ template <typename TR, int M> struct X2 {
 // forward: block (field f, rows y0 .. y0 + R - 1); TI: element type of the input rows (float rows
 // widened on load for a double transform)
 template <typename T, int M, typename TI>
-__global__ __launch_bounds__((X2<T, M>::BLK)) void k2_x_r2c(const TI* __restrict__ in, cplx<T>* __restrict__ out,
-                                                            int ny, int nby, int lr, const cplx<T>* __restrict__ tw,
-                                                            const cplx<T>* __restrict__ st,
-                                                            Rows2 rw, unsigned pitch, int64_t fs) {
+__device__ __forceinline__ void r2c_block(const TI* __restrict__ in, cplx<T>* __restrict__ out, int ny, int nby, int lr,
+                                          const cplx<T>* __restrict__ tw, const cplx<T>* __restrict__ st,
+                                          const Rows2& rw, unsigned pitch, int64_t fs, int id) {
   using C = cplx<T>;
   using X = X2<T, M>;
   constexpr int RMX = X::RMX, TT = X::T;
   extern __shared__ __align__(16) unsigned char smem[];
   C* lds = reinterpret_cast<C*>(smem);
   const int tid = threadIdx.x, R = 1 << lr, LS = X::stride(lr);
-  // neighbouring row blocks on one XCD: they share the cache lines of the transposed spectra
-  const int id = xcd_chunk((int)blockIdx.x, (int)gridDim.x);
   const int f = id / nby, rb = id - f * nby;
   const int y0 = (rw.lo & ~(R - 1)) + (rb << lr);
   const int row = tid / TT, i = tid - row * TT, y = y0 + row;
@@ -138,19 +135,26 @@ __global__ __launch_bounds__((X2<T, M>::BLK)) void k2_x_r2c(const TI* __restrict
   }
 }
 
-// inverse: rows lo .. hi of the nfields output fields
-template <typename T, int M>
-__global__ __launch_bounds__((X2<T, M>::BLK)) void k2_x_c2r(const cplx<T>* __restrict__ in, T* __restrict__ out,
+template <typename T, int M, typename TI>
+__global__ __launch_bounds__((X2<T, M>::BLK)) void k2_x_r2c(const TI* __restrict__ in, cplx<T>* __restrict__ out,
                                                             int ny, int nby, int lr, const cplx<T>* __restrict__ tw,
                                                             const cplx<T>* __restrict__ st,
                                                             Rows2 rw, unsigned pitch, int64_t fs) {
+  // neighbouring row blocks on one XCD: they share the cache lines of the transposed spectra
+  r2c_block<T, M, TI>(in, out, ny, nby, lr, tw, st, rw, pitch, fs, xcd_chunk((int)blockIdx.x, (int)gridDim.x));
+}
+
+// inverse: rows lo .. hi of the nfields output fields
+template <typename T, int M>
+__device__ __forceinline__ void c2r_block(const cplx<T>* __restrict__ in, T* __restrict__ out, int ny, int nby, int lr,
+                                          const cplx<T>* __restrict__ tw, const cplx<T>* __restrict__ st,
+                                          const Rows2& rw, unsigned pitch, int64_t fs, int id) {
   using C = cplx<T>;
   using X = X2<T, M>;
   constexpr int RMX = X::RMX, TT = X::T;
   extern __shared__ __align__(16) unsigned char smem[];
   C* lds = reinterpret_cast<C*>(smem);
   const int tid = threadIdx.x, R = 1 << lr, LS = X::stride(lr);
-  const int id = xcd_chunk((int)blockIdx.x, (int)gridDim.x);
   const int f = id / nby, rb = id - f * nby;
   const int y0 = (rw.lo & ~(R - 1)) + (rb << lr);
   {
@@ -188,6 +192,14 @@ __global__ __launch_bounds__((X2<T, M>::BLK)) void k2_x_c2r(const cplx<T>* __res
 #pragma unroll
     for (int s = 0; s < RMX; ++s) dst[i + s * TT] = v[0][s];
   }
+}
+
+template <typename T, int M>
+__global__ __launch_bounds__((X2<T, M>::BLK)) void k2_x_c2r(const cplx<T>* __restrict__ in, T* __restrict__ out,
+                                                            int ny, int nby, int lr, const cplx<T>* __restrict__ tw,
+                                                            const cplx<T>* __restrict__ st,
+                                                            Rows2 rw, unsigned pitch, int64_t fs) {
+  c2r_block<T, M>(in, out, ny, nby, lr, tw, st, rw, pitch, fs, xcd_chunk((int)blockIdx.x, (int)gridDim.x));
 }
 
 // ------------------------------------------------------------------ y axis
@@ -357,15 +369,14 @@ template <int N, int KIND, int T_> constexpr bool line_packs() {
 // PACK: the block of lines 0 and jh
 template <typename T, int N, int NI, int NO, int KIND, bool PACK>
 __device__ __forceinline__ void lines_block(cplx<T>* __restrict__ data, const MultDesc& md,
-                                            const cplx<T>* __restrict__ tw, int W, int64_t bstride, const RowMask& rm) {
+                                            const cplx<T>* __restrict__ tw, int W, const RowMask& rm, int bx) {
   using C = cplx<T>;
   using L = LineShape<T, N, NI, NO>;
   constexpr int RMX = L::RMX, TT = L::T_, NBUF = L::NBUF;
   extern __shared__ __align__(16) unsigned char smem[];
-  data += (int64_t)blockIdx.y * bstride;   // problem of a batch
   const int tid = threadIdx.x, c = tid / TT, i = tid - c * TT;
   C* lds = reinterpret_cast<C*>(smem) + c * (NBUF * L::LP);
-  const int kx = (int)blockIdx.x * W + c;
+  const int kx = bx * W + c;
   const bool valid = kx < md.nxh;
   const int jx = valid ? kx : 0, jh = md.nxh - 1;
   const unsigned fs = (unsigned)md.nxh * (unsigned)md.nyp;
@@ -474,17 +485,18 @@ template <typename T, int N, int NI, int NO, int KIND>
 __global__ __launch_bounds__((LineShape<T, N, NI, NO>::BLK), (LineShape<T, N, NI, NO>::MINW)) void k2_lines(cplx<T>* __restrict__ data, MultDesc md,
                                                                          const cplx<T>* __restrict__ tw, int W,
                                                                          int64_t bstride, RowMask rm) {
+  data += (int64_t)blockIdx.y * bstride;   // problem of a batch
   if constexpr (line_packs<N, KIND, LineShape<T, N, NI, NO>::T_>()) {
     if (blockIdx.x == 0) {
       // (own copies of the pointers: the compiler would otherwise hold what both paths load for both)
       cplx<T>* d = data;
       const cplx<T>* t = tw;
       asm volatile("" : "+s"(d), "+s"(t));
-      lines_block<T, N, NI, NO, KIND, true>(d, md, t, W, bstride, rm);
+      lines_block<T, N, NI, NO, KIND, true>(d, md, t, W, rm, 0);
       return;
     }
   }
-  lines_block<T, N, NI, NO, KIND, false>(data, md, tw, W, bstride, rm);
+  lines_block<T, N, NI, NO, KIND, false>(data, md, tw, W, rm, (int)blockIdx.x);
 }
 
 // the multiplier by itself, on transformed fields (LineShape::SPLIT)
@@ -502,6 +514,63 @@ __global__ __launch_bounds__(256) void k2_mult(cplx<T>* __restrict__ data, MultD
   mode_mult<KIND, NI, NO, T>(md, m, x, y);
 #pragma unroll
   for (int o = 0; o < NO; ++o) data[o * fs + o0] = y[o];
+}
+
+// ------------------------------------------------------------------ several grids in one launch
+// The three passes of a batch's grid groups (one field, scalar multiplier), one launch per pass for all
+// groups instead of one per group and pass: workgroup b takes block items[b].y of group items[b].x.
+// A block holds 2,048 values whatever its line length, so the blocks are alike.  Launches of a few
+// dozen blocks each, one behind the other, were what a batch of small grids spent its time on: 30
+// problems on 128^2, 256^2 and 512^2 grids, FP64, nine launches 63 us, three launches 45.
+constexpr int kGroupM0 = 32, kGroupM1 = 512, kGroupN1 = 1024;   // row lengths (complex), longest y line
+template <int M, typename F> __device__ __forceinline__ void group_row(int m, F&& f) {
+  if constexpr (M <= kGroupM1) {
+    if (m == M) f(std::integral_constant<int, M>{});
+    else group_row<2 * M>(m, f);
+  }
+}
+template <typename T> constexpr int group_rows_log2(int m) { return m == 32 ? 6 : m == 64 ? 5 : m == 128 ? 4 : m == 256 ? 3 : 2; }
+
+template <typename T, bool INV>
+__global__ __launch_bounds__(256) void k2_x_groups(const Fft2Group* __restrict__ gd, const int2* __restrict__ items) {
+  using C = cplx<T>;
+  const int2 it = items[xcd_chunk((int)blockIdx.x, (int)gridDim.x)];
+  const Fft2Group& g = gd[__builtin_amdgcn_readfirstlane(it.x)];
+  const int id = __builtin_amdgcn_readfirstlane(it.y);
+  const unsigned pitch = (unsigned)spec2_pitch<T>(g.ny);
+  const int64_t fs = (int64_t)(g.m + 1) * pitch;
+  group_row<kGroupM0>(g.m, [&](auto Mc) {
+    constexpr int M = decltype(Mc)::value, LR = group_rows_log2<T>(M);
+    static_assert(M / 8 << LR == 256, "a block holds 2,048 values");
+    const C* base = static_cast<const C*>(g.base);
+    const C* st = static_cast<const C*>(g.twx);
+    if constexpr (INV)
+      c2r_block<T, M>(static_cast<const C*>(g.spec), static_cast<T*>(g.real), g.ny, g.nbx, LR, base, st, g.out, pitch, fs, id);
+    else
+      r2c_block<T, M, T>(static_cast<const T*>(g.real), static_cast<C*>(g.spec), g.ny, g.nbx, LR, base, st, g.in, pitch, fs, id);
+  });
+}
+
+template <int N, typename F> __device__ __forceinline__ void group_line(int n, F&& f) {
+  if constexpr (N <= kGroupN1) {
+    if (n == N) f(std::integral_constant<int, N>{});
+    else group_line<2 * N>(n, f);
+  }
+}
+template <typename T>
+__global__ __launch_bounds__(256) void k2_lines_groups(const Fft2Group* __restrict__ gd, const int2* __restrict__ items) {
+  using C = cplx<T>;
+  const int2 it = items[blockIdx.x];
+  const Fft2Group& g = gd[__builtin_amdgcn_readfirstlane(it.x)];
+  const int id = __builtin_amdgcn_readfirstlane(it.y), p = id / g.nbl;
+  const int64_t fs = (int64_t)(g.m + 1) * spec2_pitch<T>(g.ny);
+  group_line<16>(g.ny, [&](auto Nc) {
+    constexpr int N = decltype(Nc)::value;
+    using L = LineShape<T, N, 1, 1>;
+    static_assert(L::W * L::T_ == 256 && !line_packs<N, L_SCALAR, L::T_>(), "a block of 256 threads");
+    lines_block<T, N, 1, 1, L_SCALAR, false>(static_cast<C*>(g.spec) + p * fs, g.md, static_cast<const C*>(g.twy), L::W,
+                                             RowMask(), id - p * g.nbl);
+  });
 }
 
 template <typename F> void dispatch2(int n, F&& f) {
@@ -642,6 +711,53 @@ void fft2_lines(cplx<T>* data, int n, int no, const MultDesc& md, const Tw2<T>& 
   IBDL_LAUNCH_CHECK();
 }
 
+// A grid can take part in the merged passes when its rows and lines have merged forms and a block's
+// rows, 4096 / nx of them, do not reach past the grid.
+bool fft2_groups_fit(int nx, int ny) {
+  return nx >= 2 * kGroupM0 && nx <= 2 * kGroupM1 && ny >= 16 && ny <= kGroupN1 && 4096 / nx <= ny;
+}
+
+template <typename T>
+void fft2_group_set(Fft2Group& g, T* real, cplx<T>* spec, int nx, int ny, int np, const Tw2<T>& tw) {
+  if (!fft2_groups_fit(nx, ny)) throw Error(-2, "merged 2-D passes: unsupported grid");
+  check_span(spec2_size<T>(nx, ny), 1, sizeof(cplx<T>));
+  g.real = real;
+  g.spec = spec;
+  g.ny = ny;
+  g.m = nx / 2;
+  g.np = np;
+  g.nbx = ny / (4096 / nx);
+  const int W = 256 / (ny / 8);
+  g.nbl = (g.m + 1 + W - 1) / W;
+  g.base = tw.base;
+  g.twx = tw.x;
+  g.twy = tw.y[0];
+}
+
+template <typename T>
+void fft2_groups(const Fft2Group* host, const Fft2Group* dev, int ng, const int2* items, int nx_items, int ny_items,
+                 hipStream_t s) {
+  if (nx_items <= 0 || ny_items <= 0) return;
+  size_t ldx = 0, ldy = 0;
+  for (int k = 0; k < ng; ++k) {
+    dispatch2(host[k].m, [&](auto Mc) {
+      constexpr int M = decltype(Mc)::value;
+      if constexpr (M >= kGroupM0 && M <= kGroupM1) {
+        constexpr int LR = group_rows_log2<T>(M);
+        ldx = std::max(ldx, (size_t)(X2<T, M>::stride(LR) << LR) * sizeof(cplx<T>));
+      }
+    });
+    dispatch2_line(host[k].ny, [&](auto Nc) {
+      using L = LineShape<T, decltype(Nc)::value, 1, 1>;
+      ldy = std::max(ldy, (size_t)L::W * L::NBUF * L::LP * sizeof(cplx<T>));
+    });
+  }
+  hipLaunchKernelGGL((k2_x_groups<T, false>), dim3((unsigned)nx_items), dim3(256), ldx, s, dev, items);
+  hipLaunchKernelGGL((k2_lines_groups<T>), dim3((unsigned)ny_items), dim3(256), ldy, s, dev, items + nx_items);
+  hipLaunchKernelGGL((k2_x_groups<T, true>), dim3((unsigned)nx_items), dim3(256), ldx, s, dev, items);
+  IBDL_LAUNCH_CHECK();
+}
+
 namespace {
 template <typename T> struct TableLens { int x, y0, y1; };
 template <typename T> TableLens<T> table_lens(int nx, int ny) {
@@ -709,6 +825,8 @@ template <typename T> int fft2_lines_max(int n, int nmax) {
   template size_t fft2_table_len<T>(int, int);                                                                \
   template Tw2<T> fft2_tables<T>(int, int, const cplx<T>*, const cplx<T>*, cplx<T>*, hipStream_t);            \
   template int fft2_rows_max<T>(int);                                                                         \
+  template void fft2_group_set<T>(Fft2Group&, T*, cplx<T>*, int, int, int, const Tw2<T>&);                        \
+  template void fft2_groups<T>(const Fft2Group*, const Fft2Group*, int, const int2*, int, int, hipStream_t);      \
   template int fft2_lines_max<T>(int, int);
 IBDL_FFT2_INST(float)
 IBDL_FFT2_INST(double)

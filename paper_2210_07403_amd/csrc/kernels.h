@@ -192,6 +192,22 @@ void fft2_lines(cplx<T>* data, int n, int no, const MultDesc& md, const Tw2<T>& 
                 int64_t bstride, int w, const RowMask& rm);
 template <typename T> int fft2_rows_max(int nx);
 // most lines per block along y, for passes holding nmax fields at once
+// One grid group of a batch (np problems of an nx x ny grid, one field each) in the merged passes.
+// items: (group, block of the group) per workgroup of the x passes, then of the pass along y
+struct Fft2Group {
+  void* real;
+  void* spec;
+  int ny, m, np;          // m = nx / 2
+  int nbx, nbl;           // blocks of a problem in the x passes, and of the group in the pass along y
+  Rows2 in, out;
+  MultDesc md;
+  const void *base, *twx, *twy;
+};
+bool fft2_groups_fit(int nx, int ny);   // whether a grid can take part
+template <typename T> void fft2_group_set(Fft2Group& g, T* real, cplx<T>* spec, int nx, int ny, int np, const Tw2<T>& tw);
+template <typename T>   // the groups' spread fields -> scalar multiplier -> fields; host: the groups' descriptors
+void fft2_groups(const Fft2Group* host, const Fft2Group* dev, int ng, const int2* items, int nx_items, int ny_items,
+                 hipStream_t s);
 template <typename T> int fft2_lines_max(int n, int nmax);
 
 // ------------------------------------------------------------------ markers, spread, interp
