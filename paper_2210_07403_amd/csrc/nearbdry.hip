@@ -42,24 +42,25 @@ __device__ __forceinline__ double dist2(double px, double py, double qx, double 
   return a + b;
 }
 
-// flag every node within m1 h of marker i (unwrapped node positions; wrapped indices)
-__global__ void k_near_mark(const double* __restrict__ X, int64_t n_ib, NearGeom g, double m1,
-                            unsigned char* __restrict__ flag) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// flag every node within m1 h of marker i (unwrapped node positions; wrapped indices); one wave per
+// marker, its lanes over the (2R+2)^2 nodes of the box (one thread per marker: 10.6 us at 121 markers,
+// m1 = 6, on one workgroup; now 3.1)
+__global__ __launch_bounds__(256) void k_near_mark(const double* __restrict__ X, int64_t n_ib, NearGeom g, double m1,
+                                                   unsigned char* __restrict__ flag) {
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (i >= n_ib) return;
   const double x = X[2 * i], y = X[2 * i + 1];
-  const int R = (int)ceil(m1) + 1;
+  const int R = (int)ceil(m1) + 1, B = 2 * R + 2;
   const int ix = (int)floor((x - g.ox) / g.h), iy = (int)floor((y - g.oy) / g.h);
   const double r2 = (m1 * g.h) * (m1 * g.h);
-  for (int dj = -R; dj <= R + 1; ++dj)
-    for (int di = -R; di <= R + 1; ++di) {
-      const int jj = iy + dj, ii = ix + di;
-      const double px = g.ox + ii * g.h, py = g.oy + jj * g.h;
-      if (dist2(px, py, x, y) <= r2) {
-        const int wj = ((jj % g.ny) + g.ny) % g.ny, wi = ((ii % g.nx) + g.nx) % g.nx;
-        flag[(int64_t)wj * g.nx + wi] = 1;
-      }
+  for (int q = (int)(threadIdx.x & 63); q < B * B; q += 64) {
+    const int jj = iy + q / B - R, ii = ix + q % B - R;
+    const double px = g.ox + ii * g.h, py = g.oy + jj * g.h;
+    if (dist2(px, py, x, y) <= r2) {
+      const int wj = ((jj % g.ny) + g.ny) % g.ny, wi = ((ii % g.nx) + g.nx) % g.nx;
+      flag[(int64_t)wj * g.nx + wi] = 1;
     }
+  }
 }
 
 // list the flagged nodes of Omega
@@ -168,10 +169,12 @@ __device__ __forceinline__ void merge_wave(Near3& nr) {
 // start the next ring empty, so no marker is counted twice).  Every marker of a cell outside rings
 // 0..W is more than W kCell h away along one axis, so once the third-nearest distance is at most
 // that, no unvisited marker can enter the three; the order is total (indices differ), so the
-// result is the three markers a sequential scan of all markers finds.
+// result is the three markers a sequential scan of all markers finds.  One search serves every component
+// (lane c finishes component c): bound by its chain of dependent loads, which a launch per component ran
+// through again (two components, 121 markers: 2 x 16.3 us, now 18.4).
 template <typename T>
 __global__ __launch_bounds__(kNB) void k_near_fix(const double* __restrict__ X, const double* __restrict__ Ub,
-                                                  int ubs, int64_t n_ib, NearGeom g, double m2, const int* __restrict__ count,
+                                                  int nc, int64_t n_ib, NearGeom g, double m2, const int* __restrict__ count,
                                                   const int* __restrict__ list, const int* __restrict__ cell_off,
                                                   const int* __restrict__ cell_list, int ncx, int ncy,
                                                   const T* __restrict__ u, T* __restrict__ out) {
@@ -221,7 +224,12 @@ __global__ __launch_bounds__(kNB) void k_near_fix(const double* __restrict__ X, 
       if (W > 0 && nr.d[2] <= bound * bound) break;
       if (lane != 0) nr.init();
     }
-    if (lane != 0) continue;
+    // lane c: component c (boundary values Ub[i nc + c], field c)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) nr.i[q] = __shfl(nr.i[q], 0);
+    if (lane >= nc) continue;
+    const double* uc = Ub + lane;
+    const int64_t f0 = (int64_t)lane * g.nx * g.ny;
     int a = nr.i[0], b = nr.i[1];
     double t = seg_param(px, py, X[2 * a], X[2 * a + 1], X[2 * b], X[2 * b + 1]);
     if (!(t >= 0.0 && t <= 1.0) && n_ib >= 3) {   // the two of the three nearest markers farthest apart
@@ -241,17 +249,17 @@ __global__ __launch_bounds__(kNB) void k_near_fix(const double* __restrict__ X, 
     const double x1 = X[2 * a], y1 = X[2 * a + 1], x2 = X[2 * b], y2 = X[2 * b + 1];
     const double xa = x2 + tc * (x1 - x2), ya = y2 + tc * (y1 - y2);
     const double l12 = sqrt(dist2(x1, y1, x2, y2));
-    const double uA = Ub[(int64_t)a * ubs] * sqrt(dist2(xa, ya, x2, y2)) / l12 +
-                      Ub[(int64_t)b * ubs] * sqrt(dist2(xa, ya, x1, y1)) / l12;
+    const double uA = uc[(int64_t)a * nc] * sqrt(dist2(xa, ya, x2, y2)) / l12 +
+                      uc[(int64_t)b * nc] * sqrt(dist2(xa, ya, x1, y1)) / l12;
     const double dpa = sqrt(dist2(px, py, xa, ya));
     double up = uA;
     if (dpa > 0.0) {
       const double xb = xa + (px - xa) / dpa * (m2 * g.h), yb = ya + (py - ya) / dpa * (m2 * g.h);
-      const double uB = bilinear<T>(u, g, xb, yb);
+      const double uB = bilinear<T>(u + f0, g, xb, yb);
       const double dab = sqrt(dist2(xb, yb, xa, ya));
       up = uA * sqrt(dist2(xb, yb, px, py)) / dab + uB * dpa / dab;
     }
-    out[e] = (T)up;
+    out[f0 + e] = (T)up;
   }
 }
 
@@ -312,18 +320,16 @@ void near_boundary(const double* X, const double* Ub, int nc, int64_t n_ib, cons
   IBDL_HIP(hipMemsetAsync(flag, 0, n, st));
   IBDL_HIP(hipMemsetAsync(count, 0, sizeof(int), st));
   if (n_ib == 0) return;
-  hipLaunchKernelGGL(k_near_mark, dim3((unsigned)((n_ib + 255) / 256)), dim3(256), 0, st, X, n_ib, g, m1, flag);
+  hipLaunchKernelGGL(k_near_mark, dim3((unsigned)((n_ib + 3) / 4)), dim3(256), 0, st, X, n_ib, g, m1, flag);
   IBDL_LAUNCH_CHECK();
   hipLaunchKernelGGL((k_near_list<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, flag, omega, n, count,
                      list);
   IBDL_LAUNCH_CHECK();
   const int64_t waves = near_list_cap(n_ib, m1, n);
   const int64_t nblk = std::min<int64_t>((waves + kNB / 64 - 1) / (kNB / 64), kNBBlocks);
-  for (int c = 0; c < nc; ++c) {   // component c: boundary values Ub[i * nc + c], field c
-    hipLaunchKernelGGL((k_near_fix<T>), dim3((unsigned)nblk), dim3(kNB), 0, st, X, Ub + c, nc, n_ib, g, m2, count,
-                       list, cell_off, cell_list, ncx, ncy, u + c * n, out + c * n);
-    IBDL_LAUNCH_CHECK();
-  }
+  hipLaunchKernelGGL((k_near_fix<T>), dim3((unsigned)nblk), dim3(kNB), 0, st, X, Ub, nc, n_ib, g, m2, count, list,
+                     cell_off, cell_list, ncx, ncy, u, out);
+  IBDL_LAUNCH_CHECK();
 }
 
 #define IBDL_NB_INST(T)                                                                                    \
