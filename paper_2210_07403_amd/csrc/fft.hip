@@ -71,17 +71,17 @@ __device__ __forceinline__ void line_gstore(const C* v, C* __restrict__ base, un
 // Full line transform on registers v (pattern i + s*T).  All threads of the block must call it
 // (it contains block barriers when N needs more than one stage).  lds: this line's exchange
 // buffer with element stride es; the caller must not rely on its contents afterwards.
-template <int N, bool INV, bool BATCH = false, int RMX = plan_rmax(N), int PAD = 0, int S = 0, typename C>
+template <int N, bool INV, bool BATCH = false, int RMX = plan_rmax(N), int S = 0, typename C>
 __device__ __forceinline__ void fft_line(C* v, int i, C* lds, int es, const C* __restrict__ tw, int tws) {
   if constexpr (S < Plan<N, RMX>::NST) {
     stage_compute<N, S, INV, BATCH, RMX>(v, i, tw, tws);
     if constexpr (S + 1 < Plan<N, RMX>::NST) {
       __syncthreads();
-      stage_store<N, S, RMX, PAD>(v, i, lds, es);
+      stage_store<N, S, RMX>(v, i, lds, es);
       __syncthreads();
-      line_load<N, RMX, PAD>(v, i, lds, es);
+      line_load<N, RMX>(v, i, lds, es);
     }
-    fft_line<N, INV, BATCH, RMX, PAD, S + 1>(v, i, lds, es, tw, tws);
+    fft_line<N, INV, BATCH, RMX, S + 1>(v, i, lds, es, tw, tws);
   }
 }
 

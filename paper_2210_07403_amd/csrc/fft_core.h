@@ -117,11 +117,8 @@ __device__ __forceinline__ void stage_compute(C* v, int i, const C* __restrict__
   }
 }
 
-// LDS slot of line element e: e * es, or, for a contiguous line (es = 1) with PAD > 0, e plus one
-// pad slot every 2^PAD elements, so that a stage's strided stores do not fall into the same banks
-template <int PAD> __device__ __forceinline__ int lslot(int e, int es) { return PAD ? e + (e >> PAD) : e * es; }
-
-template <int N, int S, int RMX, int PAD = 0, typename C>
+// exchange of a line whose elements lie es apart in LDS
+template <int N, int S, int RMX, typename C>
 __device__ __forceinline__ void stage_store(const C* v, int i, C* lds, int es) {
   using P = Plan<N, RMX>;
   constexpr int R = P::radix(S), PP = P::pw(S), NB = P::RMAX / R, TT = P::T;
@@ -130,14 +127,14 @@ __device__ __forceinline__ void stage_store(const C* v, int i, C* lds, int es) {
     const int b = i + m * TT;
     const int k = b & (PP - 1);
 #pragma unroll
-    for (int j = 0; j < R; ++j) lds[lslot<PAD>((b - k) * R + k + j * PP, es)] = v[m + j * NB];
+    for (int j = 0; j < R; ++j) lds[((b - k) * R + k + j * PP) * es] = v[m + j * NB];
   }
 }
 
-template <int N, int RMX, int PAD = 0, typename C>
+template <int N, int RMX, typename C>
 __device__ __forceinline__ void line_load(C* v, int i, const C* lds, int es) {
 #pragma unroll
-  for (int s = 0; s < RMX; ++s) v[s] = lds[lslot<PAD>(i + s * Plan<N, RMX>::T, es)];
+  for (int s = 0; s < RMX; ++s) v[s] = lds[(i + s * Plan<N, RMX>::T) * es];
 }
 
 // element at a byte offset from a launch-uniform base: a scalar base and one 32-bit register per access
