@@ -117,7 +117,8 @@ struct ibdl_s {
   double* hmap_dev = nullptr;
   unsigned seq = 0;
   // the working-precision operator apply (and its transpose) captured in HIP graphs, replayed from
-  // the fixed vectors gx -> gy inside GMRES (rebuilt when the markers change)
+  // the fixed vectors gx -> gy inside GMRES (rebuilt when the markers change, and when the grid arrays
+  // that they were captured with are replaced: ensure_fields)
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t gexec[2] = {nullptr, nullptr};
   double *gx = nullptr, *gy = nullptr;
@@ -125,7 +126,6 @@ struct ibdl_s {
   bool graph_seen[2] = {false, false};   // GRAPH_SECOND: a solve has run with these markers
   void drop_graphs() {
     for (int k = 0; k < 2; ++k) {
-      graph_seen[k] = false;
       if (gexec[k]) (void)hipGraphExecDestroy(gexec[k]);
       if (graph[k]) (void)hipGraphDestroy(graph[k]);
       gexec[k] = nullptr;
@@ -295,10 +295,17 @@ template <typename T> GridWork<T>& ensure_work(ibdl_s* h) {
 template <typename T> GridWork<T>& ensure_fields(ibdl_s* h, int nf) {
   GridWork<T>& W = ensure_work<T>(h);
   if (W.nfields >= nf) return W;
+  // the captured applies hold the arrays that go: the next solve captures them again
+  IBDL_HIP(hipStreamSynchronize(h->st));
+  h->drop_graphs();
   h->dfree(W.real);
   h->dfree(W.spec);
+  W.real = nullptr;
+  W.spec = nullptr;
+  W.nfields = 0;
+  cplx<T>* spec = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * h->nspec<T>() * nf);
   W.real = (T*)h->dalloc<T>(sizeof(T) * h->ntot * nf);
-  W.spec = (cplx<T>*)h->dalloc<T>(sizeof(cplx<T>) * h->nspec<T>() * nf);
+  W.spec = spec;
   W.nfields = nf;
   return W;
 }
@@ -1273,6 +1280,7 @@ void sl_markers(ibdl_s* h) {
 
 void build_markers(ibdl_s* h) {
   h->drop_graphs();
+  h->graph_seen[0] = h->graph_seen[1] = false;
   h->nb_cells_ready = false;
   markers_setup(h->geom, h->cfg.kernel, h->n_ib, h->X, h->s, h->f, h->wt, h->tile_count, h->st);
   markers_bin(h->geom, h->n_ib, h->s, h->tile_count, h->tile_off, h->tile_cur, h->list, h->list_tmp, h->busy,
