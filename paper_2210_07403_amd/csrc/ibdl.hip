@@ -991,6 +991,14 @@ void wait_published(ibdl_s* h, int slot, unsigned seq, double* out) {
   }
 }
 
+// the vectors an apply of a Krylov solver reads (replayed) and writes
+void ensure_gxy(ibdl_s* h) {
+  if (h->gx) return;
+  double* gx = (double*)h->dalloc<double>(sizeof(double) * h->n_aug);
+  h->gy = (double*)h->dalloc<double>(sizeof(double) * h->n_aug);
+  h->gx = gx;
+}
+
 // GMRES applies the working-precision operator (transposed with trans) by replaying a HIP graph
 // captured from direct launches, reading gx and writing gy.  Captures it on first use (or on the
 // second, by graph_mode); returns false when applies are launched directly instead.
@@ -999,10 +1007,6 @@ bool ensure_graph(ibdl_s* h, bool trans) {
   const int64_t n = h->n_aug;
   const int k = trans ? 1 : 0;
   if (h->gexec[k]) return true;
-  if (!h->gx) {
-    h->gx = (double*)h->dalloc<double>(sizeof(double) * n);
-    h->gy = (double*)h->dalloc<double>(sizeof(double) * n);
-  }
   if (h->graph_mode == ibdl_s::GRAPH_SECOND && !h->graph_seen[k]) {
     h->graph_seen[k] = true;
     return false;
@@ -1054,6 +1058,7 @@ int gmres(ibdl_s* h, const double* b, double tol, int maxit, double* x, ibdl_inf
   ensure_partial(h, std::max(nblk * (maxit + 2), anblk * (2 * maxit + 3)));
   *iters = 0;
   *relres = 0.0;
+  ensure_gxy(h);
   const bool graph = ensure_graph(h, trans);
   double* gin = graph ? h->gx : nullptr;
   // |b|^2 (small[GM_BNORM2_AT]) and V[0] = b / |b| (also the graph's input) on the device, so that
@@ -1063,17 +1068,11 @@ int gmres(ibdl_s* h, const double* b, double tol, int maxit, double* x, ibdl_inf
   // queue Arnoldi step j (V[j] is in place, and in gx for the graph): apply, orthogonalise, update
   // the least-squares state, publish it and, in the same launch, normalise w into V[j+1] (and gx)
   auto step = [&](int j) {
-    double* w;
-    if (graph) {
-      IBDL_HIP(hipGraphLaunch(h->gexec[trans ? 1 : 0], h->st));
-      w = h->gy;
-    } else {
-      w = h->V + (int64_t)(j + 1) * n;
-      apply_any(h, h->V + (int64_t)j * n, w, false, trans);
-    }
+    if (graph) IBDL_HIP(hipGraphLaunch(h->gexec[trans ? 1 : 0], h->st));
+    else apply_any(h, h->V + (int64_t)j * n, h->gy, false, trans);
     const int slot = j & 1;
     seq[slot] = ++h->seq;
-    kr_arnoldi_step(h->V, n, j + 1, w, n, h->partial, anblk, h->small, h->gm, mx, tol, h->hmap_dev + slot * GM_REC,
+    kr_arnoldi_step(h->V, n, j + 1, h->gy, n, h->partial, anblk, h->small, h->gm, mx, tol, h->hmap_dev + slot * GM_REC,
                     seq[slot], h->V + (int64_t)(j + 1) * n, gin, h->st);
   };
   step(0);
@@ -1151,11 +1150,8 @@ int minres(ibdl_s* h, const double* b, double tol, int maxit, double* x, ibdl_in
     h->mr_hist_cap = maxit;
   }
   ensure_partial(h, 2 * mr_nblk(n));
+  ensure_gxy(h);
   const bool graph = ensure_graph(h, false);
-  if (!h->gx) {
-    h->gx = (double*)h->dalloc<double>(sizeof(double) * n);
-    h->gy = (double*)h->dalloc<double>(sizeof(double) * n);
-  }
   double *vprev = h->mr, *w1 = h->mr + n, *w2 = h->mr + 2 * n;
   double* st[2] = {h->mr_state, h->mr_state + 16};
   mr_start(b, h->mr_wt, n, tol, h->gx, vprev, w1, w2, x, h->partial, st[0], h->st);

@@ -429,7 +429,7 @@ size_t kr_gmres_state_doubles(int mx);
 int kr_arnoldi_nblk(int64_t n);
 constexpr int kArnoldiOne = 1024;   // longest vectors whose Arnoldi step one workgroup does
 // One Arnoldi step, step k - 1: classical Gram-Schmidt twice on w against V_0..V_{k-1} (w is scratch
-// afterwards unless it is vdst), |w|, the least-squares update in gs (tolerance tol, at most mx <= 256
+// afterwards, and neither vdst nor vdst2), |w|, the least-squares update in gs (tolerance tol, at most mx <= 256
 // steps), vdst (and vdst2 if set) = w / |w| (0 where that is 0 or not finite), the state's record of
 // step number seq to host_dst (device address of host-mapped, coherent pinned memory).  partial: (2 k + 1) * nblk doubles with nblk = kr_arnoldi_nblk(n).
 void kr_arnoldi_step(const double* V, int64_t ldv, int k, double* w, int64_t n, double* partial, int nblk, double* h,

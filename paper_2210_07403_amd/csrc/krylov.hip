@@ -380,10 +380,8 @@ __device__ __forceinline__ void publish_state(const double* gs, double* dst, uns
 //   k_arn0  pout[j][b] = block b's part of V_j . w
 //   k_arn1  h1 = sums of pin (reduced in every workgroup, in the same order), w -= V h1,
 //           pout[j][b] = parts of V_j . w (j < k) and of w . w (j = k)
-//   k_arn2  h2 likewise, w -= V h2, |w|^2 = (w . w before the update) - |h2|^2 (the update takes the
-//           h2 components out of w, so this is its norm to rounding; h2 itself is of the size of the
-//           first pass's rounding), then V_k (and vdst2) = w / |w|; workgroup 0 runs the
-//           least-squares update and publishes the state.
+//   k_arn2  h2 likewise, |w|^2 (arn_norm2), V_k (and vdst2) = (w - V h2) / |w|; workgroup 0 runs the
+//           least-squares update and publishes the state.  w itself stays as k_arn1 left it.
 // What bounds a step at these lengths is the chain of each launch (read what the last launch wrote,
 // fold, write; a vector is a few tens of KB), so it has one launch and two folds fewer than with an LDS
 // tree per eight dots and a norm pass of its own: 20.4 -> 13.6 us a step at 4,096 unknowns (10 basis
@@ -445,11 +443,36 @@ __global__ __launch_bounds__(kB) void k_arn1(const double* __restrict__ V, int64
   }
 }
 
-__global__ __launch_bounds__(kB) void k_arn2(const double* __restrict__ V, int64_t ldv, int k, const double* w, int64_t n,
-                                             int nblk, const double* __restrict__ pin, const double* __restrict__ h1g,
+// |w - V h|^2, h = V . w (hs[0..k), and w . w at hs[k]), for an orthonormal V: the update takes the h
+// components out of w, so this is w . w - |h|^2, and the rounding of that difference stays below a few
+// units in its last place while it is more than half of w . w.  h is what the first pass's rounding left
+// behind, so it always is unless w is at the level of that rounding itself (an invariant Krylov space).
+// There the difference holds no digits and may come out negative, and every workgroup sums the updated
+// entries instead: all n of them, in the same order, so that all have the same bits.
+__device__ __forceinline__ double arn_norm2(const double* __restrict__ V, int64_t ldv, int k, const double* __restrict__ w,
+                                            int64_t n, const double* hs, double* red) {
+  double nrm2 = hs[k];
+  for (int j = 0; j < k; ++j) nrm2 -= hs[j] * hs[j];
+  if (nrm2 > 0.5 * hs[k]) return nrm2;
+  double s = 0.0;
+  for (int64_t e = threadIdx.x; e < n; e += kB) {
+    double x = w[e];
+    for (int j = 0; j < k; ++j) x -= V[(int64_t)j * ldv + e] * hs[j];
+    s += x * x;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off /= 2) s += __shfl_xor(s, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  return ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+__global__ __launch_bounds__(kB) void k_arn2(const double* __restrict__ V, int64_t ldv, int k,
+                                             const double* __restrict__ w, int64_t n, int nblk,
+                                             const double* __restrict__ pin, const double* __restrict__ h1g,
                                              const double* __restrict__ bn2, double* gs, int mx, double tol, double* dst,
-                                             unsigned seq, double* vdst, double* vdst2) {
-  __shared__ double hs[256 + kArnK], h1[256];
+                                             unsigned seq, double* __restrict__ vdst, double* __restrict__ vdst2) {
+  __shared__ double hs[256 + kArnK], h1[256], red[kB / 64];
   __shared__ GivensLds G;
   const int64_t e = (int64_t)blockIdx.x * kArnChunk + threadIdx.x;
   const bool in = e < n;
@@ -461,8 +484,7 @@ __global__ __launch_bounds__(kB) void k_arn2(const double* __restrict__ V, int64
     for (int j = threadIdx.x; j < k; j += kB) h1[j] = h1g[j];
   }
   sum_partials(pin, k + 1, nblk, hs);
-  double nrm2 = hs[k];
-  for (int j = 0; j < k; ++j) nrm2 -= hs[j] * hs[j];
+  const double nrm2 = arn_norm2(V, ldv, k, w, n, hs, red);
   if (blockIdx.x == 0 && threadIdx.x < 64) {
     givens_update(G, h1, hs, nrm2, k - 1, mx, tol, gs);
     publish_state(gs, dst, seq);
@@ -887,6 +909,7 @@ void kr_arnoldi_step(const double* V, int64_t ldv, int k, double* w, int64_t n, 
                      double* gs, int mx, double tol, double* host_dst, unsigned seq, double* vdst, double* vdst2,
                      hipStream_t st) {
   if (k < 1 || k > mx || mx > 256) throw Error(-2, "Arnoldi step: 1 <= k <= mx <= 256");
+  if (w == vdst || w == vdst2) throw Error(-2, "Arnoldi step: w must not be one of its outputs");
   const double* bn2 = h + GM_BNORM2_AT;
   // One workgroup while two entries per thread hold the vectors (9.4 us a step at 269 unknowns, 13.6 for
   // the three launches); beyond that the basis vectors' reads want more than one CU.
