@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "gm_record.h"
 
 namespace ibdl {
 
@@ -406,23 +407,7 @@ int kr_nblk(int64_t n);
 // uses), GM_DONE (1 once res <= tol or the process broke down: later steps leave the state alone),
 // GM_HN (|w| of the last step), then the rotations, the rotated right-hand side, the solution y and
 // the rotated Hessenberg columns.  The first GM_PUB scalars are what a step publishes to the host.
-enum { GM_BETA = 0, GM_RES = 1, GM_K = 2, GM_DONE = 3, GM_HN = 4, GM_PUB = 5, GM_HDR = 16 };
-// A published record: the GM_PUB scalars and a check word, the exclusive or of their bits and of a key
-// made of the step's sequence number.  The words may reach the host in any order: it takes the record
-// once the check word fits (a word of an earlier step fits only if it equals the new one), so the
-// device waits for no fence.
-constexpr int GM_REC = 8;   // doubles per record (64 bytes)
-__host__ __device__ inline unsigned long long gm_pub_key(unsigned seq) { return (seq + 1ull) * 0x9E3779B97F4A7C15ull; }
-inline bool gm_pub_read(const volatile double* rec, unsigned seq, double* out) {
-  unsigned long long c = gm_pub_key(seq), w;
-  for (int i = 0; i <= GM_PUB; ++i) {
-    const double v = rec[i];
-    __builtin_memcpy(&w, &v, 8);
-    c ^= w;
-    if (i < GM_PUB) out[i] = v;
-  }
-  return c == 0;
-}
+// (gm_record.h)
 // the Arnoldi scratch h holds the first Gram-Schmidt pass at [0, 256) and |b|^2 at GM_BNORM2_AT
 constexpr int GM_BNORM2_AT = 520;
 size_t kr_gmres_state_doubles(int mx);

@@ -357,7 +357,7 @@ __device__ __forceinline__ void givens_update(GivensLds& G, const double* h1, co
   for (int i = lane; i <= j; i += 64) R[i] = G.col[i];
 }
 
-// By the wave that ran givens_update: the state's record to host-mapped memory (see GM_REC)
+// By the wave that ran givens_update: the state's record to host-mapped memory (gm_record.h)
 __device__ __forceinline__ void publish_state(const double* gs, double* dst, unsigned seq) {
   __threadfence_block();
   const int lane = threadIdx.x & 63;
@@ -366,7 +366,7 @@ __device__ __forceinline__ void publish_state(const double* gs, double* dst, uns
     const double v = *const_cast<const volatile double*>(gs + lane);
     w = __builtin_bit_cast(unsigned long long, v);
   }
-  unsigned long long c = w;
+  unsigned long long c = lane < GM_PUB ? gm_pub_mix(w, lane) : 0;
 #pragma unroll
   for (int off = 1; off < 8; off *= 2) c ^= __shfl_xor(c, off);
   if (lane == GM_PUB) w = c ^ gm_pub_key(seq);
