@@ -232,12 +232,12 @@ __global__ void k_wtab(const double* __restrict__ wt, int64_t n_ib, cplx<T>* __r
 }
 
 // busy tiles along x of each listed row as a bit mask of seg_row_words words: bit t & 63 of word t >> 6
-// for tile (t, strip of the row), t < ntx; one thread per row and word
-__global__ void k_row_segments(MarkerGeom g, const int* __restrict__ tile_off, const int* __restrict__ rows,
-                               int64_t nact, unsigned long long* __restrict__ seg) {
+// for tile (t, strip of the row), t < ntx; one thread per row and word (its mask returned, 0 past the last)
+__device__ __forceinline__ unsigned long long row_segments(const MarkerGeom& g, const int* __restrict__ tile_off,
+                                                           const int* __restrict__ rows, int64_t nact, int64_t e,
+                                                           unsigned long long* __restrict__ seg) {
   const int nw = seg_row_words(g);
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nact * nw) return;
+  if (e >= nact * nw) return 0;
   const int64_t r = e / nw;
   const int t0 = 64 * (int)(e - r * nw);
   const int w = rows ? rows[r] : (int)r, y = w % g.n[1], z = w / g.n[1];
@@ -250,6 +250,37 @@ __global__ void k_row_segments(MarkerGeom g, const int* __restrict__ tile_off, c
   for (int t = 0; t < nt; ++t)
     if (off[t + 1] > off[t]) m |= 1ull << t;
   seg[e] = m;
+  return m;
+}
+__global__ __launch_bounds__(256) void k_row_segments(MarkerGeom g, const int* __restrict__ tile_off,
+                                                      const int* __restrict__ rows, int64_t nact,
+                                                      unsigned long long* __restrict__ seg) {
+  row_segments(g, tile_off, rows, nact, (int64_t)blockIdx.x * 256 + threadIdx.x, seg);
+}
+// The masks of every row, and the number of bits set in those of the active rows (lim) to *host, pinned:
+// the workgroups add (1 above, their bits below) to *count, and the last one has the sum.
+__global__ __launch_bounds__(256) void k_all_row_segments(MarkerGeom g, const int* __restrict__ tile_off, int64_t nrows,
+                                                          const int2* __restrict__ lim, unsigned long long* __restrict__ seg,
+                                                          unsigned long long* count, int* __restrict__ host) {
+  __shared__ int red[4];
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const unsigned long long m = row_segments(g, tile_off, nullptr, nrows, e, seg);
+  int c = 0;
+  if (m) {
+    const int64_t r = e / seg_row_words(g);
+    const int y = (int)(r % g.n[1]);
+    const int2 l = lim[r / g.n[1]];
+    if (y >= l.x && y <= l.y) c = __popcll(m);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned long long mine = (1ull << 32) + (unsigned)(red[0] + red[1] + red[2] + red[3]);
+    const unsigned long long sum = atomicAdd(count, mine) + mine;
+    if ((unsigned)(sum >> 32) == gridDim.x) *host = (int)(sum & 0xffffffffu);
+  }
 }
 
 // The busy tiles in decreasing order of their candidate count (ties by tile id): the spread's
@@ -1096,8 +1127,10 @@ __global__ __launch_bounds__(256) void k_interp_div(InterpArgs a, const cplx<T>*
 // ------------------------------------------------------------------ active rows
 // Rows y of plane z that a marker's 6-node window meets: [s_y, s_y + 5] for z in [s_z, s_z + 5]
 // (mod n); a window that wraps around y marks the whole plane.
-__global__ void k_rows_init(int* __restrict__ lo, int* __restrict__ hi, int nplanes, int ny) {
+__global__ void k_rows_init(int* __restrict__ lo, int* __restrict__ hi, int nplanes, int ny,
+                            unsigned long long* __restrict__ count) {
   const int z = blockIdx.x * blockDim.x + threadIdx.x;
+  if (z == 0) *count = 0;
   if (z < nplanes) {
     lo[z] = ny;
     hi[z] = -1;
@@ -1399,9 +1432,10 @@ void markers_row_segments(const MarkerGeom& g, const int* tile_off, const int* r
 }
 
 void markers_rows(const MarkerGeom& g, int64_t n_ib, const int* s, int* lo, int* hi, int* cnt, int* off, int2* lim,
-                  int* rows, const int* nbusy, int* host, hipStream_t st) {
+                  int* rows, const int* nbusy, const int* tile_off, unsigned long long* seg, unsigned long long* count,
+                  int* host, hipStream_t st) {
   const int nplanes = g.dim == 3 ? g.n[2] : 1;
-  hipLaunchKernelGGL(k_rows_init, dim3((nplanes + 255) / 256), dim3(256), 0, st, lo, hi, nplanes, g.n[1]);
+  hipLaunchKernelGGL(k_rows_init, dim3((nplanes + 255) / 256), dim3(256), 0, st, lo, hi, nplanes, g.n[1], count);
   IBDL_LAUNCH_CHECK();
   if (n_ib > 0)
     hipLaunchKernelGGL(k_rows_mark, dim3((unsigned)((n_ib + 255) / 256)), dim3(256), sizeof(int) * 2 * nplanes, st,
@@ -1410,6 +1444,10 @@ void markers_rows(const MarkerGeom& g, int64_t n_ib, const int* s, int* lo, int*
   hipLaunchKernelGGL(k_rows_count, dim3(1), dim3(1024), 0, st, lo, hi, nplanes, cnt, off, lim, nbusy, host);
   IBDL_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_rows_list, dim3(nplanes), dim3(256), 0, st, lo, cnt, off, nplanes, g.n[1], rows);
+  IBDL_LAUNCH_CHECK();
+  const int64_t nrows = (int64_t)g.n[1] * nplanes;
+  hipLaunchKernelGGL(k_all_row_segments, dim3((unsigned)((nrows * seg_row_words(g) + 255) / 256)), dim3(256), 0, st, g,
+                     tile_off, nrows, lim, seg, count, host + 2 + 2 * nplanes);
   IBDL_LAUNCH_CHECK();
 }
 

@@ -87,6 +87,7 @@ struct ibdl_s {
   int nbusy = 0;
   unsigned long long* seg = nullptr;       // 3-D: busy x-segments of each active row (RowList::seg)
   unsigned long long* seg_all = nullptr;   // busy x-segments of every row of a field
+  unsigned long long* seg_count = nullptr; // scratch of markers_rows
   int seg_words = 1;                       // 64-bit words of a row's segments
   // active rows (rows of the markers' windows): list for the x passes, per-plane limits for y
   int *row_lo = nullptr, *row_hi = nullptr, *row_cnt = nullptr, *row_off = nullptr, *rows = nullptr;
@@ -1284,7 +1285,7 @@ void build_markers(ibdl_s* h) {
   const int ntile = h->geom.ntile[0] * h->geom.ntile[1] * h->geom.ntile[2];
   const int nplanes = h->dim == 3 ? h->n[2] : 1;
   markers_rows(h->geom, h->n_ib, h->s, h->row_lo, h->row_hi, h->row_cnt, h->row_off, h->row_lim, h->rows,
-               h->busy_off + ntile, h->minfo, h->st);
+               h->busy_off + ntile, h->tile_off, h->seg_all, h->seg_count, h->minfo, h->st);
   IBDL_HIP(hipStreamSynchronize(h->st));
   const int nb = h->minfo[0], na = h->minfo[1];
   const int2* lim = reinterpret_cast<const int2*>(h->minfo + 2);
@@ -1302,10 +1303,9 @@ void build_markers(ibdl_s* h) {
       h->zlim[0] = std::min(h->zlim[0], z);
       h->zlim[1] = std::max(h->zlim[1], z);
     }
-  // busy x-segments of the rows (of the active rows, too, where the x passes run over a list of them)
+  // busy x-segments of the active rows, where the x passes run over a list of them
   if (h->dim == 3) markers_row_segments(h->geom, h->tile_off, h->rows, na, h->seg, h->st);
-  markers_row_segments(h->geom, h->tile_off, nullptr, (int64_t)h->n[1] * nplanes, h->seg_all, h->st);
-  h->seg_read = -1;
+  h->seg_read = h->minfo[2 + 2 * nplanes];
   if (h->w32 && h->w32->wtab) weight_table<float>(h->wt, h->n_ib, h->w32->wtab, h->st);
   if (h->w64 && h->w64->wtab) weight_table<double>(h->wt, h->n_ib, h->w64->wtab, h->st);
 }
@@ -1562,6 +1562,7 @@ ibdl_status_t ibdl_create(const ibdl_config_t* cfg, int64_t n_ib, const double* 
     h->seg_words = seg_row_words(g);
     if (h->dim == 3) h->seg = (unsigned long long*)h->dalloc<unsigned long long>(nseg);
     h->seg_all = (unsigned long long*)h->dalloc<unsigned long long>(nseg * h->seg_words);
+    h->seg_count = (unsigned long long*)h->dalloc<unsigned long long>(sizeof(unsigned long long));
     h->small = (double*)h->dalloc<double>(sizeof(double) * 1024);
     h->vb = (double*)h->dalloc<double>(sizeof(double) * h->n_aug);
     h->vr = (double*)h->dalloc<double>(sizeof(double) * h->n_aug);
@@ -1570,7 +1571,7 @@ ibdl_status_t ibdl_create(const ibdl_config_t* cfg, int64_t n_ib, const double* 
                            hipHostMallocMapped | hipHostMallocCoherent));
     IBDL_HIP(hipHostGetDevicePointer((void**)&h->hmap_dev, h->hmap, 0));
     memset(h->hmap, 0, sizeof(double) * kHmap);
-    IBDL_HIP(hipHostMalloc((void**)&h->minfo, sizeof(int) * (2 + 2 * nplanes), hipHostMallocMapped | hipHostMallocCoherent));
+    IBDL_HIP(hipHostMalloc((void**)&h->minfo, sizeof(int) * (3 + 2 * nplanes), hipHostMallocMapped | hipHostMallocCoherent));
     IBDL_HIP(hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
     IBDL_HIP(hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming));
     IBDL_HIP(hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming));
@@ -2079,25 +2080,11 @@ ibdl_status_t ibdl_active_span(ibdl_t h, int32_t* first, int32_t* last) {
 
 ibdl_status_t ibdl_spread_tiles(ibdl_t h, int64_t* nbusy, int64_t* segments_read, int32_t* tile) {
   if (!h) return IBDL_ERR_ARG;
-  return guarded(h, [&]() {
-    if (segments_read && h->seg_read < 0) {   // counted at the first question after the markers changed
-      const bool d3 = h->dim == 3;
-      const int64_t nw = d3 ? h->nact : h->nact * h->seg_words;
-      std::vector<unsigned long long> seg(nw);
-      if (nw > 0)
-        IBDL_HIP(hipMemcpyAsync(seg.data(), d3 ? h->seg : h->seg_all + (int64_t)h->lim2d[0] * h->seg_words,
-                                sizeof(unsigned long long) * nw, hipMemcpyDeviceToHost, h->st));
-      IBDL_HIP(hipStreamSynchronize(h->st));
-      int64_t cnt = 0;
-      for (unsigned long long m : seg) cnt += __builtin_popcountll(m);
-      h->seg_read = cnt;
-    }
-    if (nbusy) *nbusy = h->nbusy;
-    if (segments_read) *segments_read = h->seg_read;
-    if (tile)
-      for (int d = 0; d < 3; ++d) tile[d] = h->geom.tile[d];
-    return IBDL_OK;
-  });
+  if (nbusy) *nbusy = h->nbusy;
+  if (segments_read) *segments_read = h->seg_read;
+  if (tile)
+    for (int d = 0; d < 3; ++d) tile[d] = h->geom.tile[d];
+  return IBDL_OK;
 }
 
 ibdl_status_t ibdl_launch_shape(ibdl_t h, int32_t* rows_per_block, int32_t* lines_y, int32_t* lines_last) {

@@ -245,10 +245,12 @@ void markers_list_offsets(const MarkerGeom& g, const int4* busy, int nbusy, cons
 
 // Active rows of the markers' windows: lo/hi [planes] (scratch), cnt/off [planes + 1] (scratch),
 // lim [planes] = (lo, hi) per plane, rows = the row list (up to ny * planes entries), increasing;
-// the count is off[planes].  planes = nz in 3-D, 1 in 2-D.  host [2 + 2 planes] (pinned) receives
-// *nbusy, the count and lim.
+// the count is off[planes].  planes = nz in 3-D, 1 in 2-D.  seg: the busy segments of every row
+// (markers_row_segments).  host [3 + 2 planes] (pinned) receives *nbusy, the count, lim and the number of
+// busy segments of the active rows (count: scratch).
 void markers_rows(const MarkerGeom& g, int64_t n_ib, const int* s, int* lo, int* hi, int* cnt, int* off, int2* lim,
-                  int* rows, const int* nbusy, int* host, hipStream_t st);
+                  int* rows, const int* nbusy, const int* tile_off, unsigned long long* seg, unsigned long long* count,
+                  int* host, hipStream_t st);
 // seg[r][seg_row_words(g)] = bit mask of the busy tiles along x that listed row r (rows[r], r < nact;
 // row r itself when rows is NULL) passes through
 void markers_row_segments(const MarkerGeom& g, const int* tile_off, const int* rows, int64_t nact,
