@@ -16,6 +16,10 @@ struct LaunchShape {
   int pz = 0;    // radix plan of the single-field last-axis pass
 };
 
+// Revision of the kernels that the measurements time (the FFT passes, the 2-D spread): raised whenever one
+// of them changes, so that shapes measured on its predecessor are measured again.
+constexpr int kTuneKernels = 2;
+
 // (kind, dim, n0, n1, n2, bytes per value, fields, size bucket); kinds 10 and above: the passes over
 // transposed 2-D spectra
 using TuneKey = std::array<int, 8>;

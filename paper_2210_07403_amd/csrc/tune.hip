@@ -5,11 +5,13 @@
 // $XDG_CACHE_HOME/ibdl/tune.json or $HOME/.cache/ibdl/tune.json.  Layout, one entry per line:
 //   {"format": "ibdl-tune-3", "device": "<arch> <CUs>",
 //    "entries": [
-//     {"key": [k0, ..., k7], "rpb": r, "wy": y, "wz": z, "tile": t, "blocks": b, "py": p, "pz": q},
+//     {"kernels": v, "key": [k0, ..., k7], "rpb": r, "wy": y, "wz": z, "tile": t, "blocks": b, "py": p,
+//      "pz": q},
 //     ...
 //    ]}
 // A file written for another device, or one that does not parse, is ignored (and replaced at the next
-// measurement).  Failures to read or write the file are not errors: the cache only saves time.
+// measurement), and so are entries timed on other kernels (kTuneKernels).  Failures to read or write the
+// file are not errors: the cache only saves time.
 #include <hip/hip_runtime.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -70,12 +72,13 @@ void load_locked() {
     if (!device_ok) break;
     TuneKey k{};
     LaunchShape v;
+    int kernels = 0;
     const int n = sscanf(line,
-                         " {\"key\": [%d, %d, %d, %d, %d, %d, %d, %d], \"rpb\": %d, \"wy\": %d, \"wz\": %d, \"tile\": %d, "
-                         "\"blocks\": %d, \"py\": %d, \"pz\": %d}",
-                         &k[0], &k[1], &k[2], &k[3], &k[4], &k[5], &k[6], &k[7], &v.rpb, &v.wy, &v.wz, &v.tile, &v.blocks,
-                         &v.py, &v.pz);
-    if (n == 15) got[k] = v;
+                         " {\"kernels\": %d, \"key\": [%d, %d, %d, %d, %d, %d, %d, %d], \"rpb\": %d, \"wy\": %d, "
+                         "\"wz\": %d, \"tile\": %d, \"blocks\": %d, \"py\": %d, \"pz\": %d}",
+                         &kernels, &k[0], &k[1], &k[2], &k[3], &k[4], &k[5], &k[6], &k[7], &v.rpb, &v.wy, &v.wz, &v.tile,
+                         &v.blocks, &v.py, &v.pz);
+    if (n == 16 && kernels == kTuneKernels) got[k] = v;
   }
   fclose(f);
   if (device_ok)
@@ -96,10 +99,10 @@ void save_locked() {
     const TuneKey& k = kv.first;
     const LaunchShape& v = kv.second;
     fprintf(f,
-            "  {\"key\": [%d, %d, %d, %d, %d, %d, %d, %d], \"rpb\": %d, \"wy\": %d, \"wz\": %d, \"tile\": %d, "
-            "\"blocks\": %d, \"py\": %d, \"pz\": %d}%s\n",
-            k[0], k[1], k[2], k[3], k[4], k[5], k[6], k[7], v.rpb, v.wy, v.wz, v.tile, v.blocks, v.py, v.pz,
-            ++i < g_reg.size() ? "," : "");
+            "  {\"kernels\": %d, \"key\": [%d, %d, %d, %d, %d, %d, %d, %d], \"rpb\": %d, \"wy\": %d, \"wz\": %d, "
+            "\"tile\": %d, \"blocks\": %d, \"py\": %d, \"pz\": %d}%s\n",
+            kTuneKernels, k[0], k[1], k[2], k[3], k[4], k[5], k[6], k[7], v.rpb, v.wy, v.wz, v.tile, v.blocks, v.py,
+            v.pz, ++i < g_reg.size() ? "," : "");
   }
   fprintf(f, " ]}\n");
   const bool ok = fclose(f) == 0;
