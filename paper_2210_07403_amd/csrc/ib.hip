@@ -717,18 +717,24 @@ __global__ __launch_bounds__(64 * NW, 8) void k_spread3f(SpreadArgs a, const cpl
 // 2-D: a tile of TX x TY nodes (TX TY = 256, TY = 4 (64 / TX) rows); lane (x, y-group) owns
 // y = 4 yg + j' (j' < 4).  Wave w takes candidates w, w + 4, ... of the tile's list, LW at a time: 64 / LW
 // lanes copy a candidate's x and y weight rows to LDS, the first of them keeps its window start and
-// coefficients, which are broadcast; a node's taps are picked by index (6 and 7 are zero).  The rows
-// are copied as they are, so everything a candidate needs is loaded at once behind its list entry:
-// the launch is a chain of dependent loads (tile, list entry, marker), a few candidates' work per wave,
-// and the sum over the waves.  (The y rows had been aligned to the tile as they were staged, one more
-// dependent load and 48 KiB of LDS in double, then copied by one lane per candidate, sixteen loads each
-// and 34 KiB: five Stokes fields on 95 tiles 6.7 -> 5.4 us with several lanes and 17 KiB, on the 774 tiles
-// of a 4096^2 array 9.7 -> 7.8 us, the tiles of a 30-problem batch 22.2 -> 18.2 -> 14.2 us.)
-// s_w is the caller's LDS, [4][LW][17] (T, T) pairs (one
-// of padding, so that the lanes' copies fall into different banks).
+// coefficients, which are broadcast; a node's taps are picked by index.  The rows are copied as they are,
+// so everything a candidate needs is loaded at once behind its list entry (which is read a round ahead): the
+// launch is a chain of dependent loads (tile, list entry, marker), a few candidates' work per wave, and the
+// sum over the waves.  (The y rows had been aligned to the tile as they were staged, one more dependent load
+// and 48 KiB of LDS in double, then copied by one lane per candidate, sixteen loads each and 34 KiB: five
+// Stokes fields on 95 tiles 6.7 -> 5.4 us with several lanes, on the 774 tiles of a 4096^2 array 9.7 -> 7.8 us,
+// the tiles of a 30-problem batch 22.2 -> 18.2 -> 14.2 us.)
+// s_w is the caller's LDS, [4][LW][kSpreadRow] (W, G) pairs: a candidate's x taps at 0 .. 5, its y taps at
+// 9 .. 14, zeros between and after, so that a lane's four y nodes are four neighbouring pairs of one clamped
+// index.  On crowded tiles a candidate's instructions are what counts: 24,000 markers on a ring of a 512^2
+// grid (28 to a cell's length) took 57 us in double and 44 in single precision with aligned rows, 54 and 49
+// with an index for each y node, and take 43 and 34 with one index and two candidates at a time; 1,600
+// markers 8.8 and 8.2, 8.0 and 8.0, 7.5 and 7.2.  Single precision with several fields gains nothing from
+// the pairs and takes its candidates one by one.
+constexpr int kSpreadRow = 19;
 template <typename T, int NF, int TX>
 __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>* __restrict__ wtab, T* __restrict__ out,
-                                             const int4 bt, cplx<T> (*s_w)[spread_lanes<T>()][17]) {
+                                             const int4 bt, cplx<T> (*s_w)[spread_lanes<T>()][kSpreadRow]) {
   using T2 = cplx<T>;
   constexpr int LW = spread_lanes<T>();
   constexpr int TY = 256 / TX;
@@ -752,6 +758,14 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
     for (int c = 0; c < NF; ++c) acc[j][c] = 0;
   const int beg = bt.y, end = bt.z;
   const double hD = g.h * g.h;
+  constexpr int NP = 64 / LW, NW = 16 / NP;   // lanes per candidate, weights copied by each
+  const int cd = lane % LW, part = lane / LW;
+  static_assert(NW <= 8, "a lane copies taps of one axis");
+  T2* mine = &s_w[wave][cd][part * NW + (part * NW >= 8 ? 1 : 0)];
+  if (part == 0) s_w[wave][cd][8] = mk<T2>((T)0, (T)0);
+  if (part == 1) s_w[wave][cd][17] = s_w[wave][cd][18] = mk<T2>((T)0, (T)0);
+  const int at = beg + 4 * cd + wave;
+  int m_next = at < end ? a.list[at] : -1;   // a list entry is read a round ahead
   for (int c0 = beg; c0 < end; c0 += 4 * LW) {
     const int left = end - c0 - wave;
     const int cnt = left <= 0 ? 0 : ((left + 3) / 4 < LW ? (left + 3) / 4 : LW);
@@ -759,10 +773,9 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
     T cf[5];
 #pragma unroll
     for (int c = 0; c < 5; ++c) cf[c] = 0;
-    constexpr int NP = 64 / LW, NW = 16 / NP;   // lanes per candidate, weights copied by each
-    const int cd = lane % LW, part = lane / LW;
-    if (cd < cnt) {
-      const int m = a.list[c0 + 4 * cd + wave];
+    const int m = m_next, an = c0 + 4 * (LW + cd) + wave;
+    m_next = an < end ? a.list[an] : -1;
+    if (m >= 0) {
       const T2* row = wtab + (int64_t)m * 24 + part * NW;
       T2 w[NW];
 #pragma unroll
@@ -774,17 +787,19 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
 #pragma unroll
       for (int c = 0; c < 5; ++c) cf[c] = (T)c8[c];
 #pragma unroll
-      for (int t = 0; t < NW; ++t) s_w[wave][cd][part * NW + t] = w[t];
+      for (int t = 0; t < NW; ++t) mine[t] = w[t];
     }
     // (each wave reads its own rows only)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    for (int j = 0; j < cnt; ++j) {
-      const int bx = bcast(sx, j), by = y0 + 4 * yg - bcast(sy, j);
-      const T2 xv = s_w[wave][j][min((x0 + lx - bx) & mx, 6)];
-      T2 yv[4];
+    auto taps = [&](int j, T2& xv, T2 (&yv)[4]) {
+      // node - window start: taps 0 .. 5 of x, rows -3 .. 5 of the lane's first y node
+      xv = s_w[wave][j][min((x0 + lx - bcast(sx, j)) & mx, 6)];
+      const T2* yp = &s_w[wave][j][6 + min((y0 + 4 * yg + 3 - bcast(sy, j)) & my, 9)];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) yv[q] = s_w[wave][j][8 + min((by + q) & my, 6)];
+      for (int q = 0; q < 4; ++q) yv[q] = yp[q];
+    };
+    auto add = [&](int j, const T2& xv, const T2 (&yv)[4]) {
       if (fddiv) {
         // v = c_x G_x W_y + c_y W_x G_y + c_mass W_x W_y
         const T ax = bcast(cf[0], j) * xv.y + bcast(cf[3], j) * xv.x, ay = bcast(cf[1], j) * xv.x;
@@ -800,6 +815,22 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
           }
         }
       }
+    };
+    int j = 0;
+    if constexpr (NF == 1 || sizeof(T) == 8) {   // two at a time: the second's taps arrive while the first is summed
+      for (; j + 1 < cnt; j += 2) {
+        T2 xa, ya[4], xb, yb[4];
+        taps(j, xa, ya);
+        taps(j + 1, xb, yb);
+        __builtin_amdgcn_sched_barrier(0);
+        add(j, xa, ya);
+        add(j + 1, xb, yb);
+      }
+    }
+    for (; j < cnt; ++j) {
+      T2 xa, ya[4];
+      taps(j, xa, ya);
+      add(j, xa, ya);
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -831,7 +862,7 @@ __device__ __forceinline__ void spread2_tile(const SpreadArgs& a, const cplx<T>*
 
 template <typename T, int NF>
 __global__ __launch_bounds__(256) void k_spread2(SpreadArgs a, const cplx<T>* __restrict__ wtab, T* __restrict__ out) {
-  __shared__ cplx<T> s_w[4][spread_lanes<T>()][17];
+  __shared__ cplx<T> s_w[4][spread_lanes<T>()][kSpreadRow];
   spread2_tile<T, NF, kT2X>(a, wtab, out, a.busy[blockIdx.x], s_w);
 }
 
@@ -844,7 +875,7 @@ __global__ __launch_bounds__(256) void k_spread2(SpreadArgs a, const cplx<T>* __
 template <typename T>
 __global__ __launch_bounds__(256) void k_spread2_queue(const SpreadGroup* __restrict__ gd, const int2* __restrict__ items,
                                                        int nitems, const double* __restrict__ qbase) {
-  __shared__ cplx<T> s_w[4][spread_lanes<T>()][17];
+  __shared__ cplx<T> s_w[4][spread_lanes<T>()][kSpreadRow];
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 gi = items[it];
     const int gsel = __builtin_amdgcn_readfirstlane(gi.x);

@@ -18,7 +18,7 @@ struct LaunchShape {
 
 // Revision of the kernels that the measurements time (the FFT passes, the 2-D spread): raised whenever one
 // of them changes, so that shapes measured on its predecessor are measured again.
-constexpr int kTuneKernels = 2;
+constexpr int kTuneKernels = 3;
 
 // (kind, dim, n0, n1, n2, bytes per value, fields, size bucket); kinds 10 and above: the passes over
 // transposed 2-D spectra
