@@ -990,21 +990,14 @@ __global__ __launch_bounds__(256) void k_interp(InterpArgs a, const T* __restric
 
 // 4-point kernels: a group of RL = 4^(D-1) lanes per marker, lane r of the group sums the 4 x-taps of
 // stencil row r of each of the nf <= NF fields (every field's loads issued before the first sum); the
-// row sums are reduced across the group by a fixed butterfly (deterministic).  ADJ: lane 0 combines the
-// fields into the transposed operator's marker values instead of storing them.  (Latency-bound: with the
-// border sums and the combination in its launch, a 1024^2 Stokes apply went from 56.3 to 50.6 us and a
-// 512^2 Stokes adjoint step lost three launches of 1.8 to 4.6 us.)
-template <typename T, int D, int NF, bool ADJ>
-__global__ __launch_bounds__(256) void k_interp4(InterpArgs a, AdjArgs ad, const cplx<T>* __restrict__ wtab,
-                                                 const T* __restrict__ u, double* __restrict__ out, int nmain,
-                                                 BorderArgs bd) {
+// row sums are reduced across the group by a fixed butterfly (deterministic).  Workgroup b of nmain; the
+// group's lane 0 calls done(i, v) with marker i's sums.
+template <typename T, int D, int NF, typename F>
+__device__ __forceinline__ void interp4_block(const InterpArgs& a, const cplx<T>* __restrict__ wtab,
+                                              const T* __restrict__ u, int b, int nmain, F&& done) {
   constexpr int RL = (D == 3) ? 16 : 4;
-  if ((int)blockIdx.x >= nmain) {
-    border_block(bd, (int)blockIdx.x - nmain);
-    return;
-  }
   // XCD-contiguous marker ranges: markers close in index share grid lines, so they share an L2
-  const int64_t gid = (int64_t)xcd_chunk(blockIdx.x, nmain) * blockDim.x + threadIdx.x;
+  const int64_t gid = (int64_t)xcd_chunk(b, nmain) * 256 + threadIdx.x;
   const int64_t i = gid / RL;
   const int r = (int)(gid % RL);
   const bool valid = i < a.n_ib;
@@ -1028,30 +1021,64 @@ __global__ __launch_bounds__(256) void k_interp4(InterpArgs a, AdjArgs ad, const
   T v[NF];
 #pragma unroll
   for (int c = 0; c < NF; ++c) {
-    const T* uc = u + (c < a.nf ? c : 0) * ntot + base;
+    const T* uc = u + (NF > 1 && c < a.nf ? c : 0) * ntot + base;
     v[c] = ((uc[ix[0]] * wx[0] + uc[ix[1]] * wx[1]) + uc[ix[2]] * wx[2] + uc[ix[3]] * wx[3]) * wyz;
   }
 #pragma unroll
   for (int c = 0; c < NF; ++c)
 #pragma unroll
     for (int off = 1; off < RL; off <<= 1) v[c] += __shfl_xor(v[c], off, RL);
-  if (!valid || r != 0) return;
-  if constexpr (ADJ) {
-    double G[NF];
+  if (valid && r == 0) done(i, v);
+}
+template <typename T, int NF> __device__ __forceinline__ void interp4_store(const InterpArgs& a, int64_t i, const T (&v)[NF],
+                                                                            double* __restrict__ out) {
 #pragma unroll
-    for (int c = 0; c < NF; ++c) G[c] = (double)v[c];
-    adj_marker(ad, i, a.nf, G, out);
-  } else {
-#pragma unroll
-    for (int c = 0; c < NF; ++c) {
-      if (c < a.nf) {
-        double o = a.a * (double)v[c];
-        if (a.x) o += a.b * a.x[i * a.nf + c];
-        if (a.ub) o += a.ub[c];
-        out[i * a.nf + c] = o;
-      }
+  for (int c = 0; c < NF; ++c) {
+    if (NF == 1 || c < a.nf) {
+      double o = a.a * (double)v[c];
+      if (a.x) o += a.b * a.x[i * a.nf + c];
+      if (a.ub) o += a.ub[c];
+      out[i * a.nf + c] = o;
     }
   }
+}
+
+template <typename T, int D, int NF>
+__global__ __launch_bounds__(256) void k_interp4(InterpArgs a, const cplx<T>* __restrict__ wtab, const T* __restrict__ u,
+                                                 double* __restrict__ out) {
+  interp4_block<T, D, NF>(a, wtab, u, blockIdx.x, gridDim.x,
+                          [&](int64_t i, const T (&v)[NF]) { interp4_store<T, NF>(a, i, v, out); });
+}
+// With border sums in further workgroups, a kernel of its own: the branch in front cost the others half a
+// microsecond (18,500 markers in 3-D).  Latency-bound: with the border sums and the adjoint's combination in
+// the interpolation's launch, a 1024^2 Stokes apply went from 56.3 to 50.6 us and a 512^2 Stokes adjoint step
+// lost three launches of 1.8 to 4.6 us.
+template <typename T, int D, int NF>
+__global__ __launch_bounds__(256) void k_interp4_border(InterpArgs a, const cplx<T>* __restrict__ wtab,
+                                                        const T* __restrict__ u, double* __restrict__ out, int nmain,
+                                                        BorderArgs bd) {
+  if ((int)blockIdx.x >= nmain) {
+    border_block(bd, (int)blockIdx.x - nmain);
+    return;
+  }
+  interp4_block<T, D, NF>(a, wtab, u, blockIdx.x, nmain,
+                          [&](int64_t i, const T (&v)[NF]) { interp4_store<T, NF>(a, i, v, out); });
+}
+// The fields combined into the transposed operator's marker values instead of stored
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_interp4_adj(InterpArgs a, AdjArgs ad, const cplx<T>* __restrict__ wtab,
+                                                     const T* __restrict__ u, double* __restrict__ out, int nmain,
+                                                     BorderArgs bd) {
+  if ((int)blockIdx.x >= nmain) {
+    border_block(bd, (int)blockIdx.x - nmain);
+    return;
+  }
+  interp4_block<T, D, 5>(a, wtab, u, blockIdx.x, nmain, [&](int64_t i, const T (&v)[5]) {
+    double G[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) G[c] = (double)v[c];
+    adj_marker(ad, i, a.nf, G, out);
+  });
 }
 
 // The interpolation (4-point kernels, 2-D) of several grid groups in one launch: marker i of the
@@ -1552,17 +1579,24 @@ void interp(const InterpArgs& a, const cplx<T>* wtab, const T* u, double* out, h
   const int64_t lanes = six ? a.n_ib : a.n_ib * (a.g.dim == 3 ? 16 : 4);
   const int nm = (int)((lanes + 255) / 256);
   const dim3 grid((unsigned)(nm + (bd.q ? bd.nq : 0)));
-  const AdjArgs ad;
+  auto four = [&](auto dc, auto nc) {
+    constexpr int D = decltype(dc)::value, NF = decltype(nc)::value;
+    if (bd.q) hipLaunchKernelGGL((k_interp4_border<T, D, NF>), grid, dim3(256), 0, st, a, wtab, u, out, nm, bd);
+    else hipLaunchKernelGGL((k_interp4<T, D, NF>), grid, dim3(256), 0, st, a, wtab, u, out);
+  };
+  using std::integral_constant;
+  using d2 = integral_constant<int, 2>;
+  using d3 = integral_constant<int, 3>;
   if (six) {
     if (a.g.dim == 2) hipLaunchKernelGGL((k_interp<T, 2, 6>), grid, dim3(256), 0, st, a, u, out, nm, bd);
     else hipLaunchKernelGGL((k_interp<T, 3, 6>), grid, dim3(256), 0, st, a, u, out, nm, bd);
   } else if (a.g.dim == 2) {
-    if (a.nf == 1) hipLaunchKernelGGL((k_interp4<T, 2, 1, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
-    else if (a.nf == 2) hipLaunchKernelGGL((k_interp4<T, 2, 2, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
-    else hipLaunchKernelGGL((k_interp4<T, 2, 5, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
+    if (a.nf == 1) four(d2{}, integral_constant<int, 1>{});
+    else if (a.nf == 2) four(d2{}, integral_constant<int, 2>{});
+    else four(d2{}, integral_constant<int, 5>{});
   } else {
-    if (a.nf == 1) hipLaunchKernelGGL((k_interp4<T, 3, 1, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
-    else hipLaunchKernelGGL((k_interp4<T, 3, 5, false>), grid, dim3(256), 0, st, a, ad, wtab, u, out, nm, bd);
+    if (a.nf == 1) four(d3{}, integral_constant<int, 1>{});
+    else four(d3{}, integral_constant<int, 5>{});
   }
   IBDL_LAUNCH_CHECK();
 }
@@ -1574,8 +1608,8 @@ void interp_adj(const InterpArgs& a, const AdjArgs& ad, const cplx<T>* wtab, con
   if (a.kernel == KID_BSPLINE6 || a.nf < 1 || a.nf > 5) throw Error(-2, "interp_adj: 4-point kernels, 1..5 fields");
   const int nm = (int)((a.n_ib * (a.g.dim == 3 ? 16 : 4) + 255) / 256);
   const dim3 grid((unsigned)(nm + (bd.q ? bd.nq : 0)));
-  if (a.g.dim == 2) hipLaunchKernelGGL((k_interp4<T, 2, 5, true>), grid, dim3(256), 0, st, a, ad, wtab, u, y, nm, bd);
-  else hipLaunchKernelGGL((k_interp4<T, 3, 5, true>), grid, dim3(256), 0, st, a, ad, wtab, u, y, nm, bd);
+  if (a.g.dim == 2) hipLaunchKernelGGL((k_interp4_adj<T, 2>), grid, dim3(256), 0, st, a, ad, wtab, u, y, nm, bd);
+  else hipLaunchKernelGGL((k_interp4_adj<T, 3>), grid, dim3(256), 0, st, a, ad, wtab, u, y, nm, bd);
   IBDL_LAUNCH_CHECK();
 }
 
