@@ -207,7 +207,7 @@ ibdl_status_t ibdl_backward(ibdl_t h, const double* q, const void* u_grid, const
  * solved together.  Problems with the same grid (sizes, box, origin, kappa) form a group.  In 2-D
  * the spread of every group is one persistent launch over a single work queue of busy tiles and
  * the interpolation of every group one launch, and so is each FFT pass (rows of 64 to 1024 points,
- * lines of at most 1024; other grids: once per group).  The batched
+ * lines of at most 1024, up to 100 MB of grid fields; otherwise once per group).  The batched
  * operator is replayed from a HIP graph every GMRES iteration, and each iteration's Arnoldi step,
  * Givens rotations and convergence test run on the device for every problem in one launch, so the
  * host only watches the published residuals.  The FFT passes' launch shapes and the 2-D spread's

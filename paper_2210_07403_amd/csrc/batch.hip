@@ -482,10 +482,16 @@ template <typename T> void build_queue(ibdl_batch_s* B) {
   IBDL_HIP(hipMemcpyAsync(Q.sg, sg.data(), sizeof(SpreadGroup) * ng, hipMemcpyHostToDevice, B->st));
   IBDL_HIP(hipMemcpyAsync(Q.ig, ig.data(), sizeof(InterpGroup) * ng, hipMemcpyHostToDevice, B->st));
   IBDL_HIP(hipMemcpyAsync(Q.items, it.data(), sizeof(int2) * it.size(), hipMemcpyHostToDevice, B->st));
-  // The FFT passes of all groups in one launch each where there is more than one group (30 problems in
-  // three groups: 45 us an apply, group by group 63); a single group's passes keep the launch shapes
-  // chosen by timing.
-  bool merge = ng > 1;
+  // The FFT passes of all groups in one launch each where there is more than one group, up to 100 MB of grid
+  // fields.  Group by group the passes keep the launch shapes chosen by timing; what merging saves is their
+  // launches and their last, half-empty rounds, which count for less the longer a pass is.  Solves merged and
+  // group by group, FP64: thirty problems on 128^2, 256^2 and 512^2 grids (28 MB) 1229 and 1377 us, six each on
+  // 256^2 to 1024^2 (66 MB) 1752 and 1876, 60 each on 256^2 and 512^2 (157 MB) 3753 and 3601, 24 each on 512^2
+  // and 1024^2 (252 MB) 5428 and 4803; on float grids the last three 1297 and 1527 (33 MB), 2500 and 2637
+  // (79 MB), 3135 and 3000 (126 MB).
+  int64_t bytes = 0;
+  for (const Group& G : B->groups) bytes += (int64_t)sizeof(T) * G.ntot * (int64_t)G.probs.size();
+  bool merge = ng > 1 && bytes <= 100000000;
   for (const Group& G : B->groups) merge = merge && fft2_groups_fit(G.n[0], G.n[1]);
   std::vector<int2> fi, fl;
   if (merge) {
