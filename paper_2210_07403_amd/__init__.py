@@ -198,7 +198,8 @@ class Problem:
 
     def active_span(self):
         """(first, last) index along the last grid axis holding an active row: the part of the
-        spectra the operator apply's last-axis pass loads and stores."""
+        spectra the operator apply's last-axis pass loads and stores (the whole axis for 2-D grids
+        over 1024 points along y, though their pass masks rows too)."""
         a, b = ctypes.c_int32(), ctypes.c_int32()
         B.check(B.load().ibdl_active_span(self._h, ctypes.byref(a), ctypes.byref(b)), self._h)
         return int(a.value), int(b.value)

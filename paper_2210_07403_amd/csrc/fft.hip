@@ -476,8 +476,6 @@ template <typename F> void dispatch_m(int m, F&& f) {
 }
 }  // namespace
 
-int fft_supported(int n) { return n >= 16 && n <= 1024 && (n & (n - 1)) == 0; }
-
 template <typename T>
 int fft_x_rpb_max(int nx) {
   int r = 0;

@@ -298,8 +298,9 @@ __device__ __forceinline__ void mode_mult(const MultDesc& md, const Mode<T>& m, 
 // Elements per thread of a y line: 8 for one field.  Passes that hold several fields at once take 4 in
 // double (five fields at 4 take 80 registers), in float from 2048 points on, where a block of 512 or
 // 1024 threads leaves 128 registers.  Double lines of 2048 and 4096 points take 8: 2048 lines of 2048
-// points, five fields and two: 82 us with 4 on 512 threads (which spill), 62 with 8 on 256 threads and
-// twiddles read as they are used; lines of 1024 with 8: 24 us, with 4: 17.
+// points, five fields and two: 82 us with 4 on 512 threads, 62 with 8 on 256 threads and twiddles read as
+// they are used; lines of 1024 with 8: 24 us, with 4: 17.  Registers spill all the same, mostly in the packed
+// block (line_packs): with five fields 205 of them at 2048 points (6 without it) and 208 at 4096 (none).
 // Lines of 8192 points need 8 to fit 1024 threads.
 template <typename T> constexpr int line_rmx(int N, int nmax) {
   if (N <= 8) return N;
@@ -323,6 +324,9 @@ template <typename T, int N, int NI, int NO> struct LineShape {
   // symbols are read as they are used.
   static constexpr bool D2048 = sizeof(T) == 8 && N == 2048 && NM > 1;   // 8 elements on 256 threads
   static constexpr bool LEAN = T_ >= 512 || D2048;
+  // Double passes of 4096 points with two or three fields get 128 registers for 64 or 96 of data and spill in
+  // every block (one field in, three out 318 of them, three in and two out 521, three in and one out 574):
+  // applies on 4096^2 with them take 451, 501 and 637 us, with one field in and out 153.
   static constexpr int MINW = D2048 ? 2 : !LEAN ? 1 : ALONE ? 2 : 4;
   // two exchange buffers per line where two blocks then still share a CU, or where the block has
   // the CU to itself anyway

@@ -1516,7 +1516,9 @@ ibdl_status_t ibdl_create(const ibdl_config_t* cfg, int64_t n_ib, const double* 
     // and the instantiation, is 0.2 ms for each of A and A^T after every change of markers.  Solves
     // replayed and launched: 64^2 Stokes 700 and 715 us, 128^2 471 and 481, 256^2 and 512^2 scalar
     // 412 and 417, 428 and 427; 512^2 Stokes 983 and 953, 1024^2 572 and 562, Stokes 1520 and 1413;
-    // a 512^2 training step 2480 and 2100.  So up to 2^14 points, from a marker set's second solve on.
+    // a 512^2 training step 2480 and 2100.  MINRES iterations of the single layer: 128^2 12.0 and 12.5 us,
+    // 256^2 21 and 21, 512^2 30.1 and 30.4, 1024^2 37.7 and 36.8; on float grids the same within 4 %.
+    // So up to 2^14 points, from a marker set's second solve on.
     h->graph_mode = h->ntot <= ((int64_t)1 << 14) ? ibdl_s::GRAPH_SECOND : ibdl_s::GRAPH_OFF;
     h->nxh = h->n[0] / 2 + 1;
     h->nxp = (h->nxh + 15) / 16 * 16;

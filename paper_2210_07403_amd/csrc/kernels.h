@@ -69,8 +69,6 @@ struct RowMask {
     }
     return m;
   }
-  __device__ bool keep(int y) const { return !load || (y >= lo && y <= hi); }
-  __device__ bool keep_out(int y) const { return !store || (y >= lo && y <= hi); }
 };
 
 // Rows of the 2-D x passes: lo .. hi of every field.  seg: busy x-segments of a row, seg_words 64-bit
@@ -159,7 +157,6 @@ template <typename T>
 void fft_fused_last(cplx<T>* data, int n, int64_t P, int no, const MultDesc& md, const cplx<T>* tw,
                     hipStream_t s, int batch = 1, int64_t bstride = 0, int w = 0,
                     const RowMask& rm = RowMask(), int plan = 0);
-int fft_supported(int n);
 
 // Twiddle tables of the 2-D passes: the plain table along x (exp(-2 pi i m / nx), for the even/odd
 // split) and, in the order the stages read them, those of the transforms along x and along y (y[1]:
@@ -193,6 +190,7 @@ void fft2_lines(cplx<T>* data, int n, int no, const MultDesc& md, const Tw2<T>& 
                 int64_t bstride, int w, const RowMask& rm);
 template <typename T> int fft2_rows_max(int nx);
 // most lines per block along y, for passes holding nmax fields at once
+template <typename T> int fft2_lines_max(int n, int nmax);
 // One grid group of a batch (np problems of an nx x ny grid, one field each) in the merged passes.
 // items: (group, block of the group) per workgroup of the x passes, then of the pass along y
 struct Fft2Group {
@@ -209,7 +207,6 @@ template <typename T> void fft2_group_set(Fft2Group& g, T* real, cplx<T>* spec, 
 template <typename T>   // the groups' spread fields -> scalar multiplier -> fields; host: the groups' descriptors
 void fft2_groups(const Fft2Group* host, const Fft2Group* dev, int ng, const int2* items, int nx_items, int ny_items,
                  hipStream_t s);
-template <typename T> int fft2_lines_max(int n, int nmax);
 
 // ------------------------------------------------------------------ markers, spread, interp
 enum KernelId { KID_PESKIN4 = 0, KID_COS4 = 1, KID_BSPLINE6 = 2 };
@@ -407,9 +404,8 @@ int kr_nblk(int64_t n);
 // GMRES least-squares state in device memory (kr_gmres_state_doubles(mx) doubles for at most mx
 // steps): scalars GM_BETA (|b|), GM_RES (Krylov residual estimate / |b|), GM_K (steps the solution
 // uses), GM_DONE (1 once res <= tol or the process broke down: later steps leave the state alone),
-// GM_HN (|w| of the last step), then the rotations, the rotated right-hand side, the solution y and
-// the rotated Hessenberg columns.  The first GM_PUB scalars are what a step publishes to the host.
-// (gm_record.h)
+// GM_HN (|w| of the last step), then the rotations, the rotated right-hand side and the rotated
+// Hessenberg columns.  The first GM_PUB scalars are what a step publishes to the host (gm_record.h).
 // the Arnoldi scratch h holds the first Gram-Schmidt pass at [0, 256) and |b|^2 at GM_BNORM2_AT
 constexpr int GM_BNORM2_AT = 520;
 size_t kr_gmres_state_doubles(int mx);
@@ -418,7 +414,8 @@ constexpr int kArnoldiOne = 1024;   // longest vectors whose Arnoldi step one wo
 // One Arnoldi step, step k - 1: classical Gram-Schmidt twice on w against V_0..V_{k-1} (w is scratch
 // afterwards, and neither vdst nor vdst2), |w|, the least-squares update in gs (tolerance tol, at most mx <= 256
 // steps), vdst (and vdst2 if set) = w / |w| (0 where that is 0 or not finite), the state's record of
-// step number seq to host_dst (device address of host-mapped, coherent pinned memory).  partial: (2 k + 1) * nblk doubles with nblk = kr_arnoldi_nblk(n).
+// step number seq to host_dst (device address of host-mapped, coherent pinned memory).  partial:
+// (2 k + 1) * nblk doubles with nblk = kr_arnoldi_nblk(n).
 void kr_arnoldi_step(const double* V, int64_t ldv, int k, double* w, int64_t n, double* partial, int nblk, double* h,
                      double* gs, int mx, double tol, double* host_dst, unsigned seq, double* vdst, double* vdst2,
                      hipStream_t st);

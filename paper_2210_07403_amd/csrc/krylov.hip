@@ -282,8 +282,7 @@ __global__ void k_blincomb(const double* __restrict__ V, int64_t ldv, int k, con
 __device__ __forceinline__ double* gm_cs(double* gs) { return gs + GM_HDR; }
 __device__ __forceinline__ double* gm_sn(double* gs, int mx) { return gs + GM_HDR + mx; }
 __device__ __forceinline__ double* gm_g(double* gs, int mx) { return gs + GM_HDR + 2 * mx; }
-__device__ __forceinline__ double* gm_y(double* gs, int mx) { return gs + GM_HDR + 3 * mx + 1; }
-__device__ __forceinline__ double* gm_R(double* gs, int mx) { return gs + GM_HDR + 4 * mx + 2; }
+__device__ __forceinline__ double* gm_R(double* gs, int mx) { return gs + GM_HDR + 3 * mx + 1; }
 
 // What a step's least-squares update reads of the state, staged in LDS when the step's kernel starts
 // (beside its first vector loads) so that the update waits for no memory.
@@ -842,7 +841,7 @@ inline unsigned blocks_for(int64_t n) {
 
 }  // namespace
 
-size_t kr_gmres_state_doubles(int mx) { return (size_t)GM_HDR + 4 * (size_t)mx + 2 + (size_t)mx * (mx + 1); }
+size_t kr_gmres_state_doubles(int mx) { return (size_t)GM_HDR + 3 * (size_t)mx + 1 + (size_t)mx * (mx + 1); }
 
 void kr_gmres_finish(const double* gs, int mx, const double* V, int64_t ldv, double* x, int64_t n, bool gate,
                      hipStream_t st) {
