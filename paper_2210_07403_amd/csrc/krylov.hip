@@ -447,12 +447,12 @@ __global__ __launch_bounds__(kB) void k_arn1(const double* __restrict__ V, int64
 // units in its last place while it is more than half of w . w.  h is what the first pass's rounding left
 // behind, so it always is unless w is at the level of that rounding itself (an invariant Krylov space).
 // There the difference holds no digits and may come out negative, and every workgroup sums the updated
-// entries instead: all n of them, in the same order, so that all have the same bits.
+// entries instead: all n of them, in the same order, so that all have the same bits (w = 0 needs no sum).
 __device__ __forceinline__ double arn_norm2(const double* __restrict__ V, int64_t ldv, int k, const double* __restrict__ w,
                                             int64_t n, const double* hs, double* red) {
   double nrm2 = hs[k];
   for (int j = 0; j < k; ++j) nrm2 -= hs[j] * hs[j];
-  if (nrm2 > 0.5 * hs[k]) return nrm2;
+  if (!(nrm2 <= 0.5 * hs[k]) || hs[k] == 0.0) return nrm2;
   double s = 0.0;
   for (int64_t e = threadIdx.x; e < n; e += kB) {
     double x = w[e];

@@ -44,3 +44,14 @@ def test_norm_of_a_vector_at_rounding_level(n_ib, graph):
                 assert 0.0 < info.krylov_relres <= 3.2e-30
         # |V_0|^2 is 1 to the last place now and then, not as a rule
         assert exact < SEEDS - 1
+
+
+@pytest.mark.parametrize("n_ib", [1000, 1025, 5000])
+def test_zero_data(n_ib):
+    mk = geo.circle((0.5, 0.5), 0.27, n_ib)
+    spec = P.ProblemSpec("circle", 2, (64, 64), (1.0, 1.0), (0.0, 0.0), "screened", 2.0, 1.0, "dirichlet", 0.0, "peskin4",
+                         "fd2", mk, np.zeros(n_ib), None)
+    with make_problem(spec) as pr:
+        q, u, info = pr.solve(spec.data, None, tol=1e-10, maxit=20)
+        assert info.status == 0 and info.iters == 0 and info.krylov_relres == 0.0
+        assert not to_np(q).any() and not to_np(u).any()
